@@ -3,29 +3,42 @@
 //
 // C = A * B with A (m x k) and Bt (n x k) both K-contiguous, so an MFMA operand fragment
 // (8 consecutive bf16 along K) is one 16-byte access for either matrix.  Four 64-lane
-// waves in a 2x2 arrangement each own a 128x128 sub-tile as 4x4 MFMA 32x32x16 blocks
+// waves in a 2x2 arrangement each own a 128x128 sub-tile as 8x8 MFMA 16x16x32 blocks
 // (256 fp32 accumulators per lane, which stay in accumulation registers).
 //
-// K is walked in steps of 32 through a ring of FOUR LDS stages (32 KB each, 128 KB in
-// all): the loads of step i+3 are issued while step i is multiplied, so a tile tolerates
-// about three step-times of memory latency.  With two stages of 64 the kernel spent more
-// than half its time waiting for the next stage (L2/Infinity-Cache latency under load is
-// longer than one step of MFMA work).
+// What bounds it is how full the one wave of a SIMD keeps its matrix pipe: 131 k cycles of
+// MFMA per 256x256x4096 tile.  A first form of this kernel (stages of k = 32, 64-byte row
+// pieces, 32x32x16 MFMAs) took 202 k cycles.  Three things were in the way:
+//  - half of every cache line: a direct load of 64-byte pieces costs the address unit 16
+//    requests per KB, a whole line's 128 bytes 8 (17.3 M L2 requests per 4096^3 product);
+//    an LDS stage is therefore k = 64 wide, one line per row;
+//  - the epilogue's 2900 vector instructions per wave (16-bit LDS writes): with B as the
+//    first MFMA operand a lane holds four neighbouring columns of one row, which leave as
+//    one 8-byte LDS write;
+//  - a barrier per 1024 cycles with the reads of the next half-step bunched behind it.
+// 4096^3 in its original form: 122 us (1.12 PFLOP/s) before, 103 us (1.33) now; 8192^3
+// 874 -> 765 us (1.44); as persistent workers 8192^3 1065 -> 855 us.
 //
-// Global memory goes straight to LDS (16 bytes per lane, no staging registers): a wave
-// load fills 1 KB of LDS contiguously, lane l supplying the 16-byte slot l.  A stage
-// holds 256 rows of 64 bytes; slot s holds row s/4, k-chunk (s%4) xor ((row/4)%4), which
+// LDS holds two stages of both operands (64 KB each, 128 KB in all).  A stage's place is
+// refilled as soon as its fragments are in registers, not when its products are done: B's
+// after the first half of the stage (the fragments of the second half are read during the
+// first), A's six eighths through the second half, so that loads have one to two
+// thousand cycles to arrive without a third stage.
+//
+// Global memory goes straight to LDS (16 bytes per lane, no staging registers).  A stage
+// holds 256 rows of 128 bytes; slot chunk c of a row holds k-chunk c xor ((row/2)%8), which
 // makes the 16 lanes that a 128-bit LDS read serves together (64 banks, 256 bytes per
-// clock) fall into 16 different 16-byte bank groups, without padding; with the xor taken
-// from row/2 the bank-conflict counter showed every read served at half rate.  The
-// lane-to-address map of the global side is chosen to produce that layout.
+// clock) fall into 16 different 16-byte bank groups, without padding.  The lane-to-address
+// map of the global side is chosen to produce that layout.
 //
-// Register budget: the arithmetic VGPRs are kept low on purpose so that, with the 256
-// accumulators, a wave stays well under the 512 registers of its SIMD and waves of a
-// high-priority kernel can become resident beside a running tile.
+// Register budget: the arithmetic VGPRs are kept low on purpose (100 beside the 256
+// accumulators) so that waves of a high-priority kernel can become resident beside a
+// running tile.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "../../include/tally.h"
 #include "kernels_stream.h"
@@ -40,31 +53,33 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef const __attribute__((address_space(1))) void *gptr_t;
 typedef __attribute__((address_space(3))) void *lptr_t;
 
-// NB = 32-column MFMA blocks per wave: 4 gives the 256x256 tile, 2 a 256x128 tile (128
+// NB = 32-column strips per wave: 4 gives the 256x256 tile, 2 a 256x128 tile (128
 // accumulators per lane) for operands whose n is only a multiple of 128.
 template <int NB>
 struct GemmBodyT {
-  static_assert(NB == 2 || NB == 4, "two or four column blocks per wave");
+  static_assert(NB == 2 || NB == 4, "two or four column strips per wave");
   using Args = tally_gemm_bf16_args;
   static constexpr int THREADS = 256;
   static constexpr int MIN_WAVES = 1;
   static constexpr int TILE = 256;                        // rows of C per logical block
   static constexpr int TILE_N = 64 * NB;                  // columns of C per logical block
-  static constexpr int BK = 32;
-  static constexpr int STAGES = 4;
-  static constexpr int OPA = TILE * BK * 2;               // bytes of A in one stage (16 KB)
+  static constexpr int KSTEP = 32;                        // k of one MFMA: what k is a multiple of
+  static constexpr int BK = 64;                           // k of one LDS stage: 128 bytes of a row
+  static constexpr int STAGES = 2;
+  static constexpr int MF = 8, NF = 2 * NB;               // 16-row / 16-column blocks of a wave
+  static constexpr int LDA_N = 8, LDB_N = 2 * NB;         // direct loads per wave and stage
+  static constexpr int OPA = TILE * BK * 2;               // bytes of A in one stage (32 KB)
   static constexpr int OPB = TILE_N * BK * 2;             // bytes of B in one stage
   static constexpr unsigned DYN_LDS = (unsigned)(OPA + OPB) * STAGES;  // 128 KB / 96 KB
-  // every k-step starts with a barrier that follows the LDS reads of the step before, so
-  // the next tile's first loads cannot overtake a reader of this tile
+  // a tile opens with a barrier that follows the LDS reads of the tile before
   static constexpr bool END_BARRIER = false;
   static constexpr bool YIELDS = true;
   static constexpr bool RANGE = false;
-  // share of a tile between two looks at the pause word, `every` k-steps apart (host side,
-  // for turnaround estimates)
+  // share of a tile between two looks at the pause word, `every` k-steps of 32 apart (a stage
+  // is two of them and is looked at once); host side, for turnaround estimates
   static double pause_fraction(const Args &a, uint32_t every) {
-    const uint32_t nk = a.k / BK;
-    return nk > every ? (double)every / nk : 1.0;
+    const uint32_t nk = a.k / KSTEP, e = every < 2 ? 2 : every;
+    return nk > e ? (double)e / nk : 1.0;
   }
 
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
@@ -83,241 +98,192 @@ struct GemmBodyT {
   template <bool NT>
   static __device__ __forceinline__ void run_impl(const Args &a, uint32_t bx, uint32_t by,
                                                   uint32_t bz, const YieldCtl ctl) {
+#ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
     extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
-    unsigned char *sA = tally_dyn_lds;                    // STAGES x 16 KB
+    unsigned char *sA = tally_dyn_lds;                    // STAGES x 32 KB
     unsigned char *sB = tally_dyn_lds + STAGES * OPA;
 
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x;
+    // (the lane index is made opaque here and again before the epilogue: a worker runs tile
+    // after tile, and addresses derived from a plain threadIdx would be kept in registers
+    // across the whole worker loop, beyond what a high-priority wave needs free beside it)
+    uint32_t lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t wm = wave >> 1, wn = wave & 1;
     const uint32_t K = a.k;
     const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;   // row pitches
+    const uint32_t nh = K / KSTEP;                        // 32-wide k-steps
+    const uint32_t ns = (nh + 1) / 2;                     // stages; the last one may be half full
+    const bool half_last = (nh & 1) != 0;
 
-    // global side of the direct loads: wave w fills rows [64 w, 64 w + 64) of A with 4 loads
-    // of 16 rows and rows [16 NB w, 16 NB (w + 1)) of B with NB loads; lane l supplies row
-    // l/4, k-chunk (l%4) xor ((l/16)%4).  Addresses are split into a wave-uniform base that
-    // advances by 64 bytes per k-step and per-lane byte offsets that never change.  The
-    // loads of an operand share one LDS base (M0) and differ by the instruction's immediate
-    // offset, which also moves the global address; the uniform bases compensate for that.
-    const uint32_t ld_kc = (lane & 3) ^ ((lane >> 4) & 3);
-    const unsigned char *uA =
-        reinterpret_cast<const unsigned char *>(a.A + bz * a.stride_a + (uint64_t)(by * TILE) * LDA);
-    const unsigned char *uB =
-        reinterpret_cast<const unsigned char *>(a.Bt + bz * a.stride_b + (uint64_t)(bx * TILE_N) * LDB);
-    // one per-lane offset per operand; what distinguishes the loads of an operand (16 rows
-    // further down, less the 1024 bytes the immediate adds) is uniform and goes to the base
-    const uint32_t voffA = ((wave * 64 + (lane >> 2)) * LDA + ld_kc * 8) * 2;
-    const uint32_t voffB = ((wave * 16 * NB + (lane >> 2)) * LDB + ld_kc * 8) * 2;
-    const uint64_t stepA = (uint64_t)32 * LDA - 1024, stepB = (uint64_t)32 * LDB - 1024;
-    const uint32_t ldsA_wave = wave * 64 * BK * 2;        // byte offset of the wave's rows
-    const uint32_t ldsB_wave = wave * 16 * NB * BK * 2;
-
-    // one direct load: 16 rows of A (B) of the 64 (16 NB) a wave contributes to a stage
-    // (the operands keep ordinary loads in every form: tiles share them through the L2s and
-    // the Infinity Cache; with non-temporal loads of both operands a co-located decode step
-    // ran as fast as alone, but the GEMM itself took 1.7 to 2.1 times as long, and with
-    // non-temporal loads of A alone 1.1 to 1.4 times for a tenth off the decode step)
-    constexpr int AUX = 0;
-    constexpr int AUXA = 0;
-    auto load_a = [&](const unsigned char *g, lptr_t l, int j) {
-      if (j == 0) __builtin_amdgcn_global_load_lds((gptr_t)(g + voffA), l, 16, 0, AUXA);
-      if (j == 1) __builtin_amdgcn_global_load_lds((gptr_t)(g + stepA + voffA), l, 16, 1024, AUXA);
-      if (j == 2) __builtin_amdgcn_global_load_lds((gptr_t)(g + 2 * stepA + voffA), l, 16, 2048, AUXA);
-      if (j == 3) __builtin_amdgcn_global_load_lds((gptr_t)(g + 3 * stepA + voffA), l, 16, 3072, AUXA);
+    // Global side of the direct loads.  One load moves 8 rows x 128 bytes to 1 KB of LDS; lane
+    // l supplies 16-byte slot l, that is row l/8, k-chunk (l%8) xor ((row/2)%8): for the even
+    // loads of a wave that is c = (l%8) xor (l/16), for the odd ones c xor 4.  Buffer
+    // addressing: per-lane offsets that never change, one scalar offset per load; the buffers
+    // start 4 KB before the tile because the instruction's immediate, which separates the
+    // loads of an LDS base, moves the global address too and is taken out again.
+    const uint32_t ld_c = (lane & 7) ^ (lane >> 4);
+    const uint32_t rowA = wave * 64 + (lane >> 3), rowB = wave * (8 * LDB_N) + (lane >> 3);
+    const uint32_t vA0 = (rowA * LDA + ld_c * 8) * 2, vA1 = (rowA * LDA + (ld_c ^ 4) * 8) * 2;
+    const uint32_t vB0 = (rowB * LDB + ld_c * 8) * 2, vB1 = (rowB * LDB + (ld_c ^ 4) * 8) * 2;
+    // A lane whose offset has its top bit set is outside the buffer: it moves nothing and its
+    // slot is filled with zeros.  So are the upper halves of the rows in the last stage of an
+    // odd number of k-steps, and whole stages past the last one: the loop below is the same
+    // for every stage and needs no peeled ends, whose merging paths cost the compiler copies
+    // of the accumulators.
+    constexpr uint32_t OOB = 0x80000000u;
+    const uint32_t hm0 = (ld_c & 4) ? OOB : 0u, hm1 = hm0 ^ OOB;
+    const auto rA = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const unsigned char *)(a.A + bz * a.stride_a + (uint64_t)(by * TILE) * LDA) - 4096),
+        0, 0x7fffffff, 0x00027000);
+    const auto rB = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const unsigned char *)(a.Bt + bz * a.stride_b + (uint64_t)(bx * TILE_N) * LDB) - 4096),
+        0, 0x7fffffff, 0x00027000);
+    const uint32_t stepA = 16 * LDA, stepB = 16 * LDB;    // bytes between the rows of two loads
+    struct Offs { uint32_t even, odd; };
+    auto offs = [&](uint32_t v0, uint32_t v1, uint32_t kt) {
+      const uint32_t none = kt >= ns ? OOB : 0u, half = (half_last && kt + 1 == ns) ? OOB : 0u;
+      return Offs{v0 | (hm0 & half) | none, v1 | (hm1 & half) | none};
     };
-    auto load_b = [&](const unsigned char *g, lptr_t l, int j) {
-      if (j == 0) __builtin_amdgcn_global_load_lds((gptr_t)(g + voffB), l, 16, 0, AUX);
-      if (j == 1) __builtin_amdgcn_global_load_lds((gptr_t)(g + stepB + voffB), l, 16, 1024, AUX);
-      if constexpr (NB > 2) {
-        if (j == 2) __builtin_amdgcn_global_load_lds((gptr_t)(g + 2 * stepB + voffB), l, 16, 2048, AUX);
-        if (j == 3) __builtin_amdgcn_global_load_lds((gptr_t)(g + 3 * stepB + voffB), l, 16, 3072, AUX);
-      }
+    auto load_a = [&](const Offs &v, uint32_t kt, int j) {
+      lptr_t l = (lptr_t)(sA + (kt & 1) * OPA + wave * (64 * BK * 2) + (j & 4) * 1024);
+      const uint32_t so = 4096u + kt * (BK * 2) + (uint32_t)j * stepA - (uint32_t)(j & 3) * 1024u;
+      if ((j & 3) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.even, so, 0, 0);
+      if ((j & 3) == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.odd, so, 1024, 0);
+      if ((j & 3) == 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.even, so, 2048, 0);
+      if ((j & 3) == 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.odd, so, 3072, 0);
     };
-    auto issue_loads = [&](uint32_t kt) {
-      const uint32_t st = kt & (STAGES - 1);
-      const unsigned char *gA = uA + (uint64_t)kt * (BK * 2);
-      const unsigned char *gB = uB + (uint64_t)kt * (BK * 2);
-      lptr_t lA = (lptr_t)(sA + st * OPA + ldsA_wave);
-      lptr_t lB = (lptr_t)(sB + st * OPB + ldsB_wave);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) load_a(gA, lA, j);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) load_b(gB, lB, j);
+    auto load_b = [&](const Offs &v, uint32_t kt, int j) {
+      lptr_t l = (lptr_t)(sB + (kt & 1) * OPB + wave * (8 * LDB_N * BK * 2) + (j & 4) * 1024);
+      const uint32_t so = 4096u + kt * (BK * 2) + (uint32_t)j * stepB - (uint32_t)(j & 3) * 1024u;
+      if ((j & 3) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.even, so, 0, 0);
+      if ((j & 3) == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.odd, so, 1024, 0);
+      if ((j & 3) == 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.even, so, 2048, 0);
+      if ((j & 3) == 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.odd, so, 3072, 0);
     };
-    constexpr int LOADS = 4 + NB;                         // direct loads per wave per k-step
 
-    f32x16_t acc[4][NB];
+    f32x4_t acc[MF][NF];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MF; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int j = 0; j < NF; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    const uint32_t nk = K / BK;
     uint32_t pause_left = ctl.ticks;   // what is left of this block's pause budget
     // A tile's first loads (every resident tile starts at once after a launch) and its
     // epilogue (32 MiB written by all compute units together) are its heaviest bursts of
     // memory traffic: a tile long enough to afford two more looks at the pause word takes
     // them just before either, so that neither burst starts on top of a high-priority kernel.
-    const bool edge_polls = ctl.ticks != 0 && nk >= 32;
+    const bool edge_polls = ctl.ticks != 0 && nh >= 32;
     if (edge_polls && wave == 0) yield_while_preempted(ctl, pause_left);
-    // a previous tile's waves may still be reading its last stage: fence them off before
-    // refilling the ring
+    // a previous tile's waves may still be reading LDS: fence them off before refilling it
     __syncthreads();
-    issue_loads(0);
-    if (nk > 1) issue_loads(1);
-    if (nk > 2) issue_loads(2);
+    {
+      const Offs vb = offs(vB0, vB1, 0), va = offs(vA0, vA1, 0);
+#pragma unroll
+      for (int j = 0; j < LDB_N; ++j) load_b(vb, 0, j);
+#pragma unroll
+      for (int j = 0; j < LDA_N; ++j) load_a(va, 0, j);
+      const Offs vb1 = offs(vB0, vB1, 1), va1 = offs(vA0, vA1, 1);
+#pragma unroll
+      for (int j = 0; j < LDB_N; ++j) load_b(vb1, 1, j);
+#pragma unroll
+      for (int j = 0; j < LDA_N / 2; ++j) load_a(va1, 1, j);
+    }
 
-    // fragment reads: lane l takes row (l%32) of a 32-row block and k-chunk 2 ks + l/32
-    const uint32_t f_row = lane & 31, f_half = lane >> 5, f_x = (lane >> 2) & 3;
-    const uint32_t fA = (wm * 128 + f_row) * (BK * 2);
-    const uint32_t fB = (wn * 32 * NB + f_row) * (BK * 2);
-    const uint32_t koff0 = ((0u + f_half) ^ f_x) * 16, koff1 = ((2u + f_half) ^ f_x) * 16;
+    // Two B fragment sets (this half-step's and the next one's) and a window of four A fragments;
+    // a step is one A fragment against all of B's.  A wave is alone on its SIMD: whatever it
+    // issues between two MFMAs that does not fit into the 16 cycles the earlier one occupies
+    // the matrix pipe leaves the pipe idle, so reads and direct loads are written one at a
+    // time between pairs of MFMAs and pinned there.  The MFMAs are inline assembly because the
+    // compiler otherwise puts part of the accumulators into arithmetic registers.
+    // Fragment reads: lane l takes row l%16 of a 16-row block and k-chunk 4 kk + l/16
+    const uint32_t f_off = (lane & 15) * (BK * 2) + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16);
+    const uint32_t fA = wm * (128 * BK * 2) + f_off, fB = wn * (16 * NF * BK * 2) + f_off;
+    bf16x8_t fa[4], fb[2][NF];
+    auto read_a = [&](uint32_t st, int kk, int i) {
+      fa[(8 * kk + i) & 3] = *reinterpret_cast<const bf16x8_t *>(sA + st * OPA + (fA ^ (kk * 64)) + i * (16 * BK * 2));
+    };
+    auto read_b = [&](uint32_t st, int kk, int j) {
+      fb[kk][j] = *reinterpret_cast<const bf16x8_t *>(sB + st * OPB + (fB ^ (kk * 64)) + j * (16 * BK * 2));
+    };
+    auto mma = [&](int kk, int i, int j0, int n) {
+#pragma unroll
+      for (int j = j0; j < j0 + n; ++j)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                     : "+a"(acc[i][j]) : "v"(fb[kk][j]), "v"(fa[(8 * kk + i) & 3]));
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int Q = NF / 4;                             // MFMAs between two other instructions
 
-    // Two fragment sets: the LDS reads of the next half-step travel while the MFMAs of the
-    // current one run.  A wave is alone on its SIMD, so whatever it issues between two
-    // MFMAs that does not fit into the 32 cycles the earlier MFMA occupies the matrix pipe
-    // leaves the pipe idle.  Reads and direct loads are therefore written, and pinned by
-    // scheduling groups, one at a time between MFMAs: the reads the first MFMAs of the next
-    // half need come first, then the remaining reads alternate with the half's direct
-    // loads (with four column blocks three MFMAs apart: the four waves issue theirs
-    // together and the address unit takes 16 cycles per 1 KB load).  Reads and direct loads
-    // both touch LDS, so the compiler keeps them in source order: the source order below is
-    // the issue order.  Against reads and loads bunched in front of sixteen MFMAs this took
-    // a quarter of the cycles out of the loop.
-    bf16x8_t fa0[4], fb0[NB], fa1[4], fb1[NB];
-    auto lfrag = [&](bf16x8_t(&fa)[4], bf16x8_t(&fb)[NB], uint32_t kt, uint32_t koff) {
-      const unsigned char *cA = sA + (kt & (STAGES - 1)) * OPA + fA + koff;
-      const unsigned char *cB = sB + (kt & (STAGES - 1)) * OPB + fB + koff;
-      fa[0] = *reinterpret_cast<const bf16x8_t *>(cA);
-#pragma unroll
-      for (int t = 0; t < NB; ++t) fb[t] = *reinterpret_cast<const bf16x8_t *>(cB + t * 32 * BK * 2);
-#pragma unroll
-      for (int t = 1; t < 4; ++t) fa[t] = *reinterpret_cast<const bf16x8_t *>(cA + t * 32 * BK * 2);
-    };
-    // fragment reads of (kt, half) interleaved with the loads of one operand of a later
-    // stage: the three last reads each follow one load, loads left over come after them
-    auto lfrag_and_loads = [&](bf16x8_t(&fa)[4], bf16x8_t(&fb)[NB], uint32_t kt, uint32_t koff,
-                               const unsigned char *g, lptr_t l, bool operand_a) {
-      const unsigned char *cA = sA + (kt & (STAGES - 1)) * OPA + fA + koff;
-      const unsigned char *cB = sB + (kt & (STAGES - 1)) * OPB + fB + koff;
-      const int nloads = operand_a ? 4 : NB;
-      fa[0] = *reinterpret_cast<const bf16x8_t *>(cA);
-#pragma unroll
-      for (int t = 0; t < NB; ++t) fb[t] = *reinterpret_cast<const bf16x8_t *>(cB + t * 32 * BK * 2);
-#pragma unroll
-      for (int t = 1; t < 4; ++t) {
-        if (t - 1 < nloads) { if (operand_a) load_a(g, l, t - 1); else load_b(g, l, t - 1); }
-        fa[t] = *reinterpret_cast<const bf16x8_t *>(cA + t * 32 * BK * 2);
-      }
-      if (3 < nloads) { if (operand_a) load_a(g, l, 3); else load_b(g, l, 3); }
-    };
-    auto mma = [&](const bf16x8_t(&fa)[4], const bf16x8_t(&fb)[NB]) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    };
-    // issue order of one half-step: M = MFMA (mask 0x8), d = LDS read (0x100), G = direct
-    // load (0x10).  Four column blocks:  Md Md Md Md Md  MG Md M  MG Md M  MG Md M  MG M
-    // two column blocks, A half:  Md Md Md  MGd MGd MGd  MG M;  B half:  Md Md Md  MGd MGd  Md M M
-    auto half_step_order = [&](bool operand_a) {
-#pragma unroll
-      for (int i = 0; i < 1 + NB; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      if constexpr (NB == 4) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      } else if (operand_a) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      }
-    };
-
-    // stage 0 has landed once only the two younger stages are in flight
-    if (nk > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
-    else if (nk > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    lfrag(fa0, fb0, 0, koff0);
-    lfrag(fa1, fb1, 0, koff1);
+    // stage 0 has landed once only what belongs to stage 1 is in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LDB_N + LDA_N / 2) : "memory");
+    __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    mma(fa0, fb0);
+    read_a(0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < NF; ++j) read_b(0, 0, j);
+    read_a(0, 0, 1);
     __builtin_amdgcn_sched_barrier(0);
-    // Loop invariant at the top of iteration kt: the MFMAs of (kt, first half) are issued,
-    // set 1 holds (kt, second half).  An iteration opens with the barrier, so the one wait
-    // the compiler places conservatively (at a loop header) coincides with the wait a
-    // barrier needs anyway; all other waits sit inside a basic block and name exactly the
-    // reads they need.
+    const uint32_t poll_mask = ctl.mask >> 1;             // in stages
     uint32_t kt = 0;
-    // steady state: stages kt+1 and kt+2 are in flight, stage kt+3 is issued here (its
-    // slot in the ring held stage kt-1, whose last reads were issued a whole step ago)
-    for (; kt + 3 < nk; ++kt) {
-      // one wave polls; the others meet it at the barrier below
-      if (ctl.ticks != 0 && wave == 0 && (kt & ctl.mask) == ctl.mask)
+    do {
+      // one wave polls; the others meet it at the barrier
+      if (ctl.ticks != 0 && wave == 0 && (kt & poll_mask) == poll_mask)
         yield_while_preempted(ctl, pause_left);
-      // stage kt+1 complete, kt+2 in flight
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
-      __syncthreads();  // stage kt+1 is in LDS for everyone; everyone is done with kt-1
-      const uint32_t st = (kt + 3) & (STAGES - 1);
-      const unsigned char *gA = uA + (uint64_t)(kt + 3) * (BK * 2);
-      const unsigned char *gB = uB + (uint64_t)(kt + 3) * (BK * 2);
-      lfrag_and_loads(fa0, fb0, kt + 1, koff0, gA, (lptr_t)(sA + st * OPA + ldsA_wave), true);
-      mma(fa1, fb1);
-      half_step_order(true);
+      const uint32_t st = kt & 1;
+      const Offs va1 = offs(vA0, vA1, kt + 1);
+      // first half of the stage; the second half of A's loads of stage kt+1 go out
+#pragma unroll
+      for (int i = 0; i < MF; ++i) {
+        mma(0, i, 0, Q);
+        if (i < NF) read_b(st, 1, i);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(0, i, Q, Q);
+        if (i + 2 < MF) read_a(st, 0, i + 2);
+        else read_a(st, 1, i + 2 - MF);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(0, i, 2 * Q, Q);
+        if (i < LDA_N / 2) load_a(va1, kt + 1, LDA_N / 2 + i);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(0, i, 3 * Q, Q);
+      }
+      // second half.  B of stage kt+1 is in LDS for everyone; everyone is done with B of stage
+      // kt, whose place takes the loads of stage kt+2
+      const Offs vb2 = offs(vB0, vB1, kt + 2), va2 = offs(vA0, vA1, kt + 2);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(1)" ::"n"(LDA_N) : "memory");
+      __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      lfrag_and_loads(fa1, fb1, kt + 1, koff1, gB, (lptr_t)(sB + st * OPB + ldsB_wave), false);
-      mma(fa0, fb0);
-      half_step_order(false);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // the last steps drain the ring
-    for (; kt + 1 < nk; ++kt) {
-      if (kt + 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      lfrag(fa0, fb0, kt + 1, koff0);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(fa1, fb1);
-      __builtin_amdgcn_sched_barrier(0);
-      lfrag(fa1, fb1, kt + 1, koff1);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(fa0, fb0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+#pragma unroll
+      for (int i = 0; i < MF; ++i) {
+        if (i == MF - 2) {
+          // the same for A
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)" ::"n"(LDB_N), "n"(NF > 5 ? 1 : 0) : "memory");
+          __builtin_amdgcn_s_barrier();
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        mma(1, i, 0, Q);
+        if (i + 2 < MF) read_a(st, 1, i + 2);
+        else read_a(st ^ 1, 0, i + 2 - MF);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(1, i, Q, Q);
+        if (i < NF) read_b(st ^ 1, 0, i);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(1, i, 2 * Q, Q);
+        if (i < 4) load_b(vb2, kt + 2, i);
+        if (i >= MF - 2) load_a(va2, kt + 2, 2 * (i - (MF - 2)));
+        __builtin_amdgcn_sched_barrier(0);
+        mma(1, i, 3 * Q, Q);
+        if (i < 4 && LDB_N > 4) load_b(vb2, kt + 2, 4 + i);
+        if (i >= MF - 2) load_a(va2, kt + 2, 2 * (i - (MF - 2)) + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } while (++kt < ns);
+    // what was still on its way is the zeros of stages past the last one
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (edge_polls && wave == 0) yield_while_preempted(ctl, pause_left);
-    // every wave is past its last fragment read: the ring can be reused as staging space
+    // every wave is past its last fragment read: LDS can be reused as staging space
     __syncthreads();
-    mma(fa1, fb1);
     // The accumulators are read below through inline assembly, which the compiler's
     // hazard recogniser cannot see into: keep the last MFMAs from being interleaved with
     // those reads and give the matrix pipe time to retire its last results first.
@@ -325,26 +291,26 @@ struct GemmBodyT {
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 
-    // Epilogue.  Lane l, register r of a 32x32 block holds row 8 (r/4) + 4 (l/32) + r%4,
-    // column l%32: stored straight from there a wave instruction would write 2 bytes per
-    // lane.  Each wave instead stages its 128 x 32 NB sub-tile through LDS, 64 rows at a time
-    // (a region of its own, rows 16 bytes more than their length apart so that the two
-    // half-waves of a write and the rows of a read fall into different banks), and writes
-    // whole row pieces, 16 bytes per lane.  Registers r and r+1 are adjacent rows: one
-    // hardware conversion packs both (round to nearest even) and the halves go to LDS
-    // separately.  Each accumulator is read where it is used: a wholesale copy of the
-    // accumulators into arithmetic registers would double the wave's register footprint,
-    // which decides how many other waves fit beside this one.
+    // Epilogue.  B was the first MFMA operand, so lane l, register r of block (i, j) holds
+    // row 16 i + l%16, column 16 j + 4 (l/16) + r: four neighbours of one row, packed to 8
+    // bytes with two hardware conversions (round to nearest even).  Each wave stages its
+    // 128 x 16 NF sub-tile through a region of LDS of its own (16-byte chunks xor-swizzled by
+    // the row, so that neither the 8-byte writes nor the 16-byte reads conflict) and writes
+    // whole row pieces, 16 bytes per lane.  Each accumulator is read where it is used: a
+    // wholesale copy of the accumulators into arithmetic registers would double the wave's
+    // register footprint, which decides how many other waves fit beside this one.
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    constexpr uint32_t ROWB = 64 * NB;                    // bytes of a sub-tile row
-    constexpr uint32_t PITCH = ROWB + 16;
-    constexpr uint32_t LPR = ROWB / 16;                   // lanes per row when reading back
+    constexpr uint32_t ROWB = 32 * NF;                    // bytes of a sub-tile row (256 / 128)
+    constexpr uint32_t LPR = ROWB / 16;                   // chunks (and lanes reading back) per row
     constexpr uint32_t RPI = 64 / LPR;                    // rows per wave instruction
-    unsigned char *stage = tally_dyn_lds + wave * (64 * PITCH);
-    const uint32_t w_row = (lane >> 5) * 4, w_col = (lane & 31) * 2;
+    asm volatile("" : "+v"(lane));
+    auto swz = [](uint32_t row) { return NF == 8 ? (row & 15) : ((row >> 1) & 7); };
+    unsigned char *stage = tally_dyn_lds + wave * (128 * ROWB);
+    const uint32_t w_row = lane & 15, w_sw = (lane >> 5) ^ swz(w_row);
+    unsigned char *w_base = stage + w_row * ROWB + ((lane >> 4) & 1) * 8;
     const uint32_t r_row = lane / LPR, r_chunk = lane % LPR;
-    uint16_t *gC = a.C + bz * a.stride_c;
+    uint16_t *gC = a.C + bz * a.stride_c + (uint64_t)(by * TILE + wm * 128) * a.n + bx * TILE_N + wn * (16 * NF);
+    const uint32_t g_off = r_row * a.n + r_chunk * 8;
     // an output too large to stay in the 256 MB Infinity Cache beside anything else is
     // written with non-temporal stores in the original form too (2 GB of attention scores:
     // 960 us -> 620 us)
@@ -352,35 +318,35 @@ struct GemmBodyT {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
+      for (int ii = 0; ii < MF / 2; ++ii)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int j = 0; j < NF; ++j) {
+          const int i = h * (MF / 2) + ii;
+          float v0, v1, v2, v3;
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v0) : "a"(acc[i][j][0]));
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v1) : "a"(acc[i][j][1]));
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v2) : "a"(acc[i][j][2]));
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v3) : "a"(acc[i][j][3]));
+          const f32x2_t p0 = {v0, v1}, p1 = {v2, v3};
+          uint2 w;
+          w.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(p0, bf16x2_t));
+          w.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(p1, bf16x2_t));
+          *reinterpret_cast<uint2 *>(w_base + i * (16 * ROWB) + ((w_sw ^ (2 * j)) * 16)) = w;
+        }
 #pragma unroll
-          for (int r = 0; r < 16; r += 2) {
-            float v0, v1;
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v0) : "a"(acc[2 * h + ii][j][r]));
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v1) : "a"(acc[2 * h + ii][j][r + 1]));
-            const f32x2_t p = {v0, v1};
-            const uint32_t pk = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
-            const uint32_t row = ii * 32 + (r >> 2) * 8 + w_row + (r & 3);
-            unsigned char *w = stage + row * PITCH + j * 64 + w_col;
-            *reinterpret_cast<uint16_t *>(w) = (uint16_t)pk;
-            *reinterpret_cast<uint16_t *>(w + PITCH) = (uint16_t)(pk >> 16);
-          }
-#pragma unroll
-      for (uint32_t t = 0; t < 64 / RPI; ++t) {
+      for (uint32_t t = h * (64 / RPI); t < (h + 1) * (64 / RPI); ++t) {
         const uint32_t row = t * RPI + r_row;
-        const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * PITCH + r_chunk * 16);
-        const uint32_t grow = by * TILE + wm * 128 + h * 64 + row;
-        const uint32_t gcol = bx * TILE_N + wn * 32 * NB + r_chunk * 8;
+        const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * ROWB + ((r_chunk ^ swz(row)) * 16));
+        uint16_t *g = gC + (uint64_t)(t * RPI) * a.n + g_off;
         if (NT || big_output) {
           const u32x4_nt w = {v.x, v.y, v.z, v.w};
-          __builtin_nontemporal_store(w, reinterpret_cast<u32x4_nt *>(gC + (uint64_t)grow * a.n + gcol));
+          __builtin_nontemporal_store(w, reinterpret_cast<u32x4_nt *>(g));
         } else {
-          *reinterpret_cast<uint4 *>(gC + (uint64_t)grow * a.n + gcol) = v;
+          *reinterpret_cast<uint4 *>(g) = v;
         }
       }
     }
+#endif
   }
 };
 using GemmBody = GemmBodyT<4>;

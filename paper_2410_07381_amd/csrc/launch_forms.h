@@ -262,7 +262,7 @@ __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const 
       s_idx[it & 1] = __hip_atomic_fetch_add(c.counter, c.chunk, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT) - c.counter_base;
     __syncthreads();
-    const uint32_t first = s_idx[it & 1];
+    const uint32_t first = __builtin_amdgcn_readfirstlane(s_idx[it & 1]);
     if (first >= c.limit) break;  // uniform across the workgroup
     const uint32_t last = (c.limit - first < c.chunk) ? c.limit : first + c.chunk;
     if constexpr (Body::RANGE) {

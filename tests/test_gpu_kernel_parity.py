@@ -77,6 +77,29 @@ def test_gemm_short_k(env, k, form):
     assert_bf16_close(host(Cd), a["C"])
 
 
+@pytest.mark.parametrize("n128", [False, True])
+@pytest.mark.parametrize("k", [32, 96, 128, 160, 224])
+def test_gemm_stage_ends(env, k, n128):
+    """K-loop ends: one to four 64-wide LDS stages, the last one whole or half full (its upper
+    half must count as zero whatever lies beyond the row's end: NaN here), several tiles per
+    worker; same tolerance as every bf16 product."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_bf16_close
+    m, n = 512, 384 if n128 else 512
+    name = "gemm_bf16_n128" if n128 else "gemm_bf16"
+    g = TI.gemm_inputs(m, n, k, config_index=3, scale=0.25)
+    a = dict(g, C=np.zeros((1, m, n), np.uint16))
+    OS.run_native(name, OK.grid_of(name, a), a)
+    Ap = torch.full((1, m, k + 40), 0x7FC0, dtype=torch.int16, device="cuda")
+    Bp = torch.full((1, n, k + 40), 0x7FC0, dtype=torch.int16, device="cuda")
+    Ap[:, :, :k], Bp[:, :, :k] = dev(g["A"]), dev(g["Bt"])
+    for form in FORMS:
+        Cd = torch.full((1, m, n), 0x7FC0, dtype=torch.int16, device="cuda")
+        torch.cuda.synchronize()
+        _run_form(B, ctx, torch, B.gemm_bf16(Ap[:, :, :k], Bp[:, :, :k], Cd, n128=n128), form)
+        assert_bf16_close(host(Cd), a["C"])
+
+
 def test_gemm_training_step_shapes(env):
     """Shapes of the transformer-layer step: attention scores (batched, K = 128, 2048 x 2048
     outputs per batch) and the second FFN product (K = 16384), persistent workers; the
