@@ -30,6 +30,7 @@ __device__ __forceinline__ float wave_max(float v) {
 // (measured: a decode step beside a streaming softmax took 65 us instead of 41 on the
 // device with ordinary accesses, 36 us with non-temporal ones).  The original form of a
 // kernel keeps ordinary accesses.
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_nt __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_nt __attribute__((ext_vector_type(4)));
 template <bool NT>
@@ -60,6 +61,22 @@ __device__ __forceinline__ void st1(float *p, float v) {
   if constexpr (NT) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
+
+#ifdef __HIP_DEVICE_COMPILE__   // (buffer resources have no type in the host compiler's pass)
+// A buffer of `bytes` bytes: 16-byte reads past its end give zeros, writes there do nothing.
+typedef __amdgpu_buffer_rsrc_t buf_t;
+__device__ __forceinline__ buf_t make_buf(const float *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00027000);
+}
+template <bool NT>
+__device__ __forceinline__ float4 buf_ld4(buf_t b, uint32_t byte) {   // (aux bit 1: non-temporal)
+  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b, byte, 0, NT ? 2 : 0));
+}
+template <bool NT>
+__device__ __forceinline__ void buf_st4(buf_t b, uint32_t byte, float4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), b, byte, 0, NT ? 2 : 0);
+}
+#endif
 
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
@@ -176,23 +193,47 @@ struct ReduceSumBody {
 struct ReduceFinalBody {
   using Args = tally_reduce_final_args;
   static constexpr int THREADS = kThreads;
-  static constexpr int MIN_WAVES = 4;
+  static constexpr int MIN_WAVES = 8;   // <= 64 registers: as many may be resident as ever
   static constexpr unsigned DYN_LDS = 0;
   static constexpr bool YIELDS = false;
   static constexpr bool RANGE = false;
   static constexpr bool END_BARRIER = true;   // s_d is reused by the next block
   static __device__ __forceinline__ void run_be(const Args &a, uint32_t x, uint32_t y, uint32_t z) { run(a, x, y, z); }
+  // The grid is ONE block, so what bounds it is how many bytes one compute unit keeps on their
+  // way: a thread asks for eight 16-byte pieces before it uses the first (32 KB per trip).
+  // With one 4-byte element per thread and trip, 65536 partials were 256 memory latencies in a
+  // row: 64 us against 6 now (1 GiB sum with its final pass: 256 -> 198 us).
   static __device__ __forceinline__ void run(const Args &a, uint32_t, uint32_t, uint32_t) {
-    __shared__ double s_d[kThreads];
-    double s = 0.0;
-    for (uint32_t i = threadIdx.x; i < a.count; i += kThreads) s += (double)a.partial[i];
-    s_d[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = kThreads / 2; o > 0; o >>= 1) {
-      if ((int)threadIdx.x < o) s_d[threadIdx.x] += s_d[threadIdx.x + o];
-      __syncthreads();
+#ifdef __HIP_DEVICE_COMPILE__
+    __shared__ double s_d[kThreads / kWave];
+    constexpr uint32_t U = 8, TRIP = U * kThreads;         // vectors per trip
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));   // (a worker has no registers to keep the addresses in)
+    // partial[] need not be 16-byte aligned: up to three elements before the first whole vector
+    const uint32_t mis = (uint32_t)(reinterpret_cast<uintptr_t>(a.partial) >> 2) & 3u;
+    const uint32_t lead = mis ? 4u - mis : 0u, head = lead < a.count ? lead : a.count;
+    const float *v = a.partial + head;
+    const uint32_t nv = (a.count - head) / 4, tail = head + nv * 4;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    for (uint32_t i = 0; i < nv; i += TRIP, v += 4 * TRIP) {   // (nv < 2^30: no wrap)
+      const buf_t b = make_buf(v, (nv - i < TRIP ? nv - i : TRIP) * 16);
+      float4 f[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) f[u] = buf_ld4<false>(b, (u * kThreads + t) * 16);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        s0 += (double)f[u].x; s1 += (double)f[u].y; s2 += (double)f[u].z; s3 += (double)f[u].w;
+      }
     }
-    if (threadIdx.x == 0) *a.total = s_d[0];
+    if (t < head) s0 += (double)a.partial[t];
+    if (t < a.count - tail) s1 += (double)a.partial[tail + t];
+    double s = (s0 + s1) + (s2 + s3);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+    if ((t & (kWave - 1)) == 0) s_d[t / kWave] = s;
+    __syncthreads();
+    if (t == 0) *a.total = (s_d[0] + s_d[1]) + (s_d[2] + s_d[3]);
+#endif
   }
 };
 

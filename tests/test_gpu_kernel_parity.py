@@ -322,6 +322,23 @@ def test_layernorm(env, rows, cols, form):
     assert_close_rel(host(y), a["y"], 1e-5, 2e-6)
 
 
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 1023, 8191, 8192, 8197, 65536, 70001])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_reduce_final_edges(env, count, offset):
+    """Fewer partials than a vector, ends of a trip of 2048 vectors, starts off a 16-byte
+    boundary; doubles hold the sum of these floats to 2^-50 of the largest partial sum."""
+    B, ctx, torch = env
+    from gpu_util import dev, host
+    p = TI.reduce_inputs(n=count + offset + 1, config_index=2)["x"].reshape(-1)
+    buf = dev(p)
+    total = dev(np.zeros(1, np.float64))
+    torch.cuda.synchronize()
+    ctx.launch_native(B.reduce_final(buf[offset:offset + count], total))
+    torch.cuda.synchronize()
+    want = float(np.sum(p[offset:offset + count].astype(np.float64)))
+    assert abs(host(total)[0] - want) <= 1e-12 * max(1.0, abs(want))
+
+
 # ------------------------------------------------------------------ decode attention
 @pytest.mark.parametrize("tokens,heads,scale", [(2048, 32, 0.02), (777, 3, 1.0), (5, 2, 1.0)])
 def test_attn_decode(env, tokens, heads, scale):
