@@ -70,11 +70,7 @@ __global__ __launch_bounds__(256, 4) void attn_decode_partial(tally_attn_decode_
     for (int u = 0; u < U; ++u) {
       const uint32_t t = tb + 16 * u;
       if (t < chunk) {                                     // chunk is a multiple of 16: wave-uniform
-        float s = GemvBody::dot8(kk[u], qq, 0.f);
-        s += __shfl_xor(s, 8, kWave);
-        s += __shfl_xor(s, 4, kWave);
-        s += __shfl_xor(s, 2, kWave);
-        s += __shfl_xor(s, 1, kWave);
+        float s = row16_all<AddOp>(GemvBody::dot8(kk[u], qq, 0.f));
         s = (t < cnt) ? s * scale : -INFINITY;
         if (sub == 0) s_score[t] = s;
         mloc = fmaxf(mloc, s);
@@ -115,12 +111,8 @@ __global__ __launch_bounds__(256, 4) void attn_decode_partial(tally_attn_decode_
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    acc[e] += __shfl_xor(acc[e], 16, kWave);
-    acc[e] += __shfl_xor(acc[e], 32, kWave);
-  }
-  l += __shfl_xor(l, 16, kWave);
-  l += __shfl_xor(l, 32, kWave);
+  for (int e = 0; e < 8; ++e) acc[e] = across_rows<AddOp>(acc[e]);
+  l = across_rows<AddOp>(l);
   __syncthreads();                                         // s_red reuse
   if (grp == 0) {
 #pragma unroll

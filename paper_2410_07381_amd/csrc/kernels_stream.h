@@ -14,16 +14,41 @@ constexpr int kThreads = 256;
 constexpr int kWave = 64;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// Butterflies over a wave.  A shuffle through LDS costs about a hundred cycles a step, six in a
+// row for every sum or maximum of a row; here the halves and the 16-lane rows are exchanged by
+// the lane swaps and what lies within a row by DPP operands, a few cycles a step.  The partners
+// are those of an xor by 32, 16, 8, 4, 2 and 1 in this order (a rotation by 4 pairs the same
+// values as an xor by 4 once both lanes of an xor by 8 hold the same), so the sums are the same
+// bits.
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+struct AddOp { static __device__ __forceinline__ float of(float a, float b) { return a + b; } };
+struct MaxOp { static __device__ __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
+// over each row of 16 lanes
+template <class F>
+__device__ __forceinline__ float row16_all(float v) {
+  v = F::of(v, lane_dpp<0x128>(v));                        // row_ror:8
+  v = F::of(v, lane_dpp<0x124>(v));                        // row_ror:4
+  v = F::of(v, lane_dpp<0x4e>(v));                         // quad_perm:[2,3,0,1]
+  return F::of(v, lane_dpp<0xb1>(v));                      // quad_perm:[1,0,3,2]
 }
+// over lanes l, l xor 16, l xor 32 and l xor 48.  (Assembly: the compiler reads the swap
+// builtins' two results from one register.  A swap needs two wait states after the vector
+// instruction that wrote its operands.)
+template <class F>
+__device__ __forceinline__ float across_rows(float v) {
+  float w = v;
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(v), "+v"(w));
+  v = F::of(v, w);
+  w = v;
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(v), "+v"(w));
+  return F::of(v, w);
+}
+__device__ __forceinline__ float wave_sum(float v) { return row16_all<AddOp>(across_rows<AddOp>(v)); }
+__device__ __forceinline__ float wave_max(float v) { return row16_all<MaxOp>(across_rows<MaxOp>(v)); }
+
 // Best-effort forms stream their data with non-temporal accesses (NT): what a best-effort
 // kernel reads once and writes once would otherwise push the high-priority job's weights
 // and caches out of the L2s and the 256 MB Infinity Cache between two of its requests
