@@ -332,194 +332,222 @@ struct GemvBody {
   }
 };
 
-// ---- row-wise kernels: a wave keeps its row in registers as NV float4 per lane --------
-template <int NV, bool NT>
-__device__ __forceinline__ void load_row(const float *row, uint32_t cols, uint32_t lane,
-                                         float4 (&v)[NV], float fill) {
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    uint32_t c = (i * kWave + lane) * 4;
-    v[i] = (c < cols) ? ld4<NT>(row + c) : make_float4(fill, fill, fill, fill);
-  }
+// ---- row-wise kernels: softmax and LayerNorm over fp32 rows ---------------------------
+// A row is held in registers by a GROUP of lanes, NV float4 each: a wave for rows of up to
+// 4096 columns, the whole workgroup for wider ones (a wave would need 128 registers for the
+// row alone, and walking such rows three times out of the caches took 393 us for 9001 x 8192,
+// 590 MB).  What bounds these kernels is bytes on their way: a persistent worker is often the
+// only workgroup of its compute unit, so it keeps DEPTH rows per group in flight: the loads of
+// a row are issued as soon as the registers of the row DEPTH before it have been stored.
+//
+// Rows are addressed as buffers of exactly their own length: a lane past the end reads zeros
+// and writes nothing, and a row past the last one is a buffer of length zero.  So there is no
+// branch around a load, and with it none of the waits for everything outstanding that the
+// compiler places where two paths meet.  A single row per group (every form but a fetch of
+// several blocks) has nothing to wait for but itself and takes ordinary loads under a mask,
+// which stream up to 8 % faster than buffer loads; so do the stores.
+//
+// Softmax 9001 x 8192 as 256 workers x 4: 415 -> 150 us (3.9 TB/s), original form 208 -> 116
+// (5.1, what a copy reaches); 200000 x 300 as 256 x 4: 308 -> 180 us, bound by the task
+// counter (12500 fetches at 11 ns) and a round trip per fetch.
+#ifdef __HIP_DEVICE_COMPILE__
+__device__ __forceinline__ buf_t row_buf(const float *base, uint64_t row, uint32_t cols, bool exists) {
+  return make_buf(base + row * cols, exists ? cols * 4 : 0u);
+}
+#endif
+
+template <bool NT>
+__device__ __forceinline__ void row_st4(float *row, uint32_t cols, uint32_t c, float4 v) {
+  if (c < cols) st4<NT>(row + c, v);
 }
 
-template <int NV, bool NT>
-__device__ __forceinline__ void softmax_row(const float *x, float *y, uint32_t cols, uint32_t lane) {
-  float4 v[NV];
-  load_row<NV, NT>(x, cols, lane, v, -INFINITY);
-  float m = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) m = fmaxf(m, fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)));
-  m = wave_max(m);
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    v[i].x = __expf(v[i].x - m); v[i].y = __expf(v[i].y - m);
-    v[i].z = __expf(v[i].z - m); v[i].w = __expf(v[i].w - m);
-    s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+// A group of LANES threads; `part` is LDS that the waves of a workgroup-wide group share sums
+// and maxima through.  Each use is followed by a barrier, and between two uses of one array
+// lies the barrier of the other: neither is overwritten while a wave still reads it.
+template <uint32_t LANES>
+struct RowGroup {
+  static constexpr bool WAVE = LANES == (uint32_t)kWave;
+  static constexpr uint32_t STEP = WAVE ? kThreads / kWave : 1;   // groups in a workgroup
+  static __device__ __forceinline__ void share(float *part, float v) {
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
+    __syncthreads();
   }
-  s = wave_sum(s);
-  const float inv = 1.0f / s;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    uint32_t c = (i * kWave + lane) * 4;
-    if (c < cols) st4<NT>(y + c, make_float4(v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv));
+  static __device__ __forceinline__ float sum(float v, float *part) {
+    v = wave_sum(v);
+    if constexpr (WAVE) return v;
+    share(part, v);
+    return (part[0] + part[1]) + (part[2] + part[3]);
   }
+  static __device__ __forceinline__ float max(float v, float *part) {
+    v = wave_max(v);
+    if constexpr (WAVE) return v;
+    share(part, v);
+    return fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+  }
+};
+
+// Op::row(args, row, lane, v) on the rows [r0, r1): group g takes r0 + g, r0 + g + STEP, ...
+template <class Op, uint32_t LANES, int NV, int DEPTH, bool NT, bool ONE = false>
+__device__ __forceinline__ void rows_walk(const typename Op::Args &a, uint32_t r0, uint32_t r1) {
+#ifdef __HIP_DEVICE_COMPILE__
+  typedef RowGroup<LANES> G;
+  __shared__ float s_part[2][kThreads / kWave];
+  uint32_t lane = threadIdx.x & (LANES - 1);
+  uint32_t r = r0 + (G::WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0u);
+  float4 v[DEPTH][NV];
+  auto load = [&](uint32_t row, float4 (&x)[NV]) {
+    if constexpr (ONE) {
+      const float *p = a.x + (uint64_t)row * a.cols;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const uint32_t c = (i * LANES + lane) * 4;
+        x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c < a.cols) x[i] = ld4<NT>(p + c);
+      }
+    } else {
+      const buf_t b = row_buf(a.x, row, a.cols, row < r1);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) x[i] = buf_ld4<NT>(b, (i * LANES + lane) * 16);
+    }
+  };
+  // (opaque, and again for each row: a worker would otherwise keep every address that derives
+  // from it, and LayerNorm's gamma and beta, in registers across its whole loop)
+  asm volatile("" : "+v"(lane));
+  if constexpr (ONE) {                                     // a logical block has one row per group
+    if (r >= r1) return;
+    load(r, v[0]);
+    Op::template row<G, LANES, NV, NT>(a, r, lane, v[0], s_part[0], s_part[1]);
+    return;
+  }
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) load(r + d * G::STEP, v[d]);
+  for (;; r += DEPTH * G::STEP) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      const uint32_t row = r + d * G::STEP;
+      if (row >= r1) return;                               // uniform over the group
+      asm volatile("" : "+v"(lane));
+      Op::template row<G, LANES, NV, NT>(a, row, lane, v[d], s_part[0], s_part[1]);
+      if (DEPTH > 1) load(row + DEPTH * G::STEP, v[d]);
+    }
+    if constexpr (DEPTH == 1) {
+      if (r + G::STEP >= r1) return;
+      load(r + G::STEP, v[0]);
+    }
+  }
+#endif
 }
 
-// Rows wider than 4096 would need more than 64 registers per lane to stay resident, and
-// the widest instantiation sets the register allocation (hence the occupancy) of the
-// whole kernel; such rows are walked three times instead and come from cache after the
-// first pass.
-__device__ __forceinline__ void softmax_row_streamed(const float *x, float *y, uint32_t cols,
-                                                     uint32_t lane) {
-  float m = -INFINITY;
-  for (uint32_t c = lane * 4; c < cols; c += kWave * 4) {
-    float4 v = *reinterpret_cast<const float4 *>(x + c);
-    m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
-  }
-  m = wave_max(m);
-  float s = 0.f;
-  for (uint32_t c = lane * 4; c < cols; c += kWave * 4) {
-    float4 v = *reinterpret_cast<const float4 *>(x + c);
-    s += (__expf(v.x - m) + __expf(v.y - m)) + (__expf(v.z - m) + __expf(v.w - m));
-  }
-  const float inv = 1.0f / wave_sum(s);
-  for (uint32_t c = lane * 4; c < cols; c += kWave * 4) {
-    float4 v = *reinterpret_cast<const float4 *>(x + c);
-    *reinterpret_cast<float4 *>(y + c) = make_float4(__expf(v.x - m) * inv, __expf(v.y - m) * inv,
-                                                     __expf(v.z - m) * inv, __expf(v.w - m) * inv);
-  }
+// `v` where the lane is within the row, else `other`: a select, never a branch around what
+// computes v (which would split the loads' block and wait for all of them)
+__device__ __forceinline__ float row_pick(bool in, float v, float other) {
+  asm("" : "+v"(v));
+  return in ? v : other;
 }
 
-// MAXNV bounds the widest row instantiated (in float4 per lane): the widest instantiation
-// sets the register allocation of the whole kernel, so rows of up to 1024 columns get a
-// kernel of their own that needs a quarter of the registers.  A high-priority kernel over
-// narrow rows then fits several waves per SIMD beside paused best-effort workgroups.
-template <int MAXNV>
-struct SoftmaxBodyT {
+struct SoftmaxOp {
   using Args = tally_softmax_f32_args;
+  template <class G, uint32_t LANES, int NV, bool NT>
+  static __device__ __forceinline__ void row(const Args &a, uint32_t r, uint32_t lane, float4 (&v)[NV],
+                                             float *part0, float *part1) {
+#ifdef __HIP_DEVICE_COMPILE__
+    auto in = [&](int i) { return (i * LANES + lane) * 4 < a.cols; };
+    float m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      m = fmaxf(m, row_pick(in(i), fmaxf(fmaxf(v[i].x, v[i].y), fmaxf(v[i].z, v[i].w)), -INFINITY));
+    m = G::max(m, part0);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      v[i].x = __expf(v[i].x - m); v[i].y = __expf(v[i].y - m);
+      v[i].z = __expf(v[i].z - m); v[i].w = __expf(v[i].w - m);
+      s += row_pick(in(i), (v[i].x + v[i].y) + (v[i].z + v[i].w), 0.f);
+    }
+    const float inv = 1.0f / G::sum(s, part1);
+    float *out = a.y + (uint64_t)r * a.cols;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      row_st4<NT>(out, a.cols, (i * LANES + lane) * 4, make_float4(v[i].x * inv, v[i].y * inv, v[i].z * inv, v[i].w * inv));
+#endif
+  }
+};
+
+struct LayerNormOp {
+  using Args = tally_layernorm_f32_args;
+  template <class G, uint32_t LANES, int NV, bool NT>
+  static __device__ __forceinline__ void row(const Args &a, uint32_t r, uint32_t lane, float4 (&v)[NV],
+                                             float *part0, float *part1) {
+#ifdef __HIP_DEVICE_COMPILE__
+    float s = 0.f;                                         // (lanes past the end hold zeros)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    const float mu = G::sum(s, part0) / (float)a.cols;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const float dx = v[i].x - mu, dy = v[i].y - mu, dz = v[i].z - mu, dw = v[i].w - mu;
+      q += row_pick((i * LANES + lane) * 4 < a.cols, (dx * dx + dy * dy) + (dz * dz + dw * dw), 0.f);
+    }
+    const float rstd = 1.0f / sqrtf(G::sum(q, part1) / (float)a.cols + a.eps);
+    float *out = a.y + (uint64_t)r * a.cols;
+    const buf_t g = row_buf(a.gamma, 0, a.cols, true), b = row_buf(a.beta, 0, a.cols, true);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const uint32_t byte = (i * LANES + lane) * 16;
+      const float4 gg = buf_ld4<false>(g, byte), bb = buf_ld4<false>(b, byte);
+      row_st4<NT>(out, a.cols, byte / 4, make_float4(__builtin_fmaf((v[i].x - mu) * rstd, gg.x, bb.x),
+                                                     __builtin_fmaf((v[i].y - mu) * rstd, gg.y, bb.y),
+                                                     __builtin_fmaf((v[i].z - mu) * rstd, gg.z, bb.z),
+                                                     __builtin_fmaf((v[i].w - mu) * rstd, gg.w, bb.w)));
+    }
+#endif
+  }
+};
+
+// Three kernels per operator, by width: the widest rows a kernel can hold set the registers,
+// hence the occupancy, of all of it.  Rows of up to 1024 columns get one that needs a quarter
+// of the registers of the next (a high-priority kernel over narrow rows then fits several
+// waves per SIMD beside paused best-effort workgroups), rows of up to 4096 the one that the
+// operator's footprint is stated for, wider ones the workgroup-wide groups.  WAVES is what the
+// original form leaves room for; DEEP instances, which the worker uses for narrow rows, trade
+// registers for rows in flight.
+template <class Op, int MAXNV, int WAVES, bool DEEP>
+struct RowsBodyT {
+  using Args = typename Op::Args;
   static constexpr int THREADS = kThreads;
-  static constexpr int MIN_WAVES = MAXNV <= 4 ? 8 : 4;
+  static constexpr int MIN_WAVES = WAVES;
   static constexpr unsigned DYN_LDS = 0;
   static constexpr bool YIELDS = false;
-  static constexpr bool RANGE = false;
+  static constexpr bool RANGE = true;
   static constexpr bool END_BARRIER = false;
   static constexpr uint32_t MAX_COLS = MAXNV * kWave * 4;   // widest row held in registers
-  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t, uint32_t) { run_t<false>(a, bx); }
-  static __device__ __forceinline__ void run_be(const Args &a, uint32_t bx, uint32_t, uint32_t) { run_t<true>(a, bx); }
-  template <bool NT>
-  static __device__ __forceinline__ void run_t(const Args &a, uint32_t bx) {
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t row = bx * 4 + threadIdx.x / kWave;
-    if (row >= a.rows) return;
-    const float *x = a.x + (uint64_t)row * a.cols;
-    float *y = a.y + (uint64_t)row * a.cols;
-    if (a.cols <= 256) softmax_row<1, NT>(x, y, a.cols, lane);
-    else if (a.cols <= 512) softmax_row<2, NT>(x, y, a.cols, lane);
-    else if (a.cols <= 1024) softmax_row<4, NT>(x, y, a.cols, lane);
-    else if constexpr (MAXNV >= 16) {
-      if (a.cols <= 2048) softmax_row<8, NT>(x, y, a.cols, lane);
-      else if (a.cols <= 4096) softmax_row<16, NT>(x, y, a.cols, lane);
-      else softmax_row_streamed(x, y, a.cols, lane);   // (re-read twice: ordinary accesses)
+  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t, uint32_t) { walk<false, true>(a, bx, bx + 1); }
+  static __device__ __forceinline__ void run_be(const Args &a, uint32_t bx, uint32_t, uint32_t) { walk<true, true>(a, bx, bx + 1); }
+  static __device__ __forceinline__ void run_range(const Args &a, uint32_t first, uint32_t last) { walk<true, false>(a, first, last); }
+  template <bool NT, bool ONE>
+  static __device__ __forceinline__ void walk(const Args &a, uint32_t first, uint32_t last) {
+    const uint32_t r0 = first * 4, r1 = last * 4 < a.rows ? last * 4 : a.rows;
+    if constexpr (MAXNV > 16) {
+      rows_walk<Op, kThreads, MAXNV / 4, 2, NT>(a, r0, r1);
+    } else {
+      if (a.cols <= 256) rows_walk<Op, kWave, 1, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, r1);
+      else if (a.cols <= 512) rows_walk<Op, kWave, 2, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, r1);
+      else if (a.cols <= 1024) rows_walk<Op, kWave, 4, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, r1);
+      else if constexpr (MAXNV >= 16) {
+        if (a.cols <= 2048) rows_walk<Op, kWave, 8, DEEP && !ONE ? (WAVES <= 2 ? 4 : 2) : 1, NT, ONE>(a, r0, r1);
+        else rows_walk<Op, kWave, 16, DEEP && !ONE && WAVES <= 2 ? 2 : 1, NT, ONE>(a, r0, r1);
+      }
     }
   }
 };
-using SoftmaxBody = SoftmaxBodyT<16>;
-using SoftmaxNarrowBody = SoftmaxBodyT<4>;
-
-template <int NV, bool NT>
-__device__ __forceinline__ void layernorm_row(const float *x, const float *g, const float *b,
-                                              float *y, uint32_t cols, float eps, uint32_t lane) {
-  float4 v[NV];
-  load_row<NV, NT>(x, cols, lane, v, 0.f);
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-  const float mu = wave_sum(s) / (float)cols;
-  float q = 0.f;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    uint32_t c = (i * kWave + lane) * 4;
-    if (c < cols) {
-      float dx = v[i].x - mu, dy = v[i].y - mu, dz = v[i].z - mu, dw = v[i].w - mu;
-      q += (dx * dx + dy * dy) + (dz * dz + dw * dw);
-    }
-  }
-  const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)cols + eps);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    uint32_t c = (i * kWave + lane) * 4;
-    if (c < cols) {
-      float4 gg = *reinterpret_cast<const float4 *>(g + c);
-      float4 bb = *reinterpret_cast<const float4 *>(b + c);
-      st4<NT>(y + c, make_float4(
-          __builtin_fmaf((v[i].x - mu) * rstd, gg.x, bb.x),
-          __builtin_fmaf((v[i].y - mu) * rstd, gg.y, bb.y),
-          __builtin_fmaf((v[i].z - mu) * rstd, gg.z, bb.z),
-          __builtin_fmaf((v[i].w - mu) * rstd, gg.w, bb.w)));
-    }
-  }
-}
-
-__device__ __forceinline__ void layernorm_row_streamed(const float *x, const float *g,
-                                                       const float *b, float *y, uint32_t cols,
-                                                       float eps, uint32_t lane) {
-  float s = 0.f;
-  for (uint32_t c = lane * 4; c < cols; c += kWave * 4) {
-    float4 v = *reinterpret_cast<const float4 *>(x + c);
-    s += (v.x + v.y) + (v.z + v.w);
-  }
-  const float mu = wave_sum(s) / (float)cols;
-  float q = 0.f;
-  for (uint32_t c = lane * 4; c < cols; c += kWave * 4) {
-    float4 v = *reinterpret_cast<const float4 *>(x + c);
-    float dx = v.x - mu, dy = v.y - mu, dz = v.z - mu, dw = v.w - mu;
-    q += (dx * dx + dy * dy) + (dz * dz + dw * dw);
-  }
-  const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)cols + eps);
-  for (uint32_t c = lane * 4; c < cols; c += kWave * 4) {
-    float4 v = *reinterpret_cast<const float4 *>(x + c);
-    float4 gg = *reinterpret_cast<const float4 *>(g + c);
-    float4 bb = *reinterpret_cast<const float4 *>(b + c);
-    *reinterpret_cast<float4 *>(y + c) =
-        make_float4(__builtin_fmaf((v.x - mu) * rstd, gg.x, bb.x),
-                    __builtin_fmaf((v.y - mu) * rstd, gg.y, bb.y),
-                    __builtin_fmaf((v.z - mu) * rstd, gg.z, bb.z),
-                    __builtin_fmaf((v.w - mu) * rstd, gg.w, bb.w));
-  }
-}
-
-template <int MAXNV>
-struct LayerNormBodyT {
-  using Args = tally_layernorm_f32_args;
-  static constexpr int THREADS = kThreads;
-  static constexpr int MIN_WAVES = MAXNV <= 4 ? 8 : 2;
-  static constexpr unsigned DYN_LDS = 0;
-  static constexpr bool YIELDS = false;
-  static constexpr bool RANGE = false;
-  static constexpr bool END_BARRIER = false;
-  static constexpr uint32_t MAX_COLS = MAXNV * kWave * 4;
-  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t, uint32_t) { run_t<false>(a, bx); }
-  static __device__ __forceinline__ void run_be(const Args &a, uint32_t bx, uint32_t, uint32_t) { run_t<true>(a, bx); }
-  template <bool NT>
-  static __device__ __forceinline__ void run_t(const Args &a, uint32_t bx) {
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t row = bx * 4 + threadIdx.x / kWave;
-    if (row >= a.rows) return;
-    const float *x = a.x + (uint64_t)row * a.cols;
-    float *y = a.y + (uint64_t)row * a.cols;
-    if (a.cols <= 256) layernorm_row<1, NT>(x, a.gamma, a.beta, y, a.cols, a.eps, lane);
-    else if (a.cols <= 512) layernorm_row<2, NT>(x, a.gamma, a.beta, y, a.cols, a.eps, lane);
-    else if (a.cols <= 1024) layernorm_row<4, NT>(x, a.gamma, a.beta, y, a.cols, a.eps, lane);
-    else if constexpr (MAXNV >= 16) {
-      if (a.cols <= 2048) layernorm_row<8, NT>(x, a.gamma, a.beta, y, a.cols, a.eps, lane);
-      else if (a.cols <= 4096) layernorm_row<16, NT>(x, a.gamma, a.beta, y, a.cols, a.eps, lane);
-      else layernorm_row_streamed(x, a.gamma, a.beta, y, a.cols, a.eps, lane);
-    }
-  }
-};
-using LayerNormBody = LayerNormBodyT<16>;
-using LayerNormNarrowBody = LayerNormBodyT<4>;
+using SoftmaxBody = RowsBodyT<SoftmaxOp, 16, 4, true>;
+using SoftmaxNarrowBody = RowsBodyT<SoftmaxOp, 4, 8, false>;
+using SoftmaxNarrowDeepBody = RowsBodyT<SoftmaxOp, 4, 4, true>;
+using SoftmaxTeamBody = RowsBodyT<SoftmaxOp, 32, 4, true>;
+using LayerNormBody = RowsBodyT<LayerNormOp, 16, 2, true>;
+using LayerNormNarrowBody = RowsBodyT<LayerNormOp, 4, 8, false>;
+using LayerNormNarrowDeepBody = RowsBodyT<LayerNormOp, 4, 4, true>;
+using LayerNormTeamBody = RowsBodyT<LayerNormOp, 32, 4, true>;
 
 }  // namespace tally

@@ -114,6 +114,16 @@ int occupancy_t(int *blocks_per_cu) {
   return TALLY_OK;
 }
 
+// The same where fewer workgroups than the registers allow are offered: two LayerNorm workers
+// per compute unit, as many as have ever been (more of them add no bandwidth: 16384 x 4096
+// takes 104 us with 512).
+template <class Body, int CAP>
+int occupancy_capped_t(int *blocks_per_cu) {
+  const int rc = occupancy_t<Body>(blocks_per_cu);
+  if (rc == TALLY_OK && *blocks_per_cu > CAP) *blocks_per_cu = CAP;
+  return rc;
+}
+
 template <class Body>
 hipError_t footprint_t(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
   hipFuncAttributes attr;
@@ -145,14 +155,31 @@ hipError_t footprint_attn(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_p
   return hipSuccess;
 }
 
-// Row kernels in their original form: rows that fit the narrow instantiation get the kernel
-// that needs a quarter of the registers.
-template <class Wide, class Narrow>
+// Row kernels: one kernel per range of widths (see RowsBodyT).  No variant needs more
+// registers or LDS than `Wide`, whose footprint and residency stand for all of them.
+template <class Wide, class Narrow, class Team>
 hipError_t launch_native_rows_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
   typename Wide::Args a;
   memcpy(&a, args, sizeof(a));
   if (a.cols <= Narrow::MAX_COLS) return launch_native_t<Narrow>(s, args, g, urgent);
+  if (a.cols > Wide::MAX_COLS) return launch_native_t<Team>(s, args, g, urgent);
   return launch_native_t<Wide>(s, args, g, urgent);
+}
+template <class Wide, class Narrow, class Team>
+hipError_t launch_sliced_rows_t(hipStream_t s, const void *args, uint32_t nblocks, const SliceCtl &c) {
+  typename Wide::Args a;
+  memcpy(&a, args, sizeof(a));
+  if (a.cols <= Narrow::MAX_COLS) return launch_sliced_t<Narrow>(s, args, nblocks, c);
+  if (a.cols > Wide::MAX_COLS) return launch_sliced_t<Team>(s, args, nblocks, c);
+  return launch_sliced_t<Wide>(s, args, nblocks, c);
+}
+template <class Wide, class Narrow, class Team>
+hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
+  typename Wide::Args a;
+  memcpy(&a, args, sizeof(a));
+  if (a.cols <= Narrow::MAX_COLS) return launch_ptb_t<Narrow>(s, args, c);
+  if (a.cols > Wide::MAX_COLS) return launch_ptb_t<Team>(s, args, c);
+  return launch_ptb_t<Wide>(s, args, c);
 }
 
 const tally_dim3 kBlock256 = {256, 1, 1};
@@ -283,13 +310,15 @@ const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(GemmBody, "gemm_bf16", grid_gemm),
     OPS(GemvBody, "gemv_bf16", grid_gemv),
     {"softmax_f32", sizeof(SoftmaxBody::Args), true, grid_softmax,
-     launch_native_rows_t<SoftmaxBody, SoftmaxNarrowBody>, launch_sliced_t<SoftmaxBody>,
-     launch_ptb_t<SoftmaxBody>, init_t<SoftmaxBody>, occupancy_t<SoftmaxBody>,
-     pause_fraction_t<SoftmaxBody>, footprint_t<SoftmaxBody>, footprint_native_t<SoftmaxBody>},
+     launch_native_rows_t<SoftmaxBody, SoftmaxNarrowBody, SoftmaxTeamBody>,
+     launch_sliced_rows_t<SoftmaxBody, SoftmaxNarrowBody, SoftmaxTeamBody>,
+     launch_ptb_rows_t<SoftmaxBody, SoftmaxNarrowDeepBody, SoftmaxTeamBody>, init_t<SoftmaxBody>,
+     occupancy_t<SoftmaxBody>, pause_fraction_t<SoftmaxBody>, footprint_t<SoftmaxBody>, footprint_native_t<SoftmaxBody>},
     {"layernorm_f32", sizeof(LayerNormBody::Args), true, grid_layernorm,
-     launch_native_rows_t<LayerNormBody, LayerNormNarrowBody>, launch_sliced_t<LayerNormBody>,
-     launch_ptb_t<LayerNormBody>, init_t<LayerNormBody>, occupancy_t<LayerNormBody>,
-     pause_fraction_t<LayerNormBody>, footprint_t<LayerNormBody>, footprint_native_t<LayerNormBody>},
+     launch_native_rows_t<LayerNormBody, LayerNormNarrowBody, LayerNormTeamBody>,
+     launch_sliced_rows_t<LayerNormBody, LayerNormNarrowBody, LayerNormTeamBody>,
+     launch_ptb_rows_t<LayerNormBody, LayerNormNarrowDeepBody, LayerNormTeamBody>, init_t<LayerNormBody>,
+     occupancy_capped_t<LayerNormBody, 2>, pause_fraction_t<LayerNormBody>, footprint_t<LayerNormBody>, footprint_native_t<LayerNormBody>},
     {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_attn_decode,
      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, footprint_attn},
     OPS(GemmSmallBody, "gemm_bf16_small", grid_gemm_small),

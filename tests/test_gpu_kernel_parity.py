@@ -322,6 +322,50 @@ def test_layernorm(env, rows, cols, form):
     assert_close_rel(host(y), a["y"], 1e-5, 2e-6)
 
 
+@pytest.mark.parametrize("cols", [4, 100, 256, 260, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 8188, 8192])
+@pytest.mark.parametrize("op", ["softmax", "layernorm"])
+def test_rows_width_edges(env, op, cols):
+    """Both sides of every width at which the kernel or the registers per lane change, an odd
+    number of rows, workers that take several blocks at once (rows in flight, a last fetch cut
+    short), one worker with the whole grid, slices; negative rows (a lane past the end must not
+    count as zero); nothing is written behind the last row; in place."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_close_rel
+    rows = 61
+    if op == "softmax":
+        xs = TI.rows_f32(rows, cols, scale=2.0, config_index=3)
+        xs[1::3] -= 50.0
+        a = {"x": xs, "y": np.zeros_like(xs), "rows": rows, "cols": cols}
+        make, abs_ = lambda x, y: B.softmax_f32(x, y), 1e-7
+        OS.run_native("softmax_f32", OK.grid_of("softmax_f32", a), a)
+    else:
+        li = TI.layernorm_inputs(rows, cols, scale=1.0)
+        xs, a = li["x"], dict(li, y=np.zeros_like(li["x"]))
+        g, b = dev(li["gamma"]), dev(li["beta"])
+        make, abs_ = lambda x, y: B.layernorm_f32(x, g, b, y, li["eps"]), 2e-6
+        OS.run_native("layernorm_f32", OK.grid_of("layernorm_f32", a), a)
+    for workers, chunk in [(None, 0), (None, 5), (3, 3), (1, 64), (2, 1)]:
+        buf = torch.full((rows + 1, cols), 7.0, device="cuda")
+        y = buf[:rows]
+        x = dev(xs) if chunk != 3 else y                  # (3, 3): in place
+        y.copy_(dev(xs))
+        torch.cuda.synchronize()
+        kern = make(x, y)
+        if workers:
+            job = ctx.launch_ptb(kern, workers, chunk=chunk)
+        elif chunk:
+            job = ctx.launch_sliced(kern, chunk)
+        else:
+            job = None
+            ctx.launch_native(kern)
+        if job:
+            assert job.wait() == B.JOB_COMPLETE
+            job.free()
+        torch.cuda.synchronize()
+        assert_close_rel(host(y), a["y"], 1e-5, abs_)
+        assert (host(buf[rows]) == 7.0).all()
+
+
 @pytest.mark.parametrize("count", [1, 3, 4, 5, 1023, 8191, 8192, 8197, 65536, 70001])
 @pytest.mark.parametrize("offset", [0, 1, 3])
 def test_reduce_final_edges(env, count, offset):
