@@ -88,18 +88,17 @@ __device__ __forceinline__ void st1(float *p, float v) {
 }
 
 #ifdef __HIP_DEVICE_COMPILE__   // (buffer resources have no type in the host compiler's pass)
-// A buffer of `bytes` bytes: 16-byte reads past its end give zeros, writes there do nothing.
+// A buffer of `bytes` bytes: 16-byte reads past its end give zeros.
 typedef __amdgpu_buffer_rsrc_t buf_t;
-__device__ __forceinline__ buf_t make_buf(const float *base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00027000);
+__device__ __forceinline__ buf_t make_buf(const void *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ uint4 buf_ld16(buf_t b, uint32_t byte, uint32_t scalar_byte) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, byte, scalar_byte, 0));
 }
 template <bool NT>
 __device__ __forceinline__ float4 buf_ld4(buf_t b, uint32_t byte) {   // (aux bit 1: non-temporal)
   return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b, byte, 0, NT ? 2 : 0));
-}
-template <bool NT>
-__device__ __forceinline__ void buf_st4(buf_t b, uint32_t byte, float4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), b, byte, 0, NT ? 2 : 0);
 }
 #endif
 

@@ -265,6 +265,29 @@ def test_gemm_small_forms(env, form):
     assert_bf16_close(host(Cd), a["C"])
 
 
+@pytest.mark.parametrize("m,n,k,batch", [(1, 1, 32, 1), (31, 33, 64, 1), (33, 31, 96, 3), (32, 64, 224, 1),
+                                         (64, 30, 256, 1), (17, 101, 288, 2), (40, 36, 544, 1), (65, 95, 800, 1)])
+def test_gemm_small_edges(env, m, n, k, batch):
+    """Rows and columns past the matrix, K that ends in half a 64-wide chunk, fewer chunks than
+    waves, one, two and more rounds of chunks per wave, output rows that no wide store may touch;
+    what lies beyond K and between the rows is NaN, and nothing is written behind C."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_bf16_close
+    g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
+    a = dict(g, C=np.zeros((batch, m, n), np.uint16))
+    OS.run_native("gemm_bf16_small", OK.grid_of("gemm_bf16_small", a), a)
+    Ap = torch.full((batch, m + 2, k + 40), 0x7FC0, dtype=torch.int16, device="cuda")
+    Bp = torch.full((batch, n + 2, k + 8), 0x7FC0, dtype=torch.int16, device="cuda")
+    Ap[:, :m, :k], Bp[:, :n, :k] = dev(g["A"]), dev(g["Bt"])
+    for form in FORMS:
+        buf = torch.full((batch * m * n + 8,), 0x7FC0, dtype=torch.int16, device="cuda")
+        Cd = buf[:batch * m * n].view(batch, m, n)
+        torch.cuda.synchronize()
+        _run_form(B, ctx, torch, B.gemm_bf16(Ap[:, :m, :k], Bp[:, :n, :k], Cd, small=True), form)
+        assert_bf16_close(host(Cd), a["C"])
+        assert (host(buf[batch * m * n:]) == 0x7FC0).all()
+
+
 # ------------------------------------------------------------------ GEMV
 @pytest.mark.parametrize("n,k,form", [(130, 96, "native"), (130, 96, "ptb_preempted"),
                                       (4096, 4096, "native_hi"), (4096, 11008, "native_hi"),
