@@ -365,8 +365,8 @@ using GemmN128Body = GemmBodyT<2>;
 // therefore loaded as whole 128-byte lines of 8 rows (8 requests per KB), two chunks ahead in
 // registers, and each wave turns them into fragments through 4 KB of LDS of its own: A in and
 // out, then B in and out.  LDS serves a wave's accesses in order, so this takes neither a
-// barrier nor a second buffer.  1000 x 2300 x 768 28 -> 18 us, 128 x 768 x 3072 13.4 -> 7.3,
-// 2048 x 4096 x 4096 475 -> 194.
+// barrier nor a second buffer.  1000 x 2300 x 768 28 -> 15 us, 128 x 768 x 3072 13.4 -> 7.2,
+// 2048 x 4096 x 4096 475 -> 198 (larger tiles there: see below).
 struct GemmSmallBody {
   using Args = tally_gemm_bf16_args;
   static constexpr int THREADS = 256;
@@ -413,7 +413,7 @@ struct GemmSmallBody {
     struct Set { uint4 a[4], b[4]; };
     auto request = [&](Set &s, uint32_t i) {
       const uint32_t c = wave + 4 * i, none = (c >= nchunk ? OOB : 0u) | (c + 1 == nchunk ? half : 0u);
-      const uint32_t so = c >= nchunk ? 0u : c * 128;
+      const uint32_t so = __builtin_amdgcn_readfirstlane(c >= nchunk ? 0u : c * 128);
 #pragma unroll
       for (int j = 0; j < 4; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
 #pragma unroll
@@ -444,11 +444,15 @@ struct GemmSmallBody {
     };
     Set s0, s1;
     request(s0, 0);
+    __builtin_amdgcn_sched_barrier(0);                    // (in the order in which they are waited for)
     request(s1, 1);
+    // (the only way round the second half is out of the loop: where a path that skips it meets
+    // one that does not, the compiler waits for every load on its way)
     for (uint32_t i = 0; i < mine; i += 2) {
       multiply(s0);
+      if (i + 1 >= mine) break;
       request(s0, i + 2);
-      if (i + 1 < mine) multiply(s1);
+      multiply(s1);
       request(s1, i + 3);
     }
 
@@ -477,6 +481,149 @@ struct GemmSmallBody {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (col + e < a.n) g[e] = v[e];
+      }
+    }
+#endif
+  }
+};
+
+// The small GEMM's operator with a workgroup per (64 MB) x 64 outputs, for its original form
+// where the 32x32 tiles are several times as many as the GPU holds: how the original form
+// covers the output is its own business (slices and workers keep to the logical blocks, and so
+// do all coverage records).  The 32x32 tiles are then bound by what they load and move through
+// LDS per product: every output line and column is fetched for 32 columns or rows only.  Here
+// four waves share a stage of 64 k through LDS, each with MB 32x32 blocks of its own, which
+// halves (MB = 1) or takes to 3/8 (MB = 2) the bytes per product.  The price is a serial chain
+// of K / 64 stages that one workgroup per compute unit cannot hide (0.4 us each).
+// Within 128 registers and 31 KB of LDS, to fit beside a paused best-effort GEMM tile.
+// 32x32 tiles / MB = 1 / MB = 2: 1000 x 2300 x 768 15.1 / 12.7 / 14.1 us; 512 x 4096 x 4096
+// 49.9 / 33.6 / 33.7; 2048 x 4096 x 4096 199 / 125 / 106 (0.65 PFLOP/s); 12 of these 2198 /
+// 1357 / 1076; but 512 x 1024 x 4096 (128 tiles of 64 x 64) 16.4 / 25.9 / 31.0.
+template <int MB>
+struct GemmMidBodyT {
+  using Args = tally_gemm_bf16_args;
+  static constexpr int THREADS = 256;
+  static constexpr int MIN_WAVES = 4;                     // (as the small tile)
+  static constexpr unsigned DYN_LDS = 0;
+  static constexpr uint32_t TM = 64 * MB, TN = 64;
+  static constexpr int NA = 2 * MB, NBL = 2;              // loads per wave and stage
+  static constexpr int AHEAD = MB == 1 ? 2 : 1;           // stages on their way (registers)
+
+  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
+#ifdef __HIP_DEVICE_COMPILE__
+    __shared__ __align__(16) unsigned char s_ab[(TM + TN) * 128];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wm = wave >> 1, wn = wave & 1;
+    const uint32_t K = a.k;
+    const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
+    const uint32_t ns = (K + 63) / 64;
+    constexpr uint32_t OOB = 0x80000000u;
+    const uint32_t r8 = lane >> 3, p8 = lane & 7;
+    const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TM * LDA, 0x7fffffffu);
+    const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TN * LDB, 0x7fffffffu);
+    uint32_t vA[NA], vB[NBL];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+      const uint32_t r = (wave * NA + j) * 8 + r8;
+      vA[j] = by * TM + r < a.m ? (r * LDA + p8 * 8) * 2 : OOB;
+    }
+#pragma unroll
+    for (int j = 0; j < NBL; ++j) {
+      const uint32_t r = (wave * NBL + j) * 8 + r8;
+      vB[j] = bx * TN + r < a.n ? (r * LDB + p8 * 8) * 2 : OOB;
+    }
+    const uint32_t half = (K & 32) && (p8 & 4) ? OOB : 0u;
+    struct Set { uint4 a[NA], b[NBL]; };
+    auto request = [&](Set &s, uint32_t c) {
+      const uint32_t none = (c >= ns ? OOB : 0u) | (c + 1 == ns ? half : 0u);
+      const uint32_t so = __builtin_amdgcn_readfirstlane(c >= ns ? 0u : c * 128);
+#pragma unroll
+      for (int j = 0; j < NA; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
+#pragma unroll
+      for (int j = 0; j < NBL; ++j) s.b[j] = buf_ld16(rB, vB[j] | none, so);
+    };
+    unsigned char *sA = s_ab, *sB = s_ab + TM * 128;
+    const uint32_t w_off = r8 * 128 + (p8 ^ (r8 >> 1)) * 16;
+    const uint32_t f_row = lane & 31, f_sw = (f_row >> 1) & 7;
+    const uint32_t fA = (wm * 32 * MB + f_row) * 128, fB = (wn * 32 + f_row) * 128;
+    f32x16_t acc[MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    auto step = [&](Set &s, uint32_t next) {
+#pragma unroll
+      for (int j = 0; j < NA; ++j)
+        *reinterpret_cast<uint4 *>(sA + (wave * NA + j) * 1024 + (w_off ^ (((wave * NA + j) & 1) * 64))) = s.a[j];
+#pragma unroll
+      for (int j = 0; j < NBL; ++j)
+        *reinterpret_cast<uint4 *>(sB + (wave * NBL + j) * 1024 + (w_off ^ (((wave * NBL + j) & 1) * 64))) = s.b[j];
+      request(s, next);
+      __syncthreads();
+      // (fragments are read in batches ahead of the products, not one by one between them)
+      constexpr int Q = MB == 1 ? 4 : 2;
+#pragma unroll
+      for (int q0 = 0; q0 < 4; q0 += Q) {
+        uint4 fa[Q][MB], fb[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const uint32_t slot = ((2 * (q0 + q) + (lane >> 5)) ^ f_sw) * 16;
+          fb[q] = *reinterpret_cast<const uint4 *>(sB + fB + slot);
+#pragma unroll
+          for (int i = 0; i < MB; ++i) fa[q][i] = *reinterpret_cast<const uint4 *>(sA + fA + i * 4096 + slot);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[q][i]),
+                                                             __builtin_bit_cast(bf16x8_t, fb[q]), acc[i], 0, 0, 0);
+      }
+      __syncthreads();
+    };
+    Set s[AHEAD];
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d) {
+      request(s[d], d);
+      __builtin_amdgcn_sched_barrier(0);                  // (in the order in which they are waited for)
+    }
+    // (the only way round a stage is out of the loop: see the small tile)
+    [&] {
+      for (uint32_t c = 0;; c += AHEAD)
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d) {
+          step(s[d], c + d + AHEAD);
+          if (c + d + 1 >= ns) return;
+        }
+    }();
+    // Output through 4 KB of LDS per wave, one 32x32 block at a time (layout as in the small
+    // tile): lane l leaves with columns 8 (l%4) .. +7 of rows l/4 and l/4 + 16
+    unsigned char *buf = s_ab + wave * 4096;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) *reinterpret_cast<float *>(buf + (r * 64 + lane) * 4) = acc[i][r];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t tr = (lane >> 2) + 16 * h, tc = (lane & 3) * 8;
+        const float *p = reinterpret_cast<const float *>(buf) + ((tr >> 3) * 4 + (tr & 3)) * 64 + ((tr >> 2) & 1) * 32 + tc;
+        uint16_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16(p[e]);
+        const uint32_t row = by * TM + (wm * MB + i) * 32 + tr, col = bx * TN + wn * 32 + tc;
+        if (row < a.m) {
+          uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
+          if (col + 8 <= a.n && (reinterpret_cast<uintptr_t>(g) & 7u) == 0) {
+            *reinterpret_cast<uint2 *>(g) = make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
+            *reinterpret_cast<uint2 *>(g + 4) = make_uint2(v[4] | (uint32_t)v[5] << 16, v[6] | (uint32_t)v[7] << 16);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (col + e < a.n) g[e] = v[e];
+          }
+        }
       }
     }
 #endif

@@ -182,6 +182,33 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
   return launch_ptb_t<Wide>(s, args, c);
 }
 
+// The original form of the small GEMM takes larger tiles once there are enough of them: 64x64
+// from one and a half per compute unit (at 1.1, 512 x 2304 x 768, both take 9 us; at 0.5 the
+// serial chain over K loses), 128x64 from two per compute unit (at 1.1, 1000 x 2300 x 768, it
+// loses to 64x64, 14.1 against 12.7 us; at 2.1, 12 x 500 x 700 x 512, it wins, 18.7 against 21.7).
+hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+  tally_gemm_bf16_args a;
+  memcpy(&a, args, sizeof(a));
+  const uint64_t tiles64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
+  const uint64_t tiles128 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch;
+  if (tiles128 >= 512) return launch_native_t<GemmMidBodyT<2>>(s, args, {cdiv(a.n, 64), cdiv(a.m, 128), a.batch}, urgent);
+  if (tiles64 >= 384) return launch_native_t<GemmMidBodyT<1>>(s, args, {cdiv(a.n, 64), cdiv(a.m, 64), a.batch}, urgent);
+  return launch_native_t<GemmSmallBody>(s, args, g, urgent);
+}
+// (whichever of its kernels occupies most)
+hipError_t footprint_native_gemm_small(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
+  *lds_bytes = *waves = *regs_per_lane = 0;
+  for (auto f : {footprint_native_t<GemmSmallBody>, footprint_native_t<GemmMidBodyT<1>>, footprint_native_t<GemmMidBodyT<2>>}) {
+    uint32_t l, w, r;
+    hipError_t e = f(&l, &w, &r);
+    if (e != hipSuccess) return e;
+    *lds_bytes = *lds_bytes > l ? *lds_bytes : l;
+    *waves = *waves > w ? *waves : w;
+    *regs_per_lane = *regs_per_lane > r ? *regs_per_lane : r;
+  }
+  return hipSuccess;
+}
+
 const tally_dim3 kBlock256 = {256, 1, 1};
 
 int grid_saxpy(const void *p, tally_dim3 *g, tally_dim3 *b) {
@@ -321,7 +348,9 @@ const KernelOps kOps[TALLY_K_COUNT] = {
      occupancy_capped_t<LayerNormBody, 2>, pause_fraction_t<LayerNormBody>, footprint_t<LayerNormBody>, footprint_native_t<LayerNormBody>},
     {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_attn_decode,
      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, footprint_attn},
-    OPS(GemmSmallBody, "gemm_bf16_small", grid_gemm_small),
+    {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
+     launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
+     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, footprint_native_gemm_small},
     OPS(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128),
 };
 

@@ -288,6 +288,29 @@ def test_gemm_small_edges(env, m, n, k, batch):
         assert (host(buf[batch * m * n:]) == 0x7FC0).all()
 
 
+@pytest.mark.parametrize("k", [32, 64, 96, 160, 224])
+@pytest.mark.parametrize("m,n,batch", [(70, 130, 64), (64, 64, 400), (130, 65, 128), (127, 129, 171)])
+def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
+    """Grids that the original form covers with 64x64 (first two) and 128x64 tiles: rows and
+    columns past the matrix, one to four stages, a last stage half full, NaN beyond K and
+    between the rows, nothing written behind C."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_bf16_close
+    g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
+    a = dict(g, C=np.zeros((batch, m, n), np.uint16))
+    OS.run_native("gemm_bf16_small", OK.grid_of("gemm_bf16_small", a), a)
+    Ap = torch.full((batch, m + 1, k + 40), 0x7FC0, dtype=torch.int16, device="cuda")
+    Bp = torch.full((batch, n + 1, k + 8), 0x7FC0, dtype=torch.int16, device="cuda")
+    Ap[:, :m, :k], Bp[:, :n, :k] = dev(g["A"]), dev(g["Bt"])
+    buf = torch.full((batch * m * n + 8,), 0x7FC0, dtype=torch.int16, device="cuda")
+    Cd = buf[:batch * m * n].view(batch, m, n)
+    torch.cuda.synchronize()
+    ctx.launch_native(B.gemm_bf16(Ap[:, :m, :k], Bp[:, :n, :k], Cd, small=True), hi=True)
+    torch.cuda.synchronize()
+    assert_bf16_close(host(Cd), a["C"])
+    assert (host(buf[batch * m * n:]) == 0x7FC0).all()
+
+
 # ------------------------------------------------------------------ GEMV
 @pytest.mark.parametrize("n,k,form", [(130, 96, "native"), (130, 96, "ptb_preempted"),
                                       (4096, 4096, "native_hi"), (4096, 11008, "native_hi"),
