@@ -53,6 +53,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef const __attribute__((address_space(1))) void *gptr_t;
 typedef __attribute__((address_space(3))) void *lptr_t;
 
+// bytes of output from which GemmBodyT writes it past the caches
+constexpr uint64_t kGemmBigOutput = 128ull << 20;
+
 // NB = 32-column strips per wave: 4 gives the 256x256 tile, 2 a 256x128 tile (128
 // accumulators per lane) for operands whose n is only a multiple of 128.
 template <int NB>
@@ -314,7 +317,7 @@ struct GemmBodyT {
     // an output too large to stay in the 256 MB Infinity Cache beside anything else is
     // written with non-temporal stores in the original form too (2 GB of attention scores:
     // 960 us -> 620 us)
-    const bool big_output = (uint64_t)a.m * a.n * a.batch * 2u > (128ull << 20);
+    const bool big_output = (uint64_t)a.m * a.n * a.batch * 2u > kGemmBigOutput;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll

@@ -182,18 +182,55 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
   return launch_ptb_t<Wide>(s, args, c);
 }
 
-// The original form of the small GEMM takes larger tiles once there are enough of them: 64x64
-// from one and a half per compute unit (at 1.1, 512 x 2304 x 768, both take 9 us; at 0.5 the
-// serial chain over K loses), 128x64 from two per compute unit (at 1.1, 1000 x 2300 x 768, it
-// loses to 64x64, 14.1 against 12.7 us; at 2.1, 12 x 500 x 700 x 512, it wins, 18.7 against 21.7).
-hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+// How the original form of a GEMM covers its output: with the largest tiles that still leave no
+// compute unit idle, whatever the logical blocks are (only slices and workers have to keep to
+// those).  Counted in tiles for 256 compute units; us at m x n x 2048 for 32x32 with split K /
+// 64x64 / 128x64 / 256x128 / 256x256 tiles:
+//    512 x 1024   9.0 /  12.8 /  17.2 / 25.1 / 40.9   (128 of 64x64)
+//   1024 x 1024  15.1 /  15.2 /  18.1 / 25.4 / 41.3   (256; at k = 512 6.7 / 5.5)
+//   1024 x 2048  26.5 /  18.9 /  19.2 / 26.3 / 41.9   (512; 256 of 128x64)
+//   2048 x 2048  47.1 /  33.0 /  29.9 / 27.8 / 42.2   (128 of 256x128)
+//   2048 x 4096  89.1 /  60.2 /  51.2 / 34.4 / 45.2   (256 of 256x128)
+//   4096 x 4096   174 /   113 /  93.1 / 68.6 / 56.2   (256 of 256x256)
+// and the same order from k = 512 to 8192.  Below k = 128 there is no loop to speak of and the
+// large tiles' long prologue and epilogue lose to 128x64 (4352 x 4864 x 64: 17.4 against 14.2),
+// unless the output is one that GemmBodyT writes past the caches.
+enum class GemmCover { k32, k64, k128x64, k256x128, k256x256 };
+GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
+  const uint64_t t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
+  if (t64 < 256) return GemmCover::k32;
+  if (t64 <= 512) return GemmCover::k64;
+  if (a.k <= 128 && (uint64_t)a.m * a.n * a.batch * 2u <= kGemmBigOutput) return GemmCover::k128x64;
+  if ((uint64_t)cdiv(a.n, 128) * cdiv(a.m, 256) * a.batch <= 256) return GemmCover::k256x128;
+  return GemmCover::k256x256;
+}
+template <class Body>
+hipError_t launch_gemm_cover(hipStream_t s, const tally_gemm_bf16_args &a, uint32_t tn, uint32_t tm, uint32_t urgent) {
+  return launch_native_t<Body>(s, &a, {cdiv(a.n, tn), cdiv(a.m, tm), a.batch}, urgent);
+}
+// Body: what covers the output where the rule asks for tiles at least as large
+template <class Body>
+hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  const uint64_t tiles64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
-  const uint64_t tiles128 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch;
-  if (tiles128 >= 512) return launch_native_t<GemmMidBodyT<2>>(s, args, {cdiv(a.n, 64), cdiv(a.m, 128), a.batch}, urgent);
-  if (tiles64 >= 384) return launch_native_t<GemmMidBodyT<1>>(s, args, {cdiv(a.n, 64), cdiv(a.m, 64), a.batch}, urgent);
-  return launch_native_t<GemmSmallBody>(s, args, g, urgent);
+  switch (gemm_cover(a)) {
+    case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
+    case GemmCover::k64: return launch_gemm_cover<GemmMidBodyT<1>>(s, a, 64, 64, urgent);
+    case GemmCover::k128x64: return launch_gemm_cover<GemmMidBodyT<2>>(s, a, 64, 128, urgent);
+    case GemmCover::k256x128: return launch_gemm_cover<GemmN128Body>(s, a, 128, 256, urgent);
+    default: return launch_native_t<Body>(s, args, g, urgent);
+  }
+}
+// The ragged GEMM: only the tiles with predicated edges, which also fit beside a paused
+// best-effort tile.  128x64 tiles pay from two per compute unit (1000 x 2300 x 768, 288 of
+// them, 12.7 us with 64x64 and 14.1; 12 x 500 x 700 x 512, 528, 21.7 and 18.7).
+hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t urgent) {
+  tally_gemm_bf16_args a;
+  memcpy(&a, args, sizeof(a));
+  if (gemm_cover(a) == GemmCover::k32) return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
+  if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512)
+    return launch_gemm_cover<GemmMidBodyT<2>>(s, a, 64, 128, urgent);
+  return launch_gemm_cover<GemmMidBodyT<1>>(s, a, 64, 64, urgent);
 }
 // (whichever of its kernels occupies most)
 hipError_t footprint_native_gemm_small(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
@@ -334,7 +371,9 @@ const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(SaxpyBody, "saxpy", grid_saxpy),
     OPS(ReduceSumBody, "reduce_sum", grid_reduce_sum),
     OPS(ReduceFinalBody, "reduce_final", grid_reduce_final),
-    OPS(GemmBody, "gemm_bf16", grid_gemm),
+    {"gemm_bf16", sizeof(GemmBody::Args), true, grid_gemm, launch_native_gemm_t<GemmBody>, launch_sliced_t<GemmBody>,
+     launch_ptb_t<GemmBody>, init_t<GemmBody>, occupancy_t<GemmBody>, pause_fraction_t<GemmBody>,
+     footprint_t<GemmBody>, footprint_native_t<GemmBody>},
     OPS(GemvBody, "gemv_bf16", grid_gemv),
     {"softmax_f32", sizeof(SoftmaxBody::Args), true, grid_softmax,
      launch_native_rows_t<SoftmaxBody, SoftmaxNarrowBody, SoftmaxTeamBody>,
@@ -351,7 +390,9 @@ const KernelOps kOps[TALLY_K_COUNT] = {
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
      pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, footprint_native_gemm_small},
-    OPS(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128),
+    {"gemm_bf16_n128", sizeof(GemmN128Body::Args), true, grid_gemm_n128, launch_native_gemm_t<GemmN128Body>,
+     launch_sliced_t<GemmN128Body>, launch_ptb_t<GemmN128Body>, init_t<GemmN128Body>, occupancy_t<GemmN128Body>,
+     pause_fraction_t<GemmN128Body>, footprint_t<GemmN128Body>, footprint_native_t<GemmN128Body>},
 };
 
 constexpr size_t kMaxArgs = 96;

@@ -250,6 +250,31 @@ def test_gemm_cfg1_full_size_sampled_tiles(env):
     assert (host(Cd) == 0x3F80).all()
 
 
+@pytest.mark.parametrize("m,n,k,batch", [(256, 768, 96, 4), (1024, 1024, 96, 1), (512, 1024, 96, 4),
+                                         (512, 768, 64, 8), (2048, 1536, 160, 1), (2048, 4352, 160, 1)])
+@pytest.mark.parametrize("n128", [False, True])
+def test_gemm_original_form_covers(env, m, n, k, batch, n128):
+    """The original form's tiles by the size of the output, on both sides of each line (192, 256
+    and 512 tiles of 64x64; short k; 96 and 272 of 256x128), operands with NaN beyond k, nothing
+    written behind C."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_bf16_close
+    name = "gemm_bf16_n128" if n128 else "gemm_bf16"
+    g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
+    a = dict(g, C=np.zeros((batch, m, n), np.uint16))
+    OS.run_native(name, OK.grid_of(name, a), a)
+    Ap = torch.full((batch, m, k + 40), 0x7FC0, dtype=torch.int16, device="cuda")
+    Bp = torch.full((batch, n, k + 8), 0x7FC0, dtype=torch.int16, device="cuda")
+    Ap[:, :, :k], Bp[:, :, :k] = dev(g["A"]), dev(g["Bt"])
+    buf = torch.full((batch * m * n + 8,), 0x7FC0, dtype=torch.int16, device="cuda")
+    Cd = buf[:batch * m * n].view(batch, m, n)
+    torch.cuda.synchronize()
+    ctx.launch_native(B.gemm_bf16(Ap[:, :, :k], Bp[:, :, :k], Cd, n128=n128))
+    torch.cuda.synchronize()
+    assert_bf16_close(host(Cd), a["C"])
+    assert (host(buf[batch * m * n:]) == 0x7FC0).all()
+
+
 # ------------------------------------------------------------------ GEMM, 32-wide ragged tiles
 @pytest.mark.parametrize("form", FORMS)
 def test_gemm_small_forms(env, form):
