@@ -512,7 +512,16 @@ struct GemmMidBodyT {
   static constexpr int NA = 2 * MB, NBL = 2;              // loads per wave and stage
   static constexpr int AHEAD = MB == 1 ? 2 : 1;           // stages on their way (registers)
 
+  static constexpr bool YIELDS = true;
+
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
+    run_impl<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15});
+  }
+  static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
+    run_impl<true>(a, bx, by, bz, ctl);
+  }
+  template <bool YIELD>
+  static __device__ __forceinline__ void run_impl(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
 #ifdef __HIP_DEVICE_COMPILE__
     __shared__ __align__(16) unsigned char s_ab[(TM + TN) * 128];
     const uint32_t lane = threadIdx.x & 63;
@@ -555,7 +564,13 @@ struct GemmMidBodyT {
     for (int i = 0; i < MB; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    uint32_t pause_left = ctl.ticks;
+    // (a look at the pause word costs this workgroup 0.7 us, two stages: eight times as many
+    // stages lie between two looks as GemmBodyT has, whose stages last eight times as long)
+    const uint32_t poll_mask = (ctl.mask << 2) | 3;
     auto step = [&](Set &s, uint32_t next) {
+      // one wave polls; the others meet it at the barrier
+      if (YIELD && ctl.ticks != 0 && wave == 0 && (next & poll_mask) == poll_mask) yield_while_preempted(ctl, pause_left);
 #pragma unroll
       for (int j = 0; j < NA; ++j)
         *reinterpret_cast<uint4 *>(sA + (wave * NA + j) * 1024 + (w_off ^ (((wave * NA + j) & 1) * 64))) = s.a[j];

@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/tally.h"
 
 namespace tally {
@@ -49,13 +51,13 @@ struct PtbCtl {
   unsigned long long *host_relay;   // pinned: (epoch << 32 | raw counter) when the relay has ended
   uint32_t *host_relay_flags;       // pinned: bit 0 the relay gave up early, bit 1 it folded a request in
   tally_cover_rec *cover;   // device, may be null
-  uint32_t total;           // logical blocks in the grid
-  uint32_t limit;           // workers treat this as the end of the grid (== total normally)
+  uint32_t parts;           // the counter counts parts of a logical block (1: whole blocks)
+  uint32_t limit;           // workers treat this as the end of the grid (normally all of it); in parts
   uint32_t epoch;           // id of this launch segment, unique for the life of the slot
   uint32_t exit_target;     // value of *exited after the last worker of this segment leaves
   uint32_t counter_base;    // raw counter value that stands for task index 0 of this job
   uint32_t workers;
-  uint32_t chunk;           // task indices per fetch
+  uint32_t chunk;           // task indices per fetch (1 where blocks have several parts)
   uint32_t single_pass;     // the workers' first fetches cover every index left: none fetches twice
   uint32_t segment;         // 0-based segment number, for the coverage records
   uint32_t gx, gy;          // logical grid extents (x fastest)
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
             p = p < c.limit ? p : c.limit;
             __hip_atomic_store(c.pre, ((unsigned long long)c.epoch << 32) | p, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(c.host_live, p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(c.host_live, p / c.parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
           }
           added = true;
           ctr0 += kPreemptStep;
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
       if (!added) {
         const uint32_t ctr = raw - c.counter_base;
         if (threadIdx.x == 0)
-          __hip_atomic_store(c.host_live, ctr < c.limit ? ctr : c.limit, __ATOMIC_RELAXED,
+          __hip_atomic_store(c.host_live, (ctr < c.limit ? ctr : c.limit) / c.parts, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
@@ -250,8 +252,68 @@ __device__ __forceinline__ void yield_while_preempted(const YieldCtl &y, uint32_
 constexpr uint32_t kPreSpinCap = 1u << 22;   // polls of `pre` before the last worker reports failure
 constexpr uint32_t kProgressLost = 0xFFFFFFFFu;
 
+// What the relay's fetch-and-add returned (in parts), once it has left it in `pre`.  The relay
+// stores it right after that fetch-and-add, whose effect the caller has seen in the counter, so
+// the wait is short and ends whatever the relay does next; the cap is a backstop that reports
+// failure instead of hanging.
+__device__ __forceinline__ uint32_t progress_at_request(const PtbCtl &c) {
+  for (uint32_t spin = 0; spin < kPreSpinCap; ++spin) {
+    const unsigned long long pre = __hip_atomic_load(c.pre, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)(pre >> 32) == c.epoch) return (uint32_t)pre;
+    __builtin_amdgcn_s_sleep(2);
+  }
+  return kProgressLost;
+}
+
+// Logical blocks in parts.  A grid of fewer blocks than there are workers leaves most of them
+// without work while the others take a whole block's time; where the workers are enough for it
+// the counter therefore hands out PX * PY parts of each block (Sub's own, smaller blocks), and
+// every worker takes at most one.  To the host nothing changes: progress is in whole blocks, and
+// a request still lets every block that was begun be finished: the parts of the block in which
+// the request fell that were not handed out before it are handed out after it, to workers that
+// would otherwise leave (there are as many fetches as parts, so all of them are).  A block is
+// recorded with its first part.
+template <class SubBody, uint32_t PX, uint32_t PY>
+struct PartsBody {
+  using Sub = SubBody;
+  using Args = typename Sub::Args;
+  static constexpr int THREADS = Sub::THREADS;
+  static constexpr int MIN_WAVES = Sub::MIN_WAVES;
+  static constexpr unsigned DYN_LDS = Sub::DYN_LDS;
+  static constexpr uint32_t PARTS_X = PX, PARTS = PX * PY;
+};
 template <class Body>
-__device__ __forceinline__ void ptb_body(const typename Body::Args &args, const PtbCtl &c) {
+__device__ __forceinline__ void ptb_parts(const typename Body::Args &args, const PtbCtl &c) {
+  using Sub = typename Body::Sub;
+  constexpr uint32_t P = Body::PARTS, PX = Body::PARTS_X, PY = P / PX;
+  __shared__ uint32_t s_idx;
+  if (threadIdx.x == 0) {
+    uint32_t idx = __hip_atomic_fetch_add(c.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - c.counter_base;
+    if (idx & kPreemptStep) {
+      idx -= kPreemptStep;
+      const uint32_t at = progress_at_request(c);
+      if (at == kProgressLost || idx >= (at + P - 1) / P * P) idx = c.limit;
+    }
+    s_idx = idx;
+  }
+  __syncthreads();
+  const uint32_t idx = __builtin_amdgcn_readfirstlane(s_idx);
+  if (idx >= c.limit) return;
+  const uint32_t block = idx / P, part = idx % P;
+  uint32_t bx, by, bz;
+  delinearize(block, c.gx, c.gy, bx, by, bz);
+  const uint32_t x = bx * PX + part % PX, y = by * PY + part / PX;
+  if constexpr (Sub::YIELDS)
+    Sub::run_yielding(args, x, y, bz,
+                      YieldCtl{c.flag_copies + (blockIdx.x % kFlagCopies) * kFlagCopyStride, c.epoch,
+                               c.flag_copies != nullptr ? c.yield_ticks : 0u, c.yield_mask});
+  else
+    Sub::run_be(args, x, y, bz);
+  if (part == 0) record(c.cover, block, bx, by, bz, c.segment, blockIdx.x);
+}
+
+template <class Body>
+__device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, const PtbCtl &c) {
   __shared__ uint32_t s_idx[2];
   const uint32_t worker = blockIdx.x;
   // One lane fetches and broadcasts through LDS, so the exit decision is uniform over the
@@ -291,33 +353,26 @@ __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const 
     // the first fetches of all workers cover what is left: a second one could only fail
     if (c.single_pass) break;
   }
-  // leave: the last worker of the segment publishes the progress to the host.
-  // All of this is relaxed on purpose: an agent- or system-scope release here would make
-  // every worker write back its whole L2 (tens of microseconds with a dirty output
-  // tile).  Ordering comes from data dependence instead: a worker adds to `exited` only
-  // after its last counter fetch has returned, so when the last worker sees the target
-  // every other fetch has been performed, and it reads the counter after that.  Kernel
-  // outputs become visible to the host at the end of the kernel as usual; the status
-  // word only says that the workers are gone.
+}
+
+// A worker leaves: the last one of the segment publishes the progress to the host.
+// All of this is relaxed on purpose: an agent- or system-scope release here would make
+// every worker write back its whole L2 (tens of microseconds with a dirty output
+// tile).  Ordering comes from data dependence instead: a worker adds to `exited` only
+// after its last counter fetch has returned, so when the last worker sees the target
+// every other fetch has been performed, and it reads the counter after that.  Kernel
+// outputs become visible to the host at the end of the kernel as usual; the status
+// word only says that the workers are gone.
+__device__ __forceinline__ void ptb_leave(const PtbCtl &c) {
   if (threadIdx.x == 0) {
     uint32_t old = __hip_atomic_fetch_add(c.exited, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (old + 1 == c.exit_target) {
       const uint32_t raw = __hip_atomic_load(c.counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t ctr = raw - c.counter_base;
       uint32_t progress = ctr < c.limit ? ctr : c.limit;
-      if (ctr & kPreemptStep) {
-        // a request was folded in: the progress is what the relay's fetch-and-add returned.
-        // The relay stores it right after that fetch-and-add, which has been performed
-        // (its effect is in the counter), so this wait is short and ends whatever the
-        // relay does next; the cap is a backstop that reports failure instead of hanging.
-        progress = kProgressLost;
-        for (uint32_t spin = 0; spin < kPreSpinCap; ++spin) {
-          const unsigned long long pre =
-              __hip_atomic_load(c.pre, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if ((uint32_t)(pre >> 32) == c.epoch) { progress = (uint32_t)pre; break; }
-          __builtin_amdgcn_s_sleep(2);
-        }
-      }
+      // a request was folded in: the progress is what the relay's fetch-and-add returned
+      if (ctr & kPreemptStep) progress = progress_at_request(c);
+      if (progress != kProgressLost) progress = (progress + c.parts - 1) / c.parts;   // every begun block is done
       __hip_atomic_store(c.host_raw, raw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       if (progress != kProgressLost)
         __hip_atomic_store(c.host_live, progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -326,6 +381,16 @@ __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const 
                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
+}
+template <class Body, class = void>
+struct HasParts : std::false_type {};
+template <class Body>
+struct HasParts<Body, std::void_t<typename Body::Sub>> : std::true_type {};
+template <class Body>
+__device__ __forceinline__ void ptb_body(const typename Body::Args &args, const PtbCtl &c) {
+  if constexpr (HasParts<Body>::value) ptb_parts<Body>(args, c);
+  else ptb_blocks<Body>(args, c);
+  ptb_leave(c);
 }
 template <class Body>
 __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void ptb_kernel(typename Body::Args args, PtbCtl c) {

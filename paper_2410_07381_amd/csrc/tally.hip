@@ -65,6 +65,8 @@ struct KernelOps {
   hipError_t (*footprint)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
   // the same for one workgroup of the kernel in its original form
   hipError_t (*footprint_native)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
+  // parts the persistent-worker form splits each of `blocks` logical blocks in (null: never)
+  uint32_t (*parts)(uint64_t blocks, uint32_t workers);
 };
 
 template <class Body>
@@ -232,6 +234,39 @@ hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3,
     return launch_gemm_cover<GemmMidBodyT<2>>(s, a, 64, 128, urgent);
   return launch_gemm_cover<GemmMidBodyT<1>>(s, a, 64, 64, urgent);
 }
+// Persistent workers of a grid so small that a worker per part of a block suffices: the smallest
+// parts for which it does.  PX x PY parts of a 256 x TN block, in the order of gemm_cover's table
+// (one workgroup per compute unit, k = 2048: 6 / 12 / 17 / 25 us a part against 40 for a 256x256
+// block).  In parts the counter stays far below the bit that a request sets.
+template <class Body>
+struct GemmParts {
+  static constexpr uint32_t X = Body::TILE_N / 32, Y = Body::TILE / 32;
+  typedef PartsBody<GemmSmallBody, X, Y> P32;
+  typedef PartsBody<GemmMidBodyT<1>, X / 2, Y / 2> P64;
+  typedef PartsBody<GemmMidBodyT<2>, X / 2, Y / 4> P128;
+  typedef PartsBody<GemmN128Body, X / 4, 1> PN128;
+  static uint32_t parts(uint64_t blocks, uint32_t workers) {
+    for (uint32_t p : {P32::PARTS, P64::PARTS, P128::PARTS, PN128::PARTS})
+      if (blocks * p <= workers) return p;
+    return 1;
+  }
+  static hipError_t launch(hipStream_t s, const void *args, const PtbCtl &c) {
+    if (c.parts == 1) return launch_ptb_t<Body>(s, args, c);
+    if (c.parts == P32::PARTS) return launch_ptb_t<P32>(s, args, c);
+    if (c.parts == P64::PARTS) return launch_ptb_t<P64>(s, args, c);
+    if (c.parts == P128::PARTS) return launch_ptb_t<P128>(s, args, c);
+    if constexpr (PN128::PARTS > 1) return launch_ptb_t<PN128>(s, args, c);
+    return hipErrorInvalidValue;
+  }
+  static hipError_t init() {
+    const hipError_t e = init_t<Body>();
+    if constexpr (PN128::PARTS > 1)
+      if (e == hipSuccess)
+        return hipFuncSetAttribute((const void *)ptb_kernel<PN128>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   PN128::DYN_LDS);
+    return e;
+  }
+};
 // (whichever of its kernels occupies most)
 hipError_t footprint_native_gemm_small(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
   *lds_bytes = *waves = *regs_per_lane = 0;
@@ -372,8 +407,8 @@ const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(ReduceSumBody, "reduce_sum", grid_reduce_sum),
     OPS(ReduceFinalBody, "reduce_final", grid_reduce_final),
     {"gemm_bf16", sizeof(GemmBody::Args), true, grid_gemm, launch_native_gemm_t<GemmBody>, launch_sliced_t<GemmBody>,
-     launch_ptb_t<GemmBody>, init_t<GemmBody>, occupancy_t<GemmBody>, pause_fraction_t<GemmBody>,
-     footprint_t<GemmBody>, footprint_native_t<GemmBody>},
+     GemmParts<GemmBody>::launch, GemmParts<GemmBody>::init, occupancy_t<GemmBody>, pause_fraction_t<GemmBody>,
+     footprint_t<GemmBody>, footprint_native_t<GemmBody>, GemmParts<GemmBody>::parts},
     OPS(GemvBody, "gemv_bf16", grid_gemv),
     {"softmax_f32", sizeof(SoftmaxBody::Args), true, grid_softmax,
      launch_native_rows_t<SoftmaxBody, SoftmaxNarrowBody, SoftmaxTeamBody>,
@@ -391,8 +426,9 @@ const KernelOps kOps[TALLY_K_COUNT] = {
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
      pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, footprint_native_gemm_small},
     {"gemm_bf16_n128", sizeof(GemmN128Body::Args), true, grid_gemm_n128, launch_native_gemm_t<GemmN128Body>,
-     launch_sliced_t<GemmN128Body>, launch_ptb_t<GemmN128Body>, init_t<GemmN128Body>, occupancy_t<GemmN128Body>,
-     pause_fraction_t<GemmN128Body>, footprint_t<GemmN128Body>, footprint_native_t<GemmN128Body>},
+     launch_sliced_t<GemmN128Body>, GemmParts<GemmN128Body>::launch, GemmParts<GemmN128Body>::init,
+     occupancy_t<GemmN128Body>, pause_fraction_t<GemmN128Body>, footprint_t<GemmN128Body>,
+     footprint_native_t<GemmN128Body>, GemmParts<GemmN128Body>::parts},
 };
 
 constexpr size_t kMaxArgs = 96;
@@ -630,9 +666,14 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   // The counter is never rewound: failed fetches of the last segment (after a request, or
   // beyond a stop_at limit) have advanced it, so the value that stands for task index 0
   // moves instead, such that the next index handed out is `start` again.
-  j->counter_base = ctx->slot_counter[slot] - start;
   j->epoch = ctx->slot_epoch[slot] + 1;
   j->limit = limit < j->total ? limit : j->total;
+  const uint64_t blocks = j->limit > start ? j->limit - start : 0u;
+  // (with indices counted in parts, the end of the grid has to stay a valid index)
+  uint32_t parts = j->ops->parts && blocks ? j->ops->parts(blocks, j->workers) : 1u;
+  if ((uint64_t)j->limit * parts > 0x40000000ull) parts = 1;
+  const uint32_t chunk = parts > 1 ? 1u : j->chunk;
+  j->counter_base = ctx->slot_counter[slot] - start * parts;
   __atomic_store_n(j->h_flag(), 0u, __ATOMIC_RELEASE);   // no request stands against the new segment
   j->request_word = 0;
   PtbCtl c;
@@ -646,15 +687,14 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   c.host_relay = (unsigned long long *)(j->h_base_dev() + 80);
   c.host_relay_flags = (uint32_t *)(j->h_base_dev() + 88);
   c.cover = j->cover;
-  c.total = j->total;
-  c.limit = j->limit;
+  c.parts = parts;
+  c.limit = j->limit * parts;
   c.epoch = j->epoch;
   c.exit_target = ctx->slot_exited[slot] + j->workers;
   c.counter_base = j->counter_base;
   c.workers = j->workers;
-  c.chunk = j->chunk;
-  c.single_pass = (j->limit > start ? (uint64_t)(j->limit - start) : 0ull) <=
-                          (uint64_t)j->chunk * j->workers ? 1u : 0u;
+  c.chunk = chunk;
+  c.single_pass = blocks * parts <= (uint64_t)chunk * j->workers ? 1u : 0u;
   c.segment = j->segments;
   c.gx = j->grid.x;
   c.gy = j->grid.y;

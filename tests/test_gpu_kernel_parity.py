@@ -275,6 +275,88 @@ def test_gemm_original_form_covers(env, m, n, k, batch, n128):
     assert (host(buf[batch * m * n:]) == 0x7FC0).all()
 
 
+def _ptb_parts_case(B, torch, m, n, k, batch, n128):
+    from gpu_util import dev
+    name = "gemm_bf16_n128" if n128 else "gemm_bf16"
+    g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
+    a = dict(g, C=np.zeros((batch, m, n), np.uint16))
+    grid = OK.grid_of(name, a)
+    OS.run_native(name, grid, a)
+    A, Bt = dev(g["A"]), dev(g["Bt"])
+    Cd = torch.full((batch, m, n), 0x7FC0, dtype=torch.int16, device="cuda")
+    torch.cuda.synchronize()
+    return a["C"], Cd, B.gemm_bf16(A, Bt, Cd, n128=n128), grid
+
+
+def _check_blocks(got, want, grid, tn, done):
+    """Blocks [0, done) of the grid hold the product, the others what was there before (NaN)."""
+    from gpu_util import assert_bf16_close
+    for idx in range(grid[0] * grid[1] * grid[2]):
+        bx, by, bz = idx % grid[0], idx // grid[0] % grid[1], idx // (grid[0] * grid[1])
+        r, c = slice(by * 256, by * 256 + 256), slice(bx * tn, bx * tn + tn)
+        if idx < done:
+            assert_bf16_close(got[bz, r, c], want[bz, r, c])
+        else:
+            assert (got[bz, r, c] == 0x7FC0).all()
+
+
+@pytest.mark.parametrize("m,n,batch", [(256, 256, 3), (512, 768, 2), (768, 1024, 2), (1024, 1536, 2)])
+@pytest.mark.parametrize("k", [96, 1056])
+@pytest.mark.parametrize("n128", [False, True])
+def test_gemm_workers_take_parts_of_blocks(env, m, n, batch, k, n128):
+    """Grids of fewer blocks than workers (3 to 96 blocks, 256 workers: every size of part):
+    coverage by whole blocks, a stop between blocks and the rest from there."""
+    B, ctx, torch = env
+    from gpu_util import host
+    want, Cd, kern, grid = _ptb_parts_case(B, torch, m, n, k, batch, n128)
+    total, tn = kern.total_blocks, 128 if n128 else 256
+    stop = total // 2 + 1
+    job = ctx.launch_ptb(kern, 256, chunk=2, coverage=True, stop_at=stop)
+    assert job.wait() == B.JOB_STOPPED and job.progress()[0] == stop
+    torch.cuda.synchronize()
+    _check_blocks(host(Cd), want, grid, tn, stop)
+    job.resume()
+    assert job.wait() == B.JOB_COMPLETE and job.progress()[0] == total
+    rec = job.coverage()
+    job.free()
+    torch.cuda.synchronize()
+    _check_blocks(host(Cd), want, grid, tn, total)
+    idx = np.arange(total)
+    assert (rec["count"] == 1).all() and (rec["worker"] < 256).all()
+    assert (rec["segment"] == (idx >= stop)).all()
+    assert (rec["bx"] == idx % grid[0]).all() and (rec["bz"] == idx // (grid[0] * grid[1])).all()
+
+
+@pytest.mark.parametrize("m,n,n128", [(512, 512, False), (1024, 1024, False), (2048, 2048, False), (512, 512, True)])
+def test_gemm_parts_preempted_anywhere(env, m, n, n128):
+    """A request at any moment leaves whole blocks: those below the progress are finished, parts
+    handed out after the request included, and the others are untouched."""
+    import time
+    B, ctx, torch = env
+    from gpu_util import host
+    want, Cd, kern, grid = _ptb_parts_case(B, torch, m, n, 512, 1, n128)
+    tn = 128 if n128 else 256
+    for delay_us in (0, 2, 4, 6, 8, 10, 12, 15, 20, 30):
+        Cd.fill_(0x7FC0)
+        torch.cuda.synchronize()
+        job = ctx.launch_ptb(kern, 256, coverage=True)
+        t0 = time.perf_counter()
+        while (time.perf_counter() - t0) * 1e6 < delay_us:
+            pass
+        job.preempt()
+        state = job.wait()
+        done, total, _ = job.progress()
+        assert (state == B.JOB_COMPLETE) == (done == total)
+        torch.cuda.synchronize()
+        _check_blocks(host(Cd), want, grid, tn, done)
+        job.resume()
+        assert job.wait() == B.JOB_COMPLETE
+        assert (job.coverage()["count"] == 1).all()
+        job.free()
+        torch.cuda.synchronize()
+        _check_blocks(host(Cd), want, grid, tn, total)
+
+
 # ------------------------------------------------------------------ GEMM, 32-wide ragged tiles
 @pytest.mark.parametrize("form", FORMS)
 def test_gemm_small_forms(env, form):
