@@ -47,9 +47,9 @@ struct PtbCtl {
   const uint32_t *host_flag;  // pinned host memory: epoch the host wants preempted (| kNoPauseBit)
   unsigned long long *host_status;  // pinned: (epoch << 32 | progress) once drained
   uint32_t *host_live;      // pinned: progress mirrored while running
-  uint32_t *host_raw;       // pinned: raw counter value at the drain (written before status)
+  unsigned long long *host_raw;     // pinned: (epoch << 32 | raw counter) at the drain
   unsigned long long *host_relay;   // pinned: (epoch << 32 | raw counter) when the relay has ended
-  uint32_t *host_relay_flags;       // pinned: bit 0 the relay gave up early, bit 1 it folded a request in
+  unsigned long long *host_gave_up; // pinned: (epoch << 32 | 1 if the relay gave up early), written with it
   tally_cover_rec *cover;   // device, may be null
   uint32_t parts;           // the counter counts parts of a logical block (1: whole blocks)
   uint32_t limit;           // workers treat this as the end of the grid (normally all of it); in parts
@@ -165,34 +165,37 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
   uint32_t ctr0 = scalar_load_coherent(c.counter);
   const uint32_t gone0 = scalar_load_coherent(c.exited);
   bool alive = false;
+  uint32_t mirrored = 0u;
   for (uint32_t n = 0;; ++n) {
     // once the request is in the counter only its withdrawal (the end of a pause) is news
     // from the host, and the exit counter is what matters: look at the host less often
-    if (!added || (n & 3u) == 0u) {
-      const uint32_t want = scalar_load_coherent(c.host_flag);
-      if (want != last) {
-        const bool mine = (want & ~kNoPauseBit) == c.epoch;
-        if (mine && !added) {
-          uint32_t p = 0;
-          if (threadIdx.x == 0) {
-            const uint32_t old = __hip_atomic_fetch_add(c.counter, kPreemptStep, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
-            p = old - c.counter_base;
-            p = p < c.limit ? p : c.limit;
-            __hip_atomic_store(c.pre, ((unsigned long long)c.epoch << 32) | p, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(c.host_live, p / c.parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          }
-          added = true;
-          ctr0 += kPreemptStep;
-        }
-        // pause word: this segment's epoch while its workers are to pause inside blocks
-        const uint32_t pause = (mine && !(want & kNoPauseBit)) ? c.epoch : 0u;
-        if (c.flag_copies != nullptr && threadIdx.x < kFlagCopies)
-          __hip_atomic_store(c.flag_copies + threadIdx.x * kFlagCopyStride, pause, __ATOMIC_RELAXED,
+    // (host's word and exit counter one after the other, about 2 us a round: asked for together
+    // they made the worker beside the relay fall behind the others, 100 us of a training-like
+    // step of 7890, and slower rounds are felt by the requests)
+    uint32_t want = last;
+    if (!added || (n & 3u) == 0u) want = scalar_load_coherent(c.host_flag);
+    if (want != last) {
+      const bool mine = (want & ~kNoPauseBit) == c.epoch;
+      if (mine && !added) {
+        uint32_t p = 0;
+        if (threadIdx.x == 0) {
+          const uint32_t old = __hip_atomic_fetch_add(c.counter, kPreemptStep, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+          p = old - c.counter_base;
+          p = p < c.limit ? p : c.limit;
+          __hip_atomic_store(c.pre, ((unsigned long long)c.epoch << 32) | p, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
-        last = want;
+          __hip_atomic_store(c.host_live, p / c.parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        added = true;
+        ctr0 += kPreemptStep;
       }
+      // pause word: this segment's epoch while its workers are to pause inside blocks
+      const uint32_t pause = (mine && !(want & kNoPauseBit)) ? c.epoch : 0u;
+      if (c.flag_copies != nullptr && threadIdx.x < kFlagCopies)
+        __hip_atomic_store(c.flag_copies + threadIdx.x * kFlagCopyStride, pause, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      last = want;
     }
     // the counters of a slot only ever grow (they are never reset), so a relay that
     // starts late, even after its workers are long gone, still sees the target passed
@@ -204,11 +207,13 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
       const uint32_t raw = scalar_load_coherent(c.counter);
       if (raw != ctr0 || gone != gone0) alive = true;
       if (!alive && wall_clock64() - born > kRelayGiveUpTicks) { gave_up = true; break; }
-      if (!added) {
-        const uint32_t ctr = raw - c.counter_base;
+      // (only news: a store to the host occupies the vector-memory queue of the compute unit for a
+      // microsecond, and whichever worker shares that unit falls behind the others)
+      const uint32_t ctr = raw - c.counter_base, live = (ctr < c.limit ? ctr : c.limit) / c.parts;
+      if (!added && live != mirrored) {
         if (threadIdx.x == 0)
-          __hip_atomic_store(c.host_live, (ctr < c.limit ? ctr : c.limit) / c.parts, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_SYSTEM);
+          __hip_atomic_store(c.host_live, live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        mirrored = live;
       }
     }
   }
@@ -216,12 +221,12 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
   // the counter holds now (every worker has exited unless the relay gave up, in which case
   // the last worker's own report is the final one).
   if (threadIdx.x == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no mirrored progress may land after this report)
     const uint32_t raw = __hip_atomic_load(c.counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(c.host_relay_flags, (gave_up ? 1u : 0u) | (added ? 2u : 0u), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __hip_atomic_store(c.host_relay, ((unsigned long long)c.epoch << 32) | raw, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
+    // (each word carries the epoch: the host waits for both, so they need no order)
+    const unsigned long long tag = (unsigned long long)c.epoch << 32;
+    __hip_atomic_store(c.host_gave_up, tag | (gave_up ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(c.host_relay, tag | raw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -373,12 +378,10 @@ __device__ __forceinline__ void ptb_leave(const PtbCtl &c) {
       // a request was folded in: the progress is what the relay's fetch-and-add returned
       if (ctr & kPreemptStep) progress = progress_at_request(c);
       if (progress != kProgressLost) progress = (progress + c.parts - 1) / c.parts;   // every begun block is done
-      __hip_atomic_store(c.host_raw, raw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      if (progress != kProgressLost)
-        __hip_atomic_store(c.host_live, progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // both acknowledged before the status
-      __hip_atomic_store(c.host_status, ((unsigned long long)c.epoch << 32) | progress,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      // (both words carry the epoch and need no order, hence no round trip to the host between them)
+      const unsigned long long tag = (unsigned long long)c.epoch << 32;
+      __hip_atomic_store(c.host_status, tag | progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(c.host_raw, tag | raw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
 }

@@ -437,7 +437,8 @@ constexpr int kMaxShunned = 64;
 constexpr int kMaxSide = 2 * 8 + 2;
 constexpr int kMaxBeClients = 8;
 constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited, 128 B apart
-constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,raw,relay,relay_flags | slice_done
+constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw | slice_done,ended
+constexpr size_t kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostEnded = 132;
 constexpr size_t kCopySlotBytes = kFlagCopies * kFlagCopyStride * sizeof(uint32_t);
 
 enum JobKind { KIND_PTB = 0, KIND_SLICED = 1, KIND_NATIVE = 2 };
@@ -493,6 +494,8 @@ struct tally_ctx {
   // device words of a slot are never reset: the host tracks their current values instead
   // (slot_counter: the raw task counter as the slot's last job left it)
   uint32_t slot_counter[kSlots], slot_exited[kSlots], slot_epoch[kSlots];
+  bool slot_relay[kSlots];     // the relay of epoch slot_epoch may still be running (its report is not in)
+  hipStream_t slot_ctl[kSlots];  // the stream it went to
   uint32_t *marker_host;     // pinned: [0] hi, [32] be (separate lines)
   uint32_t *marker_dev;
   uint32_t num_cus;
@@ -504,6 +507,7 @@ struct tally_ctx {
   uint32_t yield_ticks;      // bound of a mid-block pause, 10 ns ticks
   uint32_t yield_every;      // steps between two looks at the pause word (a power of two)
   void *static_attn_scratch; // this device's address of static_scratch
+  std::atomic<uint32_t> wait_seq;   // numbers the markers that waits put on a stream
   int device;
   int live_jobs;
   // profile-guided configuration (Section 4.2): per (kernel, grid, block) the candidate
@@ -530,7 +534,6 @@ struct tally_job {
   uint32_t yield_every;
   uint32_t counter_base;     // raw counter value standing for task index 0
   uint32_t segments;         // launch segments so far
-  bool relay_pending;        // a relay of this job may still be running (its report is not in)
   bool failed;               // the device could not report the progress of a preempted segment
   std::atomic<uint32_t> request_word;  // what was last stored in the host's request word
   // sliced
@@ -548,9 +551,7 @@ struct tally_job {
   uint32_t *h_flag() { return (uint32_t *)h_base(); }
   unsigned long long *h_status() { return (unsigned long long *)(h_base() + 64); }
   uint32_t *h_live() { return (uint32_t *)(h_base() + 72); }
-  uint32_t *h_raw() { return (uint32_t *)(h_base() + 76); }
-  unsigned long long *h_relay() { return (unsigned long long *)(h_base() + 80); }
-  uint32_t *h_relay_flags() { return (uint32_t *)(h_base() + 88); }
+  uint32_t *h_ended() { return (uint32_t *)(h_base() + kHostEnded); }
   uint32_t *h_slice_done() { return (uint32_t *)(h_base() + 128); }
 };
 
@@ -573,6 +574,33 @@ int check_desc(const tally_kernel_desc *d, const KernelOps **ops_out, tally_dim3
   return TALLY_OK;
 }
 
+// The relay of a slot's last segment reports when it has ended and what the counter then
+// held.  Until that report is in, the relay may still fold a late request into the counter,
+// so neither a new segment nor a new job may use the slot's counter.  The relay ends within
+// microseconds of its workers (or after its 20 ms give-up bound when it ran before them); a
+// freed job leaves the waiting to whoever takes the slot next, 64 jobs later as a rule.
+int settle_relay(tally_ctx *ctx, int slot) {
+  if (!ctx->slot_relay[slot]) return TALLY_OK;
+  const uint32_t epoch = ctx->slot_epoch[slot];
+  unsigned char *h = ctx->host_pool + slot * kHostSlotBytes;
+  auto word = [&](size_t at) { return __atomic_load_n((unsigned long long *)(h + at), __ATOMIC_ACQUIRE); };
+  for (uint64_t spins = 1;; ++spins) {
+    const unsigned long long r = word(kHostRelay), gave_up = word(kHostGaveUp), raw = word(kHostRaw);
+    if ((uint32_t)(r >> 32) == epoch && (uint32_t)(gave_up >> 32) == epoch) {
+      // a relay that gave up ended before its workers: their own report has the final value
+      if (!((uint32_t)gave_up & 1u) || (uint32_t)(raw >> 32) == epoch) {
+        ctx->slot_counter[slot] = (uint32_t)(((uint32_t)gave_up & 1u) ? raw : r);
+        ctx->slot_relay[slot] = false;
+        return TALLY_OK;
+      }
+    }
+    if ((spins & 0xFFFFFu) == 0) {
+      hipError_t q = hipStreamQuery(ctx->slot_ctl[slot]);
+      if (q != hipSuccess && q != hipErrorNotReady) { g_last_hip = (int)q; return TALLY_ERR_HIP; }
+    }
+  }
+}
+
 int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverage, tally_job **out) {
   const KernelOps *ops;
   tally_dim3 g;
@@ -586,6 +614,8 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
     if (!ctx->slot_used[s]) { slot = s; break; }
   }
   if (slot < 0) return TALLY_ERR_NOMEM;
+  rc = settle_relay(ctx, slot);
+  if (rc) return rc;
   ctx->next_slot = (slot + 1) % kSlots;
   tally_job *j = new (std::nothrow) tally_job();
   if (!j) return TALLY_ERR_NOMEM;
@@ -606,7 +636,6 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
   j->yield_ticks = ctx->yield_ticks;
   j->yield_every = ctx->yield_every;
   j->limit = j->total;
-  j->relay_pending = false;
   j->failed = false;
   j->request_word = 0;
   j->slice_blocks = j->max_in_flight = j->next_off = j->issued = j->retired = j->segment = 0;
@@ -626,33 +655,11 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
     return e == hipErrorOutOfMemory ? TALLY_ERR_NOMEM : TALLY_ERR_HIP;
   }
   memset(j->h_base(), 0, kHostSlotBytes);
+  *j->h_ended() = ctx->wait_seq.load();
   ctx->slot_used[slot] = true;
   ctx->live_jobs++;
   *out = j;
   return TALLY_OK;
-}
-
-// The relay of the job's last segment reports when it has ended and what the counter then
-// held.  Until that report is in, the relay may still fold a late request into the counter,
-// so neither a new segment nor a new job may use the slot's counter.  The relay ends within
-// microseconds of its workers (or after its 20 ms give-up bound when it ran before them).
-int settle_relay(tally_job *j) {
-  if (!j->relay_pending) return TALLY_OK;
-  for (uint64_t spins = 1;; ++spins) {
-    const unsigned long long r = __atomic_load_n(j->h_relay(), __ATOMIC_ACQUIRE);
-    if ((uint32_t)(r >> 32) == j->epoch) {
-      const uint32_t flags = __atomic_load_n(j->h_relay_flags(), __ATOMIC_RELAXED);
-      // a relay that gave up ended before its workers: their own report has the final value
-      const uint32_t raw = (flags & 1u) ? __atomic_load_n(j->h_raw(), __ATOMIC_RELAXED) : (uint32_t)r;
-      j->ctx->slot_counter[j->slot] = raw;
-      j->relay_pending = false;
-      return TALLY_OK;
-    }
-    if ((spins & 0xFFFFFu) == 0) {
-      hipError_t q = hipStreamQuery(j->ctl);
-      if (q != hipSuccess && q != hipErrorNotReady) { g_last_hip = (int)q; return TALLY_ERR_HIP; }
-    }
-  }
 }
 
 // Launch the workers (and their relay) for task indices [progress, limit).  Requires the
@@ -660,7 +667,7 @@ int settle_relay(tally_job *j) {
 int ptb_launch_segment(tally_job *j, uint32_t limit) {
   tally_ctx *ctx = j->ctx;
   const int slot = j->slot;
-  int rc = settle_relay(j);
+  int rc = settle_relay(ctx, slot);
   if (rc) return rc;
   const uint32_t start = j->progress.load();
   // The counter is never rewound: failed fetches of the last segment (after a request, or
@@ -683,9 +690,9 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   c.host_flag = (const uint32_t *)j->h_base_dev();
   c.host_status = (unsigned long long *)(j->h_base_dev() + 64);
   c.host_live = (uint32_t *)(j->h_base_dev() + 72);
-  c.host_raw = (uint32_t *)(j->h_base_dev() + 76);
-  c.host_relay = (unsigned long long *)(j->h_base_dev() + 80);
-  c.host_relay_flags = (uint32_t *)(j->h_base_dev() + 88);
+  c.host_raw = (unsigned long long *)(j->h_base_dev() + kHostRaw);
+  c.host_relay = (unsigned long long *)(j->h_base_dev() + kHostRelay);
+  c.host_gave_up = (unsigned long long *)(j->h_base_dev() + kHostGaveUp);
   c.cover = j->cover;
   c.parts = parts;
   c.limit = j->limit * parts;
@@ -714,7 +721,8 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
     g_last_hip = (int)e;
     return TALLY_ERR_HIP;
   }
-  j->relay_pending = true;
+  ctx->slot_relay[slot] = true;
+  ctx->slot_ctl[slot] = j->ctl;
   e = j->ops->ptb(j->be, j->args, c);
   ctx->slot_epoch[slot] = j->epoch;
   ctx->slot_exited[slot] = c.exit_target;
@@ -897,7 +905,9 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
   memset(c->slot_counter, 0, sizeof(c->slot_counter));
   memset(c->slot_exited, 0, sizeof(c->slot_exited));
   memset(c->slot_epoch, 0, sizeof(c->slot_epoch));
+  memset(c->slot_relay, 0, sizeof(c->slot_relay));
   c->live_jobs = 0;
+  c->wait_seq = 0;
   c->next_slot = 0;
   c->n_shunned = 0;
   c->n_side = 0;
@@ -1219,6 +1229,14 @@ int tally_pump(tally_job *job) {
 
 int tally_wait(tally_job *job, int *state) {
   if (!job) return TALLY_ERR_INVALID_ARG;
+  const uint32_t issued = job->issued;
+  uint32_t seq = 0;
+  bool marked = false;
+  if (job->kind == KIND_PTB) {
+    seq = ++job->ctx->wait_seq;
+    hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, job->be, (uint32_t *)(job->h_base_dev() + kHostEnded), seq);
+    marked = hipGetLastError() == hipSuccess;
+  }
   for (uint32_t spins = 1;; ++spins) {
     int rc = tally_pump(job);
     if (rc) return rc;
@@ -1231,7 +1249,20 @@ int tally_wait(tally_job *job, int *state) {
       if (q != hipSuccess && q != hipErrorNotReady) { g_last_hip = (int)q; return TALLY_ERR_HIP; }
     }
   }
-  HIPCHK(hipStreamSynchronize(job->be));
+  // Everything on the best-effort stream before this call has to have ended, not only the
+  // workers' last instruction.  A marker behind it says so 5 us sooner than the runtime's own
+  // wait, which enqueues one only now; a sub-kernel enqueued by this call has one already.
+  if (marked) {
+    for (uint32_t spins = 1; (int32_t)(__atomic_load_n(job->h_ended(), __ATOMIC_ACQUIRE) - seq) < 0; ++spins) {
+      if ((spins & 0xFFFFu) == 0) {
+        hipError_t q = hipStreamQuery(job->be);
+        if (q == hipSuccess) break;
+        if (q != hipErrorNotReady) { g_last_hip = (int)q; return TALLY_ERR_HIP; }
+      }
+    }
+  } else if (job->kind != KIND_SLICED || job->issued == issued) {
+    HIPCHK(hipStreamSynchronize(job->be));
+  }
   if (state) *state = job->state.load();
   return TALLY_OK;
 }
@@ -1246,12 +1277,6 @@ int tally_job_free(tally_job *job) {
   if (job->cover) {
     (void)hipStreamSynchronize(job->be);
     (void)hipFree(job->cover);
-  }
-  if (job->kind == KIND_PTB) {
-    // the slot's counter may not be handed to another job before this job's last relay has
-    // ended (it could still fold a late request in) and has reported the counter's value
-    refresh(job);
-    (void)settle_relay(job);
   }
   ctx->slot_used[job->slot] = false;
   ctx->live_jobs--;
