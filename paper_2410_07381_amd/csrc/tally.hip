@@ -148,11 +148,11 @@ hipError_t footprint_native_t(uint32_t *lds_bytes, uint32_t *waves, uint32_t *re
   return hipSuccess;
 }
 hipError_t footprint_attn(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
-  hipFuncAttributes attr;
-  hipError_t e = hipFuncGetAttributes(&attr, (const void *)attn_decode_partial);
+  hipFuncAttributes attr;   // (the kernel of eight waves: the other occupies less)
+  hipError_t e = hipFuncGetAttributes(&attr, (const void *)attn_decode_partial<8>);
   if (e != hipSuccess) return e;
   *lds_bytes = (uint32_t)attr.sharedSizeBytes;
-  *waves = 4;
+  *waves = 8;
   *regs_per_lane = ((uint32_t)attr.numRegs + 7u) & ~7u;
   return hipSuccess;
 }

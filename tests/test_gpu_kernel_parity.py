@@ -561,6 +561,24 @@ def test_attn_decode(env, tokens, heads, scale):
     assert (host(out) == first).all()
 
 
+@pytest.mark.parametrize("tokens,heads", [(3840, 3), (3841, 3), (4081, 16), (4096, 17), (9001, 4)])
+def test_attn_decode_waves_per_workgroup(env, tokens, heads):
+    """Both sides of the lines between four and eight waves per workgroup (16 heads, 256 tokens per
+    workgroup), a last split that is short or nearly empty."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_bf16_close
+    at = TI.attn_decode_inputs(tokens, heads, 128, scale=0.5)
+    a = dict(at, out=np.zeros((heads, 128), np.uint16))
+    OS.run_native("attn_decode_bf16", OK.grid_of("attn_decode_bf16", a), a)
+    out = dev(np.zeros((heads, 128), np.uint16))
+    scratch = torch.full((B.attn_decode_scratch_bytes(heads),), 0xFF, dtype=torch.uint8, device="cuda")
+    q, Kc, Vc = dev(at["q"]), dev(at["K"]), dev(at["V"])
+    torch.cuda.synchronize()
+    ctx.launch_native(B.attn_decode_bf16(q, Kc, Vc, out, scratch), hi=True)
+    torch.cuda.synchronize()
+    assert_bf16_close(host(out), a["out"])
+
+
 def test_attn_decode_longest_cache(env):
     """16 splits x 2048 tokens is the longest cache one call takes; one token more is refused."""
     B, ctx, torch = env
