@@ -59,6 +59,7 @@ struct PtbCtl {
   uint32_t workers;
   uint32_t chunk;           // task indices per fetch (1 where blocks have several parts)
   uint32_t single_pass;     // the workers' first fetches cover every index left: none fetches twice
+  uint32_t whole;           // fetches of whole blocks per worker before it takes parts (TailBody)
   uint32_t segment;         // 0-based segment number, for the coverage records
   uint32_t gx, gy;          // logical grid extents (x fastest)
   uint32_t yield_ticks;     // longest pause inside ONE block, in 10 ns wall-clock ticks (0: never)
@@ -287,34 +288,75 @@ struct PartsBody {
   static constexpr unsigned DYN_LDS = Sub::DYN_LDS;
   static constexpr uint32_t PARTS_X = PX, PARTS = PX * PY;
 };
+// The same for the last blocks of a grid that does not divide by the workers: each worker takes
+// `whole` whole blocks (one fetch of PARTS parts each), then parts, so that the last round, in
+// which most workers would find nothing, takes a part's time.  Nothing depends on the order in
+// which the workers get there: a fetch of PARTS that comes after another worker's first part
+// runs what it got part by part.
+template <class WholeBody, class SubBody, uint32_t PX, uint32_t PY>
+struct TailBody : PartsBody<SubBody, PX, PY> {
+  using Whole = WholeBody;
+  static constexpr int MIN_WAVES = Whole::MIN_WAVES;
+  static constexpr unsigned DYN_LDS = Whole::DYN_LDS > SubBody::DYN_LDS ? Whole::DYN_LDS : SubBody::DYN_LDS;
+};
+
+// One fetch of `add` parts: the parts [first, last) to run, none if last <= first.
+__device__ __forceinline__ uint2 fetch_parts(const PtbCtl &c, uint32_t add, uint32_t P) {
+  uint32_t idx = __hip_atomic_fetch_add(c.counter, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - c.counter_base;
+  uint32_t end = c.limit;
+  if (idx & kPreemptStep) {
+    idx -= kPreemptStep;
+    const uint32_t at = progress_at_request(c);
+    end = at == kProgressLost ? 0u : (at + P - 1) / P * P;
+  }
+  return make_uint2(idx, idx + add < end ? idx + add : end);
+}
+
+// part `idx` of the grid (counted in parts)
 template <class Body>
-__device__ __forceinline__ void ptb_parts(const typename Body::Args &args, const PtbCtl &c) {
+__device__ __forceinline__ void run_part(const typename Body::Args &args, const PtbCtl &c, const YieldCtl &y, uint32_t idx) {
   using Sub = typename Body::Sub;
   constexpr uint32_t P = Body::PARTS, PX = Body::PARTS_X, PY = P / PX;
-  __shared__ uint32_t s_idx;
-  if (threadIdx.x == 0) {
-    uint32_t idx = __hip_atomic_fetch_add(c.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - c.counter_base;
-    if (idx & kPreemptStep) {
-      idx -= kPreemptStep;
-      const uint32_t at = progress_at_request(c);
-      if (at == kProgressLost || idx >= (at + P - 1) / P * P) idx = c.limit;
-    }
-    s_idx = idx;
-  }
-  __syncthreads();
-  const uint32_t idx = __builtin_amdgcn_readfirstlane(s_idx);
-  if (idx >= c.limit) return;
   const uint32_t block = idx / P, part = idx % P;
   uint32_t bx, by, bz;
   delinearize(block, c.gx, c.gy, bx, by, bz);
-  const uint32_t x = bx * PX + part % PX, y = by * PY + part / PX;
-  if constexpr (Sub::YIELDS)
-    Sub::run_yielding(args, x, y, bz,
-                      YieldCtl{c.flag_copies + (blockIdx.x % kFlagCopies) * kFlagCopyStride, c.epoch,
-                               c.flag_copies != nullptr ? c.yield_ticks : 0u, c.yield_mask});
-  else
-    Sub::run_be(args, x, y, bz);
+  if constexpr (Sub::YIELDS) Sub::run_yielding(args, bx * PX + part % PX, by * PY + part / PX, bz, y);
+  else Sub::run_be(args, bx * PX + part % PX, by * PY + part / PX, bz);
   if (part == 0) record(c.cover, block, bx, by, bz, c.segment, blockIdx.x);
+}
+__device__ __forceinline__ YieldCtl yield_ctl(const PtbCtl &c) {
+  return YieldCtl{c.flag_copies + (blockIdx.x % kFlagCopies) * kFlagCopyStride, c.epoch,
+                  c.flag_copies != nullptr ? c.yield_ticks : 0u, c.yield_mask};
+}
+
+template <class Body>
+__device__ __forceinline__ void ptb_parts(const typename Body::Args &args, const PtbCtl &c) {
+  __shared__ uint2 s_got;
+  if (threadIdx.x == 0) s_got = fetch_parts(c, 1, Body::PARTS);
+  __syncthreads();
+  const uint32_t idx = __builtin_amdgcn_readfirstlane(s_got.x), end = __builtin_amdgcn_readfirstlane(s_got.y);
+  if (idx < end) run_part<Body>(args, c, yield_ctl(c), idx);
+}
+
+template <class Body>
+__device__ __forceinline__ void ptb_tail(const typename Body::Args &args, const PtbCtl &c) {
+  constexpr uint32_t P = Body::PARTS;
+  __shared__ uint2 s_got[2];
+  for (uint32_t it = 0;; ++it) {
+    if (threadIdx.x == 0) s_got[it & 1] = fetch_parts(c, it < c.whole ? P : 1, P);
+    __syncthreads();
+    uint32_t idx = __builtin_amdgcn_readfirstlane(s_got[it & 1].x);
+    const uint32_t end = __builtin_amdgcn_readfirstlane(s_got[it & 1].y);
+    if (idx >= end) break;
+    if (idx % P == 0 && end - idx == P) {
+      uint32_t bx, by, bz;
+      delinearize(idx / P, c.gx, c.gy, bx, by, bz);
+      Body::Whole::run_yielding(args, bx, by, bz, yield_ctl(c));
+      record(c.cover, idx / P, bx, by, bz, c.segment, blockIdx.x);
+    } else {
+      for (; idx < end; ++idx) run_part<Body>(args, c, yield_ctl(c), idx);
+    }
+  }
 }
 
 template <class Body>
@@ -345,9 +387,7 @@ __device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, cons
       uint32_t bx, by, bz;
       delinearize(idx, c.gx, c.gy, bx, by, bz);
       if constexpr (Body::YIELDS)
-        Body::run_yielding(args, bx, by, bz,
-                           YieldCtl{c.flag_copies + (worker % kFlagCopies) * kFlagCopyStride, c.epoch,
-                                    c.flag_copies != nullptr ? c.yield_ticks : 0u, c.yield_mask});
+        Body::run_yielding(args, bx, by, bz, yield_ctl(c));
       else
         Body::run_be(args, bx, by, bz);
       record(c.cover, idx, bx, by, bz, c.segment, worker);
@@ -389,9 +429,14 @@ template <class Body, class = void>
 struct HasParts : std::false_type {};
 template <class Body>
 struct HasParts<Body, std::void_t<typename Body::Sub>> : std::true_type {};
+template <class Body, class = void>
+struct HasWhole : std::false_type {};
+template <class Body>
+struct HasWhole<Body, std::void_t<typename Body::Whole>> : std::true_type {};
 template <class Body>
 __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const PtbCtl &c) {
-  if constexpr (HasParts<Body>::value) ptb_parts<Body>(args, c);
+  if constexpr (HasWhole<Body>::value) ptb_tail<Body>(args, c);
+  else if constexpr (HasParts<Body>::value) ptb_parts<Body>(args, c);
   else ptb_blocks<Body>(args, c);
   ptb_leave(c);
 }

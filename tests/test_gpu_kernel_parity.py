@@ -357,6 +357,52 @@ def test_gemm_parts_preempted_anywhere(env, m, n, n128):
         _check_blocks(host(Cd), want, grid, tn, total)
 
 
+@pytest.mark.parametrize("m,n,workers", [(256, 1792, 5), (768, 1024, 5), (1024, 1280, 9), (256, 2560, 8)])
+@pytest.mark.parametrize("k", [96, 2048])
+def test_gemm_last_round_in_parts(env, m, n, workers, k):
+    """Grids one to several rounds long whose last round is handed out in halves (7 and 12 blocks
+    on 5 workers, 20 on 9, 10 on 8): coverage by whole blocks, a stop between blocks, requests at
+    any moment, the rest from there."""
+    import time
+    B, ctx, torch = env
+    from gpu_util import host
+    want, Cd, kern, grid = _ptb_parts_case(B, torch, m, n, k, 1, False)
+    total = kern.total_blocks
+    stop = workers + 1
+    job = ctx.launch_ptb(kern, workers, coverage=True, stop_at=stop)
+    assert job.wait() == B.JOB_STOPPED and job.progress()[0] == stop
+    torch.cuda.synchronize()
+    _check_blocks(host(Cd), want, grid, 256, stop)
+    job.resume()
+    assert job.wait() == B.JOB_COMPLETE
+    rec = job.coverage()
+    job.free()
+    torch.cuda.synchronize()
+    _check_blocks(host(Cd), want, grid, 256, total)
+    idx = np.arange(total)
+    assert (rec["count"] == 1).all() and (rec["worker"] < workers).all()
+    assert (rec["bx"] == idx % grid[0]).all() and (rec["by"] == idx // grid[0]).all()
+    for delay_us in (0, 5, 10, 15, 20, 30, 40, 50, 60, 80):
+        Cd.fill_(0x7FC0)
+        torch.cuda.synchronize()
+        job = ctx.launch_ptb(kern, workers, coverage=True)
+        t0 = time.perf_counter()
+        while (time.perf_counter() - t0) * 1e6 < delay_us:
+            pass
+        job.preempt()
+        state = job.wait()
+        done = job.progress()[0]
+        assert (state == B.JOB_COMPLETE) == (done == total)
+        torch.cuda.synchronize()
+        _check_blocks(host(Cd), want, grid, 256, done)
+        job.resume()
+        assert job.wait() == B.JOB_COMPLETE
+        assert (job.coverage()["count"] == 1).all()
+        job.free()
+        torch.cuda.synchronize()
+        _check_blocks(host(Cd), want, grid, 256, total)
+
+
 # ------------------------------------------------------------------ GEMM, 32-wide ragged tiles
 @pytest.mark.parametrize("form", FORMS)
 def test_gemm_small_forms(env, form):
