@@ -269,8 +269,8 @@ int tally_pump(tally_job *job);
 
 /* Wait for the drain Section 4.1 describes (after a preemption signal every worker finishes
  * its current block and exits) or for completion: blocks (host spin, pumping a sliced job)
- * until the job is STOPPED or COMPLETE, then synchronises the best-effort stream so that
- * outputs are visible.  TALLY_ERR_BAD_STATE if the device could not report the progress of
+ * until the job is STOPPED or COMPLETE and what was on the best-effort stream before the call
+ * has ended, so that outputs are visible.  TALLY_ERR_BAD_STATE if the device could not report the progress of
  * a preempted segment (never seen; the job then cannot be resumed). */
 int tally_wait(tally_job *job, int *state);
 int tally_job_free(tally_job *job); /* waits for in-flight launches of the job first */

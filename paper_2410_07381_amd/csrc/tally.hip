@@ -746,8 +746,11 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   ctx->slot_epoch[slot] = j->epoch;
   ctx->slot_exited[slot] = c.exit_target;
   if (e != hipSuccess) {
-    // no workers will ever count themselves out: do it for them, so that the relay ends
+    // no workers will ever count themselves out or report: do it for them, so that the relay ends
+    // and whoever settles a relay that gave up first finds the counter
     g_last_hip = (int)e;
+    __atomic_store_n((unsigned long long *)(j->h_base() + kHostRaw),
+                     (unsigned long long)j->epoch << 32 | ctx->slot_counter[slot], __ATOMIC_RELEASE);
     hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(64), 0, j->be, j->d_exited(), c.exit_target);
     (void)hipGetLastError();
     return TALLY_ERR_HIP;
