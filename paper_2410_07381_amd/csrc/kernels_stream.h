@@ -385,18 +385,19 @@ struct RowGroup {
   }
 };
 
-// Op::row(args, row, lane, v) on the rows [r0, r1): group g takes r0 + g, r0 + g + STEP, ...
+// Op::row(args, row, lane, v) on the `count` rows from r0: group g takes r0 + g, r0 + g + STEP, ...
+// (Counted from r0: the row after a matrix of nearly 2^32 rows has no 32-bit number.)
 template <class Op, uint32_t LANES, int NV, int DEPTH, bool NT, bool ONE = false>
-__device__ __forceinline__ void rows_walk(const typename Op::Args &a, uint32_t r0, uint32_t r1) {
+__device__ __forceinline__ void rows_walk(const typename Op::Args &a, uint32_t r0, uint32_t count) {
 #ifdef __HIP_DEVICE_COMPILE__
   typedef RowGroup<LANES> G;
   __shared__ float s_part[2][kThreads / kWave];
   uint32_t lane = threadIdx.x & (LANES - 1);
-  uint32_t r = r0 + (G::WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0u);
+  uint32_t r = G::WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0u;
   float4 v[DEPTH][NV];
   auto load = [&](uint32_t row, float4 (&x)[NV]) {
     if constexpr (ONE) {
-      const float *p = a.x + (uint64_t)row * a.cols;
+      const float *p = a.x + (uint64_t)(r0 + row) * a.cols;
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         const uint32_t c = (i * LANES + lane) * 4;
@@ -404,7 +405,7 @@ __device__ __forceinline__ void rows_walk(const typename Op::Args &a, uint32_t r
         if (c < a.cols) x[i] = ld4<NT>(p + c);
       }
     } else {
-      const buf_t b = row_buf(a.x, row, a.cols, row < r1);
+      const buf_t b = row_buf(a.x, r0 + row, a.cols, row < count);
 #pragma unroll
       for (int i = 0; i < NV; ++i) x[i] = buf_ld4<NT>(b, (i * LANES + lane) * 16);
     }
@@ -413,9 +414,9 @@ __device__ __forceinline__ void rows_walk(const typename Op::Args &a, uint32_t r
   // from it, and LayerNorm's gamma and beta, in registers across its whole loop)
   asm volatile("" : "+v"(lane));
   if constexpr (ONE) {                                     // a logical block has one row per group
-    if (r >= r1) return;
+    if (r >= count) return;
     load(r, v[0]);
-    Op::template row<G, LANES, NV, NT>(a, r, lane, v[0], s_part[0], s_part[1]);
+    Op::template row<G, LANES, NV, NT>(a, r0 + r, lane, v[0], s_part[0], s_part[1]);
     return;
   }
 #pragma unroll
@@ -424,13 +425,13 @@ __device__ __forceinline__ void rows_walk(const typename Op::Args &a, uint32_t r
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
       const uint32_t row = r + d * G::STEP;
-      if (row >= r1) return;                               // uniform over the group
+      if (row >= count) return;                            // uniform over the group
       asm volatile("" : "+v"(lane));
-      Op::template row<G, LANES, NV, NT>(a, row, lane, v[d], s_part[0], s_part[1]);
+      Op::template row<G, LANES, NV, NT>(a, r0 + row, lane, v[d], s_part[0], s_part[1]);
       if (DEPTH > 1) load(row + DEPTH * G::STEP, v[d]);
     }
     if constexpr (DEPTH == 1) {
-      if (r + G::STEP >= r1) return;
+      if (r + G::STEP >= count) return;
       load(r + G::STEP, v[0]);
     }
   }
@@ -526,16 +527,16 @@ struct RowsBodyT {
   static __device__ __forceinline__ void run_range(const Args &a, uint32_t first, uint32_t last) { walk<true, false>(a, first, last); }
   template <bool NT, bool ONE>
   static __device__ __forceinline__ void walk(const Args &a, uint32_t first, uint32_t last) {
-    const uint32_t r0 = first * 4, r1 = last * 4 < a.rows ? last * 4 : a.rows;
+    const uint32_t r0 = first * 4, want = (last - first) * 4, n = a.rows - r0 < want ? a.rows - r0 : want;
     if constexpr (MAXNV > 16) {
-      rows_walk<Op, kThreads, MAXNV / 4, 2, NT>(a, r0, r1);
+      rows_walk<Op, kThreads, MAXNV / 4, 2, NT>(a, r0, n);
     } else {
-      if (a.cols <= 256) rows_walk<Op, kWave, 1, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, r1);
-      else if (a.cols <= 512) rows_walk<Op, kWave, 2, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, r1);
-      else if (a.cols <= 1024) rows_walk<Op, kWave, 4, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, r1);
+      if (a.cols <= 256) rows_walk<Op, kWave, 1, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, n);
+      else if (a.cols <= 512) rows_walk<Op, kWave, 2, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, n);
+      else if (a.cols <= 1024) rows_walk<Op, kWave, 4, DEEP && !ONE ? 4 : 1, NT, ONE>(a, r0, n);
       else if constexpr (MAXNV >= 16) {
-        if (a.cols <= 2048) rows_walk<Op, kWave, 8, DEEP && !ONE ? (WAVES <= 2 ? 4 : 2) : 1, NT, ONE>(a, r0, r1);
-        else rows_walk<Op, kWave, 16, DEEP && !ONE && WAVES <= 2 ? 2 : 1, NT, ONE>(a, r0, r1);
+        if (a.cols <= 2048) rows_walk<Op, kWave, 8, DEEP && !ONE ? (WAVES <= 2 ? 4 : 2) : 1, NT, ONE>(a, r0, n);
+        else rows_walk<Op, kWave, 16, DEEP && !ONE && WAVES <= 2 ? 2 : 1, NT, ONE>(a, r0, n);
       }
     }
   }

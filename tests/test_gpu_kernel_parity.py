@@ -565,6 +565,39 @@ def test_rows_width_edges(env, op, cols):
         assert (host(buf[rows]) == 7.0).all()
 
 
+@pytest.mark.parametrize("op", ["softmax", "layernorm"])
+def test_rows_up_to_the_largest_count(env, op):
+    """2^32 - 1 rows (2^30 blocks, the most a grid may have, 64 GiB in place): the last block's end
+    has no 32-bit row number, and neither has the row after the last one that a worker asks for.
+    Every row is the same, so the oracle's first rows are all of it; a row that is run twice in
+    place would differ."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_close_rel
+    rows, cols = 2**32 - 1, 4
+    one = np.array([[0.5, -1.0, 2.0, 0.0]], np.float32)
+    x = torch.empty((rows, cols), device="cuda")
+    x.copy_(dev(one).expand(rows, cols))
+    if op == "softmax":
+        a = {"x": one, "y": np.zeros_like(one), "rows": 1, "cols": cols}
+        kern = B.softmax_f32(x, x)
+        OS.run_native("softmax_f32", OK.grid_of("softmax_f32", a), a)
+    else:
+        g, b = np.ones(cols, np.float32), np.zeros(cols, np.float32)
+        a = {"x": one, "y": np.zeros_like(one), "gamma": g, "beta": b, "rows": 1, "cols": cols, "eps": 1e-5}
+        kern = B.layernorm_f32(x, dev(g), dev(b), x, 1e-5)
+        OS.run_native("layernorm_f32", OK.grid_of("layernorm_f32", a), a)
+    assert kern.total_blocks == 2**30
+    torch.cuda.synchronize()
+    job = ctx.launch_ptb(kern, 512, chunk=4096)
+    assert job.wait() == B.JOB_COMPLETE
+    job.free()
+    torch.cuda.synchronize()
+    assert_close_rel(host(x[:1]), a["y"], 1e-5, 2e-6)
+    assert bool((x == x[:1]).all())
+    kern = x = None
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("count", [1, 3, 4, 5, 1023, 8191, 8192, 8197, 65536, 70001])
 @pytest.mark.parametrize("offset", [0, 1, 3])
 def test_reduce_final_edges(env, count, offset):
