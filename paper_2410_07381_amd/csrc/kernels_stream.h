@@ -131,10 +131,12 @@ struct SaxpyBody {
   // block by block, but the loads of eight blocks are in flight together instead of one
   // block's loads waiting for the previous block's store.
   static __device__ __forceinline__ void run_range(const Args &a, uint32_t first, uint32_t last) {
-    const float *__restrict__ x = a.x;
-    float *__restrict__ y = a.y;
-    const uint32_t end = last * kThreads < a.n ? last * kThreads : a.n;
-    uint32_t i = first * kThreads + threadIdx.x;
+    // (counted from the first element: the one after 2^32 - 1 of them has no 32-bit index)
+    const uint32_t base = first * kThreads, want = (last - first) * kThreads;
+    const float *__restrict__ x = a.x + base;
+    float *__restrict__ y = a.y + base;
+    const uint32_t end = a.n - base < want ? a.n - base : want;
+    uint32_t i = threadIdx.x;
     for (; i + 7 * kThreads < end; i += 8 * kThreads) {
       float xv[8], yv[8];
 #pragma unroll

@@ -94,6 +94,24 @@ def test_saxpy_ptb_small(env, n, workers, chunk, pts):
     assert_close_rel(host(y), want_y, 1e-6)
 
 
+def test_saxpy_up_to_the_largest_count(env):
+    """2^32 - 1 elements as workers that take several blocks per fetch: the element after the last
+    one has no 32-bit index.  fma(1.5, 1, 2) = 3.5 everywhere, exactly."""
+    B, ctx, torch = env
+    n = 2**32 - 1
+    x, y = torch.ones(n, device="cuda"), torch.full((n,), 2.0, device="cuda")
+    torch.cuda.synchronize()
+    k = B.saxpy(x, y, 1.5)
+    assert k.total_blocks == 2**24
+    job = ctx.launch_ptb(k, 512, chunk=1024)
+    assert job.wait() == B.JOB_COMPLETE
+    job.free()
+    torch.cuda.synchronize()
+    assert bool((y == 3.5).all())
+    k = x = y = None
+    torch.cuda.empty_cache()
+
+
 def test_degenerate_schedules(env):
     """A zero-block segment (preempted before the first fetch), one worker, a chunk and a
     slice larger than the whole grid, an empty input."""
