@@ -455,7 +455,7 @@ constexpr int kMaxSide = 2 * 8 + 2;
 constexpr int kMaxBeClients = 8;
 constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited, 128 B apart
 constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw | slice_done,ended
-constexpr size_t kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostEnded = 132;
+constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostEnded = 132;
 constexpr size_t kCopySlotBytes = kFlagCopies * kFlagCopyStride * sizeof(uint32_t);
 
 enum JobKind { KIND_PTB = 0, KIND_SLICED = 1, KIND_NATIVE = 2 };
@@ -566,7 +566,7 @@ struct tally_job {
   unsigned char *h_base() { return ctx->host_pool + slot * kHostSlotBytes; }
   unsigned char *h_base_dev() { return ctx->host_pool_dev + slot * kHostSlotBytes; }
   uint32_t *h_flag() { return (uint32_t *)h_base(); }
-  unsigned long long *h_status() { return (unsigned long long *)(h_base() + 64); }
+  unsigned long long *h_status() { return (unsigned long long *)(h_base() + kHostStatus); }
   uint32_t *h_live() { return (uint32_t *)(h_base() + 72); }
   uint32_t *h_ended() { return (uint32_t *)(h_base() + kHostEnded); }
   uint32_t *h_slice_done() { return (uint32_t *)(h_base() + 128); }
@@ -595,7 +595,7 @@ int check_desc(const tally_kernel_desc *d, const KernelOps **ops_out, tally_dim3
 // held.  Until that report is in, the relay may still fold a late request into the counter,
 // so neither a new segment nor a new job may use the slot's counter.  The relay ends within
 // microseconds of its workers (or after its 20 ms give-up bound when it ran before them); a
-// freed job leaves the waiting to whoever takes the slot next, 64 jobs later as a rule.
+// freed job leaves the waiting to whoever launches next on the relay's stream or takes the slot.
 int settle_relay(tally_ctx *ctx, int slot) {
   if (!ctx->slot_relay[slot]) return TALLY_OK;
   const uint32_t epoch = ctx->slot_epoch[slot];
@@ -679,12 +679,31 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
   return TALLY_OK;
 }
 
+// A new relay on `ctl` starts once the one before it there has ended, whichever slot that was for.
+// The last worker's word is out a polling round and a report before that (2 to 4 us), and a job
+// may be followed by the next as soon as the word is seen: workers launched then would start
+// first.  So the relays of drained segments are settled before another is enqueued.  (A segment
+// whose workers are still at work is not waited for: the new workers are behind them.)
+int settle_relays_before(tally_ctx *ctx, hipStream_t ctl) {
+  for (int s = 0; s < kSlots; ++s) {
+    if (!ctx->slot_relay[s] || ctx->slot_ctl[s] != ctl) continue;
+    const unsigned char *h = ctx->host_pool + s * kHostSlotBytes;
+    auto epoch = [&](size_t at) { return (uint32_t)(__atomic_load_n((const unsigned long long *)(h + at), __ATOMIC_ACQUIRE) >> 32); };
+    // (of the last worker's two words either may be seen first)
+    if (epoch(kHostStatus) != ctx->slot_epoch[s] && epoch(kHostRaw) != ctx->slot_epoch[s]) continue;
+    const int rc = settle_relay(ctx, s);
+    if (rc) return rc;
+  }
+  return TALLY_OK;
+}
+
 // Launch the workers (and their relay) for task indices [progress, limit).  Requires the
 // job's previous segment, if any, to have drained.
 int ptb_launch_segment(tally_job *j, uint32_t limit) {
   tally_ctx *ctx = j->ctx;
   const int slot = j->slot;
   int rc = settle_relay(ctx, slot);
+  if (rc == TALLY_OK) rc = settle_relays_before(ctx, j->ctl);
   if (rc) return rc;
   const uint32_t start = j->progress.load();
   // The counter is never rewound: failed fetches of the last segment (after a request, or
@@ -706,7 +725,7 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   c.exited = j->d_exited();
   c.pre = j->d_pre();
   c.host_flag = (const uint32_t *)j->h_base_dev();
-  c.host_status = (unsigned long long *)(j->h_base_dev() + 64);
+  c.host_status = (unsigned long long *)(j->h_base_dev() + kHostStatus);
   c.host_live = (uint32_t *)(j->h_base_dev() + 72);
   c.host_raw = (unsigned long long *)(j->h_base_dev() + kHostRaw);
   c.host_relay = (unsigned long long *)(j->h_base_dev() + kHostRelay);

@@ -386,6 +386,44 @@ def test_preemption_reaches_workers_that_fill_the_gpu(env):
     assert_close_rel(host(y)[::4099], oracle_softmax_rows(host(x)[::4099]), 1e-5, 1e-7)
 
 
+@pytest.mark.parametrize("op", ["saxpy", "softmax"])
+def test_preemption_reaches_workers_right_behind_another_job(env, op):
+    """The same where the job before has only just drained: the scheduler frees it and launches the
+    next one on the word that its last worker sent, when its relay still has to look once more, and
+    to report.  The second job's relay has to be on the GPU before its workers all the same."""
+    B, ctx, torch = env
+    if op == "saxpy":
+        x, y = torch.zeros(1 << 26, device="cuda"), torch.zeros(1 << 26, device="cuda")
+        long = B.saxpy(x, y, 1.0)                         # 2^18 blocks one by one: 3 ms
+        short = B.saxpy(x[:1 << 20], y[:1 << 20], 1.0)
+    else:
+        x = torch.zeros((65536, 2048), device="cuda")
+        long = B.softmax_f32(x, x)
+        short = B.softmax_f32(x[:4096], x[:4096])
+    u, v = torch.zeros(64, device="cuda"), torch.zeros(64, device="cuda")
+    request = [B.saxpy(u, v, 1.0)]
+    torch.cuda.synchronize()
+    cfg = (B.CFG_PTB, ctx.max_workers(long), 1)
+    s = ctx.scheduler()
+    try:
+        for rep in range(40):
+            s.submit_be(short, cfg)
+            s.submit_be(long, cfg)
+            while s.stats()["be_kernels_done"] < 2 * rep + 1:
+                s.poll()
+            t0 = time.perf_counter()
+            while time.perf_counter() - t0 < 1e-4:        # (the long job is on the GPU by now)
+                pass
+            s.submit_hi(request)
+            while s.poll():
+                pass
+            while s.stats()["be_kernels_done"] < 2 * rep + 2:
+                s.poll()
+            assert s.stats()["n_preempts"] == rep + 1     # it stopped for the request, and went on
+    finally:
+        s.close()
+
+
 # ------------------------------------------------------------------ reduction, configuration 2 shape
 @pytest.mark.parametrize("slice_blocks", [1, 8, 64])
 def test_reduce_sliced_ragged(env, slice_blocks):
