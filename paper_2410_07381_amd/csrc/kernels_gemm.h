@@ -355,298 +355,246 @@ struct GemmBodyT {
 using GemmBody = GemmBodyT<4>;
 using GemmN128Body = GemmBodyT<2>;
 
-// Same operator with 32x32 output tiles and predicated edges, for small or ragged
-// problems (the high-priority inference-like layer), where the grid is often far smaller than
-// the GPU and every kernel is a chain of memory latencies.  The four waves of a block
-// split K between them: wave w multiplies the 64-wide k-chunks w, w+4, w+8, ..., so the serial
-// chain per wave is a quarter as long and four times as many waves have loads in flight; the
-// four partial tiles are summed through LDS.
+// The same operator with smaller tiles and predicated edges: (32 RA) x (32 RB) outputs per
+// workgroup, four waves in a 2x2 arrangement of RA x RB blocks of 16x16 each.  32x32 is the
+// logical block of the small or ragged GEMM (the high-priority inference-like layer, whose grid
+// is often far smaller than the GPU and where every kernel is a chain of memory latencies);
+// 32x64, 64x64 and 128x64 cover its original form where the 32x32 tiles are more than the
+// compute units, and they are what the large tile's grid is covered with, or its blocks are
+// handed out in, where there are too few of its own (see gemm_cover and GemmParts).
 //
-// What bounds it where the grid does fill the GPU is the address unit: an MFMA fragment is
-// 16 bytes of each of 32 rows, and a load in that shape costs one request per lane (64 per KB;
-// 1000 x 2300 x 768 took 28 us, 9 tiles of 2.6 us of requests per compute unit).  Operands are
-// therefore loaded as whole 128-byte lines of 8 rows (8 requests per KB), two chunks ahead in
-// registers, and each wave turns them into fragments through 4 KB of LDS of its own: A in and
-// out, then B in and out.  LDS serves a wave's accesses in order, so this takes neither a
-// barrier nor a second buffer.  1000 x 2300 x 768 28 -> 15 us, 128 x 768 x 3072 13.4 -> 7.2,
-// 2048 x 4096 x 4096 475 -> 198 (larger tiles there: see below).
-struct GemmSmallBody {
+// Every tile of every size, the 256-row tiles included, adds its products in the same order:
+// one accumulator per output, k ascending, one 16x16x32 MFMA per 32 of it with B first, one
+// hardware conversion at the end.  The bits of a product depend neither on the form it runs in
+// nor on where a job was stopped and resumed.  (An earlier 32x32 tile split K between its waves:
+// a job finished in its parts, or run in the original form, came out in other bits.)
+//
+// Operands are loaded as whole 128-byte lines, 8 rows per load (8 requests per KB; a load in
+// fragment shape costs one per lane), AHEAD stages of 64 k ahead in registers, and shared by the
+// four waves through LDS.  What bounds the two smallest tiles is the serial chain of short
+// stages, and LDS (every operand byte is read twice: 192 cycles per stage of a 32x32 tile): they
+// have two LDS buffers, so that the fragments of one are read while the other is written and a
+// stage has one barrier.  The larger two have room for one buffer and take two barriers.
+// Within 128 registers and 31 KB of LDS: what a resident 256x256 tile leaves free, since a
+// high-priority kernel that does not fit beside the paused tiles of a best-effort GEMM waits for
+// them.
+//
+// us for 32x32 / 32x64 / 64x64 / 128x64: 128 x 768 x 3072 (96 tiles of 32x32) 7.7 / 10.7 / 16.5;
+// 128 x 3072 x 768 (384) 5.3 / 4.8 / 5.8; 1000 x 2300 x 768 13.9 / 12.0 / 10.5 / 11.7;
+// 512 x 4096 x 4096 53 / 39 / 29 / 32; 2048 x 4096 x 4096 195 / 140 / 101 / 85 (0.81 PFLOP/s).
+// With K split between the waves of the 32x32 tile: 7.7, 5.0, 15.1, 50 and 199.
+template <int RA, int RB>
+struct GemmTileT {
   using Args = tally_gemm_bf16_args;
   static constexpr int THREADS = 256;
-  // at most 128 registers per lane: that is what a resident 256x256 GEMM tile leaves free
-  // on a SIMD, and a high-priority kernel that does not fit beside the paused tiles of a
-  // best-effort GEMM waits for them
   static constexpr int MIN_WAVES = 4;
-  static constexpr int TILE = 32;
   static constexpr unsigned DYN_LDS = 0;
-  static constexpr bool YIELDS = false;
+  static constexpr bool YIELDS = RA * RB > 2;
   static constexpr bool RANGE = false;
-  // the partial sums of consecutive blocks of one workgroup share LDS
-  static constexpr bool END_BARRIER = true;
-
-  static __device__ __forceinline__ void run_be(const Args &a, uint32_t x, uint32_t y, uint32_t z) { run(a, x, y, z); }
-  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
-#ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
-    __shared__ __align__(16) unsigned char s_wave[4][4096];
-    uint32_t tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));   // (a worker keeps no addresses across its tiles)
-    const uint32_t lane = tid & 63;
-    // the wave index decides trip counts below: as a scalar, those become scalar branches
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t K = a.k;
-    const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
-    const uint32_t nchunk = (K + 63) / 64;                // this wave takes w, w + 4, ...
-    const uint32_t mine = nchunk > wave ? (nchunk - wave + 3) / 4 : 0;
-
-    // Load j of a chunk moves rows 8 j .. 8 j + 7, lane l the 16-byte piece l%8 of row l/8.  A
-    // lane whose offset has its top bit set is outside the buffer and gets zeros: rows past the
-    // matrix, pieces past K in the last chunk (K is a multiple of 32), chunks past the last one.
-    constexpr uint32_t OOB = 0x80000000u;
-    const uint32_t r8 = lane >> 3, p8 = lane & 7;
-    const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TILE * LDA, 0x7fffffffu);
-    const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TILE * LDB, 0x7fffffffu);
-    uint32_t vA[4], vB[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t r = 8 * j + r8;
-      vA[j] = by * TILE + r < a.m ? (r * LDA + p8 * 8) * 2 : OOB;
-      vB[j] = bx * TILE + r < a.n ? (r * LDB + p8 * 8) * 2 : OOB;
-    }
-    const uint32_t half = (K & 32) && (p8 & 4) ? OOB : 0u;
-    struct Set { uint4 a[4], b[4]; };
-    auto request = [&](Set &s, uint32_t i) {
-      const uint32_t c = wave + 4 * i, none = (c >= nchunk ? OOB : 0u) | (c + 1 == nchunk ? half : 0u);
-      const uint32_t so = __builtin_amdgcn_readfirstlane(c >= nchunk ? 0u : c * 128);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s.b[j] = buf_ld16(rB, vB[j] | none, so);
-    };
-    // piece p of row r lies at slot p xor ((r/2)%8): the 16 lanes that a 128-bit access serves
-    // together fall into 16 different 16-byte bank groups, writing and reading
-    unsigned char *buf = s_wave[wave];
-    const uint32_t w_off = r8 * 128 + (p8 ^ (r8 >> 1)) * 16;               // + 1024 j, slot xor 4 (j%2)
-    const uint32_t f_row = lane & 31, f_off = f_row * 128, f_sw = (f_row >> 1) & 7;
-    f32x16_t acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    auto turn = [&](const uint4(&v)[4], bf16x8_t(&f)[4]) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) *reinterpret_cast<uint4 *>(buf + ((w_off ^ ((j & 1) * 64)) + j * 1024)) = v[j];
-      // lane l takes row l%32, elements 8 (l/32) .. 8 (l/32) + 7 of each 16-wide slice
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        f[q] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(buf + f_off + ((2 * q + (lane >> 5)) ^ f_sw) * 16));
-    };
-    auto multiply = [&](const Set &s) {
-      bf16x8_t fa[4], fb[4];
-      turn(s.a, fa);
-      turn(s.b, fb);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[q], fb[q], acc, 0, 0, 0);
-    };
-    Set s0, s1;
-    request(s0, 0);
-    __builtin_amdgcn_sched_barrier(0);                    // (in the order in which they are waited for)
-    request(s1, 1);
-    // (the only way round the second half is out of the loop: where a path that skips it meets
-    // one that does not, the compiler waits for every load on its way)
-    for (uint32_t i = 0; i < mine; i += 2) {
-      multiply(s0);
-      if (i + 1 >= mine) break;
-      request(s0, i + 2);
-      multiply(s1);
-      request(s1, i + 3);
-    }
-
-    // Sum the four partial tiles.  Register r of lane l is row 8 (r/4) + 4 (l/32) + r%4, column
-    // l%32; a wave's part lies where its chunks did.  Thread t finishes four columns of row t/8.
-    float *part = reinterpret_cast<float *>(buf);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) part[r * 64 + lane] = acc[r];
-    __syncthreads();
-    const uint32_t tr = tid >> 3, tc = (tid & 7) * 4;
-    const uint32_t at = ((tr >> 3) * 4 + (tr & 3)) * 64 + ((tr >> 2) & 1) * 32 + tc;
-    float4 p[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) p[w] = *reinterpret_cast<const float4 *>(s_wave[w] + at * 4);
-    uint16_t v[4];
-    v[0] = f32_to_bf16((p[0].x + p[1].x) + (p[2].x + p[3].x));
-    v[1] = f32_to_bf16((p[0].y + p[1].y) + (p[2].y + p[3].y));
-    v[2] = f32_to_bf16((p[0].z + p[1].z) + (p[2].z + p[3].z));
-    v[3] = f32_to_bf16((p[0].w + p[1].w) + (p[2].w + p[3].w));
-    const uint32_t row = by * TILE + tr, col = bx * TILE + tc;
-    if (row < a.m) {
-      uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
-      if (col + 4 <= a.n && (reinterpret_cast<uintptr_t>(g) & 7u) == 0) {
-        *reinterpret_cast<uint2 *>(g) = make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (col + e < a.n) g[e] = v[e];
-      }
-    }
-#endif
-  }
-};
-
-// The small GEMM's operator with a workgroup per (64 MB) x 64 outputs, for its original form
-// where the 32x32 tiles are several times as many as the GPU holds: how the original form
-// covers the output is its own business (slices and workers keep to the logical blocks, and so
-// do all coverage records).  The 32x32 tiles are then bound by what they load and move through
-// LDS per product: every output line and column is fetched for 32 columns or rows only.  Here
-// four waves share a stage of 64 k through LDS, each with MB 32x32 blocks of its own, which
-// halves (MB = 1) or takes to 3/8 (MB = 2) the bytes per product.  The price is a serial chain
-// of K / 64 stages that one workgroup per compute unit cannot hide (0.4 us each).
-// Within 128 registers and 31 KB of LDS, to fit beside a paused best-effort GEMM tile.
-// 32x32 tiles / MB = 1 / MB = 2: 1000 x 2300 x 768 15.1 / 12.7 / 14.1 us; 512 x 4096 x 4096
-// 49.9 / 33.6 / 33.7; 2048 x 4096 x 4096 199 / 125 / 106 (0.65 PFLOP/s); 12 of these 2198 /
-// 1357 / 1076; but 512 x 1024 x 4096 (128 tiles of 64 x 64) 16.4 / 25.9 / 31.0.
-template <int MB>
-struct GemmMidBodyT {
-  using Args = tally_gemm_bf16_args;
-  static constexpr int THREADS = 256;
-  static constexpr int MIN_WAVES = 4;                     // (as the small tile)
-  static constexpr unsigned DYN_LDS = 0;
-  static constexpr uint32_t TM = 64 * MB, TN = 64;
-  static constexpr int NA = 2 * MB, NBL = 2;              // loads per wave and stage
-  static constexpr int AHEAD = MB == 1 ? 2 : 1;           // stages on their way (registers)
-
-  static constexpr bool YIELDS = true;
+  // a block's last barrier follows its last fragment read
+  static constexpr bool END_BARRIER = false;
+  static constexpr uint32_t TM = 32 * RA, TN = 32 * RB;
+  static constexpr bool TWO = RA * RB <= 2;               // LDS holds two stages
+  static constexpr int AHEAD = RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
+  static constexpr uint32_t SA = TM * 128, STAGE = (TM + TN) * 128;   // bytes of A, of both in a stage
 
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
     run_impl<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15});
   }
+  static __device__ __forceinline__ void run_be(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) { run(a, bx, by, bz); }
   static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
     run_impl<true>(a, bx, by, bz, ctl);
   }
   template <bool YIELD>
   static __device__ __forceinline__ void run_impl(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
-#ifdef __HIP_DEVICE_COMPILE__
-    __shared__ __align__(16) unsigned char s_ab[(TM + TN) * 128];
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ __align__(16) unsigned char s_ab[STAGE * (TWO ? 2 : 1)];
+    // (with one or two stages the loads of six more that do not exist would be most of the work)
+    if (AHEAD > 2 && a.k <= 128) run_ahead<2, YIELD>(a, s_ab, bx, by, bz, ctl);
+    else run_ahead<AHEAD, YIELD>(a, s_ab, bx, by, bz, ctl);
+  }
+  // SETS stages of operands on their way in registers
+  template <int SETS, bool YIELD>
+  static __device__ __forceinline__ void run_ahead(const Args &a, unsigned char *s_ab, uint32_t bx, uint32_t by, uint32_t bz,
+                                                   const YieldCtl ctl) {
+#ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (a worker keeps no addresses across its tiles)
+    const uint32_t lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t wm = wave >> 1, wn = wave & 1;
     const uint32_t K = a.k;
     const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
     const uint32_t ns = (K + 63) / 64;
+
+    // A load moves 8 rows, lane l the 16-byte piece l%8 of row l/8.  A lane whose offset has its
+    // top bit set is outside the buffer and gets zeros: rows past the matrix, pieces past K in
+    // the last stage (K is a multiple of 32), stages past the last one.
     constexpr uint32_t OOB = 0x80000000u;
     const uint32_t r8 = lane >> 3, p8 = lane & 7;
     const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TM * LDA, 0x7fffffffu);
     const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TN * LDB, 0x7fffffffu);
-    uint32_t vA[NA], vB[NBL];
+    uint32_t vA[RA], vB[RB];
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const uint32_t r = (wave * NA + j) * 8 + r8;
+    for (int j = 0; j < RA; ++j) {
+      const uint32_t r = (wave * RA + j) * 8 + r8;
       vA[j] = by * TM + r < a.m ? (r * LDA + p8 * 8) * 2 : OOB;
     }
 #pragma unroll
-    for (int j = 0; j < NBL; ++j) {
-      const uint32_t r = (wave * NBL + j) * 8 + r8;
+    for (int j = 0; j < RB; ++j) {
+      const uint32_t r = (wave * RB + j) * 8 + r8;
       vB[j] = bx * TN + r < a.n ? (r * LDB + p8 * 8) * 2 : OOB;
     }
     const uint32_t half = (K & 32) && (p8 & 4) ? OOB : 0u;
-    struct Set { uint4 a[NA], b[NBL]; };
+    struct Set { uint4 a[RA], b[RB]; };
     auto request = [&](Set &s, uint32_t c) {
       const uint32_t none = (c >= ns ? OOB : 0u) | (c + 1 == ns ? half : 0u);
       const uint32_t so = __builtin_amdgcn_readfirstlane(c >= ns ? 0u : c * 128);
 #pragma unroll
-      for (int j = 0; j < NA; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
+      for (int j = 0; j < RA; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
 #pragma unroll
-      for (int j = 0; j < NBL; ++j) s.b[j] = buf_ld16(rB, vB[j] | none, so);
+      for (int j = 0; j < RB; ++j) s.b[j] = buf_ld16(rB, vB[j] | none, so);
     };
-    unsigned char *sA = s_ab, *sB = s_ab + TM * 128;
-    const uint32_t w_off = r8 * 128 + (p8 ^ (r8 >> 1)) * 16;
-    const uint32_t f_row = lane & 31, f_sw = (f_row >> 1) & 7;
-    const uint32_t fA = (wm * 32 * MB + f_row) * 128, fB = (wn * 32 + f_row) * 128;
-    f32x16_t acc[MB];
+    // piece p of row r lies at slot p xor ((r/2)%8): the 16 lanes that a 128-bit access serves
+    // together fall into 16 different 16-byte bank groups, writing and reading
+    const uint32_t w_off = r8 * 128 + (p8 ^ (r8 >> 1)) * 16;               // slot xor 4 in odd groups of 8 rows
+    auto store = [&](const Set &s, uint32_t buf) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+      for (int j = 0; j < RA; ++j) {
+        const uint32_t g = wave * RA + j;
+        *reinterpret_cast<uint4 *>(s_ab + buf * STAGE + g * 1024 + (w_off ^ ((g & 1) * 64))) = s.a[j];
+      }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+      for (int j = 0; j < RB; ++j) {
+        const uint32_t g = wave * RB + j;
+        *reinterpret_cast<uint4 *>(s_ab + buf * STAGE + SA + g * 1024 + (w_off ^ ((g & 1) * 64))) = s.b[j];
+      }
+    };
+    // lane l takes row l%16 of a 16-row block, k-chunk 4 kk + l/16
+    const uint32_t f_off = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16);
+    const uint32_t fA = wm * (16 * RA * 128) + f_off, fB = SA + wn * (16 * RB * 128) + f_off;
+    auto read = [&](uint32_t buf, uint32_t at, int kk, int i) {
+      return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(s_ab + buf * STAGE + (at ^ (kk * 64)) + i * 2048));
+    };
+    f32x4_t acc[RA][RB];
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+      for (int j = 0; j < RB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    Set s[SETS];
+#pragma unroll
+    for (int d = 0; d < SETS; ++d) {
+      request(s[d], d);
+      __builtin_amdgcn_sched_barrier(0);                  // (in the order in which they are waited for)
+    }
+    if constexpr (TWO) {
+      store(s[0], 0);
+      request(s[0], SETS);
+      __syncthreads();
+    }
     uint32_t pause_left = ctl.ticks;
     // (a look at the pause word costs this workgroup 0.7 us, two stages: eight times as many
     // stages lie between two looks as GemmBodyT has, whose stages last eight times as long)
     const uint32_t poll_mask = (ctl.mask << 2) | 3;
-    auto step = [&](Set &s, uint32_t next) {
-      // one wave polls; the others meet it at the barrier
-      if (YIELD && ctl.ticks != 0 && wave == 0 && (next & poll_mask) == poll_mask) yield_while_preempted(ctl, pause_left);
+    // stage c, whose operands (with two buffers those of stage c + 1) are in set d
+    auto step = [&](int d, uint32_t c) {
+      bf16x8_t fa[2][RA], fb[2][RB];
+      if constexpr (TWO) {
+        static_assert(SETS % 2 == 0, "the buffer is that of the set");
+        const int next = (d + 1) % SETS;
 #pragma unroll
-      for (int j = 0; j < NA; ++j)
-        *reinterpret_cast<uint4 *>(sA + (wave * NA + j) * 1024 + (w_off ^ (((wave * NA + j) & 1) * 64))) = s.a[j];
+        for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-      for (int j = 0; j < NBL; ++j)
-        *reinterpret_cast<uint4 *>(sB + (wave * NBL + j) * 1024 + (w_off ^ (((wave * NBL + j) & 1) * 64))) = s.b[j];
-      request(s, next);
-      __syncthreads();
-      // (fragments are read in batches ahead of the products, not one by one between them)
-      constexpr int Q = MB == 1 ? 4 : 2;
+          for (int j = 0; j < RB; ++j) fb[kk][j] = read(d & 1, fB, kk, j);
 #pragma unroll
-      for (int q0 = 0; q0 < 4; q0 += Q) {
-        uint4 fa[Q][MB], fb[Q];
+          for (int i = 0; i < RA; ++i) fa[kk][i] = read(d & 1, fA, kk, i);
+        }
+        store(s[next], (d + 1) & 1);
+        request(s[next], c + 1 + SETS);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        // one wave polls; the others meet it at the barrier
+        if (YIELD && ctl.ticks != 0 && wave == 0 && ((c + SETS) & poll_mask) == poll_mask) yield_while_preempted(ctl, pause_left);
+        store(s[d], 0);
+        request(s[d], c + SETS);
+        __syncthreads();
+        // (fragments are read ahead of the products, not one by one between them)
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const uint32_t slot = ((2 * (q0 + q) + (lane >> 5)) ^ f_sw) * 16;
-          fb[q] = *reinterpret_cast<const uint4 *>(sB + fB + slot);
+        for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-          for (int i = 0; i < MB; ++i) fa[q][i] = *reinterpret_cast<const uint4 *>(sA + fA + i * 4096 + slot);
+          for (int j = 0; j < RB; ++j) fb[kk][j] = read(0, fB, kk, j);
+#pragma unroll
+          for (int i = 0; i < RA; ++i) fa[kk][i] = read(0, fA, kk, i);
         }
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-#pragma unroll
-          for (int i = 0; i < MB; ++i)
-            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[q][i]),
-                                                             __builtin_bit_cast(bf16x8_t, fb[q]), acc[i], 0, 0, 0);
       }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int i = 0; i < RA; ++i)
+#pragma unroll
+          for (int j = 0; j < RB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kk][j], fa[kk][i], acc[i][j], 0, 0, 0);
       __syncthreads();
     };
-    Set s[AHEAD];
+    // Rounds of SETS stages, then what is left of one: no way out of the middle of the loop, which
+    // the compiler would give an edge back to its head and with it a wait for every load there.
+    uint32_t c = 0;
+    for (; c + SETS <= ns; c += SETS)
 #pragma unroll
-    for (int d = 0; d < AHEAD; ++d) {
-      request(s[d], d);
-      __builtin_amdgcn_sched_barrier(0);                  // (in the order in which they are waited for)
-    }
-    // (the only way round a stage is out of the loop: see the small tile)
-    [&] {
-      for (uint32_t c = 0;; c += AHEAD)
-#pragma unroll
-        for (int d = 0; d < AHEAD; ++d) {
-          step(s[d], c + d + AHEAD);
-          if (c + d + 1 >= ns) return;
+      for (int d = 0; d < SETS; ++d) step(d, c + d);
+    auto rest = [&](auto &&self, auto at) -> void {
+      constexpr int d = decltype(at)::value;
+      if constexpr (d + 1 < SETS)
+        if (c + d < ns) {
+          step(d, c + d);
+          self(self, std::integral_constant<int, d + 1>{});
         }
-    }();
-    // Output through 4 KB of LDS per wave, one 32x32 block at a time (layout as in the small
-    // tile): lane l leaves with columns 8 (l%4) .. +7 of rows l/4 and l/4 + 16
-    unsigned char *buf = s_ab + wave * 4096;
+    };
+    rest(rest, std::integral_constant<int, 0>{});
+    // B was the first MFMA operand, so lane l, register r of block (i, j) holds row 16 i + l%16,
+    // column 16 j + 4 (l/16) + r: four neighbours of one row, packed to 8 bytes.  Of two column
+    // blocks the swaps make eight neighbours per lane (group l/16 columns 8 (l/16) .. +7 of the
+    // 32), so that whole 64-byte pieces leave (4352 x 4864 x 64 13.3 us; 18.8 as 32-byte pieces).
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    auto pack = [](float x, float y) {
+      const f32x2_t p = {x, y};
+      return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
+    };
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
+    for (int i = 0; i < RA; ++i) {
+      const uint32_t row = by * TM + (wm * RA + i) * 16 + (lane & 15);
+      const uint32_t col = bx * TN + wn * 16 * RB + (lane >> 4) * (4 * RB);
+      uint32_t w[2 * RB];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) *reinterpret_cast<float *>(buf + (r * 64 + lane) * 4) = acc[i][r];
+      for (int j = 0; j < RB; ++j) {
+        w[2 * j] = pack(acc[i][j][0], acc[i][j][1]);
+        w[2 * j + 1] = pack(acc[i][j][2], acc[i][j][3]);
+      }
+      if constexpr (RB == 2) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t tr = (lane >> 2) + 16 * h, tc = (lane & 3) * 8;
-        const float *p = reinterpret_cast<const float *>(buf) + ((tr >> 3) * 4 + (tr & 3)) * 64 + ((tr >> 2) & 1) * 32 + tc;
-        uint16_t v[8];
+        for (int q = 0; q < 2; ++q)
+          asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(w[q]), "+v"(w[2 + q]));
+      }
+      if (row < a.m) {
+        uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
+        const uintptr_t mis = reinterpret_cast<uintptr_t>(g) & (RB == 2 ? 15u : 7u);
+        if (col + 4 * RB <= a.n && mis == 0) {
+          if constexpr (RB == 2) *reinterpret_cast<uint4 *>(g) = make_uint4(w[0], w[1], w[2], w[3]);
+          else *reinterpret_cast<uint2 *>(g) = make_uint2(w[0], w[1]);
+        } else if (RB == 2 && col + 8 <= a.n && mis == 8) {
+          *reinterpret_cast<uint2 *>(g) = make_uint2(w[0], w[1]);
+          *reinterpret_cast<uint2 *>(g + 4) = make_uint2(w[2 * RB - 2], w[2 * RB - 1]);
+        } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16(p[e]);
-        const uint32_t row = by * TM + (wm * MB + i) * 32 + tr, col = bx * TN + wn * 32 + tc;
-        if (row < a.m) {
-          uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
-          if (col + 8 <= a.n && (reinterpret_cast<uintptr_t>(g) & 7u) == 0) {
-            *reinterpret_cast<uint2 *>(g) = make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
-            *reinterpret_cast<uint2 *>(g + 4) = make_uint2(v[4] | (uint32_t)v[5] << 16, v[6] | (uint32_t)v[7] << 16);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (col + e < a.n) g[e] = v[e];
-          }
+          for (int e = 0; e < 4 * RB; ++e)
+            if (col + e < a.n) g[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
         }
       }
     }
 #endif
   }
 };
+using GemmSmallBody = GemmTileT<1, 1>;
 
 // Measured ceiling of the matrix pipe: every wave issues independent 32x32x16 bf16 MFMAs on
 // register operands only (no LDS, no memory), one wave per SIMD on every compute unit, as

@@ -14,7 +14,8 @@
 //   static __device__ void run(const Args&, uint32_t bx, uint32_t by, uint32_t bz);
 //   static __device__ void run_be(const Args&, uint32_t bx, uint32_t by, uint32_t bz);
 // run() performs the work of original block (bx,by,bz); run_be() is the same work as the
-// best-effort forms (sliced, persistent workers) do it: identical arithmetic, but data that
+// best-effort forms (sliced, persistent workers) do it: identical arithmetic (a kernel's outputs
+// are the same bits in every form, wherever a job was stopped), but data that
 // is touched once goes through non-temporal accesses so that it does not evict the
 // high-priority job's data from the caches; every thread of the workgroup
 // calls it and returns from it (no early exit), so the workgroup-wide barriers of the

@@ -187,21 +187,25 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 
 // How the original form of a GEMM covers its output: with the largest tiles that still leave no
 // compute unit idle, whatever the logical blocks are (only slices and workers have to keep to
-// those).  Counted in tiles for 256 compute units; us at m x n x 2048 for 32x32 with split K /
-// 64x64 / 128x64 / 256x128 / 256x256 tiles:
-//    512 x 1024   9.0 /  12.8 /  17.2 / 25.1 / 40.9   (128 of 64x64)
-//   1024 x 1024  15.1 /  15.2 /  18.1 / 25.4 / 41.3   (256; at k = 512 6.7 / 5.5)
-//   1024 x 2048  26.5 /  18.9 /  19.2 / 26.3 / 41.9   (512; 256 of 128x64)
-//   2048 x 2048  47.1 /  33.0 /  29.9 / 27.8 / 42.2   (128 of 256x128)
-//   2048 x 4096  89.1 /  60.2 /  51.2 / 34.4 / 45.2   (256 of 256x128)
-//   4096 x 4096   174 /   113 /  93.1 / 68.6 / 56.2   (256 of 256x256)
+// those; the bits are the same, see GemmTileT).  Counted in tiles for 256 compute units; us at
+// m x n x 2048 for 32x32 / 32x64 / 64x64 / 128x64 / 256x128 / 256x256 tiles:
+//    512 x 512    6.6 /  8.5 / 11.6 / 17.0 / 24.6 / 40.4   (256 of 32x32)
+//    512 x 768    9.8 /  8.7 / 11.7 / 17.1 / 24.6 / 40.5   (192 of 32x64)
+//    512 x 1024  10.4 /  9.0 / 11.9 / 17.2 / 24.4 / 40.7   (256 of 32x64)
+//    768 x 1024  13.9 / 13.5 / 12.2 / 17.3 / 24.4 / 40.6   (192 of 64x64)
+//   1024 x 1024  17.4 / 14.4 / 12.8 / 17.8 / 25.2 / 40.9   (256; at k = 8192 56 / 43 / 41)
+//   1024 x 2048  30.5 / 24.6 / 18.5 / 18.7 / 25.6 / 40.6   (512; 256 of 128x64)
+//   2048 x 2048  53.9 / 42.1 / 31.2 / 26.2 / 26.3 / 40.8   (128 of 256x128)
+//   2048 x 4096   106 / 71.5 / 51.7 / 43.6 / 30.2 / 42.1   (256 of 256x128)
+//   4096 x 4096   192 /  135 / 98.0 / 83.3 / 58.0 / 51.9   (256 of 256x256)
 // and the same order from k = 512 to 8192.  Below k = 128 there is no loop to speak of and the
-// large tiles' long prologue and epilogue lose to 128x64 (4352 x 4864 x 64: 17.4 against 14.2),
+// large tiles' long prologue and epilogue lose to 128x64 (4352 x 4864 x 64: 15.4 against 13.3),
 // unless the output is one that GemmBodyT writes past the caches.
-enum class GemmCover { k32, k64, k128x64, k256x128, k256x256 };
+enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256 };
 GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
   const uint64_t t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
-  if (t64 < 256) return GemmCover::k32;
+  if (t64 < 256)
+    return (uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256 ? GemmCover::k32 : GemmCover::k32x64;
   if (t64 <= 512) return GemmCover::k64;
   if (a.k <= 128 && (uint64_t)a.m * a.n * a.batch * 2u <= kGemmBigOutput) return GemmCover::k128x64;
   if ((uint64_t)cdiv(a.n, 128) * cdiv(a.m, 256) * a.batch <= 256) return GemmCover::k256x128;
@@ -218,22 +222,25 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
   memcpy(&a, args, sizeof(a));
   switch (gemm_cover(a)) {
     case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
-    case GemmCover::k64: return launch_gemm_cover<GemmMidBodyT<1>>(s, a, 64, 64, urgent);
-    case GemmCover::k128x64: return launch_gemm_cover<GemmMidBodyT<2>>(s, a, 64, 128, urgent);
+    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
+    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
+    case GemmCover::k128x64: return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
     case GemmCover::k256x128: return launch_gemm_cover<GemmN128Body>(s, a, 128, 256, urgent);
     default: return launch_native_t<Body>(s, args, g, urgent);
   }
 }
 // The ragged GEMM: only the tiles with predicated edges, which also fit beside a paused
-// best-effort tile.  128x64 tiles pay from two per compute unit (1000 x 2300 x 768, 288 of
-// them, 12.7 us with 64x64 and 14.1; 12 x 500 x 700 x 512, 528, 21.7 and 18.7).
+// best-effort tile.  128x64 tiles pay from two per compute unit (512 x 4096 x 4096, 256 of them,
+// 29 us with 64x64 and 32; 1024 x 4096 x 4096, 512, 54 and 47).
 hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t urgent) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  if (gemm_cover(a) == GemmCover::k32) return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
+  const GemmCover cover = gemm_cover(a);
+  if (cover == GemmCover::k32) return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
+  if (cover == GemmCover::k32x64) return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
   if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512)
-    return launch_gemm_cover<GemmMidBodyT<2>>(s, a, 64, 128, urgent);
-  return launch_gemm_cover<GemmMidBodyT<1>>(s, a, 64, 64, urgent);
+    return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
+  return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
 }
 // Persistent workers of a grid so small that a worker per part of a block suffices: the smallest
 // parts for which it does.  PX x PY parts of a 256 x TN block, in the order of gemm_cover's table
@@ -243,8 +250,8 @@ template <class Body>
 struct GemmParts {
   static constexpr uint32_t X = Body::TILE_N / 32, Y = Body::TILE / 32;
   typedef PartsBody<GemmSmallBody, X, Y> P32;
-  typedef PartsBody<GemmMidBodyT<1>, X / 2, Y / 2> P64;
-  typedef PartsBody<GemmMidBodyT<2>, X / 2, Y / 4> P128;
+  typedef PartsBody<GemmTileT<2, 2>, X / 2, Y / 2> P64;
+  typedef PartsBody<GemmTileT<4, 2>, X / 2, Y / 4> P128;
   typedef PartsBody<GemmN128Body, X / 4, 1> PN128;
   typedef TailBody<Body, GemmN128Body, X / 4, 1> Tail;
   static uint32_t parts(uint64_t blocks, uint32_t workers, uint32_t chunk, uint32_t *whole) {
@@ -287,7 +294,8 @@ struct GemmParts {
 // (whichever of its kernels occupies most)
 hipError_t footprint_native_gemm_small(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
   *lds_bytes = *waves = *regs_per_lane = 0;
-  for (auto f : {footprint_native_t<GemmSmallBody>, footprint_native_t<GemmMidBodyT<1>>, footprint_native_t<GemmMidBodyT<2>>}) {
+  for (auto f : {footprint_native_t<GemmSmallBody>, footprint_native_t<GemmTileT<1, 2>>, footprint_native_t<GemmTileT<2, 2>>,
+                 footprint_native_t<GemmTileT<4, 2>>}) {
     uint32_t l, w, r;
     hipError_t e = f(&l, &w, &r);
     if (e != hipSuccess) return e;

@@ -464,6 +464,43 @@ def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
     assert (host(buf[batch * m * n:]) == 0x7FC0).all()
 
 
+@pytest.mark.parametrize("tile,m,n,k,batch", [
+    ("256", 256, 256, 96, 1), ("256", 512, 512, 1056, 1), ("256", 512, 768, 288, 1), ("256", 1024, 1024, 544, 1),
+    ("256", 1024, 2048, 2080, 1), ("256", 2048, 2048, 64, 1), ("256", 4352, 4864, 96, 1), ("256", 1280, 1280, 2048, 1),
+    ("128", 256, 384, 1056, 1), ("128", 512, 768, 2048, 3), ("small", 100, 300, 416, 2), ("small", 300, 1000, 1024, 1),
+    ("small", 1000, 2300, 768, 1), ("small", 130, 65, 96, 128), ("small", 127, 129, 224, 171)])
+def test_gemm_bits_do_not_depend_on_form_or_schedule(env, tile, m, n, k, batch):
+    """Every tile that any form covers the product with adds in the same order: one worker, several,
+    enough for parts of blocks, jobs stopped so near the end that the rest is done in parts, slices
+    and the original form give the same bits."""
+    B, ctx, torch = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + n + k)
+    A = torch.randn(batch, m, k, device="cuda", generator=gen).to(torch.bfloat16)
+    Bt = torch.randn(batch, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.empty(batch, m, n, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C, small=tile == "small", n128=tile == "128")
+    total = kern.total_blocks
+
+    def bits(launch):
+        C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        job = launch()
+        while job is not None and job.wait() != B.JOB_COMPLETE:
+            job.resume()
+        if job is not None:
+            job.free()
+        torch.cuda.synchronize()
+        return C.view(torch.int16).clone()
+
+    want = bits(lambda: ctx.launch_ptb(kern, 1))
+    for what, launch in [("native", lambda: ctx.launch_native(kern)), ("slices", lambda: ctx.launch_sliced(kern, total // 3 + 1)),
+                         ("5 workers", lambda: ctx.launch_ptb(kern, 5)), ("256 workers", lambda: ctx.launch_ptb(kern, 256)),
+                         ("1 block left", lambda: ctx.launch_ptb(kern, 256, stop_at=total - 1)),
+                         ("3 blocks left", lambda: ctx.launch_ptb(kern, 256, stop_at=max(total - 3, 0)))]:
+        assert torch.equal(bits(launch), want), what
+
+
 # ------------------------------------------------------------------ GEMV
 @pytest.mark.parametrize("n,k,form", [(130, 96, "native"), (130, 96, "ptb_preempted"),
                                       (4096, 4096, "native_hi"), (4096, 11008, "native_hi"),
