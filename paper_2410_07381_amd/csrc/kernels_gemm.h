@@ -389,7 +389,7 @@ struct GemmTileT {
   static constexpr int THREADS = 256;
   static constexpr int MIN_WAVES = 4;
   static constexpr unsigned DYN_LDS = 0;
-  static constexpr bool YIELDS = RA * RB > 2;
+  static constexpr bool YIELDS = true;
   static constexpr bool RANGE = false;
   // a block's last barrier follows its last fragment read
   static constexpr bool END_BARRIER = false;
@@ -491,10 +491,20 @@ struct GemmTileT {
       request(s[0], SETS);
       __syncthreads();
     }
-    uint32_t pause_left = ctl.ticks;
-    // (a look at the pause word costs this workgroup 0.7 us, two stages: eight times as many
-    // stages lie between two looks as GemmBodyT has, whose stages last eight times as long)
-    const uint32_t poll_mask = (ctl.mask << 2) | 3;
+    // Looks at the pause word.  Waiting for one costs the workgroup 0.7 us, several of its stages:
+    // one lane asks for the word at the start of a round of SETS stages, behind the loads on their
+    // way, and has it at the start of the next.  (Its offset, not a branch, says who asks and
+    // when: all others are outside the buffer.)
+    uint32_t pause_left = ctl.ticks, look = 0;
+    const buf_t rF = make_buf(ctl.flag, YIELD && ctl.ticks != 0 ? 4 : 0);
+    const uint32_t v_look = tid == 0 ? 0u : OOB, look_mask = (ctl.mask >> 1) & ~(SETS - 1u);   // in stages
+    auto look_round = [&](uint32_t c) {
+      if constexpr (YIELD) {
+        // one wave pauses; the others meet it at the next barrier
+        if (__builtin_amdgcn_readfirstlane(look) == ctl.epoch) yield_while_preempted(ctl, pause_left);
+        look = __builtin_amdgcn_raw_buffer_load_b32(rF, v_look | ((c & look_mask) == look_mask ? 0u : OOB), 0, 16);  // (sc1)
+      }
+    };
     // stage c, whose operands (with two buffers those of stage c + 1) are in set d
     auto step = [&](int d, uint32_t c) {
       bf16x8_t fa[2][RA], fb[2][RB];
@@ -512,8 +522,6 @@ struct GemmTileT {
         request(s[next], c + 1 + SETS);
         __builtin_amdgcn_sched_barrier(0);
       } else {
-        // one wave polls; the others meet it at the barrier
-        if (YIELD && ctl.ticks != 0 && wave == 0 && ((c + SETS) & poll_mask) == poll_mask) yield_while_preempted(ctl, pause_left);
         store(s[d], 0);
         request(s[d], c + SETS);
         __syncthreads();
@@ -539,9 +547,11 @@ struct GemmTileT {
     // Rounds of SETS stages, then what is left of one: no way out of the middle of the loop, which
     // the compiler would give an edge back to its head and with it a wait for every load there.
     uint32_t c = 0;
-    for (; c + SETS <= ns; c += SETS)
+    for (; c + SETS <= ns; c += SETS) {
+      look_round(c);
 #pragma unroll
       for (int d = 0; d < SETS; ++d) step(d, c + d);
+    }
     auto rest = [&](auto &&self, auto at) -> void {
       constexpr int d = decltype(at)::value;
       if constexpr (d + 1 < SETS)
@@ -594,7 +604,10 @@ struct GemmTileT {
 #endif
   }
 };
-using GemmSmallBody = GemmTileT<1, 1>;
+// The small GEMM's own blocks stop at their ends only, as its waves fit beside a request's.
+struct GemmSmallBody : GemmTileT<1, 1> {
+  static constexpr bool YIELDS = false;
+};
 
 // Measured ceiling of the matrix pipe: every wave issues independent 32x32x16 bf16 MFMAs on
 // register operands only (no LDS, no memory), one wave per SIMD on every compute unit, as

@@ -249,7 +249,7 @@ hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3,
 template <class Body>
 struct GemmParts {
   static constexpr uint32_t X = Body::TILE_N / 32, Y = Body::TILE / 32;
-  typedef PartsBody<GemmSmallBody, X, Y> P32;
+  typedef PartsBody<GemmTileT<1, 1>, X, Y> P32;
   typedef PartsBody<GemmTileT<2, 2>, X / 2, Y / 2> P64;
   typedef PartsBody<GemmTileT<4, 2>, X / 2, Y / 4> P128;
   typedef PartsBody<GemmN128Body, X / 4, 1> PN128;

@@ -240,3 +240,50 @@ def test_workers_pause_inside_long_blocks_while_preempted(env):
         OK.exec_block("gemm_bf16", (bx, by, 0), (4, 4, 1), a)
         r, c = slice(by * 256, by * 256 + 256), slice(bx * 256, bx * 256 + 256)
         assert_bf16_close(got[0, r, c], a["C"][0, r, c])
+
+
+@pytest.mark.parametrize("m,n,k", [(256, 512, 1 << 18), (512, 1024, 1 << 17), (1024, 2048, 1 << 16)])
+def test_workers_on_parts_of_blocks_pause_as_well(env, m, n, k):
+    """Fewer blocks than workers over a long K, handed out in parts of 32x32, 64x64 and 128x64: a
+    pausing request raised mid-part suspends the workers until the pause is ended; the numbers are
+    those of an undisturbed run."""
+    import time
+    B, ctx, torch = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    A = torch.randn(1, m, k, device="cuda", generator=gen).to(torch.bfloat16)
+    Bt = torch.randn(1, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.empty(1, m, n, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C)
+
+    def run(pause_s):
+        C.fill_(float("nan"))
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        job = ctx.launch_ptb(kern, 256, coverage=True)
+        t1 = t0 + 0.0001
+        while time.perf_counter() < t1:
+            pass
+        if pause_s:
+            job.preempt(pause=True)
+            time.sleep(pause_s)
+            job.pump()
+            assert job.progress()[2] == B.JOB_RUNNING
+            job.end_pause()
+        st = job.wait()
+        dt = time.perf_counter() - t0
+        assert st == B.JOB_COMPLETE
+        assert (job.coverage()["count"] == 1).all()
+        job.free()
+        torch.cuda.synchronize()
+        return dt, C.view(torch.int16).clone()
+
+    ctx.set_yield_bound_us(100000)
+    try:
+        run(0.0)
+        base, want = run(0.0)
+        assert 0.0003 < base < 0.004, base           # long enough to be met mid-part, shorter than the pause
+        paused, got = run(0.004)
+    finally:
+        ctx.set_yield_bound_us(1000)
+    assert paused > 0.004 and torch.equal(got, want)
