@@ -345,7 +345,9 @@ int tally_select_config(const tally_config *cands, uint32_t n, double threshold_
  * Turnaround of a persistent-worker candidate is Eq. 1; for a kernel whose workers pause
  * inside their blocks while preempted (and with the pause enabled, see
  * tally_set_yield_bound_us) it is the time of ONE block times the share of a block
- * between two pause points, since that is when the execution units are handed over. */
+ * between two pause points, since that is when the execution units are handed over.  Where
+ * workers take a GEMM's blocks in parts, one each, the part stands for the block: its time is
+ * the kernel's. */
 int tally_profile(tally_ctx *ctx, const tally_kernel_desc *desc, tally_config *cands, uint32_t n,
                   uint32_t runs, double threshold_ms, uint32_t *chosen);
 /* lookup_launch_config() of Figure 4: the fixed choice for (kernel, grid, block);

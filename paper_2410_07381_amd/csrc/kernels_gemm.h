@@ -397,6 +397,12 @@ struct GemmTileT {
   static constexpr bool TWO = RA * RB <= 2;               // LDS holds two stages
   static constexpr int AHEAD = RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
   static constexpr uint32_t SA = TM * 128, STAGE = (TM + TN) * 128;   // bytes of A, of both in a stage
+  // share of a tile between asking for the pause word and pausing on the answer to the next
+  // question, `every` k-steps of 32 apart (see look_round); host side, for turnaround estimates
+  static double pause_fraction(const Args &a, uint32_t every) {
+    const uint32_t ns = (a.k + 63) / 64, apart = every / 2 > AHEAD ? every / 2 : AHEAD;
+    return ns > apart + AHEAD ? (double)(apart + AHEAD) / ns : 1.0;
+  }
 
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
     run_impl<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15});

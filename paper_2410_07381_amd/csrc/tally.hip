@@ -58,9 +58,10 @@ struct KernelOps {
   hipError_t (*ptb)(hipStream_t, const void *args, const PtbCtl &);
   hipError_t (*init)();
   int (*occupancy)(int *blocks_per_cu);
-  // share of one logical block between two points at which a preempted worker pauses
-  // (1 for bodies that only stop at block boundaries)
-  double (*pause_fraction)(const void *args, uint32_t every);
+  // share of one logical block (or, with `parts` > 1 and no whole blocks before them, of one part)
+  // between two points at which a preempted worker pauses (1 for bodies that only stop at block
+  // boundaries)
+  double (*pause_fraction)(const void *args, uint32_t every, uint32_t parts, uint32_t whole);
   // what one workgroup of the persistent-worker kernel occupies on a compute unit
   hipError_t (*footprint)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
   // the same for one workgroup of the kernel in its original form
@@ -278,6 +279,15 @@ struct GemmParts {
     if constexpr (PN128::PARTS > 1) return launch_ptb_t<PN128>(s, args, c);
     return hipErrorInvalidValue;
   }
+  static double pause_fraction(const void *args, uint32_t every, uint32_t parts, uint32_t whole) {
+    tally_gemm_bf16_args a;
+    memcpy(&a, args, sizeof(a));
+    if (parts == 1 || whole) return Body::pause_fraction(a, every);
+    if (parts == P32::PARTS) return P32::Sub::pause_fraction(a, every);
+    if (parts == P64::PARTS) return P64::Sub::pause_fraction(a, every);
+    if (parts == P128::PARTS) return P128::Sub::pause_fraction(a, every);
+    return PN128::Sub::pause_fraction(a, every);
+  }
   static hipError_t init() {
     hipError_t e = init_t<Body>();
     if constexpr (PN128::PARTS > 1) {
@@ -412,7 +422,7 @@ int grid_attn(const void *p, tally_dim3 *g, tally_dim3 *b) {
 }
 
 template <class Body>
-double pause_fraction_t(const void *args, uint32_t every) {
+double pause_fraction_t(const void *args, uint32_t every, uint32_t, uint32_t) {
   if constexpr (Body::YIELDS) {
     typename Body::Args a;
     memcpy(&a, args, sizeof(a));
@@ -432,7 +442,7 @@ const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(ReduceSumBody, "reduce_sum", grid_reduce_sum),
     OPS(ReduceFinalBody, "reduce_final", grid_reduce_final),
     {"gemm_bf16", sizeof(GemmBody::Args), true, grid_gemm, launch_native_gemm_t<GemmBody>, launch_sliced_t<GemmBody>,
-     GemmParts<GemmBody>::launch, GemmParts<GemmBody>::init, occupancy_t<GemmBody>, pause_fraction_t<GemmBody>,
+     GemmParts<GemmBody>::launch, GemmParts<GemmBody>::init, occupancy_t<GemmBody>, GemmParts<GemmBody>::pause_fraction,
      footprint_t<GemmBody>, footprint_native_t<GemmBody>, GemmParts<GemmBody>::parts},
     OPS(GemvBody, "gemv_bf16", grid_gemv),
     {"softmax_f32", sizeof(SoftmaxBody::Args), true, grid_softmax,
@@ -452,7 +462,7 @@ const KernelOps kOps[TALLY_K_COUNT] = {
      pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, footprint_native_gemm_small},
     {"gemm_bf16_n128", sizeof(GemmN128Body::Args), true, grid_gemm_n128, launch_native_gemm_t<GemmN128Body>,
      launch_sliced_t<GemmN128Body>, GemmParts<GemmN128Body>::launch, GemmParts<GemmN128Body>::init,
-     occupancy_t<GemmN128Body>, pause_fraction_t<GemmN128Body>, footprint_t<GemmN128Body>,
+     occupancy_t<GemmN128Body>, GemmParts<GemmN128Body>::pause_fraction, footprint_t<GemmN128Body>,
      footprint_native_t<GemmN128Body>, GemmParts<GemmN128Body>::parts},
 };
 
@@ -705,6 +715,17 @@ int settle_relays_before(tally_ctx *ctx, hipStream_t ctl) {
   return TALLY_OK;
 }
 
+// Parts that workers take a segment of `blocks` blocks up to block `limit` in (GemmParts).
+uint32_t segment_parts(const KernelOps *ops, uint64_t blocks, uint64_t limit, uint32_t workers, uint32_t chunk,
+                       uint32_t *whole) {
+  *whole = 0;
+  const uint32_t parts = ops->parts && blocks ? ops->parts(blocks, workers, chunk, whole) : 1u;
+  // (with indices counted in parts, the end of the grid has to stay a valid index)
+  if (limit * parts <= 0x40000000ull) return parts;
+  *whole = 0;
+  return 1u;
+}
+
 // Launch the workers (and their relay) for task indices [progress, limit).  Requires the
 // job's previous segment, if any, to have drained.
 int ptb_launch_segment(tally_job *j, uint32_t limit) {
@@ -720,10 +741,8 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   j->epoch = ctx->slot_epoch[slot] + 1;
   j->limit = limit < j->total ? limit : j->total;
   const uint64_t blocks = j->limit > start ? j->limit - start : 0u;
-  // (with indices counted in parts, the end of the grid has to stay a valid index)
   uint32_t whole = 0;
-  uint32_t parts = j->ops->parts && blocks ? j->ops->parts(blocks, j->workers, j->chunk, &whole) : 1u;
-  if ((uint64_t)j->limit * parts > 0x40000000ull) parts = 1;
+  const uint32_t parts = segment_parts(j->ops, blocks, j->limit, j->workers, j->chunk, &whole);
   const uint32_t chunk = parts > 1 ? 1u : j->chunk;
   j->counter_base = ctx->slot_counter[slot] - start * parts;
   __atomic_store_n(j->h_flag(), 0u, __ATOMIC_RELEASE);   // no request stands against the new segment
@@ -1451,12 +1470,15 @@ ProfileKey profile_key(const tally_kernel_desc *d) {
 void fill_turnaround(tally_ctx *ctx, const KernelOps *ops, const void *args, uint64_t total,
                      tally_config *c) {
   if (c->kind == 0) {
-    c->turnaround_ms = (float)tally_ptb_turnaround_ms(c->latency_ms, c->param, c->chunk ? c->chunk : 1, total);
+    uint32_t whole = 0;
+    const uint32_t parts = segment_parts(ops, total, total, c->param, c->chunk ? c->chunk : 1, &whole);
     // a body that pauses inside its blocks hands the execution units over after a share
     // of ONE block, whatever the chunk: Eq. 1 with chunk 1, times that share
-    const double share = ctx->yield_ticks ? ops->pause_fraction(args, ctx->yield_every) : 1.0;
-    if (share < 1.0)
-      c->turnaround_ms = (float)(tally_ptb_turnaround_ms(c->latency_ms, c->param, 1, total) * share);
+    const double share = ctx->yield_ticks ? ops->pause_fraction(args, ctx->yield_every, parts, whole) : 1.0;
+    if (parts > 1 && !whole)   // one part per worker, all of them at once: a part lasts as long as the kernel
+      c->turnaround_ms = (float)(c->latency_ms * share);
+    else
+      c->turnaround_ms = (float)(tally_ptb_turnaround_ms(c->latency_ms, c->param, share < 1.0 || !c->chunk ? 1 : c->chunk, total) * share);
   } else {
     // one slice's time, times the number of slices that may be enqueued at once
     uint64_t slices = (total + c->param - 1) / c->param;

@@ -185,6 +185,30 @@ def test_profile_picks_a_config_under_the_threshold(env):
     assert got is not None and got["param"] == meas[chosen]["param"]
 
 
+@pytest.mark.parametrize("m,n,ahead", [(512, 512, 8), (1024, 1024, 2), (1024, 2048, 1)])
+def test_turnaround_of_parts_of_blocks(env, m, n, ahead):
+    """256 workers on 4, 16 and 32 blocks take a part each, all at once: a part lasts as long as the
+    kernel (Eq. 1 would say 64, 16 and 8 times as long), and a worker pauses after the stages of
+    64 k between two looks (4 steps of 32 k, at least a round of `ahead` stages) and the round in
+    which the answer is on its way."""
+    B, ctx, torch = env
+    k = 4096
+    A = torch.zeros(1, m, k, dtype=torch.bfloat16, device="cuda")
+    Bt = torch.zeros(1, n, k, dtype=torch.bfloat16, device="cuda")
+    C = torch.zeros(1, m, n, dtype=torch.bfloat16, device="cuda")
+    torch.cuda.synchronize()
+    kern = B.gemm_bf16(A, Bt, C)
+    try:
+        meas, _ = ctx.profile(kern, [(B.CFG_PTB, 256, 1)], runs=2)
+        assert meas[0]["turnaround_ms"] == pytest.approx(meas[0]["latency_ms"] * (max(2, ahead) + ahead) / 64, rel=1e-5)
+        ctx.set_yield_bound_us(0)
+        meas, _ = ctx.profile(kern, [(B.CFG_PTB, 256, 1)], runs=2)
+        assert meas[0]["turnaround_ms"] == pytest.approx(meas[0]["latency_ms"], rel=1e-5)
+    finally:
+        ctx.set_yield_bound_us(1000)
+        ctx.profile_reset()
+
+
 def test_workers_pause_inside_long_blocks_while_preempted(env):
     """A 256x256 tile over K = 32768 lasts about a millisecond.  A pausing preemption request
     raised mid-tile suspends the workers until the pause is ended; the kernel then finishes,
