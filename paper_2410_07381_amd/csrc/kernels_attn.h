@@ -164,13 +164,19 @@ __global__ __launch_bounds__(128) void attn_decode_combine(tally_attn_decode_arg
 
 inline hipError_t attn_decode_init() { return hipSuccess; }
 
+inline uint32_t attn_decode_chunk(const tally_attn_decode_args &a) {
+  return ((a.tokens + kAttnSplits - 1) / kAttnSplits + 15u) & ~15u;
+}
+inline uint32_t attn_decode_waves(const tally_attn_decode_args &a) {
+  return a.heads <= kAttnFewHeads && attn_decode_chunk(a) >= kAttnLongChunk ? 8 : 4;
+}
+
 inline hipError_t launch_attn_decode(hipStream_t s, const void *args, tally_dim3, uint32_t urgent) {
   tally_attn_decode_args a;
   memcpy(&a, args, sizeof(a));
-  uint32_t chunk = (a.tokens + kAttnSplits - 1) / kAttnSplits;
-  chunk = (chunk + 15u) & ~15u;
+  const uint32_t chunk = attn_decode_chunk(a);
   if (chunk > kAttnMaxChunk) return hipErrorInvalidValue;
-  if (a.heads <= kAttnFewHeads && chunk >= kAttnLongChunk)
+  if (attn_decode_waves(a) == 8)
     hipLaunchKernelGGL(attn_decode_partial<8>, dim3(kAttnSplits, a.heads), dim3(512), 0, s, a, chunk, urgent);
   else
     hipLaunchKernelGGL(attn_decode_partial<4>, dim3(kAttnSplits, a.heads), dim3(256), 0, s, a, chunk, urgent);

@@ -48,6 +48,9 @@ uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // ---------------------------------------------------------------------------- registry
+typedef hipError_t (*FootprintFn)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
+constexpr uint32_t kMaxNative = 6;   // kernels that one operator's original form chooses from
+
 struct KernelOps {
   const char *name;
   size_t args_size;
@@ -63,9 +66,13 @@ struct KernelOps {
   // boundaries)
   double (*pause_fraction)(const void *args, uint32_t every, uint32_t parts, uint32_t whole);
   // what one workgroup of the persistent-worker kernel occupies on a compute unit
-  hipError_t (*footprint)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
-  // the same for one workgroup of the kernel in its original form
-  hipError_t (*footprint_native)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
+  FootprintFn footprint;
+  // the same for one workgroup of each kernel that the original form chooses from
+  FootprintFn footprint_native[kMaxNative];
+  // which of them a launch of these arguments takes: in its original form, with the number of
+  // its workgroups (null: the first, one workgroup per logical block), and in slices (null: the same)
+  uint32_t (*native_choice)(const void *args, uint64_t *groups);
+  uint32_t (*sliced_choice)(const void *args);
   // parts the persistent-worker form splits each of `blocks` logical blocks in (null: never), and
   // how many whole blocks each worker takes first
   uint32_t (*parts)(uint64_t blocks, uint32_t workers, uint32_t chunk, uint32_t *whole);
@@ -149,41 +156,61 @@ hipError_t footprint_native_t(uint32_t *lds_bytes, uint32_t *waves, uint32_t *re
   *regs_per_lane = ((uint32_t)attr.numRegs + 7u) & ~7u;
   return hipSuccess;
 }
+template <uint32_t WAVES>
 hipError_t footprint_attn(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
-  hipFuncAttributes attr;   // (the kernel of eight waves: the other occupies less)
-  hipError_t e = hipFuncGetAttributes(&attr, (const void *)attn_decode_partial<8>);
+  hipFuncAttributes attr;
+  hipError_t e = hipFuncGetAttributes(&attr, (const void *)attn_decode_partial<WAVES>);
   if (e != hipSuccess) return e;
   *lds_bytes = (uint32_t)attr.sharedSizeBytes;
-  *waves = 8;
+  *waves = WAVES;
   *regs_per_lane = ((uint32_t)attr.numRegs + 7u) & ~7u;
   return hipSuccess;
 }
+uint32_t attn_choice(const void *args, uint64_t *groups) {
+  tally_attn_decode_args a;
+  memcpy(&a, args, sizeof(a));
+  *groups = (uint64_t)kAttnSplits * a.heads;
+  return attn_decode_waves(a) == 8 ? 1 : 0;
+}
 
-// Row kernels: one kernel per range of widths (see RowsBodyT).  No variant needs more
-// registers or LDS than `Wide`, whose footprint and residency stand for all of them.
-template <class Wide, class Narrow, class Team>
-hipError_t launch_native_rows_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+// Row kernels: one kernel per range of widths (see RowsBodyT).  No worker needs more registers
+// than `Wide`'s, whose footprint and residency stand for all of them.
+template <class Wide, class Narrow>
+uint32_t rows_range(const void *args) {
   typename Wide::Args a;
   memcpy(&a, args, sizeof(a));
-  if (a.cols <= Narrow::MAX_COLS) return launch_native_t<Narrow>(s, args, g, urgent);
-  if (a.cols > Wide::MAX_COLS) return launch_native_t<Team>(s, args, g, urgent);
-  return launch_native_t<Wide>(s, args, g, urgent);
+  return a.cols <= Narrow::MAX_COLS ? 0 : a.cols <= Wide::MAX_COLS ? 1 : 2;
+}
+template <class Wide, class Narrow>
+uint32_t rows_choice(const void *args, uint64_t *groups) {
+  typename Wide::Args a;
+  memcpy(&a, args, sizeof(a));
+  *groups = ((uint64_t)a.rows + 3) / 4;
+  return rows_range<Wide, Narrow>(args);
+}
+template <class Wide, class Narrow, class Team>
+hipError_t launch_native_rows_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+  switch (rows_range<Wide, Narrow>(args)) {
+    case 0: return launch_native_t<Narrow>(s, args, g, urgent);
+    case 1: return launch_native_t<Wide>(s, args, g, urgent);
+    default: return launch_native_t<Team>(s, args, g, urgent);
+  }
 }
 template <class Wide, class Narrow, class Team>
 hipError_t launch_sliced_rows_t(hipStream_t s, const void *args, uint32_t nblocks, const SliceCtl &c) {
-  typename Wide::Args a;
-  memcpy(&a, args, sizeof(a));
-  if (a.cols <= Narrow::MAX_COLS) return launch_sliced_t<Narrow>(s, args, nblocks, c);
-  if (a.cols > Wide::MAX_COLS) return launch_sliced_t<Team>(s, args, nblocks, c);
-  return launch_sliced_t<Wide>(s, args, nblocks, c);
+  switch (rows_range<Wide, Narrow>(args)) {
+    case 0: return launch_sliced_t<Narrow>(s, args, nblocks, c);
+    case 1: return launch_sliced_t<Wide>(s, args, nblocks, c);
+    default: return launch_sliced_t<Team>(s, args, nblocks, c);
+  }
 }
 template <class Wide, class Narrow, class Team>
 hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
-  typename Wide::Args a;
-  memcpy(&a, args, sizeof(a));
-  if (a.cols <= Narrow::MAX_COLS) return launch_ptb_t<Narrow>(s, args, c);
-  if (a.cols > Wide::MAX_COLS) return launch_ptb_t<Team>(s, args, c);
-  return launch_ptb_t<Wide>(s, args, c);
+  switch (rows_range<Wide, Narrow>(args)) {
+    case 0: return launch_ptb_t<Narrow>(s, args, c);
+    case 1: return launch_ptb_t<Wide>(s, args, c);
+    default: return launch_ptb_t<Team>(s, args, c);
+  }
 }
 
 // How the original form of a GEMM covers its output: with the largest tiles that still leave no
@@ -233,16 +260,42 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
 // The ragged GEMM: only the tiles with predicated edges, which also fit beside a paused
 // best-effort tile.  128x64 tiles pay from two per compute unit (512 x 4096 x 4096, 256 of them,
 // 29 us with 64x64 and 32; 1024 x 4096 x 4096, 512, 54 and 47).
+GemmCover gemm_cover_small(const tally_gemm_bf16_args &a) {
+  const GemmCover c = gemm_cover(a);
+  if (c == GemmCover::k32 || c == GemmCover::k32x64) return c;
+  return (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512 ? GemmCover::k128x64 : GemmCover::k64;
+}
 hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t urgent) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  const GemmCover cover = gemm_cover(a);
-  if (cover == GemmCover::k32) return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
-  if (cover == GemmCover::k32x64) return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
-  if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512)
-    return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
-  return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
+  switch (gemm_cover_small(a)) {
+    case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
+    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
+    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
+    default: return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
+  }
 }
+// which of the kernels in kOps (in the order of GemmCover) and how many workgroups of it
+uint32_t gemm_choice(const tally_gemm_bf16_args &a, GemmCover c, uint32_t tn, uint64_t *groups) {
+  static const uint32_t tile[][2] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}, {256, 128}};
+  const uint32_t i = (uint32_t)c;
+  *groups = (uint64_t)cdiv(a.m, i < 5 ? tile[i][0] : 256) * cdiv(a.n, i < 5 ? tile[i][1] : tn) * a.batch;
+  return i;
+}
+template <uint32_t TN>
+uint32_t gemm_native_choice(const void *args, uint64_t *groups) {
+  tally_gemm_bf16_args a;
+  memcpy(&a, args, sizeof(a));
+  return gemm_choice(a, gemm_cover(a), TN, groups);
+}
+uint32_t gemm_small_native_choice(const void *args, uint64_t *groups) {
+  tally_gemm_bf16_args a;
+  memcpy(&a, args, sizeof(a));
+  return gemm_choice(a, gemm_cover_small(a), 32, groups);
+}
+template <GemmCover C>
+uint32_t gemm_sliced_choice(const void *) { return (uint32_t)C; }
+
 // Persistent workers of a grid so small that a worker per part of a block suffices: the smallest
 // parts for which it does.  PX x PY parts of a 256 x TN block, in the order of gemm_cover's table
 // (one workgroup per compute unit, k = 2048: 6 / 12 / 17 / 25 us a part against 40 for a 256x256
@@ -301,21 +354,6 @@ struct GemmParts {
     return e;
   }
 };
-// (whichever of its kernels occupies most)
-hipError_t footprint_native_gemm_small(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
-  *lds_bytes = *waves = *regs_per_lane = 0;
-  for (auto f : {footprint_native_t<GemmSmallBody>, footprint_native_t<GemmTileT<1, 2>>, footprint_native_t<GemmTileT<2, 2>>,
-                 footprint_native_t<GemmTileT<4, 2>>}) {
-    uint32_t l, w, r;
-    hipError_t e = f(&l, &w, &r);
-    if (e != hipSuccess) return e;
-    *lds_bytes = *lds_bytes > l ? *lds_bytes : l;
-    *waves = *waves > w ? *waves : w;
-    *regs_per_lane = *regs_per_lane > r ? *regs_per_lane : r;
-  }
-  return hipSuccess;
-}
-
 const tally_dim3 kBlock256 = {256, 1, 1};
 
 int grid_saxpy(const void *p, tally_dim3 *g, tally_dim3 *b) {
@@ -435,35 +473,40 @@ double pause_fraction_t(const void *args, uint32_t every, uint32_t, uint32_t) {
 #define OPS(Body, nm, gridfn)                                                              \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_t<Body>, launch_sliced_t<Body>,     \
    launch_ptb_t<Body>, init_t<Body>, occupancy_t<Body>, pause_fraction_t<Body>,              \
-   footprint_t<Body>, footprint_native_t<Body>}
+   footprint_t<Body>, {footprint_native_t<Body>}}
+
+#define GEMM_TILES \
+  footprint_native_t<GemmSmallBody>, footprint_native_t<GemmTileT<1, 2>>, footprint_native_t<GemmTileT<2, 2>>, \
+  footprint_native_t<GemmTileT<4, 2>>
+#define OPS_ROWS(Wide, Narrow, NarrowDeep, Team, occupancy, nm, gridfn)                                   \
+  {nm, sizeof(Wide::Args), true, gridfn, launch_native_rows_t<Wide, Narrow, Team>,                        \
+   launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
+   occupancy, pause_fraction_t<Wide>, footprint_t<Wide>,                                                  \
+   {footprint_native_t<Narrow>, footprint_native_t<Wide>, footprint_native_t<Team>},                      \
+   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>}
+#define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
+  {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
+   GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
+   footprint_t<Body>, {GEMM_TILES, footprint_native_t<GemmN128Body>, footprint_native_t<Body>},           \
+   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(SaxpyBody, "saxpy", grid_saxpy),
     OPS(ReduceSumBody, "reduce_sum", grid_reduce_sum),
     OPS(ReduceFinalBody, "reduce_final", grid_reduce_final),
-    {"gemm_bf16", sizeof(GemmBody::Args), true, grid_gemm, launch_native_gemm_t<GemmBody>, launch_sliced_t<GemmBody>,
-     GemmParts<GemmBody>::launch, GemmParts<GemmBody>::init, occupancy_t<GemmBody>, GemmParts<GemmBody>::pause_fraction,
-     footprint_t<GemmBody>, footprint_native_t<GemmBody>, GemmParts<GemmBody>::parts},
+    OPS_GEMM(GemmBody, "gemm_bf16", grid_gemm, GemmCover::k256x256),
     OPS(GemvBody, "gemv_bf16", grid_gemv),
-    {"softmax_f32", sizeof(SoftmaxBody::Args), true, grid_softmax,
-     launch_native_rows_t<SoftmaxBody, SoftmaxNarrowBody, SoftmaxTeamBody>,
-     launch_sliced_rows_t<SoftmaxBody, SoftmaxNarrowBody, SoftmaxTeamBody>,
-     launch_ptb_rows_t<SoftmaxBody, SoftmaxNarrowDeepBody, SoftmaxTeamBody>, init_t<SoftmaxBody>,
-     occupancy_t<SoftmaxBody>, pause_fraction_t<SoftmaxBody>, footprint_t<SoftmaxBody>, footprint_native_t<SoftmaxBody>},
-    {"layernorm_f32", sizeof(LayerNormBody::Args), true, grid_layernorm,
-     launch_native_rows_t<LayerNormBody, LayerNormNarrowBody, LayerNormTeamBody>,
-     launch_sliced_rows_t<LayerNormBody, LayerNormNarrowBody, LayerNormTeamBody>,
-     launch_ptb_rows_t<LayerNormBody, LayerNormNarrowDeepBody, LayerNormTeamBody>, init_t<LayerNormBody>,
-     occupancy_capped_t<LayerNormBody, 2>, pause_fraction_t<LayerNormBody>, footprint_t<LayerNormBody>, footprint_native_t<LayerNormBody>},
+    OPS_ROWS(SoftmaxBody, SoftmaxNarrowBody, SoftmaxNarrowDeepBody, SoftmaxTeamBody, occupancy_t<SoftmaxBody>,
+             "softmax_f32", grid_softmax),
+    OPS_ROWS(LayerNormBody, LayerNormNarrowBody, LayerNormNarrowDeepBody, LayerNormTeamBody,
+             (occupancy_capped_t<LayerNormBody, 2>), "layernorm_f32", grid_layernorm),
     {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_attn_decode,
-     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, footprint_attn},
+     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
-     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, footprint_native_gemm_small},
-    {"gemm_bf16_n128", sizeof(GemmN128Body::Args), true, grid_gemm_n128, launch_native_gemm_t<GemmN128Body>,
-     launch_sliced_t<GemmN128Body>, GemmParts<GemmN128Body>::launch, GemmParts<GemmN128Body>::init,
-     occupancy_t<GemmN128Body>, GemmParts<GemmN128Body>::pause_fraction, footprint_t<GemmN128Body>,
-     footprint_native_t<GemmN128Body>, GemmParts<GemmN128Body>::parts},
+     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES}, gemm_small_native_choice,
+     gemm_sliced_choice<GemmCover::k32>},
+    OPS_GEMM(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128, GemmCover::k256x128),
 };
 
 constexpr size_t kMaxArgs = 96;
@@ -536,9 +579,10 @@ struct tally_ctx {
   uint32_t num_cus;
   uint32_t lds_per_cu;
   uint32_t max_workers[TALLY_K_COUNT];  // persistent-worker workgroups resident at once, per kernel
-  // what one workgroup occupies on a compute unit (LDS bytes, waves, registers per lane):
-  // [0] persistent-worker form, [1] original form; asked of the runtime once, at creation
-  uint32_t foot[TALLY_K_COUNT][2][3];
+  // what one workgroup occupies on a compute unit (LDS bytes, waves, registers per lane): of the
+  // persistent-worker form, and of each kernel that the original form chooses from; asked of the
+  // runtime once, at creation
+  uint32_t foot_worker[TALLY_K_COUNT][3], foot_native[TALLY_K_COUNT][kMaxNative][3];
   uint32_t yield_ticks;      // bound of a mid-block pause, 10 ns ticks
   uint32_t yield_every;      // steps between two looks at the pause word (a power of two)
   void *static_attn_scratch; // this device's address of static_scratch
@@ -1033,10 +1077,10 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
       tally_destroy(c);
       return TALLY_ERR_HIP;
     }
-    for (int f = 0; f < 2; ++f) {
-      uint32_t *ft = c->foot[k][f];
-      ft[0] = 0; ft[1] = 4; ft[2] = 128;
-      auto fn = f == 0 ? kOps[k].footprint : kOps[k].footprint_native;
+    for (uint32_t f = 0; f <= kMaxNative; ++f) {
+      uint32_t *ft = f == kMaxNative ? c->foot_worker[k] : c->foot_native[k][f];
+      ft[0] = ft[1] = ft[2] = 0;
+      const FootprintFn fn = f == kMaxNative ? kOps[k].footprint : kOps[k].footprint_native[f];
       if (fn && (e = fn(&ft[0], &ft[1], &ft[2])) != hipSuccess) {
         g_last_hip = (int)e;
         tally_destroy(c);
@@ -1208,9 +1252,15 @@ int tally_kernel_footprint(tally_ctx *ctx, uint32_t kernel_id, int form, uint32_
   if (!ctx || kernel_id >= TALLY_K_COUNT || form < 0 || form > 1 || !lds_bytes || !waves || !regs_per_lane)
     return TALLY_ERR_INVALID_ARG;
   if (form == 0 && !kOps[kernel_id].transformable) return TALLY_ERR_UNSUPPORTED;
-  *lds_bytes = ctx->foot[kernel_id][form][0];
-  *waves = ctx->foot[kernel_id][form][1];
-  *regs_per_lane = ctx->foot[kernel_id][form][2];
+  uint32_t most[3] = {0, 0, 0};
+  for (uint32_t f = 0; f < (form == 0 ? 1u : kMaxNative); ++f)
+    for (int i = 0; i < 3; ++i) {
+      const uint32_t v = form == 0 ? ctx->foot_worker[kernel_id][i] : ctx->foot_native[kernel_id][f][i];
+      if (v > most[i]) most[i] = v;
+    }
+  *lds_bytes = most[0];
+  *waves = most[1];
+  *regs_per_lane = most[2];
   return TALLY_OK;
 }
 
@@ -1731,6 +1781,13 @@ struct tally_sched {
 
 namespace {
 
+// What the kernel occupies that a launch in its original form takes, and its workgroups.
+const uint32_t *native_footprint(tally_ctx *ctx, const tally_kernel_desc *desc, uint64_t *groups) {
+  const KernelOps &ops = kOps[desc->kernel_id];
+  *groups = (uint64_t)desc->grid.x * desc->grid.y * desc->grid.z;
+  return ctx->foot_native[desc->kernel_id][ops.native_choice ? ops.native_choice(desc->args, groups) : 0];
+}
+
 // Per-compute-unit demand of the workgroups a best-effort kernel puts on the GPU at once
 // (all its workers; one slice; the whole grid for a native launch), spread evenly.
 int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_config &cfg, uint32_t *lds,
@@ -1739,11 +1796,12 @@ int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_confi
   tally_dim3 g;
   int rc = check_desc(desc, &ops, &g);
   if (rc) return rc;
-  const uint32_t *ft = ctx->foot[desc->kernel_id][cfg.kind == 0 ? 0 : 1];
-  const uint32_t l = ft[0], w = ft[1], r = ft[2];
   const uint64_t total = (uint64_t)g.x * g.y * g.z;
-  uint64_t groups = cfg.kind == 2 ? total : cfg.param;
-  if (groups > total) groups = total;
+  uint64_t groups = cfg.param < total ? cfg.param : total;
+  const uint32_t *ft = ctx->foot_worker[desc->kernel_id];
+  if (cfg.kind == 1) ft = ctx->foot_native[desc->kernel_id][ops->sliced_choice ? ops->sliced_choice(desc->args) : 0];
+  if (cfg.kind == 2) ft = native_footprint(ctx, desc, &groups);
+  const uint32_t l = ft[0], w = ft[1], r = ft[2];
   const uint64_t per_cu = (groups + ctx->num_cus - 1) / ctx->num_cus;
   const uint64_t cap = 64;  // beyond any compute unit's capacity: keeps the products small
   const uint32_t n = (uint32_t)(per_cu < cap ? per_cu : cap);
@@ -2075,7 +2133,8 @@ int tally_sched_submit_hi(tally_sched *s, const tally_kernel_desc *kernels, uint
     tally_dim3 g;
     int rc = check_desc(&kernels[i], &ops, &g);
     if (rc) return rc;
-    const uint32_t *ft = ctx->foot[kernels[i].kernel_id][1];
+    uint64_t groups;
+    const uint32_t *ft = native_footprint(ctx, &kernels[i], &groups);
     hl = ft[0] > hl ? ft[0] : hl;
     hw = ft[1] > hw ? ft[1] : hw;
     const uint32_t per_simd = ((ft[1] + 3) / 4) * ft[2];

@@ -369,3 +369,62 @@ def test_load_sweep_two_points(env):
         assert_close_rel(host(partial)[idx], want, 2e-6)
     assert kept[0.7] < kept[0.1], kept
     assert kept[0.1] > 0.5, kept
+
+
+def _bf16_zeros(torch, *shape):
+    return torch.zeros(shape, dtype=torch.bfloat16, device="cuda")
+
+
+@pytest.mark.parametrize("m,n,k,small", [(256, 512, 64, False), (512, 768, 64, False), (1024, 1024, 64, False),
+                                         (2048, 4096, 64, False), (128, 768, 768, True)])
+def test_a_request_is_judged_by_the_kernel_it_launches(env, m, n, k, small):
+    """A high-priority GEMM that the original form covers with 32x32, 32x64, 64x64 or 128x64 tiles
+    takes 16 to 24 KB of LDS, not the large tile's 128 KB: it fits beside paused workers, which
+    therefore pause inside their blocks (0.9 ms each) until the request has been seen to be done."""
+    B, ctx, torch = env
+    be = B.gemm_bf16(_bf16_zeros(torch, 1, 4096, 32768), _bf16_zeros(torch, 1, 4096, 32768), _bf16_zeros(torch, 1, 4096, 4096))
+    hi = B.gemm_bf16(_bf16_zeros(torch, 1, m, k), _bf16_zeros(torch, 1, n, k), _bf16_zeros(torch, 1, m, n), small=small)
+    torch.cuda.synchronize()
+    ctx.set_yield_bound_us(100000)
+    s = ctx.scheduler()
+    try:
+        s.submit_be(be, (B.CFG_PTB, 256, 1))
+        t0 = time.perf_counter()
+        while time.perf_counter() - t0 < 3e-4:
+            pass
+        s.submit_hi([hi])
+        time.sleep(0.005)
+        assert s.stats()["be_kernels_done"] == 0
+        while s.poll():
+            pass
+        while s.stats()["be_kernels_done"] == 0:
+            s.poll()
+    finally:
+        s.close()
+        ctx.set_yield_bound_us(1000)
+
+
+def test_admission_counts_the_workgroups_of_the_original_form(env):
+    """4096 x 4096 x 64 in its original form is 2048 workgroups of 128x64, eight per compute unit:
+    beside another client's workers it has to wait, where 256 workgroups of the large tile (one per
+    compute unit, 352 registers) would have found room."""
+    B, ctx, torch = env
+    n = 1 << 28
+    x, y = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    long = B.saxpy(x, y, 1.0)                             # 2^20 fetches: 11 ms
+    m = 4096
+    gemm = B.gemm_bf16(_bf16_zeros(torch, 1, m, 64), _bf16_zeros(torch, 1, m, 64), _bf16_zeros(torch, 1, m, m))
+    torch.cuda.synchronize()
+    s = ctx.scheduler(be_clients=2)
+    try:
+        s.submit_be(long, (B.CFG_PTB, 256, 1), client=0)
+        time.sleep(0.001)
+        s.submit_be(gemm, (B.CFG_NATIVE, 0, 0), client=1)
+        time.sleep(0.004)
+        assert s.stats()["be_client_kernels_done"][:2] == [0, 0]
+        t0 = time.perf_counter()
+        while s.stats()["be_kernels_done"] < 2 and time.perf_counter() - t0 < 5.0:
+            s.poll()
+        assert s.stats()["be_client_kernels_done"][:2] == [1, 1]
+    finally:
+        s.close()
