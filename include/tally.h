@@ -125,8 +125,11 @@ typedef struct {
 } tally_kernel_desc;
 
 /* Per-logical-block coverage record, written by the transformed kernels when a job is
- * created with coverage enabled (test/diagnostic).  `count` is incremented atomically;
- * b[] is the block index the kernel rebuilt from the offset or task index. */
+ * created with coverage enabled (test/diagnostic).  `count` is how often the block ran: 1, or
+ * TALLY_PARTS_UNEVEN for a block handed out in parts that did not run once each; b[] is the
+ * block index the kernel rebuilt from the offset or task index (of a block in parts, block
+ * index, segment and worker are its first part's). */
+#define TALLY_PARTS_UNEVEN 0xFFFFFFFFu
 typedef struct { uint32_t count, bx, by, bz, segment, worker; } tally_cover_rec;
 
 typedef struct tally_ctx tally_ctx; /* owns flags, counters, status words, marker words */
@@ -291,6 +294,10 @@ int tally_resume_until(tally_job *job, uint64_t stop_at);
 /* Copy the coverage records (one tally_cover_rec per logical block, x-fastest linear
  * order) to host memory.  Job must be STOPPED or COMPLETE. */
 int tally_coverage(tally_job *job, void *host_records, size_t bytes);
+/* How often a block handed out in P parts (2 to 64, a power of two) ran as a whole: every part
+ * that runs adds w = 64 / P to `pieces` and w one bits, at bit w times its number, to `which`
+ * (modulo 2^64).  0, 1, or TALLY_PARTS_UNEVEN unless each part ran exactly once. */
+uint32_t tally_parts_executions(uint32_t pieces, uint64_t which);
 
 /* Enqueue, on the high-priority (or best-effort) stream, a marker that stores `value`
  * into the context's host-visible word for that stream once all earlier work on the

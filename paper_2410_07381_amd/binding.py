@@ -54,7 +54,7 @@ EXPORTS = [
     "tally_candidate_configs", "tally_profile_table", "tally_profile_reset",
     "tally_sched_create", "tally_sched_destroy", "tally_sched_submit_be", "tally_sched_submit_hi",
     "tally_sched_poll", "tally_sched_enable_be", "tally_sched_stats",
-    "tally_sched_take_preempt_latencies", "tally_set_yield_every",
+    "tally_sched_take_preempt_latencies", "tally_set_yield_every", "tally_parts_executions",
 ]
 
 
@@ -195,6 +195,7 @@ def _load():
         "tally_strerror": ([i32], C.c_char_p),
         "tally_device_info": ([P(u32), P(u32), P(u32)], i32),
         "tally_stream_report": ([vp, P(i32), P(u32)], i32),
+        "tally_parts_executions": ([u32, u64], u32),
         "tally_ptb_turnaround_ms": ([dbl, u32, u32, u64], dbl),
         "tally_select_config": ([P(Config), u32, dbl], i32),
         "tally_profile": ([vp, P(KernelDesc), P(Config), u32, u32, dbl, P(u32)], i32),
@@ -636,6 +637,14 @@ def device_info():
 
 def ptb_turnaround_ms(latency_ms, workers, chunk, total):
     return _lib.tally_ptb_turnaround_ms(latency_ms, workers, chunk, total)
+
+
+PARTS_UNEVEN = 0xFFFFFFFF
+
+
+def parts_executions(pieces, which):
+    """How often a block handed out in parts ran as a whole (coverage records)."""
+    return _lib.tally_parts_executions(pieces, which)
 
 
 def select_config(cands, threshold_ms=0.0316):

@@ -37,6 +37,17 @@ constexpr uint32_t kPreemptStep = 0x80000000u;
 // Bit of the host's request word that says "do not pause inside blocks".
 constexpr uint32_t kNoPauseBit = 0x80000000u;
 
+// Coverage record of a logical block on the device.  `block.count` counts executions of it as a
+// whole; one handed out in P parts adds 64 / P pieces per part, and to `which` the bits of the
+// pieces.  All of them were run once exactly where 64 pieces add up to 64 one bits: no other 64
+// powers of two below 2^64 have that sum, whatever carries (tally_parts_executions).
+struct CoverRec {
+  tally_cover_rec block;
+  uint32_t pieces;
+  unsigned long long which;
+};
+constexpr uint32_t kCoverPieces = 64;
+
 // Device-side control block of one persistent-worker launch segment.
 struct PtbCtl {
   uint32_t *counter;        // device: THE shared word.  Next task index (+ counter_base), plus
@@ -51,7 +62,7 @@ struct PtbCtl {
   unsigned long long *host_raw;     // pinned: (epoch << 32 | raw counter) at the drain
   unsigned long long *host_relay;   // pinned: (epoch << 32 | raw counter) when the relay has ended
   unsigned long long *host_gave_up; // pinned: (epoch << 32 | 1 if the relay gave up early), written with it
-  tally_cover_rec *cover;   // device, may be null
+  CoverRec *cover;          // device, may be null
   uint32_t parts;           // the counter counts parts of a logical block (1: whole blocks)
   uint32_t limit;           // workers treat this as the end of the grid (normally all of it); in parts
   uint32_t epoch;           // id of this launch segment, unique for the life of the slot
@@ -74,7 +85,7 @@ constexpr uint32_t kFlagCopies = 64;
 constexpr uint32_t kFlagCopyStride = 32;  // in 32-bit words
 
 struct SliceCtl {
-  tally_cover_rec *cover;
+  CoverRec *cover;
   uint32_t offset;          // first logical block of this sub-kernel
   uint32_t gx, gy;
   uint32_t segment;
@@ -88,13 +99,25 @@ __device__ __forceinline__ void delinearize(uint32_t idx, uint32_t gx, uint32_t 
   bz = r / gy;
 }
 
-__device__ __forceinline__ void record(tally_cover_rec *cover, uint32_t idx, uint32_t bx,
-                                       uint32_t by, uint32_t bz, uint32_t segment,
-                                       uint32_t worker) {
+__device__ __forceinline__ void record_at(tally_cover_rec &r, uint32_t bx, uint32_t by, uint32_t bz,
+                                          uint32_t segment, uint32_t worker) {
+  r.bx = bx; r.by = by; r.bz = bz; r.segment = segment; r.worker = worker;
+}
+__device__ __forceinline__ void record(CoverRec *cover, uint32_t idx, uint32_t bx, uint32_t by, uint32_t bz,
+                                       uint32_t segment, uint32_t worker) {
   if (cover != nullptr && threadIdx.x == 0) {
-    tally_cover_rec *r = cover + idx;
-    atomicAdd(&r->count, 1u);
-    r->bx = bx; r->by = by; r->bz = bz; r->segment = segment; r->worker = worker;
+    atomicAdd(&cover[idx].block.count, 1u);
+    record_at(cover[idx].block, bx, by, bz, segment, worker);
+  }
+}
+// part `part` of `parts` (at least 2) of block idx; block index, segment and worker are the first part's
+__device__ __forceinline__ void record_part(CoverRec *cover, uint32_t idx, uint32_t part, uint32_t parts, uint32_t bx,
+                                            uint32_t by, uint32_t bz, uint32_t segment, uint32_t worker) {
+  if (cover != nullptr && threadIdx.x == 0) {
+    const uint32_t w = kCoverPieces / parts;
+    atomicAdd(&cover[idx].pieces, w);
+    atomicAdd(&cover[idx].which, ((1ull << w) - 1) << (part * w));
+    if (part == 0) record_at(cover[idx].block, bx, by, bz, segment, worker);
   }
 }
 
@@ -278,8 +301,7 @@ __device__ __forceinline__ uint32_t progress_at_request(const PtbCtl &c) {
 // every worker takes at most one.  To the host nothing changes: progress is in whole blocks, and
 // a request still lets every block that was begun be finished: the parts of the block in which
 // the request fell that were not handed out before it are handed out after it, to workers that
-// would otherwise leave (there are as many fetches as parts, so all of them are).  A block is
-// recorded with its first part.
+// would otherwise leave (there are as many fetches as parts, so all of them are).
 template <class SubBody, uint32_t PX, uint32_t PY>
 struct PartsBody {
   using Sub = SubBody;
@@ -288,6 +310,7 @@ struct PartsBody {
   static constexpr int MIN_WAVES = Sub::MIN_WAVES;
   static constexpr unsigned DYN_LDS = Sub::DYN_LDS;
   static constexpr uint32_t PARTS_X = PX, PARTS = PX * PY;
+  static_assert(kCoverPieces % PARTS == 0, "a part is a whole number of recorded pieces");
 };
 // The same for the last blocks of a grid that does not divide by the workers: each worker takes
 // `whole` whole blocks (one fetch of PARTS parts each), then parts, so that the last round, in
@@ -323,7 +346,7 @@ __device__ __forceinline__ void run_part(const typename Body::Args &args, const 
   delinearize(block, c.gx, c.gy, bx, by, bz);
   if constexpr (Sub::YIELDS) Sub::run_yielding(args, bx * PX + part % PX, by * PY + part / PX, bz, y);
   else Sub::run_be(args, bx * PX + part % PX, by * PY + part / PX, bz);
-  if (part == 0) record(c.cover, block, bx, by, bz, c.segment, blockIdx.x);
+  record_part(c.cover, block, part, P, bx, by, bz, c.segment, blockIdx.x);
 }
 __device__ __forceinline__ YieldCtl yield_ctl(const PtbCtl &c) {
   return YieldCtl{c.flag_copies + (blockIdx.x % kFlagCopies) * kFlagCopyStride, c.epoch,

@@ -604,7 +604,7 @@ struct tally_job {
   uint32_t total;
   int kind;
   int slot;
-  tally_cover_rec *cover;
+  CoverRec *cover;
   std::atomic<int> state;
   std::atomic<uint32_t> progress;
   // persistent workers
@@ -723,9 +723,9 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
   j->preempt_latency_us = -1.0;
   hipError_t e = hipSuccess;
   if (coverage) {
-    e = hipMalloc((void **)&j->cover, sizeof(tally_cover_rec) * (size_t)j->total);
+    e = hipMalloc((void **)&j->cover, sizeof(CoverRec) * (size_t)j->total);
     if (e == hipSuccess)
-      e = hipMemsetAsync(j->cover, 0, sizeof(tally_cover_rec) * (size_t)j->total, j->be);
+      e = hipMemsetAsync(j->cover, 0, sizeof(CoverRec) * (size_t)j->total, j->be);
   }
   if (e != hipSuccess) {
     g_last_hip = (int)e;
@@ -1408,8 +1408,24 @@ int tally_coverage(tally_job *job, void *host_records, size_t bytes) {
   refresh(job);
   if (job->state.load() == TALLY_JOB_RUNNING) return TALLY_ERR_BAD_STATE;
   HIPCHK(hipStreamSynchronize(job->be));
-  HIPCHK(hipMemcpy(host_records, job->cover, bytes, hipMemcpyDeviceToHost));
+  CoverRec *rec = (CoverRec *)malloc(sizeof(CoverRec) * (size_t)job->total);
+  if (!rec) return TALLY_ERR_NOMEM;
+  const hipError_t e = hipMemcpy(rec, job->cover, sizeof(CoverRec) * (size_t)job->total, hipMemcpyDeviceToHost);
+  if (e == hipSuccess)
+    for (uint32_t i = 0; i < job->total; ++i) {
+      tally_cover_rec r = rec[i].block;
+      const uint32_t in_parts = tally_parts_executions(rec[i].pieces, rec[i].which);
+      r.count = in_parts == TALLY_PARTS_UNEVEN ? in_parts : r.count + in_parts;
+      memcpy((unsigned char *)host_records + i * sizeof(r), &r, sizeof(r));
+    }
+  free(rec);
+  HIPCHK(e);
   return TALLY_OK;
+}
+
+uint32_t tally_parts_executions(uint32_t pieces, uint64_t which) {
+  if (pieces == 0) return 0;
+  return pieces == kCoverPieces && which == ~0ull ? 1 : TALLY_PARTS_UNEVEN;
 }
 
 int tally_marker(tally_ctx *ctx, int on_hi_stream, uint32_t value) {

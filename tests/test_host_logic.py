@@ -34,6 +34,34 @@ def test_struct_sizes_match_the_header(B):
     assert C.sizeof(B.KernelDesc) == 48
 
 
+@pytest.mark.parametrize("parts", [2, 4, 8, 16, 64])
+def test_parts_of_a_block_that_did_not_run_once_each_show_in_its_count(B, parts):
+    """Parts run any number of times, lost ones made up for by carries of others among them: only
+    once each counts as one execution of the block."""
+    import itertools
+    import random
+    w = 64 // parts
+
+    def count(runs):
+        which = sum(r * (((1 << w) - 1) << (p * w)) for p, r in enumerate(runs)) % 2**64
+        return B.parts_executions(sum(runs) * w, which)
+
+    assert count([1] * parts) == 1 and count([0] * parts) == 0
+    if parts <= 8:
+        cases = itertools.product(range(4), repeat=parts) if parts < 8 else itertools.product(range(3), repeat=8)
+    else:
+        rng = random.Random(parts)
+        cases = [[rng.choice([0, 1, 1, 1, 2, 3]) for _ in range(parts)] for _ in range(2000)]
+        for p in range(parts - 1):            # lost, doubled, and a sum that carries put right
+            cases += [[1] * p + [0, 1] + [1] * (parts - p - 2), [1] * p + [2, 1] + [1] * (parts - p - 2),
+                      [1] * p + [3, 0] + [1] * (parts - p - 2), [1] * p + [0, 2] + [1] * (parts - p - 2)]
+        cases.append([2] * parts)
+    for runs in cases:
+        runs = list(runs)
+        if any(r != 1 for r in runs) and any(runs):
+            assert count(runs) == B.PARTS_UNEVEN, runs
+
+
 def test_eq1_matches_oracle(B):
     for lat, w, c, tot in [(1.0, 256, 1, 65536), (2.0, 16, 1, 16), (0.5, 512, 4, 4096)]:
         assert B.ptb_turnaround_ms(lat, w, c, tot) == pytest.approx(
