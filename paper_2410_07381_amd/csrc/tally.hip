@@ -232,8 +232,8 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256 };
 GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
   const uint64_t t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
-  if (t64 < 256)
-    return (uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256 ? GemmCover::k32 : GemmCover::k32x64;
+  if ((uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32;
+  if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32x64;
   if (t64 <= 512) return GemmCover::k64;
   if (a.k <= 128 && (uint64_t)a.m * a.n * a.batch * 2u <= kGemmBigOutput) return GemmCover::k128x64;
   if ((uint64_t)cdiv(a.n, 128) * cdiv(a.m, 256) * a.batch <= 256) return GemmCover::k256x128;
