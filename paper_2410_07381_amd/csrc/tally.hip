@@ -744,8 +744,9 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
 // A new relay on `ctl` starts once the one before it there has ended, whichever slot that was for.
 // The last worker's word is out a polling round and a report before that (2 to 4 us), and a job
 // may be followed by the next as soon as the word is seen: workers launched then would start
-// first.  So the relays of drained segments are settled before another is enqueued.  (A segment
-// whose workers are still at work is not waited for: the new workers are behind them.)
+// first.  So the relays of drained segments are settled before the new workers are enqueued (the
+// new relay already is, so that its launch call and the wait overlap).  A segment whose workers
+// are still at work is not waited for: the new workers are behind them.
 int settle_relays_before(tally_ctx *ctx, hipStream_t ctl) {
   for (int s = 0; s < kSlots; ++s) {
     if (!ctx->slot_relay[s] || ctx->slot_ctl[s] != ctl) continue;
@@ -776,7 +777,6 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   tally_ctx *ctx = j->ctx;
   const int slot = j->slot;
   int rc = settle_relay(ctx, slot);
-  if (rc == TALLY_OK) rc = settle_relays_before(ctx, j->ctl);
   if (rc) return rc;
   const uint32_t start = j->progress.load();
   // The counter is never rewound: failed fetches of the last segment (after a request, or
@@ -830,9 +830,10 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
     g_last_hip = (int)e;
     return TALLY_ERR_HIP;
   }
+  rc = settle_relays_before(ctx, j->ctl);   // (this slot's relay is not among them: settled above)
   ctx->slot_relay[slot] = true;
   ctx->slot_ctl[slot] = j->ctl;
-  e = j->ops->ptb(j->be, j->args, c);
+  e = rc == TALLY_OK ? j->ops->ptb(j->be, j->args, c) : (hipError_t)g_last_hip;
   ctx->slot_epoch[slot] = j->epoch;
   ctx->slot_exited[slot] = c.exit_target;
   if (e != hipSuccess) {
