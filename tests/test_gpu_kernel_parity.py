@@ -250,13 +250,13 @@ def test_gemm_cfg1_full_size_sampled_tiles(env):
     assert (host(Cd) == 0x3F80).all()
 
 
-@pytest.mark.parametrize("m,n,k,batch", [(256, 768, 96, 4), (1024, 1024, 96, 1), (512, 1024, 96, 4),
+@pytest.mark.parametrize("m,n,k,batch", [(512, 512, 96, 1), (256, 512, 96, 3), (256, 768, 96, 4), (1024, 1024, 96, 1), (512, 1024, 96, 4),
                                          (512, 768, 64, 8), (2048, 1536, 160, 1), (2048, 4352, 160, 1)])
 @pytest.mark.parametrize("n128", [False, True])
 def test_gemm_original_form_covers(env, m, n, k, batch, n128):
-    """The original form's tiles by the size of the output, on both sides of each line (192, 256
-    and 512 tiles of 64x64; short k; 96 and 272 of 256x128), operands with NaN beyond k, nothing
-    written behind C."""
+    """The original form's tiles by the size of the output, on both sides of each line (256 tiles of
+    32x32, 192 of 32x64, 192, 256 and 512 of 64x64; short k; 96 and 272 of 256x128), operands with
+    NaN beyond k, nothing written behind C."""
     B, ctx, torch = env
     from gpu_util import dev, host, assert_bf16_close
     name = "gemm_bf16_n128" if n128 else "gemm_bf16"
@@ -442,11 +442,11 @@ def test_gemm_small_edges(env, m, n, k, batch):
 
 
 @pytest.mark.parametrize("k", [32, 64, 96, 160, 224])
-@pytest.mark.parametrize("m,n,batch", [(70, 130, 64), (64, 64, 400), (130, 65, 128), (127, 129, 171)])
+@pytest.mark.parametrize("m,n,batch", [(70, 130, 20), (33, 127, 64), (70, 130, 64), (64, 64, 400), (130, 65, 128), (127, 129, 171)])
 def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
-    """Grids that the original form covers with 64x64 (first two) and 128x64 tiles: rows and
-    columns past the matrix, one to four stages, a last stage half full, NaN beyond K and
-    between the rows, nothing written behind C."""
+    """Grids that the original form covers with 32x64 (180 and 256 of them), 64x64 (384 and 400) and
+    128x64 tiles (512 and 513): rows and columns past the matrix, one to four stages, a last stage
+    half full, NaN beyond K and between the rows, nothing written behind C."""
     B, ctx, torch = env
     from gpu_util import dev, host, assert_bf16_close
     g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
