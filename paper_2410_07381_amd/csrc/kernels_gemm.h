@@ -16,8 +16,9 @@
 //    first MFMA operand a lane holds four neighbouring columns of one row, which leave as
 //    one 8-byte LDS write;
 //  - a barrier per 1024 cycles with the reads of the next half-step bunched behind it.
-// 4096^3 in its original form: 122 us (1.12 PFLOP/s) before, 103 us (1.33) now; 8192^3
-// 874 -> 765 us (1.44); as persistent workers 8192^3 1065 -> 855 us.
+// In turn on one card, N(0, 1/64) operands: 4096^3 in its original form 120-123 us before and
+// 103-107 now in bursts of ten launches (1.3 PFLOP/s), 133 and 120 in bursts of fifty, where the
+// clock is lower; 8192^3 906 -> 815 (1.35); as persistent workers 1029 -> 830.
 //
 // LDS holds two stages of both operands (64 KB each, 128 KB in all).  A stage's place is
 // refilled as soon as its fragments are in registers, not when its products are done: B's
