@@ -366,7 +366,7 @@ using GemmN128Body = GemmBodyT<2>;
 //
 // Every tile of every size, the 256-row tiles included, adds its products in the same order:
 // one accumulator per output, k ascending, one 16x16x32 MFMA per 32 of it with B first, one
-// hardware conversion at the end.  The bits of a product depend neither on the form it runs in
+// rounding at the end.  The bits of a product depend neither on the form it runs in
 // nor on where a job was stopped and resumed.  (An earlier 32x32 tile split K between its waves:
 // a job finished in its parts, or run in the original form, came out in other bits.)
 //
@@ -384,7 +384,10 @@ using GemmN128Body = GemmBodyT<2>;
 // 128 x 3072 x 768 (384) 5.3 / 4.8 / 5.8; 1000 x 2300 x 768 13.9 / 12.0 / 10.5 / 11.7;
 // 512 x 4096 x 4096 53 / 39 / 29 / 32; 2048 x 4096 x 4096 195 / 140 / 101 / 85 (0.81 PFLOP/s).
 // With K split between the waves of the 32x32 tile: 7.7, 5.0, 15.1, 50 and 199.
-template <int RA, int RB>
+//
+// NAN7FC0: a NaN leaves as 0x7FC0, which is what the ragged GEMM has always written; those with
+// blocks of 256 rows write what the hardware's conversion makes of the MFMA's NaN (0xFFC0).
+template <int RA, int RB, bool NAN7FC0 = false>
 struct GemmTileT {
   using Args = tally_gemm_bf16_args;
   static constexpr int THREADS = 256;
@@ -574,6 +577,7 @@ struct GemmTileT {
     // 32), so that whole 64-byte pieces leave (4352 x 4864 x 64 13.3 us; 18.8 as 32-byte pieces).
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
     auto pack = [](float x, float y) {
+      if constexpr (NAN7FC0) return f32_to_bf16(x) | (uint32_t)f32_to_bf16(y) << 16;
       const f32x2_t p = {x, y};
       return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
     };
@@ -611,8 +615,9 @@ struct GemmTileT {
 #endif
   }
 };
+using GemmTile32 = GemmTileT<1, 1>;
 // The small GEMM's own blocks stop at their ends only, as its waves fit beside a request's.
-struct GemmSmallBody : GemmTileT<1, 1> {
+struct GemmSmallBody : GemmTileT<1, 1, true> {
   static constexpr bool YIELDS = false;
 };
 

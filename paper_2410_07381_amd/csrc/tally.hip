@@ -249,7 +249,7 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
   switch (gemm_cover(a)) {
-    case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
+    case GemmCover::k32: return launch_gemm_cover<GemmTile32>(s, a, 32, 32, urgent);
     case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
     case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
     case GemmCover::k128x64: return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
@@ -270,9 +270,9 @@ hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3,
   memcpy(&a, args, sizeof(a));
   switch (gemm_cover_small(a)) {
     case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
-    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
-    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
-    default: return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
+    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2, true>>(s, a, 64, 32, urgent);
+    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2, true>>(s, a, 64, 64, urgent);
+    default: return launch_gemm_cover<GemmTileT<4, 2, true>>(s, a, 64, 128, urgent);
   }
 }
 // which of the kernels in kOps (in the order of GemmCover) and how many workgroups of it
@@ -303,7 +303,7 @@ uint32_t gemm_sliced_choice(const void *) { return (uint32_t)C; }
 template <class Body>
 struct GemmParts {
   static constexpr uint32_t X = Body::TILE_N / 32, Y = Body::TILE / 32;
-  typedef PartsBody<GemmTileT<1, 1>, X, Y> P32;
+  typedef PartsBody<GemmTile32, X, Y> P32;
   typedef PartsBody<GemmTileT<2, 2>, X / 2, Y / 2> P64;
   typedef PartsBody<GemmTileT<4, 2>, X / 2, Y / 4> P128;
   typedef PartsBody<GemmN128Body, X / 4, 1> PN128;
@@ -475,9 +475,9 @@ double pause_fraction_t(const void *args, uint32_t every, uint32_t, uint32_t) {
    launch_ptb_t<Body>, init_t<Body>, occupancy_t<Body>, pause_fraction_t<Body>,              \
    footprint_t<Body>, {footprint_native_t<Body>}}
 
-#define GEMM_TILES \
-  footprint_native_t<GemmSmallBody>, footprint_native_t<GemmTileT<1, 2>>, footprint_native_t<GemmTileT<2, 2>>, \
-  footprint_native_t<GemmTileT<4, 2>>
+#define GEMM_TILES(Tile32, canon)                                                                         \
+  footprint_native_t<Tile32>, footprint_native_t<GemmTileT<1, 2, canon>>,                                 \
+  footprint_native_t<GemmTileT<2, 2, canon>>, footprint_native_t<GemmTileT<4, 2, canon>>
 #define OPS_ROWS(Wide, Narrow, NarrowDeep, Team, occupancy, nm, gridfn)                                   \
   {nm, sizeof(Wide::Args), true, gridfn, launch_native_rows_t<Wide, Narrow, Team>,                        \
    launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
@@ -487,7 +487,7 @@ double pause_fraction_t(const void *args, uint32_t every, uint32_t, uint32_t) {
 #define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
-   footprint_t<Body>, {GEMM_TILES, footprint_native_t<GemmN128Body>, footprint_native_t<Body>},           \
+   footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>}, \
    gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
@@ -504,7 +504,7 @@ const KernelOps kOps[TALLY_K_COUNT] = {
      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
-     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES}, gemm_small_native_choice,
+     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true)}, gemm_small_native_choice,
      gemm_sliced_choice<GemmCover::k32>},
     OPS_GEMM(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128, GemmCover::k256x128),
 };

@@ -472,18 +472,20 @@ def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
 def test_gemm_bits_do_not_depend_on_form_or_schedule(env, tile, m, n, k, batch):
     """Every tile that any form covers the product with adds in the same order: one worker, several,
     enough for parts of blocks, jobs stopped so near the end that the rest is done in parts, slices
-    and the original form give the same bits."""
+    and the original form give the same bits, those of a NaN included (0x7FC0 in the ragged GEMM)."""
     B, ctx, torch = env
     gen = torch.Generator(device="cuda")
     gen.manual_seed(m + n + k)
     A = torch.randn(batch, m, k, device="cuda", generator=gen).to(torch.bfloat16)
     Bt = torch.randn(batch, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    A[:, ::37, 3] = float("inf")                          # times a zero, and times anything else
+    Bt[:, ::11, 3] = 0.0
     C = torch.empty(batch, m, n, dtype=torch.bfloat16, device="cuda")
     kern = B.gemm_bf16(A, Bt, C, small=tile == "small", n128=tile == "128")
     total = kern.total_blocks
 
     def bits(launch):
-        C.fill_(float("nan"))
+        C.fill_(7.0)
         torch.cuda.synchronize()
         job = launch()
         while job is not None and job.wait() != B.JOB_COMPLETE:
@@ -494,6 +496,8 @@ def test_gemm_bits_do_not_depend_on_form_or_schedule(env, tile, m, n, k, batch):
         return C.view(torch.int16).clone()
 
     want = bits(lambda: ctx.launch_ptb(kern, 1))
+    nan = want[:, ::37, ::11]
+    assert bool(((nan & 0x7FFF) > 0x7F80).all()) and (tile != "small" or bool((nan == 0x7FC0).all()))
     for what, launch in [("native", lambda: ctx.launch_native(kern)), ("slices", lambda: ctx.launch_sliced(kern, total // 3 + 1)),
                          ("5 workers", lambda: ctx.launch_ptb(kern, 5)), ("256 workers", lambda: ctx.launch_ptb(kern, 256)),
                          ("1 block left", lambda: ctx.launch_ptb(kern, 256, stop_at=total - 1)),
