@@ -1409,16 +1409,21 @@ int tally_coverage(tally_job *job, void *host_records, size_t bytes) {
   refresh(job);
   if (job->state.load() == TALLY_JOB_RUNNING) return TALLY_ERR_BAD_STATE;
   HIPCHK(hipStreamSynchronize(job->be));
-  CoverRec *rec = (CoverRec *)malloc(sizeof(CoverRec) * (size_t)job->total);
+  // (a piece at a time: the largest grid's records are 40 GB)
+  const uint32_t piece = job->total < (1u << 16) ? job->total : 1u << 16;
+  CoverRec *rec = (CoverRec *)malloc(sizeof(CoverRec) * piece);
   if (!rec) return TALLY_ERR_NOMEM;
-  const hipError_t e = hipMemcpy(rec, job->cover, sizeof(CoverRec) * (size_t)job->total, hipMemcpyDeviceToHost);
-  if (e == hipSuccess)
-    for (uint32_t i = 0; i < job->total; ++i) {
+  hipError_t e = hipSuccess;
+  for (uint32_t at = 0; at < job->total && e == hipSuccess; at += piece) {
+    const uint32_t n = job->total - at < piece ? job->total - at : piece;
+    e = hipMemcpy(rec, job->cover + at, sizeof(CoverRec) * n, hipMemcpyDeviceToHost);
+    for (uint32_t i = 0; i < n && e == hipSuccess; ++i) {
       tally_cover_rec r = rec[i].block;
       const uint32_t in_parts = tally_parts_executions(rec[i].pieces, rec[i].which);
       r.count = in_parts == TALLY_PARTS_UNEVEN ? in_parts : r.count + in_parts;
-      memcpy((unsigned char *)host_records + i * sizeof(r), &r, sizeof(r));
+      memcpy((unsigned char *)host_records + (size_t)(at + i) * sizeof(r), &r, sizeof(r));
     }
+  }
   free(rec);
   HIPCHK(e);
   return TALLY_OK;
