@@ -251,8 +251,8 @@ int tally_set_yield_bound_us(tally_ctx *ctx, uint32_t us);
  * for a memory round trip, so fewer steps buy a faster pause with best-effort throughput
  * (measured on a 4096^3 GEMM: 16 -> 4 steps costs 1.6 % alone and takes 3 us off the median
  * and 1.5 us off the 99th percentile of a co-located 4096 x 4096 GEMV).  Workers that take a
- * GEMM's blocks in parts of 32x32 (64x64) look every 16 (4) steps of 32 k at most, about 1 us,
- * and act on a look as much later.
+ * GEMM's blocks in parts of 32x32 (64x64, 128x64) look every 16 (8, 4) steps of 32 k at most, 1
+ * to 2 us, and act on a look as much later.
  * Applies to jobs launched after the call. */
 int tally_set_yield_every(tally_ctx *ctx, uint32_t steps);
 

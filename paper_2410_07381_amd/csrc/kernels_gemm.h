@@ -400,12 +400,13 @@ struct GemmTileT {
   static constexpr uint32_t TM = 32 * RA, TN = 32 * RB;
   static constexpr bool TWO = RA * RB <= 2;               // LDS holds two stages
   static constexpr int AHEAD = RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
+  static constexpr int ROUND = TWO ? AHEAD : 16 / (RA * RB);   // stages between two looks at the pause word, at least
   static constexpr uint32_t SA = TM * 128, STAGE = (TM + TN) * 128;   // bytes of A, of both in a stage
   // share of a tile between asking for the pause word and pausing on the answer to the next
   // question, `every` k-steps of 32 apart (see look_round); host side, for turnaround estimates
   static double pause_fraction(const Args &a, uint32_t every) {
-    const uint32_t ns = (a.k + 63) / 64, apart = every / 2 > AHEAD ? every / 2 : AHEAD;
-    return ns > apart + AHEAD ? (double)(apart + AHEAD) / ns : 1.0;
+    const uint32_t ns = (a.k + 63) / 64, apart = every / 2 > ROUND ? every / 2 : ROUND;
+    return ns > apart + ROUND ? (double)(apart + ROUND) / ns : 1.0;
   }
 
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
@@ -502,12 +503,13 @@ struct GemmTileT {
       __syncthreads();
     }
     // Looks at the pause word.  Waiting for one costs the workgroup 0.7 us, several of its stages:
-    // one lane asks for the word at the start of a round of SETS stages, behind the loads on their
+    // one lane asks for the word at the start of a round of STEPS stages, behind the loads on their
     // way, and has it at the start of the next.  (Its offset, not a branch, says who asks and
     // when: all others are outside the buffer.)
+    constexpr int STEPS = YIELD && SETS == AHEAD ? ROUND : SETS;
     uint32_t pause_left = ctl.ticks, look = 0;
     const buf_t rF = make_buf(ctl.flag, YIELD && ctl.ticks != 0 ? 4 : 0);
-    const uint32_t v_look = tid == 0 ? 0u : OOB, look_mask = (ctl.mask >> 1) & ~(SETS - 1u);   // in stages
+    const uint32_t v_look = tid == 0 ? 0u : OOB, look_mask = (ctl.mask >> 1) & ~(STEPS - 1u);   // in stages
     auto look_round = [&](uint32_t c) {
       if constexpr (YIELD) {
         // one wave pauses; the others meet it at the next barrier
@@ -554,19 +556,19 @@ struct GemmTileT {
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kk][j], fa[kk][i], acc[i][j], 0, 0, 0);
       __syncthreads();
     };
-    // Rounds of SETS stages, then what is left of one: no way out of the middle of the loop, which
+    // Rounds of STEPS stages, then what is left of one: no way out of the middle of the loop, which
     // the compiler would give an edge back to its head and with it a wait for every load there.
     uint32_t c = 0;
-    for (; c + SETS <= ns; c += SETS) {
+    for (; c + STEPS <= ns; c += STEPS) {
       look_round(c);
 #pragma unroll
-      for (int d = 0; d < SETS; ++d) step(d, c + d);
+      for (int d = 0; d < STEPS; ++d) step(d % SETS, c + d);
     }
     auto rest = [&](auto &&self, auto at) -> void {
       constexpr int d = decltype(at)::value;
-      if constexpr (d + 1 < SETS)
+      if constexpr (d + 1 < STEPS)
         if (c + d < ns) {
-          step(d, c + d);
+          step(d % SETS, c + d);
           self(self, std::integral_constant<int, d + 1>{});
         }
     };

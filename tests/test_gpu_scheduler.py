@@ -185,11 +185,11 @@ def test_profile_picks_a_config_under_the_threshold(env):
     assert got is not None and got["param"] == meas[chosen]["param"]
 
 
-@pytest.mark.parametrize("m,n,ahead", [(512, 512, 8), (1024, 1024, 2), (1024, 2048, 1)])
-def test_turnaround_of_parts_of_blocks(env, m, n, ahead):
+@pytest.mark.parametrize("m,n,stages", [(512, 512, 8), (1024, 1024, 4), (1024, 2048, 2)])
+def test_turnaround_of_parts_of_blocks(env, m, n, stages):
     """256 workers on 4, 16 and 32 blocks take a part each, all at once: a part lasts as long as the
-    kernel (Eq. 1 would say 64, 16 and 8 times as long), and a worker pauses after the stages of
-    64 k between two looks (4 steps of 32 k, at least a round of `ahead` stages) and the round in
+    kernel (Eq. 1 would say 64, 16 and 8 times as long), and a worker pauses after a round of
+    `stages` of 64 k between two looks (at least the 4 steps of 32 k asked for) and the round in
     which the answer is on its way."""
     B, ctx, torch = env
     k = 4096
@@ -200,7 +200,7 @@ def test_turnaround_of_parts_of_blocks(env, m, n, ahead):
     kern = B.gemm_bf16(A, Bt, C)
     try:
         meas, _ = ctx.profile(kern, [(B.CFG_PTB, 256, 1)], runs=2)
-        assert meas[0]["turnaround_ms"] == pytest.approx(meas[0]["latency_ms"] * (max(2, ahead) + ahead) / 64, rel=1e-5)
+        assert meas[0]["turnaround_ms"] == pytest.approx(meas[0]["latency_ms"] * 2 * stages / 64, rel=1e-5)
         ctx.set_yield_bound_us(0)
         meas, _ = ctx.profile(kern, [(B.CFG_PTB, 256, 1)], runs=2)
         assert meas[0]["turnaround_ms"] == pytest.approx(meas[0]["latency_ms"], rel=1e-5)
