@@ -600,13 +600,10 @@ struct GemmTileT {
       }
       if (row < a.m) {
         uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
-        const uintptr_t mis = reinterpret_cast<uintptr_t>(g) & (RB == 2 ? 15u : 7u);
-        if (col + 4 * RB <= a.n && mis == 0) {
-          if constexpr (RB == 2) *reinterpret_cast<uint4 *>(g) = make_uint4(w[0], w[1], w[2], w[3]);
-          else *reinterpret_cast<uint2 *>(g) = make_uint2(w[0], w[1]);
-        } else if (RB == 2 && col + 8 <= a.n && mis == 8) {
-          *reinterpret_cast<uint2 *>(g) = make_uint2(w[0], w[1]);
-          *reinterpret_cast<uint2 *>(g + 4) = make_uint2(w[2 * RB - 2], w[2 * RB - 1]);
+        if (col + 4 * RB <= a.n) {
+          // (rows start at any multiple of 2 bytes and are stored alike: 413 x 741 x 640 x 12 in 19.0 us,
+          // 23.5 with the widest aligned stores that each row allows)
+          __builtin_memcpy(g, w, 8 * RB);
         } else {
 #pragma unroll
           for (int e = 0; e < 4 * RB; ++e)
