@@ -247,12 +247,11 @@ int tally_resume(tally_job *job);
 int tally_set_yield_bound_us(tally_ctx *ctx, uint32_t us);
 
 /* How often a pausing body looks at the pause word: every `steps` of its inner loop (a power
- * of two up to 1024; default 4, about 2 us of a GEMM tile).  Each look stalls the workgroup
- * for a memory round trip, so fewer steps buy a faster pause with best-effort throughput
- * (measured on a 4096^3 GEMM: 16 -> 4 steps costs 1.6 % alone and takes 3 us off the median
- * and 1.5 us off the 99th percentile of a co-located 4096 x 4096 GEMV).  Workers that take a
- * GEMM's blocks in parts of 32x32 (64x64, 128x64) look every 16 (8, 4) steps of 32 k at most, 1
- * to 2 us, and act on a look as much later.
+ * of two up to 1024; default 4, about 2 us of a GEMM tile).  A body asks for the word with a load
+ * among those of its operands and acts on the answer when it has come, a stage of 64 k later in
+ * tiles of 256 rows, so a look costs next to nothing (waited for on the spot, looks every 4
+ * steps cost 5 to 7 % of a product); workers that take a GEMM's blocks in parts of 32x32 (64x64,
+ * 128x64) look every 16 (8, 4) steps of 32 k at most, 1 to 2 us, and act on a look as much later.
  * Applies to jobs launched after the call. */
 int tally_set_yield_every(tally_ctx *ctx, uint32_t steps);
 

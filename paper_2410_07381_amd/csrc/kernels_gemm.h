@@ -79,27 +79,28 @@ struct GemmBodyT {
   static constexpr bool END_BARRIER = false;
   static constexpr bool YIELDS = true;
   static constexpr bool RANGE = false;
-  // share of a tile between two looks at the pause word, `every` k-steps of 32 apart (a stage
-  // is two of them and is looked at once); host side, for turnaround estimates
+  // share of a tile between two questions for the pause word, `every` k-steps of 32 apart (a stage
+  // is two of them and asks once), and the stage after the second, at whose end its answer is
+  // acted on; host side, for turnaround estimates
   static double pause_fraction(const Args &a, uint32_t every) {
-    const uint32_t nk = a.k / KSTEP, e = every < 2 ? 2 : every;
+    const uint32_t nk = a.k / KSTEP, e = (every < 2 ? 2 : every) + 2;
     return nk > e ? (double)e / nk : 1.0;
   }
 
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
-    run_impl<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15});
+    run_impl<false, false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15, false});
   }
   // best-effort forms: the output tile is written with non-temporal stores (it is not read
   // again by this kernel and would only push other data out of the caches)
   static __device__ __forceinline__ void run_be(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
-    run_impl<true>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15});
+    run_impl<true, false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15, false});
   }
   static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by,
                                                       uint32_t bz, const YieldCtl ctl) {
-    run_impl<true>(a, bx, by, bz, ctl);
+    run_impl<true, true>(a, bx, by, bz, ctl);
   }
 
-  template <bool NT>
+  template <bool NT, bool YIELD>
   static __device__ __forceinline__ void run_impl(const Args &a, uint32_t bx, uint32_t by,
                                                   uint32_t bz, const YieldCtl ctl) {
 #ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
@@ -173,13 +174,27 @@ struct GemmBodyT {
 #pragma unroll
       for (int j = 0; j < NF; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+    // Looks at the pause word.  To wait for one is a memory round trip in which the wave's matrix
+    // pipe idles and the other three wait at the next barrier (8192^3 as workers 812 us, 757
+    // without looks).  So one wave asks with an ordinary load among the operands' and acts on the
+    // answer a stage later.  The question goes out between a stage's B and its A: what waits for
+    // that B waits for the answer too, a thousand cycles after it was asked, and counts the same
+    // loads whether there was one or not.
     uint32_t pause_left = ctl.ticks;   // what is left of this block's pause budget
+    uint32_t look = 0;
+    const bool looks = YIELD && ctl.ticks != 0 && wave == 0;
+    const auto rF = __builtin_amdgcn_make_buffer_rsrc((void *)ctl.flag, 0, 4, 0x00027000);
+    auto ask = [&]() { look = __builtin_amdgcn_raw_buffer_load_b32(rF, 0, 0, 16); };   // (sc1)
+    auto act = [&]() {
+      if (__builtin_amdgcn_readfirstlane(look) == ctl.epoch) yield_while_preempted(ctl, pause_left);
+    };
+    // stages that ask and those, right after them, that act: never for the other waves
+    const uint32_t look_mask = looks ? ctl.mask >> 1 : 0u, ask_at = looks ? look_mask : 1u, act_at = looks ? 0u : 1u;
     // A tile's first loads (every resident tile starts at once after a launch) and its
     // epilogue (32 MiB written by all compute units together) are its heaviest bursts of
-    // memory traffic: a tile long enough to afford two more looks at the pause word takes
-    // them just before either, so that neither burst starts on top of a high-priority kernel.
-    const bool edge_polls = ctl.ticks != 0 && nh >= 32;
-    if (edge_polls && wave == 0) yield_while_preempted(ctl, pause_left);
+    // memory traffic: neither is to start on top of a high-priority kernel.  (The first block
+    // of a fetch has just been told by the fetch itself.)
+    if (ctl.look_first && looks && nh >= 32) yield_while_preempted(ctl, pause_left);
     // a previous tile's waves may still be reading LDS: fence them off before refilling it
     __syncthreads();
     {
@@ -229,12 +244,8 @@ struct GemmBodyT {
     for (int j = 0; j < NF; ++j) read_b(0, 0, j);
     read_a(0, 0, 1);
     __builtin_amdgcn_sched_barrier(0);
-    const uint32_t poll_mask = ctl.mask >> 1;             // in stages
     uint32_t kt = 0;
     do {
-      // one wave polls; the others meet it at the barrier
-      if (ctl.ticks != 0 && wave == 0 && (kt & poll_mask) == poll_mask)
-        yield_while_preempted(ctl, pause_left);
       const uint32_t st = kt & 1;
       const Offs va1 = offs(vA0, vA1, kt + 1);
       // first half of the stage; the second half of A's loads of stage kt+1 go out
@@ -270,6 +281,14 @@ struct GemmBodyT {
         if (i + 2 < MF) read_a(st, 1, i + 2);
         else read_a(st ^ 1, 0, i + 2 - MF);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (YIELD) {
+          // (one wave pauses, the others meet it at the next barrier)
+          if (i == MF - 2) {
+            if (__builtin_expect((kt & look_mask) == act_at, 0)) act();
+            if (__builtin_expect((kt & look_mask) == ask_at, 0)) ask();
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
         mma(1, i, Q, Q);
         if (i < NF) read_b(st ^ 1, 0, i);
         __builtin_amdgcn_sched_barrier(0);
@@ -285,7 +304,7 @@ struct GemmBodyT {
     } while (++kt < ns);
     // what was still on its way is the zeros of stages past the last one
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (edge_polls && wave == 0) yield_while_preempted(ctl, pause_left);
+    if (looks && nh >= 32) act();
     // every wave is past its last fragment read: LDS can be reused as staging space
     __syncthreads();
     // The accumulators are read below through inline assembly, which the compiler's
@@ -410,7 +429,7 @@ struct GemmTileT {
   }
 
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
-    run_impl<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15});
+    run_impl<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15, false});
   }
   static __device__ __forceinline__ void run_be(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) { run(a, bx, by, bz); }
   static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {

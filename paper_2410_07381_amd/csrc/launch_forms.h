@@ -267,6 +267,7 @@ struct YieldCtl {          // passed by value: taking the address of the kernel'
   const uint32_t *flag;    // block would force it out of scalar registers into memory
   uint32_t epoch, ticks;
   uint32_t mask;           // poll when (step & mask) == mask
+  bool look_first;         // the block may begin during a request: it does not follow a fetch at once
 };
 __device__ __forceinline__ void yield_while_preempted(const YieldCtl &y, uint32_t &left) {
   if (left == 0u || scalar_load_coherent(y.flag) != y.epoch) return;
@@ -348,9 +349,9 @@ __device__ __forceinline__ void run_part(const typename Body::Args &args, const 
   else Sub::run_be(args, bx * PX + part % PX, by * PY + part / PX, bz);
   record_part(c.cover, block, part, P, bx, by, bz, c.segment, blockIdx.x);
 }
-__device__ __forceinline__ YieldCtl yield_ctl(const PtbCtl &c) {
+__device__ __forceinline__ YieldCtl yield_ctl(const PtbCtl &c, bool look_first) {
   return YieldCtl{c.flag_copies + (blockIdx.x % kFlagCopies) * kFlagCopyStride, c.epoch,
-                  c.flag_copies != nullptr ? c.yield_ticks : 0u, c.yield_mask};
+                  c.flag_copies != nullptr ? c.yield_ticks : 0u, c.yield_mask, look_first};
 }
 
 template <class Body>
@@ -359,7 +360,7 @@ __device__ __forceinline__ void ptb_parts(const typename Body::Args &args, const
   if (threadIdx.x == 0) s_got = fetch_parts(c, 1, Body::PARTS);
   __syncthreads();
   const uint32_t idx = __builtin_amdgcn_readfirstlane(s_got.x), end = __builtin_amdgcn_readfirstlane(s_got.y);
-  if (idx < end) run_part<Body>(args, c, yield_ctl(c), idx);
+  if (idx < end) run_part<Body>(args, c, yield_ctl(c, false), idx);
 }
 
 template <class Body>
@@ -375,10 +376,10 @@ __device__ __forceinline__ void ptb_tail(const typename Body::Args &args, const 
     if (idx % P == 0 && end - idx == P) {
       uint32_t bx, by, bz;
       delinearize(idx / P, c.gx, c.gy, bx, by, bz);
-      Body::Whole::run_yielding(args, bx, by, bz, yield_ctl(c));
+      Body::Whole::run_yielding(args, bx, by, bz, yield_ctl(c, false));
       record(c.cover, idx / P, bx, by, bz, c.segment, blockIdx.x);
     } else {
-      for (; idx < end; ++idx) run_part<Body>(args, c, yield_ctl(c), idx);
+      for (; idx < end; ++idx) run_part<Body>(args, c, yield_ctl(c, true), idx);
     }
   }
 }
@@ -411,7 +412,7 @@ __device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, cons
       uint32_t bx, by, bz;
       delinearize(idx, c.gx, c.gy, bx, by, bz);
       if constexpr (Body::YIELDS)
-        Body::run_yielding(args, bx, by, bz, yield_ctl(c));
+        Body::run_yielding(args, bx, by, bz, yield_ctl(c, idx != first));
       else
         Body::run_be(args, bx, by, bz);
       record(c.cover, idx, bx, by, bz, c.segment, worker);

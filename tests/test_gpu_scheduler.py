@@ -311,3 +311,48 @@ def test_workers_on_parts_of_blocks_pause_as_well(env, m, n, k):
     finally:
         ctx.set_yield_bound_us(1000)
     assert paused > 0.004 and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n128,k,every,chunk", [(False, (1 << 16) + 32, 1, 1), (True, (1 << 16) + 32, 4, 4),
+                                                (False, 1 << 16, 64, 4)])
+def test_large_tiles_pause_on_the_answer_of_an_earlier_stage(env, n128, k, every, chunk):
+    """Tiles of 256 rows ask for the pause word among their operands' loads and act on the answer a
+    stage later: with looks every stage, every second and every 32nd, a last stage that is half
+    full, and blocks that follow another one of the same fetch.  A pause met mid-tile holds the workers
+    until it is ended, and the numbers are those of the original form."""
+    import time
+    B, ctx, torch = env
+    m, n = 512, 1024
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k + every)
+    A = torch.randn(1, m, k, device="cuda", generator=gen).to(torch.bfloat16)
+    Bt = torch.randn(1, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.empty(1, m, n, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C, n128=n128)
+    torch.cuda.synchronize()
+    ctx.launch_native(kern)
+    torch.cuda.synchronize()
+    want = C.view(torch.int16).clone()
+    ctx.set_yield_bound_us(100000)
+    ctx.set_yield_every(every)
+    try:
+        for pause_s in (0.0, 0.004):
+            C.fill_(float("nan"))
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            job = ctx.launch_ptb(kern, kern.total_blocks // chunk, chunk=chunk, coverage=True)
+            while time.perf_counter() < t0 + 0.0003:
+                pass
+            if pause_s:
+                job.preempt(pause=True)
+                time.sleep(pause_s)
+                job.pump()
+                assert job.progress()[2] == B.JOB_RUNNING
+                job.end_pause()
+            assert job.wait() == B.JOB_COMPLETE      # (every block had been fetched)
+            assert (job.coverage()["count"] == 1).all()
+            job.free()
+            assert torch.equal(C.view(torch.int16), want)
+    finally:
+        ctx.set_yield_bound_us(1000)
+        ctx.set_yield_every(4)
