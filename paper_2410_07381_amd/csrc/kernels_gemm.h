@@ -16,9 +16,14 @@
 //    first MFMA operand a lane holds four neighbouring columns of one row, which leave as
 //    one 8-byte LDS write;
 //  - a barrier per 1024 cycles with the reads of the next half-step bunched behind it.
-// In turn on one card, N(0, 1/64) operands: 4096^3 in its original form 120-123 us before and
-// 103-107 now in bursts of ten launches (1.3 PFLOP/s), 133 and 120 in bursts of fifty, where the
-// clock is lower; 8192^3 906 -> 815 (1.35); as persistent workers 1029 -> 830.
+// A second one still took 2640 cycles a stage (of 2048 of MFMA) because addresses were computed where
+// they were used, in bunches of up to 25 scalar instructions between two MFMAs; with one
+// instruction behind each MFMA (see the loop) 1.42 M cycles of 8192^3 became 1.24 M, 0.85 of
+// them MFMA.
+// In turn on one card, N(0, 1/64) operands, original form, us of the first / second / this state:
+// 4096^3 120 / 104 / 98 (bursts of ten), 8192^3 906 (fifty) / 765 / 715 (four; 1.54 PFLOP/s, the
+// library 705), 16384 x 12288 x 4096 - / 1172 / 1090, 16384 x 4096 x 16384 - / 1565 / 1460; as
+// 256 workers 8192^3 - / 801 / 739.  The clock falls as the pipe fills: 1.69 GHz before, 1.61 now.
 //
 // LDS holds two stages of both operands (64 KB each, 128 KB in all).  A stage's place is
 // refilled as soon as its fragments are in registers, not when its products are done: B's
@@ -105,9 +110,6 @@ struct GemmBodyT {
                                                   uint32_t bz, const YieldCtl ctl) {
 #ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
     extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
-    unsigned char *sA = tally_dyn_lds;                    // STAGES x 32 KB
-    unsigned char *sB = tally_dyn_lds + STAGES * OPA;
-
     const uint32_t tid = threadIdx.x;
     // (the lane index is made opaque here and again before the epilogue: a worker runs tile
     // after tile, and addresses derived from a plain threadIdx would be kept in registers
@@ -145,27 +147,30 @@ struct GemmBodyT {
     const auto rB = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const unsigned char *)(a.Bt + bz * a.stride_b + (uint64_t)(bx * TILE_N) * LDB) - 4096),
         0, 0x7fffffff, 0x00027000);
-    const uint32_t stepA = 16 * LDA, stepB = 16 * LDB;    // bytes between the rows of two loads
+    // scalar offsets of a wave's loads, kept: nothing is computed for one inside the loop
+    uint32_t soA[LDA_N], soB[LDB_N];
+#pragma unroll
+    for (int j = 0; j < LDA_N; ++j) {
+      soA[j] = 4096u + (uint32_t)j * 16 * LDA - (uint32_t)(j & 3) * 1024u;
+      asm volatile("" : "+s"(soA[j]));
+    }
+#pragma unroll
+    for (int j = 0; j < LDB_N; ++j) {
+      soB[j] = 4096u + (uint32_t)j * 16 * LDB - (uint32_t)(j & 3) * 1024u;
+      asm volatile("" : "+s"(soB[j]));
+    }
     struct Offs { uint32_t even, odd; };
     auto offs = [&](uint32_t v0, uint32_t v1, uint32_t kt) {
       const uint32_t none = kt >= ns ? OOB : 0u, half = (half_last && kt + 1 == ns) ? OOB : 0u;
-      return Offs{v0 | (hm0 & half) | none, v1 | (hm1 & half) | none};
+      return Offs{(v0 + kt * (BK * 2)) | (hm0 & half) | none, (v1 + kt * (BK * 2)) | (hm1 & half) | none};
     };
-    auto load_a = [&](const Offs &v, uint32_t kt, int j) {
-      lptr_t l = (lptr_t)(sA + (kt & 1) * OPA + wave * (64 * BK * 2) + (j & 4) * 1024);
-      const uint32_t so = 4096u + kt * (BK * 2) + (uint32_t)j * stepA - (uint32_t)(j & 3) * 1024u;
-      if ((j & 3) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.even, so, 0, 0);
-      if ((j & 3) == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.odd, so, 1024, 0);
-      if ((j & 3) == 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.even, so, 2048, 0);
-      if ((j & 3) == 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, l, 16, v.odd, so, 3072, 0);
-    };
-    auto load_b = [&](const Offs &v, uint32_t kt, int j) {
-      lptr_t l = (lptr_t)(sB + (kt & 1) * OPB + wave * (8 * LDB_N * BK * 2) + (j & 4) * 1024);
-      const uint32_t so = 4096u + kt * (BK * 2) + (uint32_t)j * stepB - (uint32_t)(j & 3) * 1024u;
-      if ((j & 3) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.even, so, 0, 0);
-      if ((j & 3) == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.odd, so, 1024, 0);
-      if ((j & 3) == 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.even, so, 2048, 0);
-      if ((j & 3) == 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, l, 16, v.odd, so, 3072, 0);
+    // load j of a stage to `at` (the wave's rows of the operand's place in LDS)
+    auto load = [&](const auto &r, uint32_t at, const Offs &v, const uint32_t *so, int j) {
+      lptr_t l = (lptr_t)(at + (j & 4) * 1024);
+      if ((j & 3) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, l, 16, v.even, so[j], 0, 0);
+      if ((j & 3) == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, l, 16, v.odd, so[j], 1024, 0);
+      if ((j & 3) == 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, l, 16, v.even, so[j], 2048, 0);
+      if ((j & 3) == 3) __builtin_amdgcn_raw_ptr_buffer_load_lds(r, l, 16, v.odd, so[j], 3072, 0);
     };
 
     f32x4_t acc[MF][NF];
@@ -197,75 +202,99 @@ struct GemmBodyT {
     if (ctl.look_first && looks && nh >= 32) yield_while_preempted(ctl, pause_left);
     // a previous tile's waves may still be reading LDS: fence them off before refilling it
     __syncthreads();
+    // LDS as addresses: the operands' places of stage 0, and this wave's rows in the place that the
+    // next loads go to
+    const uint32_t ldsA = (uint32_t)(uintptr_t)(lptr_t)tally_dyn_lds, ldsB = ldsA + STAGES * OPA;
+    uint32_t toA = ldsA + wave * (64 * BK * 2), toB = ldsB + wave * (8 * LDB_N * BK * 2);
+    // offsets of the stage whose loads are next: its second half of A's are
+    Offs vA = offs(vA0, vA1, 1), vB = offs(vB0, vB1, 1);
     {
       const Offs vb = offs(vB0, vB1, 0), va = offs(vA0, vA1, 0);
 #pragma unroll
-      for (int j = 0; j < LDB_N; ++j) load_b(vb, 0, j);
+      for (int j = 0; j < LDB_N; ++j) load(rB, toB, vb, soB, j);
 #pragma unroll
-      for (int j = 0; j < LDA_N; ++j) load_a(va, 0, j);
-      const Offs vb1 = offs(vB0, vB1, 1), va1 = offs(vA0, vA1, 1);
+      for (int j = 0; j < LDA_N; ++j) load(rA, toA, va, soA, j);
 #pragma unroll
-      for (int j = 0; j < LDB_N; ++j) load_b(vb1, 1, j);
+      for (int j = 0; j < LDB_N; ++j) load(rB, toB + OPB, vB, soB, j);
 #pragma unroll
-      for (int j = 0; j < LDA_N / 2; ++j) load_a(va1, 1, j);
+      for (int j = 0; j < LDA_N / 2; ++j) load(rA, toA + OPA, vA, soA, j);
     }
 
     // Two B fragment sets (this half-step's and the next one's) and a window of four A fragments;
-    // a step is one A fragment against all of B's.  A wave is alone on its SIMD: whatever it
-    // issues between two MFMAs that does not fit into the 16 cycles the earlier one occupies
-    // the matrix pipe leaves the pipe idle, so reads and direct loads are written one at a
-    // time between pairs of MFMAs and pinned there.  The MFMAs are inline assembly because the
-    // compiler otherwise puts part of the accumulators into arithmetic registers.
+    // a step is one A fragment against all of B's.  A wave is alone on its SIMD: it issues an
+    // instruction every four cycles, so between two MFMAs, 16 cycles apart, three others are free
+    // and every further one leaves the matrix pipe idle for four.  So each MFMA is followed by one
+    // read, load or address update at most, pinned there, and what can be is kept in registers
+    // or updated in place: offsets and LDS addresses move by a stage's k or to the other stage's
+    // place with one addition each.  (With addresses computed where they were used, 163 other
+    // instructions a stage in bunches of up to 25, a stage took 2640 cycles for its 2048 of
+    // MFMAs.)  The MFMAs are inline assembly because the compiler otherwise puts part of the
+    // accumulators into arithmetic registers, and so are the updates, which it would sum up anew.
     // Fragment reads: lane l takes row l%16 of a 16-row block and k-chunk 4 kk + l/16
     const uint32_t f_off = (lane & 15) * (BK * 2) + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16);
-    const uint32_t fA = wm * (128 * BK * 2) + f_off, fB = wn * (16 * NF * BK * 2) + f_off;
+    uint32_t aK[2], bK[2];                                // addresses of k-halves 0 and 1
+    aK[0] = ldsA + wm * (128 * BK * 2) + f_off;
+    aK[1] = ldsA + wm * (128 * BK * 2) + (f_off ^ 64);
+    bK[0] = ldsB + wn * (16 * NF * BK * 2) + f_off;
+    bK[1] = ldsB + wn * (16 * NF * BK * 2) + (f_off ^ 64);
     bf16x8_t fa[4], fb[2][NF];
-    auto read_a = [&](uint32_t st, int kk, int i) {
-      fa[(8 * kk + i) & 3] = *reinterpret_cast<const bf16x8_t *>(sA + st * OPA + (fA ^ (kk * 64)) + i * (16 * BK * 2));
+    typedef const volatile __attribute__((address_space(3))) bf16x8_t *frag_t;   // (volatile: pinned)
+    auto read_a = [&](int kk, int i) { fa[(8 * kk + i) & 3] = *(frag_t)(aK[kk] + i * (16 * BK * 2)); };
+    auto read_b = [&](int kk, int j) { fb[kk][j] = *(frag_t)(bK[kk] + j * (16 * BK * 2)); };
+    auto mma = [&](int kk, int i, int j) {
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                   : "+a"(acc[i][j]) : "v"(fb[kk][j]), "v"(fa[(8 * kk + i) & 3]));
     };
-    auto read_b = [&](uint32_t st, int kk, int j) {
-      fb[kk][j] = *reinterpret_cast<const bf16x8_t *>(sB + st * OPB + (fB ^ (kk * 64)) + j * (16 * BK * 2));
-    };
-    auto mma = [&](int kk, int i, int j0, int n) {
-#pragma unroll
-      for (int j = j0; j < j0 + n; ++j)
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                     : "+a"(acc[i][j]) : "v"(fb[kk][j]), "v"(fa[(8 * kk + i) & 3]));
-      __builtin_amdgcn_sched_barrier(0);
-    };
+    auto move = [](uint32_t &v, int32_t by) { asm volatile("v_add_u32_e32 %0, %1, %0" : "+v"(v) : "s"(by)); };
+    auto flip = [](int32_t &by) { asm volatile("s_sub_i32 %0, 0, %0" : "+s"(by) : : "scc"); };
+    auto next_k = [](uint32_t &v) { asm volatile("v_add_u32_e32 %0, 0x80, %0" : "+v"(v)); };
+    static_assert(BK * 2 == 0x80, "a stage's k in bytes");
     constexpr int Q = NF / 4;                             // MFMAs between two other instructions
 
     // stage 0 has landed once only what belongs to stage 1 is in flight
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LDB_N + LDA_N / 2) : "memory");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    read_a(0, 0, 0);
+    read_a(0, 0);
 #pragma unroll
-    for (int j = 0; j < NF; ++j) read_b(0, 0, j);
-    read_a(0, 0, 1);
+    for (int j = 0; j < NF; ++j) read_b(0, j);
+    read_a(0, 1);
     __builtin_amdgcn_sched_barrier(0);
+    int32_t d[2] = {OPA, OPB}, &dA = d[0], &dB = d[NF == MF ? 0 : 1];   // from this stage's place to the other one
+    static_assert(NF != MF || OPA == OPB, "one step for both operands");
+    toA += OPA;
     uint32_t kt = 0;
     do {
-      const uint32_t st = kt & 1;
-      const Offs va1 = offs(vA0, vA1, kt + 1);
       // first half of the stage; the second half of A's loads of stage kt+1 go out
 #pragma unroll
-      for (int i = 0; i < MF; ++i) {
-        mma(0, i, 0, Q);
-        if (i < NF) read_b(st, 1, i);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(0, i, Q, Q);
-        if (i + 2 < MF) read_a(st, 0, i + 2);
-        else read_a(st, 1, i + 2 - MF);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(0, i, 2 * Q, Q);
-        if (i < LDA_N / 2) load_a(va1, kt + 1, LDA_N / 2 + i);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(0, i, 3 * Q, Q);
+      for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+          mma(0, i, j);
+          if (j == 0 && i < NF) read_b(1, i);
+          if (j == Q) {
+            if (i + 2 < MF) read_a(0, i + 2);
+            else read_a(1, i + 2 - MF);
+          }
+          if (j == 2 * Q && i < LDA_N / 2) load(rA, toA, vA, soA, LDA_N / 2 + i);
+          if (j == 3 * Q) {
+            if (i == 0) move(bK[0], dB);
+            if (i == 1) next_k(vB.even);
+            if (i == 2) next_k(vB.odd);
+            if (i == 3) asm volatile("s_sub_i32 %0, %0, %1" : "+s"(toA) : "s"(dA) : "scc");
+            if (i == 4) next_k(vA.even);
+            if (i == 5) next_k(vA.odd);
+            if (i == 6) move(aK[0], dA);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      // From here on it is stage kt+2 that is loaded: the last one, or one that does not exist
+      if (__builtin_expect(kt + 3 >= ns, 0)) {
+        const uint32_t m0 = kt + 3 == ns ? (half_last ? hm0 : 0u) : OOB, m1 = kt + 3 == ns ? (half_last ? hm1 : 0u) : OOB;
+        vA.even |= m0; vA.odd |= m1; vB.even |= m0; vB.odd |= m1;
       }
       // second half.  B of stage kt+1 is in LDS for everyone; everyone is done with B of stage
       // kt, whose place takes the loads of stage kt+2
-      const Offs vb2 = offs(vB0, vB1, kt + 2), va2 = offs(vA0, vA1, kt + 2);
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(1)" ::"n"(LDA_N) : "memory");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
@@ -277,29 +306,36 @@ struct GemmBodyT {
           __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
         }
-        mma(1, i, 0, Q);
-        if (i + 2 < MF) read_a(st, 1, i + 2);
-        else read_a(st ^ 1, 0, i + 2 - MF);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (YIELD) {
-          // (one wave pauses, the others meet it at the next barrier)
-          if (i == MF - 2) {
-            if (__builtin_expect((kt & look_mask) == act_at, 0)) act();
-            if (__builtin_expect((kt & look_mask) == ask_at, 0)) ask();
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+          mma(1, i, j);
+          if (j == 0) {
+            if (i + 2 < MF) read_a(1, i + 2);
+            else read_a(0, i + 2 - MF);
           }
+          if constexpr (YIELD) {
+            // (one wave pauses, the others meet it at the next barrier)
+            if (i == MF - 2 && j == Q - 1) {
+              if (__builtin_expect((kt & look_mask) == act_at, 0)) act();
+              if (__builtin_expect((kt & look_mask) == ask_at, 0)) ask();
+            }
+          }
+          if (j == Q && i < NF) read_b(0, i);
+          if (j == 2 * Q) {
+            if (i < 4) load(rB, toB, vB, soB, LDB_N > 4 ? 2 * i : i);
+            if (i >= MF - 2) load(rA, toA, vA, soA, 2 * (i - (MF - 2)));
+            if (i == 4) move(bK[1], dB);
+            if (i == 5) move(aK[1], dA);
+          }
+          if (j == 3 * Q) {
+            if (i < 4 && LDB_N > 4) load(rB, toB, vB, soB, 2 * i + 1);
+            if (i >= MF - 2) load(rA, toA, vA, soA, 2 * (i - (MF - 2)) + 1);
+            if (i == 4) asm volatile("s_add_i32 %0, %0, %1" : "+s"(toB) : "s"(dB) : "scc");
+            if (i == 5) flip(d[0]);
+            if (i == 5 && NF != MF) flip(d[1]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-        mma(1, i, Q, Q);
-        if (i < NF) read_b(st ^ 1, 0, i);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(1, i, 2 * Q, Q);
-        if (i < 4) load_b(vb2, kt + 2, i);
-        if (i >= MF - 2) load_a(va2, kt + 2, 2 * (i - (MF - 2)));
-        __builtin_amdgcn_sched_barrier(0);
-        mma(1, i, 3 * Q, Q);
-        if (i < 4 && LDB_N > 4) load_b(vb2, kt + 2, 4 + i);
-        if (i >= MF - 2) load_a(va2, kt + 2, 2 * (i - (MF - 2)) + 1);
-        __builtin_amdgcn_sched_barrier(0);
       }
     } while (++kt < ns);
     // what was still on its way is the zeros of stages past the last one
