@@ -188,7 +188,10 @@ int tally_launch_sliced(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t 
  * num_workers worker blocks loop { check flag; fetch-and-add the global task counter;
  * map the task index to the logical block index; run the block; barrier }.
  * `chunk` (>= 1) is the number of consecutive task indices taken per fetch; 1 is the
- * paper's form.  A fetched index is always executed before the worker exits.
+ * paper's form.  A fetched index is always executed before the worker exits.  Where blocks are
+ * so short that 256 workers or more would queue at the counter, eight neighbours draw eight
+ * fetches at once and share them out: a worker then finishes at most one fetch more after a
+ * preemption signal.  Progress and prefix are the same.
  * num_workers must not exceed tally_max_workers(): every worker has to be resident at
  * once (Section 4.2 draws its candidates from the multiples of the compute-unit count
  * that fit).  Workgroups that wait for room keep their hardware queue's dispatcher busy,

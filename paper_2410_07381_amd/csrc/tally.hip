@@ -76,6 +76,10 @@ struct KernelOps {
   // parts the persistent-worker form splits each of `blocks` logical blocks in (null: never), and
   // how many whole blocks each worker takes first
   uint32_t (*parts)(uint64_t blocks, uint32_t workers, uint32_t chunk, uint32_t *whole);
+  // bytes that a logical block reads and writes, and up to how many of them per fetch of `chunk`
+  // blocks it pays that `workers` fetch in teams (null: blocks are long, it never does)
+  uint64_t (*block_bytes)(const void *args);
+  uint32_t (*team_bytes)(uint32_t workers, uint32_t chunk);
 };
 
 template <class Body>
@@ -470,10 +474,17 @@ double pause_fraction_t(const void *args, uint32_t every, uint32_t, uint32_t) {
   }
 }
 
+template <class Body>
+uint64_t block_bytes(const void *args) {
+  typename Body::Args a;
+  memcpy(&a, args, sizeof(a));
+  return Body::block_bytes(a);
+}
+
 #define OPS(Body, nm, gridfn)                                                              \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_t<Body>, launch_sliced_t<Body>,     \
    launch_ptb_t<Body>, init_t<Body>, occupancy_t<Body>, pause_fraction_t<Body>,              \
-   footprint_t<Body>, {footprint_native_t<Body>}}
+   footprint_t<Body>, {footprint_native_t<Body>}, nullptr, nullptr, nullptr, block_bytes<Body>, Body::team_bytes}
 
 #define GEMM_TILES(Tile32, canon)                                                                         \
   footprint_native_t<Tile32>, footprint_native_t<GemmTileT<1, 2, canon>>,                                 \
@@ -483,12 +494,12 @@ double pause_fraction_t(const void *args, uint32_t every, uint32_t, uint32_t) {
    launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
    occupancy, pause_fraction_t<Wide>, footprint_t<Wide>,                                                  \
    {footprint_native_t<Narrow>, footprint_native_t<Wide>, footprint_native_t<Team>},                      \
-   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>}
+   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>, nullptr, block_bytes<Wide>, Wide::team_bytes}
 #define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
    footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>}, \
-   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts}
+   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(SaxpyBody, "saxpy", grid_saxpy),
@@ -501,11 +512,12 @@ const KernelOps kOps[TALLY_K_COUNT] = {
     OPS_ROWS(LayerNormBody, LayerNormNarrowBody, LayerNormNarrowDeepBody, LayerNormTeamBody,
              (occupancy_capped_t<LayerNormBody, 2>), "layernorm_f32", grid_layernorm),
     {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_attn_decode,
-     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice},
+     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice,
+     nullptr, nullptr, nullptr, nullptr},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
      pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true)}, gemm_small_native_choice,
-     gemm_sliced_choice<GemmCover::k32>},
+     gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes},
     OPS_GEMM(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128, GemmCover::k256x128),
 };
 
@@ -515,8 +527,8 @@ constexpr int kMaxShunned = 64;
 constexpr int kMaxSide = 2 * 8 + 2;
 constexpr int kMaxBeClients = 8;
 constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited, 128 B apart
-constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw | slice_done,ended
-constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostEnded = 132;
+constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw,born | slice_done,ended
+constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostBorn = 104, kHostEnded = 132;
 constexpr size_t kCopySlotBytes = kFlagCopies * kFlagCopyStride * sizeof(uint32_t);
 
 enum JobKind { KIND_PTB = 0, KIND_SLICED = 1, KIND_NATIVE = 2 };
@@ -565,6 +577,7 @@ struct tally_ctx {
   bool be_delays_hi;         // the caller's best-effort stream shares the high-priority one's pipe
   unsigned char *dev_pool;   // device
   uint32_t *copy_pool;       // device: per slot, kFlagCopies copies of the flag word
+  TeamLine *team_pool;       // device: per slot, kMaxTeams lines
   unsigned char *host_pool;  // pinned host
   unsigned char *host_pool_dev;
   bool slot_used[kSlots];
@@ -747,7 +760,8 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
 // first.  So the relays of drained segments are settled before the new workers are enqueued (the
 // new relay already is, so that its launch call and the wait overlap).  A segment whose workers
 // are still at work is not waited for: the new workers are behind them.
-int settle_relays_before(tally_ctx *ctx, hipStream_t ctl) {
+int settle_relays_before(tally_ctx *ctx, hipStream_t ctl, bool *settled) {
+  *settled = false;
   for (int s = 0; s < kSlots; ++s) {
     if (!ctx->slot_relay[s] || ctx->slot_ctl[s] != ctl) continue;
     const unsigned char *h = ctx->host_pool + s * kHostSlotBytes;
@@ -756,8 +770,15 @@ int settle_relays_before(tally_ctx *ctx, hipStream_t ctl) {
     if (epoch(kHostStatus) != ctx->slot_epoch[s] && epoch(kHostRaw) != ctx->slot_epoch[s]) continue;
     const int rc = settle_relay(ctx, s);
     if (rc) return rc;
+    *settled = true;
   }
   return TALLY_OK;
+}
+
+// Do `workers` of this kernel leave no room for a relay's wave on a compute unit that they fill?
+bool fills_gpu(const tally_ctx *ctx, const KernelOps *ops, uint32_t workers) {
+  const uint32_t *ft = ctx->foot_worker[ops - kOps], n = (workers + ctx->num_cus - 1) / ctx->num_cus;
+  return n * ft[1] > 31u || n * ((ft[1] + 3) / 4) * ft[2] > 480u;
 }
 
 // Parts that workers take a segment of `blocks` blocks up to block `limit` in (GemmParts).
@@ -769,6 +790,17 @@ uint32_t segment_parts(const KernelOps *ops, uint64_t blocks, uint64_t limit, ui
   if (limit * parts <= 0x40000000ull) return parts;
   *whole = 0;
   return 1u;
+}
+
+// Teams that `workers` form to fetch `chunk` blocks at a time (none: they do not).  The counter
+// serves W workers once in W x 11.4 ns; teams pay where a fetch's work takes less than that, by
+// bytes per fetch as measured (team_bytes), and not below 256 workers (SAXPY of 2^22, 128 x 4: 81 us
+// with the counter alone, 93 in teams).
+uint32_t team_count(const KernelOps *ops, const void *args, uint32_t workers, uint32_t chunk) {
+  if (!ops->team_bytes || workers < 256) return 0u;
+  if (ops->block_bytes(args) * chunk > ops->team_bytes(workers, chunk)) return 0u;
+  const uint32_t n = workers / kTeamSize;
+  return n < kMaxTeams ? n : kMaxTeams;
 }
 
 // Launch the workers (and their relay) for task indices [progress, limit).  Requires the
@@ -801,16 +833,21 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   c.host_raw = (unsigned long long *)(j->h_base_dev() + kHostRaw);
   c.host_relay = (unsigned long long *)(j->h_base_dev() + kHostRelay);
   c.host_gave_up = (unsigned long long *)(j->h_base_dev() + kHostGaveUp);
+  c.host_born = fills_gpu(ctx, j->ops, j->workers) ? (uint32_t *)(j->h_base_dev() + kHostBorn) : nullptr;
   c.cover = j->cover;
   c.parts = parts;
   c.limit = j->limit * parts;
   c.epoch = j->epoch;
-  c.exit_target = ctx->slot_exited[slot] + j->workers;
+  const uint32_t teams = team_count(j->ops, j->args, j->workers, chunk);
+  c.teams = ctx->team_pool + (size_t)slot * kMaxTeams;
+  c.team_count = teams;
+  c.exit_target = ctx->slot_exited[slot] + (teams ? teams : j->workers);
   c.counter_base = j->counter_base;
   c.workers = j->workers;
   c.chunk = chunk;
   c.whole = whole;
-  c.single_pass = blocks * parts <= (uint64_t)chunk * j->workers ? 1u : 0u;
+  c.single_pass = blocks * parts <= (uint64_t)chunk * j->workers &&
+                          (teams == 0 || j->workers % kTeamBatch == 0) ? 1u : 0u;
   c.segment = j->segments;
   c.gx = j->grid.x;
   c.gy = j->grid.y;
@@ -830,7 +867,15 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
     g_last_hip = (int)e;
     return TALLY_ERR_HIP;
   }
-  rc = settle_relays_before(ctx, j->ctl);   // (this slot's relay is not among them: settled above)
+  bool settled;
+  rc = settle_relays_before(ctx, j->ctl, &settled);   // (this slot's relay is not among them: settled above)
+  // A relay that was enqueued behind another one has less of a head start, and workers that fill the
+  // GPU leave it no second chance: wait until it says that it is there (2 ms at most: it may start
+  // late for other reasons, and then the request finds it late).
+  if (c.host_born && settled) {
+    const double t0 = now_us();
+    while (__atomic_load_n((uint32_t *)(j->h_base() + kHostBorn), __ATOMIC_ACQUIRE) != c.epoch && now_us() - t0 < 2000.0) {}
+  }
   ctx->slot_relay[slot] = true;
   ctx->slot_ctl[slot] = j->ctl;
   e = rc == TALLY_OK ? j->ops->ptb(j->be, j->args, c) : (hipError_t)g_last_hip;
@@ -1011,6 +1056,7 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
   memset(c->client_ctl, 0, sizeof(c->client_ctl));
   c->dev_pool = nullptr;
   c->copy_pool = nullptr;
+  c->team_pool = nullptr;
   c->host_pool = nullptr;
   c->marker_host = nullptr;
   c->static_attn_scratch = nullptr;
@@ -1035,6 +1081,7 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
       (e = hipMemset(c->dev_pool, 0, kSlots * kDevSlotBytes)) != hipSuccess ||
       (e = hipMalloc((void **)&c->copy_pool, kSlots * kCopySlotBytes)) != hipSuccess ||
       (e = hipMemset(c->copy_pool, 0, kSlots * kCopySlotBytes)) != hipSuccess ||
+      (e = hipMalloc((void **)&c->team_pool, sizeof(TeamLine) * kSlots * kMaxTeams)) != hipSuccess ||
       (e = hipHostMalloc((void **)&c->host_pool, kSlots * kHostSlotBytes, hipHostMallocDefault)) != hipSuccess ||
       (e = hipHostGetDevicePointer((void **)&c->host_pool_dev, c->host_pool, 0)) != hipSuccess ||
       (e = hipGetSymbolAddress(&c->static_attn_scratch, HIP_SYMBOL(static_scratch))) != hipSuccess ||
@@ -1044,6 +1091,7 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
     if (c->ctl) (void)hipStreamDestroy(c->ctl);
     if (c->dev_pool) (void)hipFree(c->dev_pool);
     if (c->copy_pool) (void)hipFree(c->copy_pool);
+    if (c->team_pool) (void)hipFree(c->team_pool);
     if (c->host_pool) (void)hipHostFree(c->host_pool);
     if (c->marker_host) (void)hipHostFree(c->marker_host);
     delete c;
@@ -1054,11 +1102,14 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
   // the relays' stream: one that, busy beside the best-effort stream, does not hold up the
   // high-priority stream
   c->side[c->n_side++] = c->be;
-  if ((e = make_side_stream(c, &c->ctl)) != hipSuccess) {
+  hipLaunchKernelGGL(team_init_kernel, dim3(kSlots * kMaxTeams / 256), dim3(256), 0, c->be, c->team_pool, kSlots * kMaxTeams);
+  if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(c->be)) != hipSuccess ||
+      (e = make_side_stream(c, &c->ctl)) != hipSuccess) {
     g_last_hip = (int)e;
     for (int i = 0; i < c->n_shunned; ++i) (void)hipStreamDestroy(c->shunned[i]);
     (void)hipFree(c->dev_pool);
     (void)hipFree(c->copy_pool);
+    (void)hipFree(c->team_pool);
     (void)hipHostFree(c->host_pool);
     (void)hipHostFree(c->marker_host);
     delete c;
@@ -1121,6 +1172,7 @@ int tally_destroy(tally_ctx *ctx) {
   }
   (void)hipFree(ctx->dev_pool);
   (void)hipFree(ctx->copy_pool);
+  (void)hipFree(ctx->team_pool);
   (void)hipHostFree(ctx->host_pool);
   (void)hipHostFree(ctx->marker_host);
   delete ctx;

@@ -516,3 +516,43 @@ def test_error_paths(env):
     assert job.progress()[2] == B.JOB_COMPLETE
     job.free()
     torch.cuda.synchronize()
+
+
+# ------------------------------------------------------------------ workers in teams
+@pytest.mark.parametrize("workers,chunk,blocks", [(256, 1, 256), (256, 1, 1031), (261, 1, 2000), (519, 1, 519),
+                                                  (519, 3, 5003), (1024, 2, 2048), (2047, 1, 9000), (300, 16, 4801)])
+def test_teams_of_workers_run_every_block_once(env, workers, chunk, blocks):
+    """From 256 workers on short blocks fetch through their team's word, a batch at a time.  Teams of
+    eight and the odd last one, grids that one fetch each covers exactly and ones that end inside a
+    batch, stops at given counter values and on requests: always a prefix, every block once."""
+    B, ctx, torch = env
+    n = blocks * 256 - 100
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(workers + blocks)
+    x, y0 = (torch.randn(n, device="cuda", generator=gen) for _ in range(2))
+    y = y0.clone()
+    torch.cuda.synchronize()
+    want = (1.5 * x.double() + y0.double()).float()       # the product is exact in 64 bits: one rounding
+    job = ctx.launch_ptb(B.saxpy(x, y, 1.5), workers, chunk=chunk, coverage=True, stop_at=blocks // 3)
+    assert job.wait() == B.JOB_STOPPED and job.progress()[0] == blocks // 3
+    for at in (blocks // 3 + 1, blocks // 2):
+        count = job.coverage()["count"]
+        done = job.progress()[0]
+        assert (count[:done] == 1).all() and (count[done:] == 0).all()
+        job.resume(stop_at=at)
+        assert job.wait() == B.JOB_STOPPED and job.progress()[0] == at
+    job.resume()
+    for _ in range(50):
+        job.preempt()
+        if job.wait() == B.JOB_COMPLETE:
+            break
+        done = job.progress()[0]
+        count = job.coverage()["count"]
+        assert (count[:done] == 1).all() and (count[done:] == 0).all()
+        job.resume()
+    assert job.wait() == B.JOB_COMPLETE
+    assert (job.coverage()["count"] == 1).all()
+    job.free()
+    torch.cuda.synchronize()
+    # a fused multiply-add rounds once, the 64-bit sum and its conversion at most once more (2^-53 of it)
+    assert ((y - want).abs() <= 2.0 ** -23 * want.abs()).all()

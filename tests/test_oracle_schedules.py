@@ -314,3 +314,70 @@ def test_sliced_invariants_hold_for_any_run(total, slice_blocks, stops):
             seg += 1
             want_resumes.append(hi)
     assert resumes == want_resumes
+
+
+# ------------------------------------------------------------------ workers in teams
+def _walk_teams(sizes, batch, limit, request, single=False, waits_for=None):
+    """Every interleaving of workers that fetch through their team's word (base, count): a count below
+    `batch` is an index, exactly `batch` means "draw the next batch from the task counter", beyond it
+    someone is drawing.  Returns "deadlock", "lost" or "ok" (at every end exactly the blocks below the
+    progress have run, each once).  `waits_for(count)`: a waiter looks until it holds, then asks again
+    (by default it asks again and again, which changes nothing until the batch is there)."""
+    folded = 1 << 20
+    ready = waits_for or (lambda count: count <= batch)
+    start = (tuple((t, "ask", 0) for t, n in enumerate(sizes) for _ in range(n)),
+             tuple((0, batch) for _ in sizes), 0, (), None, request)
+    seen, todo = set(), [start]
+    while todo:
+        state = todo.pop()
+        if state in seen:
+            continue
+        seen.add(state)
+        workers, words, counter, ran, progress, pending = state
+        steps = []
+        for i, (team, at, held) in enumerate(workers):
+            base, count = words[team]
+            new, words2, counter2, ran2 = None, words, counter, ran
+            if at == "ask":
+                words2 = words[:team] + ((base, count + 1),) + words[team + 1:]
+                idx = base + count if count < batch else None
+                new = (team, "draw" if count == batch else "wait", 0)
+            elif at == "wait":
+                if not ready(count):
+                    continue
+                idx, new = None, (team, "ask", 0)
+            elif at == "draw":
+                idx, new, counter2 = None, (team, "publish", counter), counter + batch
+            elif at == "publish":
+                idx, words2 = held, words[:team] + ((held, 1),) + words[team + 1:]
+            else:
+                continue
+            if idx is not None:
+                if idx < limit and idx in ran:
+                    return "lost"
+                new = (team, "left" if idx >= limit or single else "ask", 0)
+                ran2 = tuple(sorted(ran + (idx,))) if idx < limit else ran
+            steps.append((workers[:i] + (new,) + workers[i + 1:], words2, counter2, ran2, progress, pending))
+        if not steps:
+            if any(w[1] != "left" for w in workers):
+                return "deadlock"
+            if ran != tuple(range(limit if progress is None else progress)):
+                return "lost"
+        if pending:
+            steps.append((workers, words, counter + folded, ran, min(counter, limit), False))
+        todo += steps
+    return "ok"
+
+
+@pytest.mark.parametrize("sizes,batch,limit", [([2, 2], 2, 5), ([3], 2, 5), ([2, 3], 2, 4), ([4], 2, 6), ([2, 1], 1, 4)])
+@pytest.mark.parametrize("request_stands", [False, True])
+def test_teams_lose_nothing_and_always_end(sizes, batch, limit, request_stands):
+    assert _walk_teams(sizes, batch, limit, request_stands) == "ok"
+
+
+def test_teams_wrong_variants_are_caught():
+    # a waiter that looks for unused indices only: they may be gone again before it looks
+    assert _walk_teams([4], 2, 6, False, waits_for=lambda count: count < 2) == "deadlock"
+    # a single pass needs teams of whole batches: an index drawn for nobody is never run
+    assert _walk_teams([2, 2], 2, 4, True, single=True) == "ok"
+    assert _walk_teams([3, 1], 2, 4, False, single=True) == "lost"
