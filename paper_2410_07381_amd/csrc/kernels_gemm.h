@@ -672,6 +672,7 @@ struct GemmTileT {
 using GemmTile32 = GemmTileT<1, 1>;
 // The small GEMM's own blocks stop at their ends only, as its waves fit beside a request's.
 struct GemmSmallBody : GemmTileT<1, 1, true> {
+  static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &a) { return 128 * (uint64_t)a.k; }
   // (us with the counter alone / in teams, 2048 x 2048: k = 512, 512 x 1 57 / 34; k = 384, 256 x 1 53.6 /
   // 49.7, k = 1024 64.9 / 69.9)

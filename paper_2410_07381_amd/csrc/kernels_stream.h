@@ -113,6 +113,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 // ---- SAXPY: thread t of block b handles element 256 b + t ----------------------------
 struct SaxpyBody {
   using Args = tally_saxpy_args;
+  static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &) { return 12 * kThreads; }
   // (us with the counter alone / in teams: 512 x 8 394 / 158, 512 x 32 135 / 129; 256 x 16 60.7 /
   // 57.4, 256 x 32 164 / 176)
@@ -155,6 +156,7 @@ struct SaxpyBody {
 // ---- sum reduction: block b -> partial[b] over 4096 consecutive elements --------------
 struct ReduceSumBody {
   using Args = tally_reduce_sum_args;
+  static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &) { return 4 * PER_BLOCK; }
   // (us with the counter alone / in teams, 2^28: 512 x 4 241 / 159, 512 x 8 175 / 163; 256 x 4 247 / 205,
   // 256 x 8 179 / 183)
@@ -226,6 +228,7 @@ struct ReduceSumBody {
 
 struct ReduceFinalBody {
   using Args = tally_reduce_final_args;
+  static constexpr bool TEAMS = false;
   static uint64_t block_bytes(const Args &a) { return 4 * (uint64_t)a.count; }
   static uint32_t team_bytes(uint32_t, uint32_t) { return 0; }   // one block
   static constexpr int THREADS = kThreads;
@@ -276,6 +279,7 @@ struct ReduceFinalBody {
 // ---- GEMV: one wave per output row, 16-byte loads along K -----------------------------
 struct GemvBody {
   using Args = tally_gemv_bf16_args;
+  static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &a) { return 8 * (uint64_t)a.k; }
   // (us with the counter alone / in teams: 16384 x 4096, 512 x 1 59 / 27; 100000 x 512, 512 x 1 296 / 74)
   static uint32_t team_bytes(uint32_t workers, uint32_t) { return workers >= 512 ? 32 << 10 : 8 << 10; }
@@ -551,6 +555,7 @@ struct LayerNormOp {
 template <class Op, int MAXNV, int WAVES, bool DEEP>
 struct RowsBodyT {
   using Args = typename Op::Args;
+  static constexpr bool TEAMS = MAXNV <= 16;              // (a block of wider rows has more bytes than team_bytes)
   static uint64_t block_bytes(const Args &a) { return 32 * (uint64_t)a.cols; }
   // (us with the counter alone / in teams: softmax 60000 x 2048, 512 x 1 200 / 159, 40000 x 2700 146 / 143,
   // LayerNorm 155 / 159; 60000 x 1024, 256 x 1 184 / 145.  The rows of several blocks take a worker 3 us

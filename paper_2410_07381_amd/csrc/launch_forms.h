@@ -365,9 +365,15 @@ __device__ __forceinline__ uint32_t team_of(const PtbCtl &c) {
 __device__ __forceinline__ uint32_t team_size(const PtbCtl &c, uint32_t team) {
   return team + 1 < c.team_count ? kTeamSize : c.workers - team * kTeamSize;
 }
+// Bodies whose workers may form teams: the others' kernels have none of this in them.
+template <class Body, class = void>
+struct HasTeams : std::false_type {};
+template <class Body>
+struct HasTeams<Body, std::enable_if_t<Body::TEAMS>> : std::true_type {};
 // A worker's fetch of `add` task indices: what the counter held.
+template <bool TEAMS>
 __device__ __forceinline__ uint32_t fetch(const PtbCtl &c, uint32_t add) {
-  if (c.team_count == 0)
+  if (!TEAMS || c.team_count == 0)
     return __hip_atomic_fetch_add(c.counter, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   unsigned long long *word = &c.teams[team_of(c)].word;
   for (;;) {
@@ -450,7 +456,7 @@ __device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, cons
   // workgroup.  An index at or beyond `limit` means: grid exhausted, or a request folded
   // into the counter; either way the worker leaves, and what it fetched before is done.
   for (uint32_t it = 0;; ++it) {
-    if (threadIdx.x == 0) s_idx[it & 1] = fetch(c, c.chunk) - c.counter_base;
+    if (threadIdx.x == 0) s_idx[it & 1] = fetch<HasTeams<Body>::value>(c, c.chunk) - c.counter_base;
     __syncthreads();
     const uint32_t first = __builtin_amdgcn_readfirstlane(s_idx[it & 1]);
     if (first >= c.limit) break;  // uniform across the workgroup
@@ -489,9 +495,10 @@ __device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, cons
 // every other fetch has been performed, and it reads the counter after that.  Kernel
 // outputs become visible to the host at the end of the kernel as usual; the status
 // word only says that the workers are gone.
+template <bool TEAMS>
 __device__ __forceinline__ void ptb_leave(const PtbCtl &c) {
   if (threadIdx.x == 0) {
-    if (c.team_count) {
+    if (TEAMS && c.team_count) {
       const uint32_t team = team_of(c);
       TeamLine &t = c.teams[team];
       if (__hip_atomic_fetch_add(&t.left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != team_size(c, team)) return;
@@ -528,7 +535,7 @@ __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const 
   if constexpr (HasWhole<Body>::value) ptb_tail<Body>(args, c);
   else if constexpr (HasParts<Body>::value) ptb_parts<Body>(args, c);
   else ptb_blocks<Body>(args, c);
-  ptb_leave(c);
+  ptb_leave<HasTeams<Body>::value>(c);
 }
 template <class Body>
 __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void ptb_kernel(typename Body::Args args, PtbCtl c) {
