@@ -65,7 +65,7 @@ constexpr uint32_t kCoverPieces = 64;
 // Leaving is counted by teams too; a team's last worker puts its line back.
 //
 // Batches twice the team kept half of it waiting (SAXPY of 2^20, 256 x 1: 47 us against 30, and 54
-// without teams); teams of four: 29, but 770 where teams of eight take 400 (2^26, 2048 x 1; 3015
+// without teams); teams of four: 29, but 766 where teams of eight take 440 (2^26, 1024 x 1; 3002
 // without).  Teams of neighbours, whose fetches go to all dies as they would without teams, beat
 // those of one die by up to 9 % (LayerNorm of 300000 x 200, 512 x 1: 315 and 345 us, 866 without).
 struct alignas(128) TeamLine {
@@ -89,7 +89,6 @@ struct PtbCtl {
   unsigned long long *host_raw;     // pinned: (epoch << 32 | raw counter) at the drain
   unsigned long long *host_relay;   // pinned: (epoch << 32 | raw counter) when the relay has ended
   unsigned long long *host_gave_up; // pinned: (epoch << 32 | 1 if the relay gave up early), written with it
-  uint32_t *host_born;      // pinned: the epoch once the relay runs (null: nobody waits for that)
   CoverRec *cover;          // device, may be null
   uint32_t parts;           // the counter counts parts of a logical block (1: whole blocks)
   uint32_t limit;           // workers treat this as the end of the grid (normally all of it); in parts
@@ -211,8 +210,6 @@ constexpr unsigned long long kRelayGiveUpTicks = 2000000ull;  // 20 ms of the 10
 __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
   uint32_t last = 0u;        // the host's word is 0 while nothing is asked
   bool added = false, gave_up = false;
-  if (c.host_born != nullptr && threadIdx.x == 0)
-    __hip_atomic_store(c.host_born, c.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   // The relay is launched before its workers.  Where the two cannot run side by side
   // (kernels executed strictly one after another) the workers cannot start until the
   // relay has ended: it leaves when neither the task counter nor the exit counter has

@@ -527,8 +527,8 @@ constexpr int kMaxShunned = 64;
 constexpr int kMaxSide = 2 * 8 + 2;
 constexpr int kMaxBeClients = 8;
 constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited, 128 B apart
-constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw,born | slice_done,ended
-constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostBorn = 104, kHostEnded = 132;
+constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw | slice_done,ended
+constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostEnded = 132;
 constexpr size_t kCopySlotBytes = kFlagCopies * kFlagCopyStride * sizeof(uint32_t);
 
 enum JobKind { KIND_PTB = 0, KIND_SLICED = 1, KIND_NATIVE = 2 };
@@ -760,8 +760,7 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
 // first.  So the relays of drained segments are settled before the new workers are enqueued (the
 // new relay already is, so that its launch call and the wait overlap).  A segment whose workers
 // are still at work is not waited for: the new workers are behind them.
-int settle_relays_before(tally_ctx *ctx, hipStream_t ctl, bool *settled) {
-  *settled = false;
+int settle_relays_before(tally_ctx *ctx, hipStream_t ctl) {
   for (int s = 0; s < kSlots; ++s) {
     if (!ctx->slot_relay[s] || ctx->slot_ctl[s] != ctl) continue;
     const unsigned char *h = ctx->host_pool + s * kHostSlotBytes;
@@ -770,15 +769,8 @@ int settle_relays_before(tally_ctx *ctx, hipStream_t ctl, bool *settled) {
     if (epoch(kHostStatus) != ctx->slot_epoch[s] && epoch(kHostRaw) != ctx->slot_epoch[s]) continue;
     const int rc = settle_relay(ctx, s);
     if (rc) return rc;
-    *settled = true;
   }
   return TALLY_OK;
-}
-
-// Do `workers` of this kernel leave no room for a relay's wave on a compute unit that they fill?
-bool fills_gpu(const tally_ctx *ctx, const KernelOps *ops, uint32_t workers) {
-  const uint32_t *ft = ctx->foot_worker[ops - kOps], n = (workers + ctx->num_cus - 1) / ctx->num_cus;
-  return n * ft[1] > 31u || n * ((ft[1] + 3) / 4) * ft[2] > 480u;
 }
 
 // Parts that workers take a segment of `blocks` blocks up to block `limit` in (GemmParts).
@@ -795,9 +787,13 @@ uint32_t segment_parts(const KernelOps *ops, uint64_t blocks, uint64_t limit, ui
 // Teams that `workers` form to fetch `chunk` blocks at a time (none: they do not).  The counter
 // serves W workers once in W x 11.4 ns; teams pay where a fetch's work takes less than that, by
 // bytes per fetch as measured (team_bytes), and not below 256 workers (SAXPY of 2^22, 128 x 4: 81 us
-// with the counter alone, 93 in teams).
-uint32_t team_count(const KernelOps *ops, const void *args, uint32_t workers, uint32_t chunk) {
+// with the counter alone, 93 in teams).  Workers that fill the GPU keep the counter alone: a short job
+// of them is over before a relay that was late is on the GPU, and the next job waits for that
+// relay (100 us and more, where a scheduler's first job was of 2048 x 1).
+uint32_t team_count(const tally_ctx *ctx, const KernelOps *ops, const void *args, uint32_t workers, uint32_t chunk) {
   if (!ops->team_bytes || workers < 256) return 0u;
+  const uint32_t *ft = ctx->foot_worker[ops - kOps], per_cu = (workers + ctx->num_cus - 1) / ctx->num_cus;
+  if (per_cu * ft[1] > 31u || per_cu * ((ft[1] + 3) / 4) * ft[2] > 480u) return 0u;   // (a relay: one wave, 32 registers)
   if (ops->block_bytes(args) * chunk > ops->team_bytes(workers, chunk)) return 0u;
   const uint32_t n = workers / kTeamSize;
   return n < kMaxTeams ? n : kMaxTeams;
@@ -833,12 +829,11 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   c.host_raw = (unsigned long long *)(j->h_base_dev() + kHostRaw);
   c.host_relay = (unsigned long long *)(j->h_base_dev() + kHostRelay);
   c.host_gave_up = (unsigned long long *)(j->h_base_dev() + kHostGaveUp);
-  c.host_born = fills_gpu(ctx, j->ops, j->workers) ? (uint32_t *)(j->h_base_dev() + kHostBorn) : nullptr;
   c.cover = j->cover;
   c.parts = parts;
   c.limit = j->limit * parts;
   c.epoch = j->epoch;
-  const uint32_t teams = team_count(j->ops, j->args, j->workers, chunk);
+  const uint32_t teams = team_count(ctx, j->ops, j->args, j->workers, chunk);
   c.teams = ctx->team_pool + (size_t)slot * kMaxTeams;
   c.team_count = teams;
   c.exit_target = ctx->slot_exited[slot] + (teams ? teams : j->workers);
@@ -867,15 +862,7 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
     g_last_hip = (int)e;
     return TALLY_ERR_HIP;
   }
-  bool settled;
-  rc = settle_relays_before(ctx, j->ctl, &settled);   // (this slot's relay is not among them: settled above)
-  // A relay that was enqueued behind another one has less of a head start, and workers that fill the
-  // GPU leave it no second chance: wait until it says that it is there (2 ms at most: it may start
-  // late for other reasons, and then the request finds it late).
-  if (c.host_born && settled) {
-    const double t0 = now_us();
-    while (__atomic_load_n((uint32_t *)(j->h_base() + kHostBorn), __ATOMIC_ACQUIRE) != c.epoch && now_us() - t0 < 2000.0) {}
-  }
+  rc = settle_relays_before(ctx, j->ctl);   // (this slot's relay is not among them: settled above)
   ctx->slot_relay[slot] = true;
   ctx->slot_ctl[slot] = j->ctl;
   e = rc == TALLY_OK ? j->ops->ptb(j->be, j->args, c) : (hipError_t)g_last_hip;

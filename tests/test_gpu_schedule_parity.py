@@ -520,7 +520,7 @@ def test_error_paths(env):
 
 # ------------------------------------------------------------------ workers in teams
 @pytest.mark.parametrize("workers,chunk,blocks", [(256, 1, 256), (256, 1, 1031), (261, 1, 2000), (519, 1, 519),
-                                                  (519, 3, 5003), (1024, 2, 2048), (2047, 1, 9000), (300, 16, 4801)])
+                                                  (519, 3, 5003), (1024, 2, 2048), (1790, 1, 9000), (2047, 1, 9000), (300, 16, 4801)])
 def test_teams_of_workers_run_every_block_once(env, workers, chunk, blocks):
     """From 256 workers on short blocks fetch through their team's word, a batch at a time.  Teams of
     eight and the odd last one, grids that one fetch each covers exactly and ones that end inside a
