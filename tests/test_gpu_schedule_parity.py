@@ -556,3 +556,48 @@ def test_teams_of_workers_run_every_block_once(env, workers, chunk, blocks):
     torch.cuda.synchronize()
     # a fused multiply-add rounds once, the 64-bit sum and its conversion at most once more (2^-53 of it)
     assert ((y - want).abs() <= 2.0 ** -23 * want.abs()).all()
+
+
+# ------------------------------------------------------------------ slices decided about on the device
+@pytest.mark.parametrize("slice_blocks,in_flight", [(1, 1), (7, 1), (64, 3), (300, 2), (40, 13), (40, 14), (2000, 1)])
+def test_slices_enqueued_ahead_stop_and_go_on(env, slice_blocks, in_flight):
+    """While a sliced job is waited for, sub-kernels are enqueued beyond max_in_flight and run or
+    leave at once as the device finds the host's stop word.  Stopped again and again, from
+    launches that cover the grid at once to ones of a single block: always whole slices, a prefix,
+    every block once, and never a slice more for a job that is stopped before it is looked at again."""
+    B, ctx, torch = env
+    blocks = 1500
+    n = blocks * 256 - 77
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(slice_blocks)
+    x, y0 = (torch.randn(n, device="cuda", generator=gen) for _ in range(2))
+    y = y0.clone()
+    torch.cuda.synchronize()
+    want = (1.5 * x.double() + y0.double()).float()       # the product is exact in 64 bits: one rounding
+    job = ctx.launch_sliced(B.saxpy(x, y, 1.5), slice_blocks, max_in_flight=in_flight, coverage=True)
+    job.preempt()                                         # exactly the first max_in_flight have been enqueued
+    st = job.wait()
+    done = job.progress()[0]
+    assert done == min(slice_blocks * in_flight, blocks)
+    for round_ in range(40):
+        count = job.coverage()["count"]
+        assert (count[:done] == 1).all() and (count[done:] == 0).all()
+        if st == B.JOB_COMPLETE:
+            break
+        assert st == B.JOB_STOPPED and done % slice_blocks == 0
+        job.resume()
+        for _ in range(round_ % 4 * 8):                   # now and then let it get ahead first
+            job.pump()
+        job.preempt()
+        st, before = job.wait(), done
+        done = job.progress()[0]
+        assert done >= min(before + slice_blocks * in_flight, blocks)
+    if st != B.JOB_COMPLETE:
+        job.resume()
+        assert job.wait() == B.JOB_COMPLETE
+    rec = job.coverage()
+    job.free()
+    assert (rec["count"] == 1).all()
+    torch.cuda.synchronize()
+    # a fused multiply-add rounds once, the 64-bit sum and its conversion at most once more (2^-53 of it)
+    assert ((y - want).abs() <= 2.0 ** -23 * want.abs()).all()
