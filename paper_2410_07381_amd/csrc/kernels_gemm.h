@@ -442,19 +442,29 @@ using GemmN128Body = GemmBodyT<2>;
 //
 // NAN7FC0: a NaN leaves as 0x7FC0, which is what the ragged GEMM has always written; those with
 // blocks of 256 rows write what the hardware's conversion makes of the MFMA's NaN (0xFFC0).
-template <int RA, int RB, bool NAN7FC0 = false>
+//
+// WAVES = 1: a 16x16 tile of one wave, for outputs of so few tiles that what bounds them is how a
+// stage's instructions follow one another in a wave (a 16-byte load, LDS read or write takes 16
+// cycles to issue), not the units.  LDS serves a wave in order, so there is neither a barrier nor
+// a second buffer; fragments are read a stage ahead.  Against 32x32 tiles, us: 128 x 768 x 3072 (384
+// tiles) 7.97 / 7.40, 128 x 768 x 768 3.74 / 3.47, 64 x 960 x 320 2.92 / 2.61, 128 x 128 x 1024 4.10 / 3.67, but
+// 256 x 1024 x 1024 (1024 tiles) 4.42 / 4.95.
+template <int RA, int RB, bool NAN7FC0 = false, int WAVES = 4>
 struct GemmTileT {
   using Args = tally_gemm_bf16_args;
-  static constexpr int THREADS = 256;
+  static_assert(WAVES == 4 || (WAVES == 1 && RA == 1 && RB == 1), "2 x 2 waves, or one with a block");
+  static constexpr int THREADS = 64 * WAVES;
   static constexpr int MIN_WAVES = 4;
   static constexpr unsigned DYN_LDS = 0;
   static constexpr bool YIELDS = true;
   static constexpr bool RANGE = false;
   // a block's last barrier follows its last fragment read
   static constexpr bool END_BARRIER = false;
-  static constexpr uint32_t TM = 32 * RA, TN = 32 * RB;
-  static constexpr bool TWO = RA * RB <= 2;               // LDS holds two stages
-  static constexpr int AHEAD = RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
+  static constexpr bool LONE = WAVES == 1;
+  static constexpr uint32_t TM = LONE ? 16 : 32 * RA, TN = LONE ? 16 : 32 * RB;
+  static constexpr int LA = TM / (8 * WAVES), LB = TN / (8 * WAVES);   // loads of a wave and stage
+  static constexpr bool TWO = !LONE && RA * RB <= 2;      // LDS holds two stages
+  static constexpr int AHEAD = LONE ? 4 : RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
   static constexpr int ROUND = TWO ? AHEAD : 16 / (RA * RB);   // stages between two looks at the pause word, at least
   static constexpr uint32_t SA = TM * 128, STAGE = (TM + TN) * 128;   // bytes of A, of both in a stage
   // share of a tile between asking for the pause word and pausing on the answer to the next
@@ -487,7 +497,7 @@ struct GemmTileT {
     asm volatile("" : "+v"(tid));   // (a worker keeps no addresses across its tiles)
     const uint32_t lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t wm = wave >> 1, wn = wave & 1;
+    const uint32_t wm = LONE ? 0u : wave >> 1, wn = LONE ? 0u : wave & 1;
     const uint32_t K = a.k;
     const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
     const uint32_t ns = (K + 63) / 64;
@@ -499,39 +509,39 @@ struct GemmTileT {
     const uint32_t r8 = lane >> 3, p8 = lane & 7;
     const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TM * LDA, 0x7fffffffu);
     const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TN * LDB, 0x7fffffffu);
-    uint32_t vA[RA], vB[RB];
+    uint32_t vA[LA], vB[LB];
 #pragma unroll
-    for (int j = 0; j < RA; ++j) {
-      const uint32_t r = (wave * RA + j) * 8 + r8;
+    for (int j = 0; j < LA; ++j) {
+      const uint32_t r = (wave * LA + j) * 8 + r8;
       vA[j] = by * TM + r < a.m ? (r * LDA + p8 * 8) * 2 : OOB;
     }
 #pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      const uint32_t r = (wave * RB + j) * 8 + r8;
+    for (int j = 0; j < LB; ++j) {
+      const uint32_t r = (wave * LB + j) * 8 + r8;
       vB[j] = bx * TN + r < a.n ? (r * LDB + p8 * 8) * 2 : OOB;
     }
     const uint32_t half = (K & 32) && (p8 & 4) ? OOB : 0u;
-    struct Set { uint4 a[RA], b[RB]; };
+    struct Set { uint4 a[LA], b[LB]; };
     auto request = [&](Set &s, uint32_t c) {
       const uint32_t none = (c >= ns ? OOB : 0u) | (c + 1 == ns ? half : 0u);
       const uint32_t so = __builtin_amdgcn_readfirstlane(c >= ns ? 0u : c * 128);
 #pragma unroll
-      for (int j = 0; j < RA; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
+      for (int j = 0; j < LA; ++j) s.a[j] = buf_ld16(rA, vA[j] | none, so);
 #pragma unroll
-      for (int j = 0; j < RB; ++j) s.b[j] = buf_ld16(rB, vB[j] | none, so);
+      for (int j = 0; j < LB; ++j) s.b[j] = buf_ld16(rB, vB[j] | none, so);
     };
     // piece p of row r lies at slot p xor ((r/2)%8): the 16 lanes that a 128-bit access serves
     // together fall into 16 different 16-byte bank groups, writing and reading
     const uint32_t w_off = r8 * 128 + (p8 ^ (r8 >> 1)) * 16;               // slot xor 4 in odd groups of 8 rows
     auto store = [&](const Set &s, uint32_t buf) {
 #pragma unroll
-      for (int j = 0; j < RA; ++j) {
-        const uint32_t g = wave * RA + j;
+      for (int j = 0; j < LA; ++j) {
+        const uint32_t g = wave * LA + j;
         *reinterpret_cast<uint4 *>(s_ab + buf * STAGE + g * 1024 + (w_off ^ ((g & 1) * 64))) = s.a[j];
       }
 #pragma unroll
-      for (int j = 0; j < RB; ++j) {
-        const uint32_t g = wave * RB + j;
+      for (int j = 0; j < LB; ++j) {
+        const uint32_t g = wave * LB + j;
         *reinterpret_cast<uint4 *>(s_ab + buf * STAGE + SA + g * 1024 + (w_off ^ ((g & 1) * 64))) = s.b[j];
       }
     };
@@ -552,10 +562,23 @@ struct GemmTileT {
       request(s[d], d);
       __builtin_amdgcn_sched_barrier(0);                  // (in the order in which they are waited for)
     }
-    if constexpr (TWO) {
+    if constexpr (TWO || LONE) {
       store(s[0], 0);
       request(s[0], SETS);
-      __syncthreads();
+    }
+    if constexpr (TWO) __syncthreads();
+    // (one wave: fragments of the stage at hand and of the next one)
+    bf16x8_t ga[2][2], gb[2][2];
+    auto read_ahead = [&](int f) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        gb[f][kk] = read(0, fB, kk, 0);
+        ga[f][kk] = read(0, fA, kk, 0);
+      }
+    };
+    if constexpr (LONE) {
+      read_ahead(0);
+      __builtin_amdgcn_sched_barrier(0);
     }
     // Looks at the pause word.  Waiting for one costs the workgroup 0.7 us, several of its stages:
     // one lane asks for the word at the start of a round of STEPS stages, behind the loads on their
@@ -574,6 +597,18 @@ struct GemmTileT {
     };
     // stage c, whose operands (with two buffers those of stage c + 1) are in set d
     auto step = [&](int d, uint32_t c) {
+      if constexpr (LONE) {
+        static_assert(SETS % 2 == 0, "the fragments are those of the set");
+        const int next = (d + 1) % SETS, f = d & 1;
+        store(s[next], 0);
+        request(s[next], c + 1 + SETS);
+        read_ahead(f ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gb[f][kk], ga[f][kk], acc[0][0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        return;
+      }
       bf16x8_t fa[2][RA], fb[2][RB];
       if constexpr (TWO) {
         static_assert(SETS % 2 == 0, "the buffer is that of the set");

@@ -49,7 +49,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // ---------------------------------------------------------------------------- registry
 typedef hipError_t (*FootprintFn)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
-constexpr uint32_t kMaxNative = 6;   // kernels that one operator's original form chooses from
+constexpr uint32_t kMaxNative = 7;   // kernels that one operator's original form chooses from
 
 struct KernelOps {
   const char *name;
@@ -232,9 +232,12 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 //   4096 x 4096   192 /  135 / 98.0 / 83.3 / 58.0 / 51.9   (256 of 256x256)
 // and the same order from k = 512 to 8192.  Below k = 128 there is no loop to speak of and the
 // large tiles' long prologue and epilogue lose to 128x64 (4352 x 4864 x 64: 15.4 against 13.3),
-// unless the output is one that GemmBodyT writes past the caches.
-enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256 };
+// unless the output is one that GemmBodyT writes past the caches.  16x16 tiles of a single wave pay up
+// to three for two compute units and from the third stage on (see GemmTileT; k = 64 x 768 tiles 2.52
+// against 2.38, 100 x 200 x 96 2.31 both).
+enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, k16 };
 GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
+  if (a.k > 128 && (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch <= 384) return GemmCover::k16;
   const uint64_t t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
   if ((uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32;
   if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32x64;
@@ -253,6 +256,7 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
   switch (gemm_cover(a)) {
+    case GemmCover::k16: return launch_gemm_cover<GemmTileT<1, 1, false, 1>>(s, a, 16, 16, urgent);
     case GemmCover::k32: return launch_gemm_cover<GemmTile32>(s, a, 32, 32, urgent);
     case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
     case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
@@ -266,13 +270,14 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
 // 29 us with 64x64 and 32; 1024 x 4096 x 4096, 512, 54 and 47).
 GemmCover gemm_cover_small(const tally_gemm_bf16_args &a) {
   const GemmCover c = gemm_cover(a);
-  if (c == GemmCover::k32 || c == GemmCover::k32x64) return c;
+  if (c == GemmCover::k16 || c == GemmCover::k32 || c == GemmCover::k32x64) return c;
   return (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512 ? GemmCover::k128x64 : GemmCover::k64;
 }
 hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t urgent) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
   switch (gemm_cover_small(a)) {
+    case GemmCover::k16: return launch_gemm_cover<GemmTileT<1, 1, true, 1>>(s, a, 16, 16, urgent);
     case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
     case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2, true>>(s, a, 64, 32, urgent);
     case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2, true>>(s, a, 64, 64, urgent);
@@ -281,9 +286,9 @@ hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3,
 }
 // which of the kernels in kOps (in the order of GemmCover) and how many workgroups of it
 uint32_t gemm_choice(const tally_gemm_bf16_args &a, GemmCover c, uint32_t tn, uint64_t *groups) {
-  static const uint32_t tile[][2] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}, {256, 128}};
+  const uint32_t tile[][2] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}, {256, 128}, {256, tn}, {16, 16}};
   const uint32_t i = (uint32_t)c;
-  *groups = (uint64_t)cdiv(a.m, i < 5 ? tile[i][0] : 256) * cdiv(a.n, i < 5 ? tile[i][1] : tn) * a.batch;
+  *groups = (uint64_t)cdiv(a.m, tile[i][0]) * cdiv(a.n, tile[i][1]) * a.batch;
   return i;
 }
 template <uint32_t TN>
@@ -498,7 +503,8 @@ uint64_t block_bytes(const void *args) {
 #define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
-   footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>}, \
+   footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
+                       footprint_native_t<GemmTileT<1, 1, false, 1>>},                                    \
    gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
@@ -516,7 +522,8 @@ const KernelOps kOps[TALLY_K_COUNT] = {
      nullptr, nullptr, nullptr, nullptr},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
-     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true)}, gemm_small_native_choice,
+     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, footprint_native_t<GemmTileT<1, 1, true, 1>>},
+     gemm_small_native_choice,
      gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes},
     OPS_GEMM(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128, GemmCover::k256x128),
 };

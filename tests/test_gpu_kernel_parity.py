@@ -464,6 +464,45 @@ def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
     assert (host(buf[batch * m * n:]) == 0x7FC0).all()
 
 
+@pytest.mark.parametrize("k", [160, 192, 224, 544, 1056])
+@pytest.mark.parametrize("m,n,batch", [(1, 1, 1), (17, 33, 3), (70, 130, 8), (128, 768, 1), (100, 880, 1), (15, 16, 384), (256, 256, 1)])
+def test_gemm_one_wave_tiles(env, m, n, k, batch):
+    """Up to 384 tiles of 16x16, the original form takes tiles of a single wave from the third stage
+    on: rows and columns past the matrix, three to seventeen stages, a last stage half full, NaN beyond K
+    and between the rows, nothing written behind C; the same bits as one worker's 32x32 blocks."""
+    B, ctx, torch = env
+    from gpu_util import dev, host, assert_bf16_close
+    g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
+    a = dict(g, C=np.zeros((batch, m, n), np.uint16))
+    OS.run_native("gemm_bf16_small", OK.grid_of("gemm_bf16_small", a), a)
+    Ap = torch.full((batch, m + 1, k + 40), 0x7FC0, dtype=torch.int16, device="cuda")
+    Bp = torch.full((batch, n + 1, k + 8), 0x7FC0, dtype=torch.int16, device="cuda")
+    Ap[:, :m, :k], Bp[:, :n, :k] = dev(g["A"]), dev(g["Bt"])
+    buf = torch.full((batch * m * n + 8,), 0x7FC0, dtype=torch.int16, device="cuda")
+    Cd = buf[:batch * m * n].view(batch, m, n)
+    kern = B.gemm_bf16(Ap[:, :m, :k], Bp[:, :n, :k], Cd, small=True)
+    torch.cuda.synchronize()
+    job = ctx.launch_ptb(kern, 1)
+    assert job.wait() == B.JOB_COMPLETE
+    job.free()
+    torch.cuda.synchronize()
+    one_worker = Cd.clone()
+    Cd.fill_(0x7FC0)
+    torch.cuda.synchronize()
+    ctx.launch_native(kern, hi=True)
+    torch.cuda.synchronize()
+    assert torch.equal(Cd, one_worker)
+    assert_bf16_close(host(Cd), a["C"])
+    assert (host(buf[batch * m * n:]) == 0x7FC0).all()
+    if m % 256 == 0:
+        C2 = torch.full((batch, m, n), 0x7FC0, dtype=torch.int16, device="cuda")
+        A2, B2 = Ap[:, :m, :k].contiguous(), Bp[:, :n, :k].contiguous()
+        torch.cuda.synchronize()
+        ctx.launch_native(B.gemm_bf16(A2, B2, C2))
+        torch.cuda.synchronize()
+        assert torch.equal(C2, one_worker)
+
+
 @pytest.mark.parametrize("tile,m,n,k,batch", [
     ("256", 256, 256, 96, 1), ("256", 512, 512, 1056, 1), ("256", 512, 768, 288, 1), ("256", 1024, 1024, 544, 1),
     ("256", 1024, 2048, 2080, 1), ("256", 2048, 2048, 64, 1), ("256", 4352, 4864, 96, 1), ("256", 1280, 1280, 2048, 1),
