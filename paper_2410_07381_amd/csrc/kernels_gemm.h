@@ -576,7 +576,10 @@ struct GemmTileT {
         ga[f][kk] = read(0, fA, kk, 0);
       }
     };
+    // (costs nothing: lanes of the wave write what others read, which only the hardware knows)
+    auto share = []() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
     if constexpr (LONE) {
+      share();
       read_ahead(0);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -600,7 +603,9 @@ struct GemmTileT {
       if constexpr (LONE) {
         static_assert(SETS % 2 == 0, "the fragments are those of the set");
         const int next = (d + 1) % SETS, f = d & 1;
+        share();
         store(s[next], 0);
+        share();
         request(s[next], c + 1 + SETS);
         read_ahead(f ^ 1);
         __builtin_amdgcn_sched_barrier(0);
