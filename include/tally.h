@@ -179,9 +179,9 @@ int tally_launch_attn_decode_static(tally_ctx *ctx, const tally_attn_decode_args
  * of slice_blocks consecutive logical blocks (last one: the remainder); each sub-kernel
  * receives a block offset and rebuilds its logical block index as offset + blockIdx.
  * At most max_in_flight (>= 1; 1 = "one at a time", Section 4.2) sub-kernels run after a stop
- * is asked for; this call issues the first ones, tally_pump() the following, of which it enqueues
- * two more ahead of time: when the sub-kernel max_in_flight before one of those ends, the device
- * finds whether a stop stands, and one that is not to run any more leaves at once.
+ * is asked for; this call issues the first ones, tally_pump() the following.  Of sub-kernels that fill
+ * the GPU twice it enqueues one more ahead of time: when the sub-kernel max_in_flight before that
+ * one ends, the device finds whether a stop stands, and if so it leaves at once.
  * coverage != 0 allocates per-block coverage records. */
 int tally_launch_sliced(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t slice_blocks,
                         uint32_t max_in_flight, int coverage, tally_job **out);

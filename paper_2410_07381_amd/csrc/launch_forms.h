@@ -122,7 +122,7 @@ struct SliceCtl {
   const uint32_t *go;       // device: nonzero if this one is to run (null: it is)
   uint32_t *next_go;        // device: the same for the one that this one decides about (null: none)
   const uint32_t *stop;     // pinned host: nonzero once the job is asked to stop
-  uint32_t *ran;            // device: sub-kernels of the job that have run, this one included
+  uint32_t *ran;            // device: sub-kernels of the job that have run, this one included (null: markers say)
   uint32_t *host_done;      // pinned: sub-kernels that have ended
 };
 
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void native_kernel(
 template <class Body>
 __device__ __forceinline__ void sliced_body(const typename Body::Args &args, const SliceCtl &ctl) {
   const bool run = ctl.go == nullptr || __builtin_amdgcn_readfirstlane(*ctl.go) != 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && run) {
+  if (ctl.ran != nullptr && blockIdx.x == 0 && threadIdx.x == 0 && run) {
     __hip_atomic_store(ctl.host_done, ctl.index, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     *ctl.ran = ctl.index + 1;
   }

@@ -537,7 +537,7 @@ constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited | slices: ran,
 constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw,report | slice_done,ended
 constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostReport = 112, kHostEnded = 132;
 constexpr size_t kDevRan = 384, kDevGo = 448;
-constexpr uint32_t kGoWords = 16, kSlicesAhead = 2;   // sub-kernels enqueued behind those that a stop leaves running
+constexpr uint32_t kGoWords = 16, kSlicesAhead = 1;   // sub-kernels enqueued behind those that a stop leaves running
 
 constexpr size_t kCopySlotBytes = kFlagCopies * kFlagCopyStride * sizeof(uint32_t);
 
@@ -903,17 +903,27 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   return TALLY_OK;
 }
 
-// Enqueue sub-kernels: `ahead` beyond the max_in_flight that are to run whatever is asked meanwhile
-// (those are decided about on the device when the ones before them end, see sliced_body), and the
-// report behind the last one.
+// Whether sub-kernels are enqueued ahead and decided about on the device (see sliced_body): those that
+// fill the GPU twice, one at a time (1 GiB sum, 4096 x 1: 202 us, the drain 12.8 us; two ahead 196 and 15.0,
+// none 299 and 9.8), as a stop waits 2.3 us for each one that has to come and go.  Of small ones that is
+// half of the drain (64 x 1: two ahead 10.0 us, none 5.4).  They were faster for it, 10.4 -> 4.7 ms, but
+// remain a form that nobody wants: with a bound that no candidate meets, LayerNorm of 4096 blocks was given
+// 256 slices as what has the shortest turnaround, 1800 us instead of 110 as workers.  (Many in flight keep
+// the stream busy as it is, and there are not as many words.)
+bool slices_lead(const tally_job *j) {
+  return j->max_in_flight + kSlicesAhead < kGoWords &&
+         (j->slice_blocks < j->total ? j->slice_blocks : j->total) >= 2u * j->ctx->num_cus;
+}
+
+// Enqueue sub-kernels: max_in_flight that are to run whatever is asked meanwhile, each with a marker
+// behind it, or `ahead` more than that and one report behind the last.
 int sliced_issue(tally_job *j, uint32_t ahead) {
   const uint32_t slices = cdiv(j->total, j->slice_blocks), d = j->max_in_flight;
   unsigned char *dev = j->ctx->dev_pool + j->slot * kDevSlotBytes;
   uint32_t *go = (uint32_t *)(dev + kDevGo);
   const bool stop = j->stop_issuing.load();
-  // (so many in flight keep the stream busy as it is, and there are not as many words)
-  const bool decided = d + kSlicesAhead < kGoWords;
-  while (!stop && j->issued < slices && j->issued - j->retired < (uint64_t)d + (decided ? ahead : 0u)) {
+  const bool lead = slices_lead(j);
+  while (!stop && j->issued < slices && j->issued - j->retired < (uint64_t)d + (lead ? ahead : 0u)) {
     SliceCtl c;
     c.cover = j->cover;
     c.index = j->issued;
@@ -921,16 +931,20 @@ int sliced_issue(tally_job *j, uint32_t ahead) {
     c.gx = j->grid.x;
     c.gy = j->grid.y;
     c.segment = j->segment;
-    c.go = !decided || j->issued - j->first_slice < d ? nullptr : go + j->issued % kGoWords;
-    c.next_go = decided && slices - j->issued > d ? go + (j->issued + d) % kGoWords : nullptr;
+    c.go = !lead || j->issued - j->first_slice < d ? nullptr : go + j->issued % kGoWords;
+    c.next_go = lead && slices - j->issued > d ? go + (j->issued + d) % kGoWords : nullptr;
     c.stop = (const uint32_t *)j->h_base_dev();
-    c.ran = (uint32_t *)(dev + kDevRan);
+    c.ran = lead ? (uint32_t *)(dev + kDevRan) : nullptr;
     c.host_done = (uint32_t *)(j->h_base_dev() + 128);
     const uint32_t left = j->total - c.offset;
     HIPCHK(j->ops->sliced(j->be, j->args, left < j->slice_blocks ? left : j->slice_blocks, c));
     j->issued += 1;
+    if (!lead) {
+      hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, j->be, c.host_done, j->issued);
+      HIPCHK(hipGetLastError());
+    }
   }
-  if (!j->reporting && (stop || j->issued == slices)) {
+  if (lead && !j->reporting && (stop || j->issued == slices)) {
     hipLaunchKernelGGL(slice_report_kernel, dim3(1), dim3(64), 0, j->be, (const uint32_t *)(dev + kDevRan),
                        (unsigned long long *)(j->h_base_dev() + kHostReport), j->report_seq + 1);
     HIPCHK(hipGetLastError());
@@ -966,9 +980,10 @@ void refresh(tally_job *j) {
       return;
     }
     const unsigned long long report = __atomic_load_n(j->h_report(), __ATOMIC_ACQUIRE);
-    const bool ended = j->reporting && (uint32_t)(report >> 32) == j->report_seq;
+    bool ended = j->reporting && (uint32_t)(report >> 32) == j->report_seq;
     if (ended) done = (uint32_t)report;
     if (done > j->retired) j->retired = done;
+    if (!slices_lead(j)) ended = j->retired == j->issued && (j->stop_issuing.load() || (uint64_t)done * j->slice_blocks >= j->total);
     uint64_t p = (uint64_t)j->retired * j->slice_blocks;
     if (p > j->total) p = j->total;
     j->progress = (uint32_t)p;
@@ -1430,7 +1445,7 @@ int tally_pump(tally_job *job) {
 
 int tally_wait(tally_job *job, int *state) {
   if (!job) return TALLY_ERR_INVALID_ARG;
-  const uint32_t reports = job->report_seq;
+  const uint32_t reports = job->report_seq, issued = job->issued;
   uint32_t seq = 0;
   bool marked = false;
   if (job->kind == KIND_PTB) {
@@ -1452,7 +1467,8 @@ int tally_wait(tally_job *job, int *state) {
   }
   // Everything on the best-effort stream before this call has to have ended, not only the
   // workers' last instruction.  A marker behind it says so 5 us sooner than the runtime's own
-  // wait, which enqueues one only now; a report enqueued by this call is one already.
+  // wait, which enqueues one only now; a report enqueued by this call is one already, and so is
+  // the marker of a sub-kernel.
   if (marked) {
     for (uint32_t spins = 1; (int32_t)(__atomic_load_n(job->h_ended(), __ATOMIC_ACQUIRE) - seq) < 0; ++spins) {
       if ((spins & 0xFFFFu) == 0) {
@@ -1461,7 +1477,7 @@ int tally_wait(tally_job *job, int *state) {
         if (q != hipErrorNotReady) { g_last_hip = (int)q; return TALLY_ERR_HIP; }
       }
     }
-  } else if (job->kind != KIND_SLICED || job->report_seq == reports) {
+  } else if (job->kind != KIND_SLICED || (slices_lead(job) ? job->report_seq == reports : job->issued == issued)) {
     HIPCHK(hipStreamSynchronize(job->be));
   }
   if (state) *state = job->state.load();

@@ -559,7 +559,8 @@ def test_teams_of_workers_run_every_block_once(env, workers, chunk, blocks):
 
 
 # ------------------------------------------------------------------ slices decided about on the device
-@pytest.mark.parametrize("slice_blocks,in_flight", [(1, 1), (7, 1), (64, 3), (300, 2), (40, 13), (40, 14), (2000, 1)])
+@pytest.mark.parametrize("slice_blocks,in_flight", [(1, 1), (7, 1), (64, 3), (300, 2), (40, 13), (40, 14), (2000, 1),
+                                                    (511, 1), (512, 1), (512, 2), (700, 1)])
 def test_slices_enqueued_ahead_stop_and_go_on(env, slice_blocks, in_flight):
     """While a sliced job is waited for, sub-kernels are enqueued beyond max_in_flight and run or
     leave at once as the device finds the host's stop word.  Stopped again and again, from
