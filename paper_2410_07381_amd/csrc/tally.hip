@@ -1488,7 +1488,8 @@ int tally_job_free(tally_job *job) {
   if (!job) return TALLY_ERR_INVALID_ARG;
   tally_ctx *ctx = job->ctx;
   if (job->state.load() == TALLY_JOB_RUNNING) {
-    job->stop_slices();
+    // (workers run what is left of the grid: in their slot the stop word would be a request)
+    if (job->kind == KIND_SLICED) job->stop_slices();
     (void)hipStreamSynchronize(job->be);
   }
   if (job->cover) {

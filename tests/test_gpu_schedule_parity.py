@@ -518,6 +518,43 @@ def test_error_paths(env):
     torch.cuda.synchronize()
 
 
+# ------------------------------------------------------------------ freeing a running job
+@pytest.mark.parametrize("form,workers", [("gemm", 16), ("saxpy", 64), ("saxpy", 512), ("sliced", 0)])
+def test_freeing_a_running_job_finishes_what_was_launched(env, form, workers):
+    """tally_job_free waits for the launches in flight: workers run their whole grid whether or not
+    their slot was used before (here the first job of a context), and nobody is asked to pause; a
+    sliced job runs the sub-kernels enqueued so far and no others."""
+    B, _, torch = env
+    ctx = B.Context(torch.cuda.Stream(), torch.cuda.Stream())
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(workers)
+    if form == "gemm":
+        A, Bt = (torch.randn(1, r, 2048, device="cuda", generator=gen).to(torch.bfloat16) for r in (2048, 1024))
+        out = torch.empty(1, 2048, 1024, dtype=torch.bfloat16, device="cuda")
+        kern = B.gemm_bf16(A, Bt, out)
+        torch.cuda.synchronize()
+        ctx.launch_native(kern)
+        torch.cuda.synchronize()
+        want = out.clone()
+        out.fill_(-3.0)
+    else:
+        x = torch.randn(1 << 25, device="cuda", generator=gen)
+        out = torch.zeros(1 << 25, device="cuda")
+        kern = B.saxpy(x, out, 1.5)
+        want = 1.5 * x                                    # (added to zero: exactly the rounded product)
+    torch.cuda.synchronize()
+    if form == "sliced":
+        job = ctx.launch_sliced(kern, 8192, max_in_flight=2)
+        want[2 * 8192 * 256:] = 0.0
+    else:
+        job = ctx.launch_ptb(kern, workers)
+    assert job.progress()[2] == B.JOB_RUNNING
+    job.free()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    ctx.close()
+
+
 # ------------------------------------------------------------------ workers in teams
 @pytest.mark.parametrize("workers,chunk,blocks", [(256, 1, 256), (256, 1, 1031), (261, 1, 2000), (519, 1, 519),
                                                   (519, 3, 5003), (1024, 2, 2048), (1790, 1, 9000), (2047, 1, 9000), (300, 16, 4801)])
