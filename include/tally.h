@@ -178,10 +178,8 @@ int tally_launch_attn_decode_static(tally_ctx *ctx, const tally_attn_decode_args
 /* Sliced form (Section 4.1, slicing transformation): the grid is cut into sub-kernels
  * of slice_blocks consecutive logical blocks (last one: the remainder); each sub-kernel
  * receives a block offset and rebuilds its logical block index as offset + blockIdx.
- * At most max_in_flight (>= 1; 1 = "one at a time", Section 4.2) sub-kernels run after a stop
- * is asked for; this call issues the first ones, tally_pump() the following.  Of sub-kernels that fill
- * the GPU twice it enqueues one more ahead of time: when the sub-kernel max_in_flight before that
- * one ends, the device finds whether a stop stands, and if so it leaves at once.
+ * At most max_in_flight (>= 1; 1 = "one at a time", Section 4.2) sub-kernels are
+ * enqueued; this call issues the first ones, tally_pump() the following.
  * coverage != 0 allocates per-block coverage records. */
 int tally_launch_sliced(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t slice_blocks,
                         uint32_t max_in_flight, int coverage, tally_job **out);

@@ -118,12 +118,6 @@ struct SliceCtl {
   uint32_t offset;          // first logical block of this sub-kernel
   uint32_t gx, gy;
   uint32_t segment;
-  uint32_t index;           // sub-kernels of the job before this one
-  const uint32_t *go;       // device: nonzero if this one is to run (null: it is)
-  uint32_t *next_go;        // device: the same for the one that this one decides about (null: none)
-  const uint32_t *stop;     // pinned host: nonzero once the job is asked to stop
-  uint32_t *ran;            // device: sub-kernels of the job that have run, this one included (null: markers say)
-  uint32_t *host_done;      // pinned: sub-kernels that have ended
 };
 
 __device__ __forceinline__ void delinearize(uint32_t idx, uint32_t gx, uint32_t gy, uint32_t &bx,
@@ -156,12 +150,6 @@ __device__ __forceinline__ void record_part(CoverRec *cover, uint32_t idx, uint3
   }
 }
 
-__device__ __forceinline__ uint32_t scalar_load_coherent(const uint32_t *p) {
-  uint32_t v;
-  asm volatile("s_load_dword %0, %1, 0x0 glc\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p) : "memory");
-  return v;
-}
-
 // ---- original form -------------------------------------------------------------------
 // `urgent` marks a launch on the high-priority stream: its waves raise their own issue
 // priority so that, where they share a SIMD with a best-effort wave that is still
@@ -176,32 +164,12 @@ __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void native_kernel(
 
 
 // ---- sliced form: logical block = offset + blockIdx (Section 4.1, slicing) -----------
-// Sub-kernels follow one another without the host between them: one that would be launched only
-// when the one `max_in_flight` before it has ended is enqueued ahead and decided about on the
-// device.  A workgroup near the end of the earlier one reads the host's stop word and leaves the
-// answer in a device word; where it is no, the later one's workgroups leave at once, and so on.  (A marker
-// after every slice, the host's look at it and a launch call were 6 us between slices of 12:
-// 16 slices of a 1 GiB sum, one at a time, 291 -> 200 us.)  That a sub-kernel runs says that all before
-// it have ended, which is what the first workgroup reports.
 template <class Body>
 __device__ __forceinline__ void sliced_body(const typename Body::Args &args, const SliceCtl &ctl) {
-  const bool run = ctl.go == nullptr || __builtin_amdgcn_readfirstlane(*ctl.go) != 0u;
-  if (ctl.ran != nullptr && blockIdx.x == 0 && threadIdx.x == 0 && run) {
-    __hip_atomic_store(ctl.host_done, ctl.index, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    *ctl.ran = ctl.index + 1;
-  }
-  if (run) {
-    uint32_t idx = ctl.offset + blockIdx.x, bx, by, bz;
-    delinearize(idx, ctl.gx, ctl.gy, bx, by, bz);
-    Body::run_be(args, bx, by, bz);
-    record(ctl.cover, idx, bx, by, bz, ctl.segment, blockIdx.x);
-  }
-  // (two workgroups per compute unit before the last one: the host's word is 2 us away)
-  const uint32_t back = gridDim.x / 2 < 512u ? gridDim.x / 2 : 512u;
-  if (ctl.next_go != nullptr && blockIdx.x == gridDim.x - 1 - back && threadIdx.x < 64) {
-    const uint32_t stop = run ? scalar_load_coherent(ctl.stop) : 1u;
-    if (threadIdx.x == 0) *ctl.next_go = stop ? 0u : 1u;
-  }
+  uint32_t idx = ctl.offset + blockIdx.x, bx, by, bz;
+  delinearize(idx, ctl.gx, ctl.gy, bx, by, bz);
+  Body::run_be(args, bx, by, bz);
+  record(ctl.cover, idx, bx, by, bz, ctl.segment, blockIdx.x);
 }
 template <class Body>
 __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void sliced_kernel(typename Body::Args args,
@@ -231,6 +199,12 @@ __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void sliced_kernel(
 // waits a microsecond on PCIe sits in the compute unit's vector-memory return queue in
 // front of the loads of whatever worker shares that unit (measured: that worker's GEMM
 // tile ran 20 % longer, and with it the whole kernel); the scalar path is separate.
+__device__ __forceinline__ uint32_t scalar_load_coherent(const uint32_t *p) {
+  uint32_t v;
+  asm volatile("s_load_dword %0, %1, 0x0 glc\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p) : "memory");
+  return v;
+}
+
 constexpr unsigned long long kRelayGiveUpTicks = 2000000ull;  // 20 ms of the 100 MHz clock
 
 __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
@@ -563,12 +537,6 @@ __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const 
 template <class Body>
 __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void ptb_kernel(typename Body::Args args, PtbCtl c) {
   ptb_body<Body>(args, c);
-}
-
-// How many sub-kernels of a sliced job have run, once none is left on the stream.
-__global__ void slice_report_kernel(const uint32_t *ran, unsigned long long *report, uint32_t seq) {
-  if (threadIdx.x == 0)
-    __hip_atomic_store(report, (unsigned long long)seq << 32 | *ran, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Marker: stores a value into a pinned host word once earlier work on the stream is done.

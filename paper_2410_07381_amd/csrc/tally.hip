@@ -533,12 +533,9 @@ constexpr int kSlots = 64;
 constexpr int kMaxShunned = 64;
 constexpr int kMaxSide = 2 * 8 + 2;
 constexpr int kMaxBeClients = 8;
-constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited | slices: ran, go words; 128 B apart
-constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw,report | slice_done,ended
-constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostReport = 112, kHostEnded = 132;
-constexpr size_t kDevRan = 384, kDevGo = 448;
-constexpr uint32_t kGoWords = 16, kSlicesAhead = 1;   // sub-kernels enqueued behind those that a stop leaves running
-
+constexpr size_t kDevSlotBytes = 512;   // counter | pre | exited, 128 B apart
+constexpr size_t kHostSlotBytes = 256;  // host_flag | status,live,relay,gave_up,raw | slice_done,ended
+constexpr size_t kHostStatus = 64, kHostRelay = 80, kHostGaveUp = 88, kHostRaw = 96, kHostEnded = 132;
 constexpr size_t kCopySlotBytes = kFlagCopies * kFlagCopyStride * sizeof(uint32_t);
 
 enum JobKind { KIND_PTB = 0, KIND_SLICED = 1, KIND_NATIVE = 2 };
@@ -639,10 +636,7 @@ struct tally_job {
   bool failed;               // the device could not report the progress of a preempted segment
   std::atomic<uint32_t> request_word;  // what was last stored in the host's request word
   // sliced
-  // (issued: sub-kernels enqueued, retired: known to have ended, first_slice: where the segment began)
-  uint32_t slice_blocks, max_in_flight, issued, retired, segment, first_slice;
-  uint32_t report_seq;         // numbers the reports that a segment of sub-kernels ends with
-  bool reporting;              // one is on its way
+  uint32_t slice_blocks, max_in_flight, next_off, issued, retired, segment;
   std::atomic<bool> stop_issuing;
   // preemption latency
   std::atomic<double> t_preempt;
@@ -657,11 +651,6 @@ struct tally_job {
   unsigned long long *h_status() { return (unsigned long long *)(h_base() + kHostStatus); }
   uint32_t *h_live() { return (uint32_t *)(h_base() + 72); }
   uint32_t *h_ended() { return (uint32_t *)(h_base() + kHostEnded); }
-  unsigned long long *h_report() { return (unsigned long long *)(h_base() + kHostReport); }
-  void stop_slices() {
-    stop_issuing = true;
-    __atomic_store_n(h_flag(), 1u, __ATOMIC_RELEASE);
-  }
   uint32_t *h_slice_done() { return (uint32_t *)(h_base() + 128); }
 };
 
@@ -748,8 +737,7 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
   j->limit = j->total;
   j->failed = false;
   j->request_word = 0;
-  j->slice_blocks = j->max_in_flight = j->issued = j->retired = j->segment = j->first_slice = j->report_seq = 0;
-  j->reporting = false;
+  j->slice_blocks = j->max_in_flight = j->next_off = j->issued = j->retired = j->segment = 0;
   j->stop_issuing = false;
   j->t_preempt = 0.0;
   j->preempt_latency_us = -1.0;
@@ -903,53 +891,23 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   return TALLY_OK;
 }
 
-// Whether sub-kernels are enqueued ahead and decided about on the device (see sliced_body): those that
-// fill the GPU twice, one at a time (1 GiB sum, 4096 x 1: 202 us, the drain 12.8 us; two ahead 196 and 15.0,
-// none 299 and 9.8), as a stop waits 2.3 us for each one that has to come and go.  Of small ones that is
-// half of the drain (64 x 1: two ahead 10.0 us, none 5.4).  They were faster for it, 10.4 -> 4.7 ms, but
-// remain a form that nobody wants: with a bound that no candidate meets, LayerNorm of 4096 blocks was given
-// 256 slices as what has the shortest turnaround, 1800 us instead of 110 as workers.  (Many in flight keep
-// the stream busy as it is, and there are not as many words.)
-bool slices_lead(const tally_job *j) {
-  return j->max_in_flight + kSlicesAhead < kGoWords &&
-         (j->slice_blocks < j->total ? j->slice_blocks : j->total) >= 2u * j->ctx->num_cus;
-}
-
-// Enqueue sub-kernels: max_in_flight that are to run whatever is asked meanwhile, each with a marker
-// behind it, or `ahead` more than that and one report behind the last.
-int sliced_issue(tally_job *j, uint32_t ahead) {
-  const uint32_t slices = cdiv(j->total, j->slice_blocks), d = j->max_in_flight;
-  unsigned char *dev = j->ctx->dev_pool + j->slot * kDevSlotBytes;
-  uint32_t *go = (uint32_t *)(dev + kDevGo);
-  const bool stop = j->stop_issuing.load();
-  const bool lead = slices_lead(j);
-  while (!stop && j->issued < slices && j->issued - j->retired < (uint64_t)d + (lead ? ahead : 0u)) {
+int sliced_issue(tally_job *j) {
+  while (!j->stop_issuing.load() && j->next_off < j->total &&
+         j->issued - j->retired < j->max_in_flight) {
+    uint32_t n = j->total - j->next_off;
+    if (n > j->slice_blocks) n = j->slice_blocks;
     SliceCtl c;
     c.cover = j->cover;
-    c.index = j->issued;
-    c.offset = j->issued * j->slice_blocks;
+    c.offset = j->next_off;
     c.gx = j->grid.x;
     c.gy = j->grid.y;
     c.segment = j->segment;
-    c.go = !lead || j->issued - j->first_slice < d ? nullptr : go + j->issued % kGoWords;
-    c.next_go = lead && slices - j->issued > d ? go + (j->issued + d) % kGoWords : nullptr;
-    c.stop = (const uint32_t *)j->h_base_dev();
-    c.ran = lead ? (uint32_t *)(dev + kDevRan) : nullptr;
-    c.host_done = (uint32_t *)(j->h_base_dev() + 128);
-    const uint32_t left = j->total - c.offset;
-    HIPCHK(j->ops->sliced(j->be, j->args, left < j->slice_blocks ? left : j->slice_blocks, c));
+    HIPCHK(j->ops->sliced(j->be, j->args, n, c));
     j->issued += 1;
-    if (!lead) {
-      hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, j->be, c.host_done, j->issued);
-      HIPCHK(hipGetLastError());
-    }
-  }
-  if (lead && !j->reporting && (stop || j->issued == slices)) {
-    hipLaunchKernelGGL(slice_report_kernel, dim3(1), dim3(64), 0, j->be, (const uint32_t *)(dev + kDevRan),
-                       (unsigned long long *)(j->h_base_dev() + kHostReport), j->report_seq + 1);
+    j->next_off += n;
+    hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, j->be,
+                       (uint32_t *)(j->h_base_dev() + 128), j->issued);
     HIPCHK(hipGetLastError());
-    j->report_seq += 1;
-    j->reporting = true;
   }
   return TALLY_OK;
 }
@@ -975,24 +933,17 @@ void refresh(tally_job *j) {
     }
   } else {
     uint32_t done = __atomic_load_n(j->h_slice_done(), __ATOMIC_ACQUIRE);
+    j->retired = done;
     if (j->kind == KIND_NATIVE) {
       if (done >= 1) { j->progress = j->total; j->state = TALLY_JOB_COMPLETE; }
       return;
     }
-    const unsigned long long report = __atomic_load_n(j->h_report(), __ATOMIC_ACQUIRE);
-    bool ended = j->reporting && (uint32_t)(report >> 32) == j->report_seq;
-    if (ended) done = (uint32_t)report;
-    if (done > j->retired) j->retired = done;
-    if (!slices_lead(j)) ended = j->retired == j->issued && (j->stop_issuing.load() || (uint64_t)done * j->slice_blocks >= j->total);
-    uint64_t p = (uint64_t)j->retired * j->slice_blocks;
+    uint64_t p = (uint64_t)done * j->slice_blocks;
     if (p > j->total) p = j->total;
     j->progress = (uint32_t)p;
-    if (!ended) return;
-    j->reporting = false;
-    j->issued = j->retired;      // what was enqueued behind them has not run
     if (p >= j->total) {
       j->state = TALLY_JOB_COMPLETE;
-    } else {
+    } else if (j->stop_issuing.load() && j->retired == j->issued) {
       double tp = j->t_preempt.load();
       j->preempt_latency_us = tp > 0.0 ? now_us() - tp : -1.0;
       j->state = TALLY_JOB_STOPPED;
@@ -1271,7 +1222,7 @@ int tally_launch_sliced(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t 
   j->slice_blocks = slice_blocks;
   j->max_in_flight = max_in_flight;
   j->state = TALLY_JOB_RUNNING;
-  rc = sliced_issue(j, 0);
+  rc = sliced_issue(j);
   if (rc) { tally_job_free(j); return rc; }
   *out = j;
   return TALLY_OK;
@@ -1377,7 +1328,7 @@ int preempt_impl(tally_job *job, bool pause) {
     job->request_word = word;
     __atomic_store_n(job->h_flag(), word, __ATOMIC_RELEASE);
   } else if (job->kind == KIND_SLICED) {
-    job->stop_slices();
+    job->stop_issuing = true;
   }
   return TALLY_OK;
 }
@@ -1397,12 +1348,10 @@ int tally_resume_until(tally_job *job, uint64_t stop_at) {
     return ptb_launch_segment(job, stop_at > job->total ? job->total : (uint32_t)stop_at);
   }
   job->stop_issuing = false;
-  __atomic_store_n(job->h_flag(), 0u, __ATOMIC_RELEASE);
-  job->first_slice = job->issued;
   job->segment += 1;
   job->t_preempt = 0.0;
   job->state = TALLY_JOB_RUNNING;
-  return sliced_issue(job, 0);
+  return sliced_issue(job);
 }
 
 int tally_resume(tally_job *job) { return tally_resume_until(job, ~0ull); }
@@ -1439,13 +1388,13 @@ int tally_progress(tally_job *job, uint64_t *done_blocks, uint64_t *total_blocks
 int tally_pump(tally_job *job) {
   if (!job) return TALLY_ERR_INVALID_ARG;
   refresh(job);
-  if (job->state.load() == TALLY_JOB_RUNNING && job->kind == KIND_SLICED) return sliced_issue(job, kSlicesAhead);
+  if (job->state.load() == TALLY_JOB_RUNNING && job->kind == KIND_SLICED) return sliced_issue(job);
   return TALLY_OK;
 }
 
 int tally_wait(tally_job *job, int *state) {
   if (!job) return TALLY_ERR_INVALID_ARG;
-  const uint32_t reports = job->report_seq, issued = job->issued;
+  const uint32_t issued = job->issued;
   uint32_t seq = 0;
   bool marked = false;
   if (job->kind == KIND_PTB) {
@@ -1467,8 +1416,7 @@ int tally_wait(tally_job *job, int *state) {
   }
   // Everything on the best-effort stream before this call has to have ended, not only the
   // workers' last instruction.  A marker behind it says so 5 us sooner than the runtime's own
-  // wait, which enqueues one only now; a report enqueued by this call is one already, and so is
-  // the marker of a sub-kernel.
+  // wait, which enqueues one only now; a sub-kernel enqueued by this call has one already.
   if (marked) {
     for (uint32_t spins = 1; (int32_t)(__atomic_load_n(job->h_ended(), __ATOMIC_ACQUIRE) - seq) < 0; ++spins) {
       if ((spins & 0xFFFFu) == 0) {
@@ -1477,7 +1425,7 @@ int tally_wait(tally_job *job, int *state) {
         if (q != hipErrorNotReady) { g_last_hip = (int)q; return TALLY_ERR_HIP; }
       }
     }
-  } else if (job->kind != KIND_SLICED || (slices_lead(job) ? job->report_seq == reports : job->issued == issued)) {
+  } else if (job->kind != KIND_SLICED || job->issued == issued) {
     HIPCHK(hipStreamSynchronize(job->be));
   }
   if (state) *state = job->state.load();
@@ -1488,8 +1436,8 @@ int tally_job_free(tally_job *job) {
   if (!job) return TALLY_ERR_INVALID_ARG;
   tally_ctx *ctx = job->ctx;
   if (job->state.load() == TALLY_JOB_RUNNING) {
-    // (workers run what is left of the grid: in their slot the stop word would be a request)
-    if (job->kind == KIND_SLICED) job->stop_slices();
+    // (a sliced job issues nothing further; workers run what is left of the grid)
+    job->stop_issuing = true;
     (void)hipStreamSynchronize(job->be);
   }
   if (job->cover) {
@@ -2050,7 +1998,7 @@ void be_thread_main(tally_sched *s) {
           // kinds "preempt" means that nothing further is issued until the request is done
           cl.preempt_seen = true;
           if (be->t_preempt.load() == 0.0) be->t_preempt = s->t_preempt.load();
-          if (be->kind == KIND_SLICED) be->stop_slices();
+          if (be->kind == KIND_SLICED) be->stop_issuing = true;
         }
         rc = tally_pump(be);   // refresh; a sliced job also issues its next slice unless stopped
         if (rc) break;
@@ -2085,7 +2033,7 @@ void be_thread_main(tally_sched *s) {
           }
         } else if (closing) {
           // shutting down: drain at block boundaries, without pausing
-          if (be->kind == KIND_SLICED) be->stop_slices();
+          if (be->kind == KIND_SLICED) be->stop_issuing = true;
           else if (be->kind == KIND_PTB) (void)tally_preempt(be);
         }
       }

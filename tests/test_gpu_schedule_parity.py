@@ -595,14 +595,13 @@ def test_teams_of_workers_run_every_block_once(env, workers, chunk, blocks):
     assert ((y - want).abs() <= 2.0 ** -23 * want.abs()).all()
 
 
-# ------------------------------------------------------------------ slices decided about on the device
+# ------------------------------------------------------------------ slices, stopped and resumed
 @pytest.mark.parametrize("slice_blocks,in_flight", [(1, 1), (7, 1), (64, 3), (300, 2), (40, 13), (40, 14), (2000, 1),
                                                     (511, 1), (512, 1), (512, 2), (700, 1)])
-def test_slices_enqueued_ahead_stop_and_go_on(env, slice_blocks, in_flight):
-    """While a sliced job is waited for, sub-kernels are enqueued beyond max_in_flight and run or
-    leave at once as the device finds the host's stop word.  Stopped again and again, from
-    launches that cover the grid at once to ones of a single block: always whole slices, a prefix,
-    every block once, and never a slice more for a job that is stopped before it is looked at again."""
+def test_slices_stop_and_go_on(env, slice_blocks, in_flight):
+    """Stopped again and again, from launches that cover the grid at once to ones of a single block:
+    always whole slices, a prefix, every block once, and no more than max_in_flight slices beyond those
+    that the last visit found ended."""
     B, ctx, torch = env
     blocks = 1500
     n = blocks * 256 - 77
@@ -626,10 +625,11 @@ def test_slices_enqueued_ahead_stop_and_go_on(env, slice_blocks, in_flight):
         job.resume()
         for _ in range(round_ % 4 * 8):                   # now and then let it get ahead first
             job.pump()
+        ended = job.progress()[0]
         job.preempt()
         st, before = job.wait(), done
         done = job.progress()[0]
-        assert done >= min(before + slice_blocks * in_flight, blocks)
+        assert min(before + slice_blocks * in_flight, blocks) <= done <= ended + slice_blocks * in_flight
     if st != B.JOB_COMPLETE:
         job.resume()
         assert job.wait() == B.JOB_COMPLETE
@@ -639,3 +639,42 @@ def test_slices_enqueued_ahead_stop_and_go_on(env, slice_blocks, in_flight):
     torch.cuda.synchronize()
     # a fused multiply-add rounds once, the 64-bit sum and its conversion at most once more (2^-53 of it)
     assert ((y - want).abs() <= 2.0 ** -23 * want.abs()).all()
+
+
+@pytest.mark.parametrize("in_flight", [1, 2])
+def test_a_stop_lets_no_more_than_max_in_flight_slices_run(env, in_flight):
+    """Slices of two rounds of GEMM tiles, stopped at changing moments between two visits of the
+    host: whatever the moment, at most max_in_flight sub-kernels run beyond those that the last
+    visit found ended.  Always whole slices, a prefix, every block once, the numbers of one launch."""
+    B, ctx, torch = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(in_flight)
+    A, Bt = (torch.randn(10, 8192, 512, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    C = torch.empty(10, 8192, 8192, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C)                          # 10240 blocks, a slice takes tens of microseconds
+    torch.cuda.synchronize()
+    ctx.launch_native(kern)
+    torch.cuda.synchronize()
+    want = C.clone()
+    C.fill_(-3.0)
+    torch.cuda.synchronize()
+    job = ctx.launch_sliced(kern, 512, max_in_flight=in_flight, coverage=True)
+    for round_ in range(100):
+        until = time.perf_counter() + 1e-6 * (10 + round_ * 13 % 70)
+        while time.perf_counter() < until:
+            job.pump()
+        ended, _, st = job.progress()
+        job.preempt()
+        job.wait()
+        done, _, st = job.progress()
+        assert done % 512 == 0 and done <= ended + 512 * in_flight, round_
+        count = job.coverage()["count"]
+        assert (count[:done] == 1).all() and (count[done:] == 0).all()
+        if st == B.JOB_COMPLETE:
+            break
+        assert st == B.JOB_STOPPED
+        job.resume()
+    assert job.wait() == B.JOB_COMPLETE and round_ >= 4
+    job.free()
+    torch.cuda.synchronize()
+    assert torch.equal(C, want)
