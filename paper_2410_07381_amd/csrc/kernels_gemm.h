@@ -340,7 +340,13 @@ struct GemmBodyT {
     } while (++kt < ns);
     // what was still on its way is the zeros of stages past the last one
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (looks && nh >= 32) act();
+    // Before the epilogue: the last answer, where its question is at most four stages old; where questions
+    // are further apart, or the tile was shorter than their distance, the word is read again (a wait of
+    // 0.7 us, once in a tile).
+    if (looks && nh >= 32) {
+      if (look_mask < 4) act();
+      else yield_while_preempted(ctl, pause_left);
+    }
     // every wave is past its last fragment read: LDS can be reused as staging space
     __syncthreads();
     // The accumulators are read below through inline assembly, which the compiler's

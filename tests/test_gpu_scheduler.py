@@ -356,3 +356,50 @@ def test_large_tiles_pause_on_the_answer_of_an_earlier_stage(env, n128, k, every
     finally:
         ctx.set_yield_bound_us(1000)
         ctx.set_yield_every(4)
+
+
+@pytest.mark.parametrize("n128,k,every", [(False, 32 * 992, 1024), (True, 32 * 991, 1024), (False, 32 * 1000, 512)])
+def test_large_tiles_look_before_their_epilogue_however_rarely_they_are_asked_to(env, n128, k, every):
+    """Looks further apart than a tile is long, or whose last one lies far before its end: a pause asked
+    for mid-tile is found before the output is written, and holds the workers until it is ended."""
+    import time
+    B, ctx, torch = env
+    m, n = 512, 1024
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k + every)
+    A = torch.randn(1, m, k, device="cuda", generator=gen).to(torch.bfloat16)
+    Bt = torch.randn(1, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.empty(1, m, n, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C, n128=n128)
+    torch.cuda.synchronize()
+    ctx.launch_native(kern)
+    torch.cuda.synchronize()
+    want = C.view(torch.int16).clone()
+    ctx.set_yield_bound_us(100000)
+    ctx.set_yield_every(every)
+    try:
+        spans = []
+        for share in (0.0, 0.0, 0.3, 0.7):                # of an undisturbed run: before and after its middle
+            C.fill_(float("nan"))
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            job = ctx.launch_ptb(kern, kern.total_blocks, coverage=True)
+            if share:
+                while time.perf_counter() < t0 + share * spans[-1]:
+                    pass
+                job.preempt(pause=True)
+                time.sleep(0.004)
+                job.pump()
+                assert job.progress()[2] == B.JOB_RUNNING
+                assert torch.isnan(C).all()
+                job.end_pause()
+            assert job.wait() == B.JOB_COMPLETE
+            if not share:
+                spans.append(time.perf_counter() - t0)
+            assert (job.coverage()["count"] == 1).all()
+            job.free()
+            assert torch.equal(C.view(torch.int16), want)
+        assert spans[-1] < 0.002                          # (otherwise the pauses prove nothing)
+    finally:
+        ctx.set_yield_bound_us(1000)
+        ctx.set_yield_every(4)
