@@ -253,9 +253,10 @@ int tally_set_yield_bound_us(tally_ctx *ctx, uint32_t us);
  * of two up to 1024; default 4, about 2 us of a GEMM tile).  A body asks for the word with a load
  * among those of its operands and acts on the answer when it has come, a stage of 64 k later in
  * tiles of 256 rows, so a look costs next to nothing (waited for on the spot, looks every 4
- * steps cost 5 to 7 % of a product).  Such a tile of 32 steps or more also looks before it writes its
- * output: from 16 steps on at the word itself, below at an answer at most four stages old.  Workers that take a GEMM's blocks in parts of 32x32 (64x64,
- * 128x64) look every 16 (8, 4) steps of 32 k at most, 1 to 2 us, and act on a look as much later.
+ * steps cost 5 to 7 % of a product).  Such a tile of 32 steps or more also looks before it writes
+ * its output: from 16 steps on at the word itself, below at an answer at most four stages old.
+ * Workers that take a GEMM's blocks in parts of 32x32 (64x64, 128x64) look every 16 (8, 4) steps of
+ * 32 k at most, 1 to 2 us, and act on a look as much later.
  * Applies to jobs launched after the call. */
 int tally_set_yield_every(tally_ctx *ctx, uint32_t steps);
 

@@ -452,9 +452,9 @@ using GemmN128Body = GemmBodyT<2>;
 // WAVES = 1: a 16x16 tile of one wave, for outputs of so few tiles that what bounds them is how a
 // stage's instructions follow one another in a wave (a 16-byte load, LDS read or write takes 16
 // cycles to issue), not the units.  LDS serves a wave in order, so there is neither a barrier nor
-// a second buffer; fragments are read a stage ahead.  Against 32x32 tiles, us: 128 x 768 x 3072 (384
-// tiles) 7.97 / 7.40, 128 x 768 x 768 3.74 / 3.47, 64 x 960 x 320 2.92 / 2.61, 128 x 128 x 1024 4.10 / 3.67, but
-// 256 x 1024 x 1024 (1024 tiles) 4.42 / 4.95.
+// a second buffer; fragments are read a stage ahead.  32x32 tiles / these, us, operands in the caches:
+// 128 x 768 x 3072 (384 tiles) 7.97 / 7.40, 128 x 768 x 768 3.74 / 3.47, 64 x 960 x 320 2.92 / 2.61, 128 x 128 x 1024
+// 4.10 / 3.67, but 256 x 1024 x 1024 (1024 tiles) 4.42 / 4.95.
 template <int RA, int RB, bool NAN7FC0 = false, int WAVES = 4>
 struct GemmTileT {
   using Args = tally_gemm_bf16_args;

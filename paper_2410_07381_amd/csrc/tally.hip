@@ -232,12 +232,23 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 //   4096 x 4096   192 /  135 / 98.0 / 83.3 / 58.0 / 51.9   (256 of 256x256)
 // and the same order from k = 512 to 8192.  Below k = 128 there is no loop to speak of and the
 // large tiles' long prologue and epilogue lose to 128x64 (4352 x 4864 x 64: 15.4 against 13.3),
-// unless the output is one that GemmBodyT writes past the caches.  16x16 tiles of a single wave pay up
-// to three for two compute units and from the third stage on (see GemmTileT; k = 64 x 768 tiles 2.52
-// against 2.38, 100 x 200 x 96 2.31 both).
+// unless the output is one that GemmBodyT writes past the caches.
+// 16x16 tiles of a single wave (see GemmTileT) pay up to three for two compute units and from the third
+// stage on (k = 64 x 768 tiles 2.52 against 2.38, 100 x 200 x 96 2.31 both).  They ask for half as many
+// bytes ahead and read operands twice as often.  With operands in the caches they are 4 to 9 % faster
+// than 32x32 tiles at every k; with a weight matrix that comes from memory it depends on k, and on whether
+// the larger tiles are whole or their second half asks for nothing (us in 32x32 / 16x16 tiles, caches
+// and memory, launched back to back):
+//   16 x 6144 x 768     3.89 / 3.80   4.67 / 4.79        32 x 3072 x 1280   4.68 / 4.42   6.21 / 5.70
+//   16 x 2048 x 1536    5.07 / 4.73   5.52 / 6.06        64 x 1536 x 1536   5.18 / 4.81   6.13 / 6.04
+//   48 x 2048 x 2048    6.00 / 5.61   6.60 / 7.25       128 x  768 x 2048   6.02 / 5.64   6.77 / 7.06
+//   16 x 6144 x 3072    7.92 / 7.56   9.63 / 10.96      128 x  768 x 3072   7.78 / 7.35   9.25 / 9.33
+//  144 x  672 x 3072    7.86 / 7.37   8.59 / 9.26       128 x  768 x 4096   9.57 / 9.07  10.77 / 11.59
+// So up to k = 768 always, up to 3072 where the larger tiles are whole, and not beyond.
 enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, k16 };
 GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
-  if (a.k > 128 && (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch <= 384) return GemmCover::k16;
+  const uint32_t n16 = cdiv(a.n, 16), m16 = cdiv(a.m, 16);
+  if (a.k > 128 && a.k <= ((n16 | m16) & 1 ? 768u : 3072u) && (uint64_t)n16 * m16 * a.batch <= 384) return GemmCover::k16;
   const uint64_t t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
   if ((uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32;
   if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32x64;

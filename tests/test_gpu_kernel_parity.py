@@ -465,11 +465,13 @@ def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
 
 
 @pytest.mark.parametrize("k", [160, 192, 224, 544, 1056])
-@pytest.mark.parametrize("m,n,batch", [(1, 1, 1), (17, 33, 3), (70, 130, 8), (128, 768, 1), (100, 880, 1), (15, 16, 384), (256, 256, 1)])
+@pytest.mark.parametrize("m,n,batch", [(1, 1, 1), (17, 33, 3), (70, 130, 8), (128, 768, 1), (100, 880, 1), (15, 16, 384), (256, 256, 1),
+                                       (17, 50, 48)])
 def test_gemm_one_wave_tiles(env, m, n, k, batch):
     """Up to 384 tiles of 16x16, the original form takes tiles of a single wave from the third stage
-    on: rows and columns past the matrix, three to seventeen stages, a last stage half full, NaN beyond K
-    and between the rows, nothing written behind C; the same bits as one worker's 32x32 blocks."""
+    on (where their number is odd either way, up to the twelfth): rows and columns past the matrix, three
+    to seventeen stages, a last stage half full, NaN beyond K and between the rows, nothing written
+    behind C; the same bits as one worker's 32x32 blocks."""
     B, ctx, torch = env
     from gpu_util import dev, host, assert_bf16_close
     g = TI.gemm_inputs(m, n, k, config_index=3, batch=batch, scale=0.125)
