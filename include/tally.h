@@ -190,8 +190,9 @@ int tally_launch_sliced(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t 
  * `chunk` (>= 1) is the number of consecutive task indices taken per fetch; 1 is the
  * paper's form.  A fetched index is always executed before the worker exits.  Where blocks are
  * so short that 256 workers or more would queue at the counter, eight neighbours draw eight
- * fetches at once and share them out: a worker then finishes at most one fetch more after a
- * preemption signal.  Progress and prefix are the same.
+ * fetches at once and give them out one by one: after a preemption signal they also finish what is
+ * left of those, up to seven fetches among them, whichever of them takes it.  Progress and prefix
+ * are the same.
  * num_workers must not exceed tally_max_workers(): every worker has to be resident at
  * once (Section 4.2 draws its candidates from the multiples of the compute-unit count
  * that fit).  Workgroups that wait for room keep their hardware queue's dispatcher busy,
@@ -222,8 +223,8 @@ int tally_max_workers(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t *m
 /* preempt_best_effort_kernel() of the scheduling algorithm (Section 4.2, Figure 4), acting
  * as Section 4.1 describes: non-blocking.  Persistent-worker job: raise its preemption
  * signal (one host store; the device folds it into the global task counter, so that every
- * later fetch of a task index fails); workers finish the block(s) they hold and exit,
- * leaving the progress in the task index.  Sliced job: stop issuing sub-kernels (those
+ * later fetch of a task index fails); workers finish the block(s) they hold, or drew together
+ * (tally_launch_ptb), and exit, leaving the progress in the task index.  Sliced job: stop issuing sub-kernels (those
  * already enqueued finish).  No-op on STOPPED / COMPLETE jobs.  Callable from any thread. */
 int tally_preempt(tally_job *job);
 

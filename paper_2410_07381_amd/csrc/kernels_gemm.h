@@ -720,8 +720,8 @@ using GemmTile32 = GemmTileT<1, 1>;
 struct GemmSmallBody : GemmTileT<1, 1, true> {
   static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &a) { return 128 * (uint64_t)a.k; }
-  // (us with the counter alone / in teams, 2048 x 2048: k = 512, 512 x 1 57 / 34; k = 384, 256 x 1 53.6 /
-  // 49.7, k = 1024 64.9 / 69.9)
+  // (us and us of drain with the counter alone / in teams, 4096 x 4096: k = 512, 512 x 1 211 11.9 / 133 8.4; k = 384,
+  // 256 x 1 205 7.6 / 191 7.5; of 2048 x 2048 in us, k = 1024, 256 x 1 64.9 / 69.9)
   static uint32_t team_bytes(uint32_t workers, uint32_t) { return workers >= 512 ? 64 << 10 : 48 << 10; }
   static constexpr bool YIELDS = false;
 };

@@ -115,9 +115,12 @@ struct SaxpyBody {
   using Args = tally_saxpy_args;
   static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &) { return 12 * kThreads; }
-  // (us with the counter alone / in teams: 512 x 8 394 / 158, 512 x 32 135 / 129; 256 x 16 60.7 /
-  // 57.4, 256 x 32 164 / 176)
-  static uint32_t team_bytes(uint32_t workers, uint32_t) { return workers >= 512 ? 96 << 10 : 48 << 10; }
+  // (us and us of drain with the counter alone / in teams, 2^26: 512 x 8 405 13.1 / 174 7.7, 512 x 24 168 11.8 /
+  // 144 10.7, 512 x 32 147 11.8 / 144 12.2; 384 x 16 227 10.4 / 166 8.8; 256 x 8 402 8.4 / 274 7.0, 256 x 16 233 7.9 /
+  // 214 8.1.  Blocks beside eights are taken one by one, longer than 256 workers queue: 256 x 12 323 7.5 / 347 9.1)
+  static uint32_t team_bytes(uint32_t workers, uint32_t chunk) {
+    return workers >= 512 ? 72 << 10 : workers >= 384 || chunk <= 4 || chunk % 8 == 0 ? 48 << 10 : 0;
+  }
   static constexpr int THREADS = kThreads;
   static constexpr int MIN_WAVES = 4;
   static constexpr unsigned DYN_LDS = 0;
@@ -158,9 +161,13 @@ struct ReduceSumBody {
   using Args = tally_reduce_sum_args;
   static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &) { return 4 * PER_BLOCK; }
-  // (us with the counter alone / in teams, 2^28: 512 x 4 241 / 159, 512 x 8 175 / 163; 256 x 4 247 / 205,
-  // 256 x 8 179 / 183)
-  static uint32_t team_bytes(uint32_t workers, uint32_t) { return workers >= 512 ? 128 << 10 : 64 << 10; }
+  // (us and us of drain with the counter alone / in teams, 2^28: 512 x 4 249 12.9 / 169 10.1, 512 x 5 220 12.4 / 172
+  // 11.9, 512 x 6 203 12.4 / 172 13.1, 512 x 8 186 13.8 / 174 16.1, 1024 x 2 427 20.6 / 171 10.6; 448 x 5 221 11.4 both;
+  // 256 x 4 260 8.4 / 216 8.1.  Blocks beside fours are taken one by one: 256 x 3 309 7.3 / 326 8.5, 384 x 3 302
+  // 10.1 / 243 9.4)
+  static uint32_t team_bytes(uint32_t workers, uint32_t chunk) {
+    return workers >= 512 ? 80 << 10 : workers >= 384 || chunk != 3 ? 64 << 10 : 0;
+  }
   static constexpr int THREADS = kThreads;
   static constexpr int MIN_WAVES = 4;
   static constexpr unsigned DYN_LDS = 0;
@@ -281,7 +288,8 @@ struct GemvBody {
   using Args = tally_gemv_bf16_args;
   static constexpr bool TEAMS = true;
   static uint64_t block_bytes(const Args &a) { return 8 * (uint64_t)a.k; }
-  // (us with the counter alone / in teams: 16384 x 4096, 512 x 1 59 / 27; 100000 x 512, 512 x 1 296 / 74)
+  // (us and us of drain with the counter alone / in teams: 16384 x 4096, 512 x 1 69 12.4 / 37 7.5; 50000 x 1000,
+  // 256 x 1 162 8.5 / 102 6.8, 512 x 4 57 11.4 / 43 8.9)
   static uint32_t team_bytes(uint32_t workers, uint32_t) { return workers >= 512 ? 32 << 10 : 8 << 10; }
   static constexpr int THREADS = kThreads;
   static constexpr int MIN_WAVES = 8;   // <= 64 registers: two waves fit beside a GEMM tile
@@ -467,6 +475,9 @@ __device__ __forceinline__ float row_pick(bool in, float v, float other) {
 
 struct SoftmaxOp {
   using Args = tally_softmax_f32_args;
+  // (512 workers, us and us of drain with the counter alone / in teams: 60000 x 2048 x 1 block 210 12.2 / 167 11.6,
+  // 200000 x 512 x 4 181 11.9 / 147 11.8; 300000 x 200 x 8 139 11.1 / 139 10.6, x 10 123 10.6 / 133 11.9)
+  static uint32_t team_bytes(uint32_t chunk) { return chunk <= 8 ? 64 << 10 : 0; }
   template <class G, uint32_t LANES, int NV, bool NT, bool ONE>
   static __device__ __forceinline__ void row(const Args &a, uint32_t r, uint32_t lane, float4 (&v)[NV],
                                              float *part0, float *part1) {
@@ -495,6 +506,9 @@ struct SoftmaxOp {
 
 struct LayerNormOp {
   using Args = tally_layernorm_f32_args;
+  // (as for the softmax: 80000 x 1500 x 1 261 11.8 / 180 10.4, 60000 x 2048 x 1 212 11.6 / 177 12.5; 200000 x 512 x 3
+  // 224 11.5 / 166 11.1, x 4 182 11.3 / 164 13.3; 300000 x 200 x 4 239 11.4 / 170 9.6, x 6 171 10.6 / 171 12.9)
+  static uint32_t team_bytes(uint32_t chunk) { return chunk <= 4 ? 48 << 10 : 0; }
   template <class G, uint32_t LANES, int NV, bool NT, bool ONE>
   static __device__ __forceinline__ void row(const Args &a, uint32_t r, uint32_t lane, float4 (&v)[NV],
                                              float *part0, float *part1) {
@@ -557,12 +571,11 @@ struct RowsBodyT {
   using Args = typename Op::Args;
   static constexpr bool TEAMS = MAXNV <= 16;              // (a block of wider rows has more bytes than team_bytes)
   static uint64_t block_bytes(const Args &a) { return 32 * (uint64_t)a.cols; }
-  // (us with the counter alone / in teams: softmax 60000 x 2048, 512 x 1 200 / 159, 40000 x 2700 146 / 143,
-  // LayerNorm 155 / 159; 60000 x 1024, 256 x 1 184 / 145.  The rows of several blocks take a worker 3 us
-  // and more however narrow they are, longer than 256 workers queue at the counter: 300000 x 100,
-  // 256 x 4 222 / 234)
+  // The rows of several blocks take a worker 3 us and more however narrow they are, longer than 256
+  // workers queue at the counter (300000 x 100, 256 x 4, us with the counter alone / in teams 222 / 234;
+  // of one block 100000 x 1024, us and us of drain, 312 8.2 / 246 7.3).
   static uint32_t team_bytes(uint32_t workers, uint32_t chunk) {
-    return workers >= 512 ? 64 << 10 : chunk == 1 ? 32 << 10 : 0;
+    return workers >= 512 ? Op::team_bytes(chunk) : chunk == 1 ? 32 << 10 : 0;
   }
   static constexpr int THREADS = kThreads;
   static constexpr int MIN_WAVES = WAVES;

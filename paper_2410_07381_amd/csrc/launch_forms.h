@@ -60,8 +60,10 @@ constexpr uint32_t kCoverPieces = 64;
 // leaves when its team's word gives it an index beyond the end, so nothing drawn is left behind (in
 // a single pass, where each worker takes one, teams are whole batches).  The drawer waits for
 // nothing, so neither do the others for long: while a draw is under way the count is beyond
-// kTeamBatch, and nobody else gets the count that means "draw".  After a request a worker
-// finishes what it holds and at most one fetch more, its share of the batch.
+// kTeamBatch, and nobody else gets the count that means "draw".  After a request the
+// workers of a team finish what they hold and what is left of the batch, up to seven fetches among
+// them: mostly one each, but whoever is free takes the next, so one worker may run all of them while
+// the others are held up.
 // Leaving is counted by teams too; a team's last worker puts its line back.
 //
 // Batches twice the team kept half of it waiting (SAXPY of 2^20, 256 x 1: 47 us against 30, and 54
