@@ -805,13 +805,14 @@ uint32_t segment_parts(const KernelOps *ops, uint64_t blocks, uint64_t limit, ui
 // Teams that `workers` form to fetch `chunk` blocks at a time (none: they do not).  The counter
 // serves W workers once in W x 11.4 ns; teams pay where a fetch's work takes less than that, by
 // bytes per fetch as measured (team_bytes), and not below 256 workers (SAXPY of 2^22, 128 x 4: 81 us
-// with the counter alone, 93 in teams).  A drain, from the request to the report, ends with the batches
-// drawn by then, without teams with the workers that queue at the counter to be refused: the lines lie
-// where it takes no longer in teams (or 0.4 us at most; readings differ by 0.2).  Beyond them a job is
-// still shorter, the sum as 512 x 8 by 6 %, but its drain 16.1 us instead of 13.8.  Jobs of one fetch per worker gain as well (SAXPY of 256 x 1
-// blocks 15.5 us instead of 16.3, 512 x 1 15.9 instead of 21.4).  Workers that fill the GPU keep the counter alone: a short job
-// of them is over before a relay that was late is on the GPU, and the next job waits for that
-// relay (100 us and more, where a scheduler's first job was of 2048 x 1).
+// with the counter alone, 93 in teams).  Jobs of one fetch per worker gain as well (SAXPY of 256 x 1
+// blocks 15.5 us instead of 16.3, of 512 x 1 15.9 instead of 21.4).  A drain, from the request to the
+// report, ends with the batches drawn by then, without teams with the workers that queue at the
+// counter to be refused: the lines lie where it takes no longer in teams (or 0.4 us at most; readings
+// differ by 0.2).  Beyond them a job is still shorter, the sum as 512 x 8 by 6 %, but its drain 16.1 us
+// instead of 13.8.  Workers that fill the GPU keep the counter alone: a short job of them is over
+// before a relay that was late is on the GPU, and the next job waits for that relay (100 us and more,
+// where a scheduler's first job was of 2048 x 1).
 uint32_t team_count(const tally_ctx *ctx, const KernelOps *ops, const void *args, uint32_t workers, uint32_t chunk) {
   if (!ops->team_bytes || workers < 256) return 0u;
   const uint32_t *ft = ctx->foot_worker[ops - kOps], per_cu = (workers + ctx->num_cus - 1) / ctx->num_cus;
