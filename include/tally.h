@@ -188,7 +188,9 @@ int tally_launch_sliced(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t 
  * num_workers worker blocks loop { check flag; fetch-and-add the global task counter;
  * map the task index to the logical block index; run the block; barrier }.
  * `chunk` (>= 1) is the number of consecutive task indices taken per fetch; 1 is the
- * paper's form.  A fetched index is always executed before the worker exits.  Where blocks are
+ * paper's form.  A fetched index is always executed before the worker exits.  Where the last
+ * round of fetches would leave workers without one, a fetch of that round may bring fewer blocks,
+ * so that it is shared by all of them.  Where blocks are
  * so short that 256 workers or more would queue at the counter, eight neighbours draw eight
  * fetches at once and give them out one by one: after a preemption signal they also finish what is
  * left of those, up to seven fetches among them, whichever of them takes it.  Progress and prefix

@@ -127,6 +127,7 @@ struct SaxpyBody {
   static constexpr bool YIELDS = false;
   static constexpr bool END_BARRIER = false;
   static constexpr bool RANGE = true;
+  static constexpr bool TOGETHER = true;                  // run_range takes eight blocks at a time
   template <bool NT>
   static __device__ __forceinline__ void run_t(const Args &a, uint32_t bx) {
     uint32_t i = bx * kThreads + threadIdx.x;
@@ -173,6 +174,7 @@ struct ReduceSumBody {
   static constexpr unsigned DYN_LDS = 0;
   static constexpr bool YIELDS = false;
   static constexpr bool RANGE = true;
+  static constexpr bool TOGETHER = true;                  // run_range takes four blocks at a time
   static constexpr bool END_BARRIER = false;
   static constexpr uint32_t PER_BLOCK = 4096;
   static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t, uint32_t) { run_t<false>(a, bx); }

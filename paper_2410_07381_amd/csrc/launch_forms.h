@@ -94,6 +94,9 @@ struct PtbCtl {
   CoverRec *cover;          // device, may be null
   uint32_t parts;           // the counter counts parts of a logical block (1: whole blocks)
   uint32_t limit;           // workers treat this as the end of the grid (normally all of it); in parts
+  uint32_t last_from;       // task indices from here on stand for fewer blocks a fetch (see block_at; none: `limit`)
+  uint32_t last_chunk;      // blocks of such a fetch
+  uint32_t end;             // the end of the grid in blocks (in parts where blocks have several)
   uint32_t epoch;           // id of this launch segment, unique for the life of the slot
   uint32_t exit_target;     // value of *exited after the last worker (or team) of this segment leaves
   uint32_t counter_base;    // raw counter value that stands for task index 0 of this job
@@ -114,6 +117,20 @@ struct PtbCtl {
 };
 constexpr uint32_t kFlagCopies = 64;
 constexpr uint32_t kFlagCopyStride = 32;  // in 32-bit words
+
+// The last round of fetches, shared.  A grid of B blocks taken C at a time by W workers ends with a
+// round in which only B mod (W C) blocks are left: as whole fetches they keep a few workers busy for as
+// long as a full round, so in that round a fetch brings as many blocks as give every worker one
+// (`last_chunk`).  A fetch still advances the counter by `chunk`; from `last_from` on, `chunk` task
+// indices stand for `last_chunk` blocks.  Nothing else knows: an index is turned into blocks where a
+// worker runs it and where progress is told to the host.
+// Softmax as 256 x 4, whole fetches / so, us: 9001 x 8192 (51 third fetches / 203 of one block) 142 / 126,
+// 700 x 6000 (44 fetches / 175) 39 / 23, 5000 x 2048 32.8 / 29.6, 200000 x 300 (49 rounds) 172 both.
+__device__ __forceinline__ uint32_t block_at(const PtbCtl &c, uint32_t index) {
+  if (index <= c.last_from) return index;
+  const uint32_t b = c.last_from + (index - c.last_from) / c.chunk * c.last_chunk;
+  return b < c.end ? b : c.end;
+}
 
 struct SliceCtl {
   CoverRec *cover;
@@ -241,7 +258,7 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
           p = p < c.limit ? p : c.limit;
           __hip_atomic_store(c.pre, ((unsigned long long)c.epoch << 32) | p, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(c.host_live, p / c.parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          __hip_atomic_store(c.host_live, block_at(c, p) / c.parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
         added = true;
         ctr0 += kPreemptStep;
@@ -265,7 +282,7 @@ __global__ __launch_bounds__(64) void relay_kernel(PtbCtl c) {
       if (!alive && wall_clock64() - born > kRelayGiveUpTicks) { gave_up = true; break; }
       // (only news: a store to the host occupies the vector-memory queue of the compute unit for a
       // microsecond, and whichever worker shares that unit falls behind the others)
-      const uint32_t ctr = raw - c.counter_base, live = (ctr < c.limit ? ctr : c.limit) / c.parts;
+      const uint32_t ctr = raw - c.counter_base, live = block_at(c, ctr < c.limit ? ctr : c.limit) / c.parts;
       if (!added && live != mirrored) {
         if (threadIdx.x == 0)
           __hip_atomic_store(c.host_live, live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -457,9 +474,10 @@ __device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, cons
   for (uint32_t it = 0;; ++it) {
     if (threadIdx.x == 0) s_idx[it & 1] = fetch<HasTeams<Body>::value>(c, c.chunk) - c.counter_base;
     __syncthreads();
-    const uint32_t first = __builtin_amdgcn_readfirstlane(s_idx[it & 1]);
-    if (first >= c.limit) break;  // uniform across the workgroup
-    const uint32_t last = (c.limit - first < c.chunk) ? c.limit : first + c.chunk;
+    const uint32_t index = __builtin_amdgcn_readfirstlane(s_idx[it & 1]);
+    if (index >= c.limit) break;  // uniform across the workgroup
+    const uint32_t first = block_at(c, index), n = index < c.last_from ? c.chunk : c.last_chunk;
+    const uint32_t last = c.end - first < n ? c.end : first + n;
     if constexpr (Body::RANGE) {
       // the blocks a fetch brought, handed to the body together (one-dimensional grids)
       if (last - first > 1) {
@@ -494,7 +512,7 @@ __device__ __forceinline__ void ptb_blocks(const typename Body::Args &args, cons
 // every other fetch has been performed, and it reads the counter after that.  Kernel
 // outputs become visible to the host at the end of the kernel as usual; the status
 // word only says that the workers are gone.
-template <bool TEAMS>
+template <bool TEAMS, bool PARTS>
 __device__ __forceinline__ void ptb_leave(const PtbCtl &c) {
   if (threadIdx.x == 0) {
     if (TEAMS && c.team_count) {
@@ -513,7 +531,7 @@ __device__ __forceinline__ void ptb_leave(const PtbCtl &c) {
       uint32_t progress = ctr < c.limit ? ctr : c.limit;
       // a request was folded in: the progress is what the relay's fetch-and-add returned
       if (ctr & kPreemptStep) progress = progress_at_request(c);
-      if (progress != kProgressLost) progress = (progress + c.parts - 1) / c.parts;   // every begun block is done
+      if (progress != kProgressLost) progress = PARTS ? (progress + c.parts - 1) / c.parts : block_at(c, progress);   // every begun block is done
       // (both words carry the epoch and need no order, hence no round trip to the host between them)
       const unsigned long long tag = (unsigned long long)c.epoch << 32;
       __hip_atomic_store(c.host_status, tag | progress, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -534,7 +552,7 @@ __device__ __forceinline__ void ptb_body(const typename Body::Args &args, const 
   if constexpr (HasWhole<Body>::value) ptb_tail<Body>(args, c);
   else if constexpr (HasParts<Body>::value) ptb_parts<Body>(args, c);
   else ptb_blocks<Body>(args, c);
-  ptb_leave<HasTeams<Body>::value>(c);
+  ptb_leave<HasTeams<Body>::value, HasParts<Body>::value>(c);
 }
 template <class Body>
 __global__ __launch_bounds__(Body::THREADS, Body::MIN_WAVES) void ptb_kernel(typename Body::Args args, PtbCtl c) {

@@ -80,6 +80,8 @@ struct KernelOps {
   // blocks it pays that `workers` fetch in teams (null: blocks are long, it never does)
   uint64_t (*block_bytes)(const void *args);
   uint32_t (*team_bytes)(uint32_t workers, uint32_t chunk);
+  // the blocks of a fetch are taken together: their number is left alone (last_round)
+  bool together;
 };
 
 template <class Body>
@@ -497,10 +499,16 @@ uint64_t block_bytes(const void *args) {
   return Body::block_bytes(a);
 }
 
+template <class Body, class = void>
+struct TakesTogether : std::false_type {};
+template <class Body>
+struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {};
+
 #define OPS(Body, nm, gridfn)                                                              \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_t<Body>, launch_sliced_t<Body>,     \
    launch_ptb_t<Body>, init_t<Body>, occupancy_t<Body>, pause_fraction_t<Body>,              \
-   footprint_t<Body>, {footprint_native_t<Body>}, nullptr, nullptr, nullptr, block_bytes<Body>, Body::team_bytes}
+   footprint_t<Body>, {footprint_native_t<Body>}, nullptr, nullptr, nullptr, block_bytes<Body>, Body::team_bytes, \
+   TakesTogether<Body>::value}
 
 #define GEMM_TILES(Tile32, canon)                                                                         \
   footprint_native_t<Tile32>, footprint_native_t<GemmTileT<1, 2, canon>>,                                 \
@@ -510,13 +518,13 @@ uint64_t block_bytes(const void *args) {
    launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
    occupancy, pause_fraction_t<Wide>, footprint_t<Wide>,                                                  \
    {footprint_native_t<Narrow>, footprint_native_t<Wide>, footprint_native_t<Team>},                      \
-   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>, nullptr, block_bytes<Wide>, Wide::team_bytes}
+   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>, nullptr, block_bytes<Wide>, Wide::team_bytes, false}
 #define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
    footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
                        footprint_native_t<GemmTileT<1, 1, false, 1>>},                                    \
-   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr}
+   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr, false}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(SaxpyBody, "saxpy", grid_saxpy),
@@ -530,12 +538,13 @@ const KernelOps kOps[TALLY_K_COUNT] = {
              (occupancy_capped_t<LayerNormBody, 2>), "layernorm_f32", grid_layernorm),
     {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_attn_decode,
      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice,
-     nullptr, nullptr, nullptr, nullptr},
+     nullptr, nullptr, nullptr, nullptr, false},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
      pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, footprint_native_t<GemmTileT<1, 1, true, 1>>},
      gemm_small_native_choice,
-     gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes},
+     gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes,
+     false},
     OPS_GEMM(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128, GemmCover::k256x128),
 };
 
@@ -802,6 +811,16 @@ uint32_t segment_parts(const KernelOps *ops, uint64_t blocks, uint64_t limit, ui
   return 1u;
 }
 
+// Blocks that a fetch brings in the last round of a segment of `blocks` blocks (see block_at): what gives
+// every worker a fetch; `chunk` where there is nothing to share out.  SAXPY and the sum, which ask for the data
+// of eight or four blocks of a fetch together, keep theirs whole: fewer blocks a fetch are fewer bytes on their way.
+uint32_t last_round(const KernelOps *ops, uint64_t blocks, uint64_t limit, uint32_t workers, uint32_t chunk) {
+  const uint64_t round = (uint64_t)workers * chunk, left = blocks % round;
+  // (the counter, advanced by whole fetches, has to stay below the bit that a request sets)
+  if (chunk == 1 || left == 0 || ops->together || limit + 2 * round > 0x40000000ull) return chunk;
+  return cdiv(left, workers);
+}
+
 // Teams that `workers` form to fetch `chunk` blocks at a time (none: they do not).  The counter
 // serves W workers once in W x 11.4 ns; teams pay where a fetch's work takes less than that, by
 // bytes per fetch as measured (team_bytes), and not below 256 workers (SAXPY of 2^22, 128 x 4: 81 us
@@ -838,7 +857,10 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   const uint64_t blocks = j->limit > start ? j->limit - start : 0u;
   uint32_t whole = 0;
   const uint32_t parts = segment_parts(j->ops, blocks, j->limit, j->workers, j->chunk, &whole);
-  const uint32_t chunk = parts > 1 ? 1u : j->chunk;
+  uint32_t chunk = parts > 1 ? 1u : j->chunk;
+  const uint32_t last_chunk = last_round(j->ops, blocks, j->limit, j->workers, chunk);
+  if (blocks < (uint64_t)j->workers * chunk) chunk = last_chunk;   // the first round is the last
+  const uint32_t left = last_chunk < chunk ? (uint32_t)(blocks % ((uint64_t)j->workers * chunk)) : 0u;
   j->counter_base = ctx->slot_counter[slot] - start * parts;
   __atomic_store_n(j->h_flag(), 0u, __ATOMIC_RELEASE);   // no request stands against the new segment
   j->request_word = 0;
@@ -854,7 +876,10 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   c.host_gave_up = (unsigned long long *)(j->h_base_dev() + kHostGaveUp);
   c.cover = j->cover;
   c.parts = parts;
-  c.limit = j->limit * parts;
+  c.end = j->limit * parts;
+  c.last_from = c.end - left;
+  c.last_chunk = left ? last_chunk : chunk;
+  c.limit = c.last_from + cdiv(left, c.last_chunk) * chunk;
   c.epoch = j->epoch;
   const uint32_t teams = team_count(ctx, j->ops, j->args, j->workers, chunk);
   c.teams = ctx->team_pool + (size_t)slot * kMaxTeams;

@@ -678,3 +678,66 @@ def test_a_stop_lets_no_more_than_max_in_flight_slices_run(env, in_flight):
     job.free()
     torch.cuda.synchronize()
     assert torch.equal(C, want)
+
+
+@pytest.mark.parametrize("workers,chunk,blocks,stop_at", [
+    (8, 4, 32, None), (8, 4, 33, None), (8, 4, 63, 40), (8, 4, 41, 35), (8, 4, 5, None), (8, 4, 31, 3), (7, 3, 50, 23),
+    (256, 4, 1024 + 203, None), (256, 16, 300, 299), (300, 2, 1000, 601), (512, 4, 2048 + 700, 2049)])
+def test_last_round_of_fetches_is_shared(env, workers, chunk, blocks, stop_at):
+    """The last round of a grid that whole fetches do not divide: every block once, the prefix at a
+    stop inside it, and the bits of the original form."""
+    B, ctx, torch = env
+    rows, cols = 4 * blocks - 1, 260
+    g = torch.Generator(device="cuda")
+    g.manual_seed(blocks)
+    x = torch.randn(rows, cols, device="cuda", generator=g)
+    want, y = torch.zeros_like(x), torch.zeros_like(x)
+    torch.cuda.synchronize()
+    ctx.launch_native(B.softmax_f32(x, want))
+    job = ctx.launch_ptb(B.softmax_f32(x, y), workers, chunk=chunk, coverage=True, stop_at=stop_at)
+    st = job.wait()
+    if stop_at is not None:
+        assert st == B.JOB_STOPPED and job.progress()[0] == stop_at
+        rec = job.coverage()
+        assert (rec["count"][:stop_at] == 1).all() and (rec["count"][stop_at:] == 0).all()
+        job.resume()
+        st = job.wait()
+    assert st == B.JOB_COMPLETE and job.progress()[0] == blocks
+    rec = job.coverage()
+    job.free()
+    assert (rec["count"] == 1).all() and (rec["bx"] == np.arange(blocks)).all()
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+
+
+def test_requests_around_a_shared_last_round_leave_a_prefix(env):
+    """Requests at growing delays, on jobs nearly half of whose blocks are their last round."""
+    B, ctx, torch = env
+    workers, chunk, blocks = 64, 8, 64 * 8 + 64 * 6 + 1
+    rows, cols = 4 * blocks, 8192
+    x = torch.randn(rows, cols, device="cuda")
+    y = torch.zeros_like(x)
+    torch.cuda.synchronize()
+    k = B.softmax_f32(x, y)
+    for attempt in range(24):
+        job = ctx.launch_ptb(k, workers, chunk=chunk, coverage=True)
+        t0 = time.perf_counter()
+        while time.perf_counter() - t0 < 6e-6 * attempt:
+            pass
+        segments = 0
+        job.preempt()
+        while job.wait() == B.JOB_STOPPED:
+            done = job.progress()[0]
+            rec = job.coverage()
+            assert done < blocks and (rec["count"][:done] == 1).all() and (rec["count"][done:] == 0).all()
+            segments += 1
+            job.resume()
+            if segments < 3:
+                job.preempt()
+        rec = job.coverage()
+        job.free()
+        assert (rec["count"] == 1).all()
+    torch.cuda.synchronize()
+    # (1e-5 of the sum of a row, as for the row kernels' other comparisons)
+    ref = torch.softmax(x[:: 97].double(), dim=1)
+    assert (y[:: 97].double() - ref).abs().max() <= 1e-5 * ref.max() + 1e-7
