@@ -316,6 +316,25 @@ struct GemvBody {
   // (the best-effort forms keep four loads in flight: their loop has no registers to spare)
   static __device__ __forceinline__ void run_be(const Args &a, uint32_t x, uint32_t y, uint32_t z) { run_t<false>(a, x, y, z); }
   static __device__ __forceinline__ void run(const Args &a, uint32_t x, uint32_t y, uint32_t z) { run_t<true>(a, x, y, z); }
+  // `left` vectors of a row, N to a lane, from buffers that end with the row: a lane past it gets zeros, which
+  // add nothing
+  template <int N>
+  static __device__ __forceinline__ void rest(const uint4 *w, const uint4 *x, uint32_t left, uint32_t lane, float &acc0,
+                                              float &acc1, float &acc2, float &acc3) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const buf_t rw = make_buf(w, left * 16), rx = make_buf(x, left * 16);
+    uint4 wv[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) wv[j] = buf_ld16(rw, lane * 16, j * kWave * 16);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const uint4 xv = buf_ld16(rx, lane * 16, j * kWave * 16);
+      float &acc = j % 4 == 0 ? acc0 : j % 4 == 1 ? acc1 : j % 4 == 2 ? acc2 : acc3;
+      acc = dot8(wv[j], xv, acc);
+      if (j == 3) __builtin_amdgcn_sched_barrier(0);       // (x's loads by fours, as above)
+    }
+#endif
+  }
   template <bool DEEP>
   static __device__ __forceinline__ void run_t(const Args &a, uint32_t bx, uint32_t, uint32_t) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -324,8 +343,8 @@ struct GemvBody {
     const uint32_t nvec = a.k / 8;
     const uint4 *w = reinterpret_cast<const uint4 *>(a.W + (uint64_t)row * a.k);
     const uint4 *x = reinterpret_cast<const uint4 *>(a.x);
-    float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;
-    uint32_t v = lane;
+    float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;   // vector j of a lane goes to accumulator j mod 4
+    uint32_t first = 0;                                    // of the batch
     // Eight 16-byte loads of the row in flight per lane (8 KB per wave; a 4096-wide row is
     // one such batch).  Beside the paused tiles of a best-effort GEMM only two of these
     // waves fit on a SIMD, and with four loads each the eight waves of a compute unit had
@@ -333,7 +352,8 @@ struct GemvBody {
     // asks for ~45 KB: the decode-like request ran at 4.3 TB/s co-located against 5.6 alone.
     // The operand x comes from the caches; its loads are taken four at a time to stay
     // within the 64 registers that let two waves fit.
-    for (; DEEP && v + 7 * kWave < nvec; v += 8 * kWave) {
+    for (; DEEP && first + 8 * kWave <= nvec; first += 8 * kWave) {
+      const uint32_t v = first + lane;
       const uint4 w0 = w[v], w1 = w[v + kWave], w2 = w[v + 2 * kWave], w3 = w[v + 3 * kWave];
       const uint4 w4 = w[v + 4 * kWave], w5 = w[v + 5 * kWave], w6 = w[v + 6 * kWave], w7 = w[v + 7 * kWave];
       uint4 x0 = x[v], x1 = x[v + kWave], x2 = x[v + 2 * kWave], x3 = x[v + 3 * kWave];
@@ -347,14 +367,25 @@ struct GemvBody {
       acc2 = dot8(w6, x2, acc2);
       acc3 = dot8(w7, x3, acc3);
     }
-    for (; v + 3 * kWave < nvec; v += 4 * kWave) {
+    for (; !DEEP && first + 4 * kWave <= nvec; first += 4 * kWave) {
+      const uint32_t v = first + lane;
       uint4 w0 = w[v], w1 = w[v + kWave], w2 = w[v + 2 * kWave], w3 = w[v + 3 * kWave];
       acc0 = dot8(w0, x[v], acc0);
       acc1 = dot8(w1, x[v + kWave], acc1);
       acc2 = dot8(w2, x[v + 2 * kWave], acc2);
       acc3 = dot8(w3, x[v + 3 * kWave], acc3);
     }
-    for (; v < nvec; v += kWave) acc0 = dot8(w[v], x[v], acc0);
+    // What is left of the row is one batch more: taken four vectors and then one by one it was up to four
+    // memory latencies in a row (us so / now: 700 x 16000 6.40 / 5.34, 16000 x 520 5.5 / 4.9, 4096 x 11008
+    // 15.3 / 14.8, 20000 x 6000 41.5 / 40.3; asking for eight where there are two costs 8000 x 1000 0.6 us).
+    switch ((nvec - first + kWave - 1) / kWave) {
+      case 0: break;
+      case 1: rest<1>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
+      case 2: rest<2>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
+      case 3: rest<3>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
+      case 4: rest<4>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
+      default: if constexpr (DEEP) rest<8>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3);
+    }
     float s = wave_sum((acc0 + acc1) + (acc2 + acc3));
     if (lane == 0) a.y[row] = f32_to_bf16(s);
   }

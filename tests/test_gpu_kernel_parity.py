@@ -567,6 +567,30 @@ def test_gemv(env, n, k, form):
     assert_bf16_close(host(y), a["y"])
 
 
+@pytest.mark.parametrize("k", [8, 504, 512, 520, 1024, 1032, 1536, 1544, 2040, 2048, 2056, 2560, 3584, 3592, 4088, 4096, 4104, 6152, 8200, 11008])
+def test_gemv_row_ends(env, k):
+    """Every number of vectors that a lane can have left behind the whole batches, each with the last one whole,
+    one lane and all but one: nothing beyond a row or x is read (NaNs lie there), and both forms give the same bits."""
+    B, ctx, torch = env
+    n = 9
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    wide = torch.full((n * k + 4096,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    wide[:n * k] = torch.randn(n * k, device="cuda", generator=g).to(torch.bfloat16)
+    xs = torch.full((k + 4096,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    xs[:k] = torch.randn(k, device="cuda", generator=g).to(torch.bfloat16)
+    W, x = wide[:n * k].view(n, k), xs[:k]
+    y, z = (torch.zeros(n, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    torch.cuda.synchronize()
+    _run_form(B, ctx, torch, B.gemv_bf16(x, W, y), "native")
+    _run_form(B, ctx, torch, B.gemv_bf16(x, W, z), "ptb")
+    assert torch.equal(y.view(torch.int16), z.view(torch.int16))
+    p = W.double() * x.double()
+    # one bf16 rounding, and k fp32 additions of at most the sum of magnitudes
+    bound = p.sum(1).abs() * 2.0 ** -8 + k * 2.0 ** -24 * p.abs().sum(1)
+    assert ((y.double() - p.sum(1)).abs() <= bound).all()
+
+
 # ------------------------------------------------------------------ softmax / LayerNorm
 @pytest.mark.parametrize("rows,cols,form", [(37, 2048, "native"), (37, 2048, "ptb_preempted"),
                                             (37, 2048, "sliced"), (1536, 128, "native_hi"),
