@@ -448,29 +448,20 @@ using GemmN128Body = GemmBodyT<2>;
 //
 // NAN7FC0: a NaN leaves as 0x7FC0, which is what the ragged GEMM has always written; those with
 // blocks of 256 rows write what the hardware's conversion makes of the MFMA's NaN (0xFFC0).
-//
-// WAVES = 1: a 16x16 tile of one wave, for outputs of so few tiles that what bounds them is how a
-// stage's instructions follow one another in a wave (a 16-byte load, LDS read or write takes 16
-// cycles to issue), not the units.  LDS serves a wave in order, so there is neither a barrier nor
-// a second buffer; fragments are read a stage ahead.  32x32 tiles / these, us, operands in the caches:
-// 128 x 768 x 3072 (384 tiles) 7.97 / 7.40, 128 x 768 x 768 3.74 / 3.47, 64 x 960 x 320 2.92 / 2.61, 128 x 128 x 1024
-// 4.10 / 3.67, but 256 x 1024 x 1024 (1024 tiles) 4.42 / 4.95.
-template <int RA, int RB, bool NAN7FC0 = false, int WAVES = 4>
+template <int RA, int RB, bool NAN7FC0 = false>
 struct GemmTileT {
   using Args = tally_gemm_bf16_args;
-  static_assert(WAVES == 4 || (WAVES == 1 && RA == 1 && RB == 1), "2 x 2 waves, or one with a block");
-  static constexpr int THREADS = 64 * WAVES;
+  static constexpr int THREADS = 256;
   static constexpr int MIN_WAVES = 4;
   static constexpr unsigned DYN_LDS = 0;
   static constexpr bool YIELDS = true;
   static constexpr bool RANGE = false;
   // a block's last barrier follows its last fragment read
   static constexpr bool END_BARRIER = false;
-  static constexpr bool LONE = WAVES == 1;
-  static constexpr uint32_t TM = LONE ? 16 : 32 * RA, TN = LONE ? 16 : 32 * RB;
-  static constexpr int LA = TM / (8 * WAVES), LB = TN / (8 * WAVES);   // loads of a wave and stage
-  static constexpr bool TWO = !LONE && RA * RB <= 2;      // LDS holds two stages
-  static constexpr int AHEAD = LONE ? 4 : RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
+  static constexpr uint32_t TM = 32 * RA, TN = 32 * RB;
+  static constexpr int LA = RA, LB = RB;                  // loads of a wave and stage
+  static constexpr bool TWO = RA * RB <= 2;               // LDS holds two stages
+  static constexpr int AHEAD = RA * RB == 1 ? 8 : RA * RB <= 2 ? 4 : RA * RB <= 4 ? 2 : 1;
   static constexpr int ROUND = TWO ? AHEAD : 16 / (RA * RB);   // stages between two looks at the pause word, at least
   static constexpr uint32_t SA = TM * 128, STAGE = (TM + TN) * 128;   // bytes of A, of both in a stage
   // share of a tile between asking for the pause word and pausing on the answer to the next
@@ -503,7 +494,7 @@ struct GemmTileT {
     asm volatile("" : "+v"(tid));   // (a worker keeps no addresses across its tiles)
     const uint32_t lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t wm = LONE ? 0u : wave >> 1, wn = LONE ? 0u : wave & 1;
+    const uint32_t wm = wave >> 1, wn = wave & 1;
     const uint32_t K = a.k;
     const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
     const uint32_t ns = (K + 63) / 64;
@@ -568,26 +559,10 @@ struct GemmTileT {
       request(s[d], d);
       __builtin_amdgcn_sched_barrier(0);                  // (in the order in which they are waited for)
     }
-    if constexpr (TWO || LONE) {
+    if constexpr (TWO) {
       store(s[0], 0);
       request(s[0], SETS);
-    }
-    if constexpr (TWO) __syncthreads();
-    // (one wave: fragments of the stage at hand and of the next one)
-    bf16x8_t ga[2][2], gb[2][2];
-    auto read_ahead = [&](int f) {
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        gb[f][kk] = read(0, fB, kk, 0);
-        ga[f][kk] = read(0, fA, kk, 0);
-      }
-    };
-    // (costs nothing: lanes of the wave write what others read, which only the hardware knows)
-    auto share = []() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
-    if constexpr (LONE) {
-      share();
-      read_ahead(0);
-      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
     }
     // Looks at the pause word.  Waiting for one costs the workgroup 0.7 us, several of its stages:
     // one lane asks for the word at the start of a round of STEPS stages, behind the loads on their
@@ -606,20 +581,6 @@ struct GemmTileT {
     };
     // stage c, whose operands (with two buffers those of stage c + 1) are in set d
     auto step = [&](int d, uint32_t c) {
-      if constexpr (LONE) {
-        static_assert(SETS % 2 == 0, "the fragments are those of the set");
-        const int next = (d + 1) % SETS, f = d & 1;
-        share();
-        store(s[next], 0);
-        share();
-        request(s[next], c + 1 + SETS);
-        read_ahead(f ^ 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gb[f][kk], ga[f][kk], acc[0][0], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        return;
-      }
       bf16x8_t fa[2][RA], fb[2][RB];
       if constexpr (TWO) {
         static_assert(SETS % 2 == 0, "the buffer is that of the set");
@@ -716,6 +677,193 @@ struct GemmTileT {
   }
 };
 using GemmTile32 = GemmTileT<1, 1>;
+
+// The same operator in tiles of one wave, (16 NA) x (16 NB), for outputs of so few tiles that what bounds them
+// is how a stage's instructions follow one another.  A tile that takes its operands through registers writes
+// them to LDS, and a 16-byte write takes a wave 35 cycles and the unit 13 (a read 17 and 4, a direct load 16
+// on the unit); here they go straight to LDS, R stages of 64 k ahead, in the large tile's layout.  LDS serves
+// a wave in order and nobody else writes there, so there is no barrier: a stage waits for the next one's loads,
+// reads its fragments, asks for the stage that takes its own place and multiplies.
+// R is what 24 KB hold (31 KB are free beside a resident 256x256 tile, and 28 KB are no faster); with fewer the
+// loads' latency shows (16x16, 128 x 768 x 3072, R = 6 / 4 / 3: 6.1 / 7.8 / 10.9 us).  The order of the products is that of every tile.
+// us through registers (16x16 of one wave, 32x32 or 32x64, the best) / so, operands from the Infinity Cache:
+// 128 x 768 x 3072 7.7 / 6.1, 128 x 768 x 768 3.7 / 3.2, 128 x 2304 x 768 4.9 / 4.1, 128 x 3072 x 768 4.9 / 4.2,
+// 48 x 2048 x 3072 7.7 / 6.3, 100 x 1000 x 1536 5.3 / 4.2, 256 x 1024 x 768 4.0 / 3.8, 33 x 5000 x 768 5.1 / 4.0.
+//
+// Tiles of one column of tiles share a panel of B.  Workgroups go to the dies in turn, so a grid of (8, rows of
+// tiles, columns of tiles / 8) sends a column's tiles to one die, and next to one another in time; with columns
+// along the grid's first extent that is so only where they are a multiple of eight (100 x 1000 x 3072, 63 columns,
+// 8.8 us, 6.6 so; 128 x 3072 x 768, 96, 4.6 and 4.2).
+template <int NA, int NB, bool NAN7FC0 = false>
+struct GemmWaveT {
+  using Args = tally_gemm_bf16_args;
+  static_assert(NA * NB <= 2, "one or two blocks");
+  static constexpr int THREADS = 64;
+  static constexpr int MIN_WAVES = 4;
+  static constexpr uint32_t TM = 16 * NA, TN = 16 * NB;
+  static constexpr int LA = 2 * NA, LB = 2 * NB, L = LA + LB;   // loads of a stage
+  static constexpr int R = NA * NB == 1 ? 6 : 4;
+  static constexpr uint32_t SA = TM * 128, STAGE = SA + TN * 128;
+  // (dynamic: the compiler gives a kernel that LDS lets on a SIMD only twice a third of its registers, whatever
+  // it uses, and 176 do not fit beside a resident tile's 352)
+  static constexpr unsigned DYN_LDS = STAGE * R;
+  static dim3 grid(const Args &a) {
+    const uint32_t x = (a.n + TN - 1) / TN, y = (a.m + TM - 1) / TM;
+    return a.batch == 1 ? dim3(8, y, (x + 7) / 8) : dim3(x, y, a.batch);
+  }
+  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
+#ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
+    extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
+    if (a.batch == 1) {
+      bx += 8 * bz;
+      bz = 0;
+      if (bx * TN >= a.n) return;
+    }
+    const uint32_t lane = threadIdx.x;
+    const uint32_t K = a.k;
+    const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
+    const uint32_t ns = (K + 63) / 64;
+    // A load moves 8 rows x 128 bytes to 1 KB of LDS; lane l supplies 16-byte slot l, that is row l/8, k-chunk
+    // (l%8) xor ((row/2)%8).  A lane whose offset has its top bit set is outside the buffer and its slot is
+    // filled with zeros: rows past the matrix, k past K in a last stage that is half full.
+    constexpr uint32_t OOB = 0x80000000u;
+    const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TM * LDA, 0x7fffffffu);
+    const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TN * LDB, 0x7fffffffu);
+    const uint32_t r8 = lane >> 3, c8 = (lane & 7) ^ (lane >> 4);   // (odd groups of 8 rows: c8 xor 4)
+    uint32_t vA[LA], vB[LB];
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+      const uint32_t r = j * 8 + r8;
+      vA[j] = by * TM + r < a.m ? (r * LDA + (c8 ^ ((j & 1) * 4)) * 8) * 2 : OOB;
+    }
+#pragma unroll
+    for (int j = 0; j < LB; ++j) {
+      const uint32_t r = j * 8 + r8;
+      vB[j] = bx * TN + r < a.n ? (r * LDB + (c8 ^ ((j & 1) * 4)) * 8) * 2 : OOB;
+    }
+    const uint32_t base = (uint32_t)(uintptr_t)(lptr_t)tally_dyn_lds, end = base + R * STAGE;
+    uint32_t to = base, so = 0, left = ns;                 // the next stage to ask for: its place, its k in bytes, how many
+    auto request = [&]() {
+      if (--left == 0 && (K & 32)) {
+        const uint32_t h0 = c8 & 4 ? OOB : 0u, h1 = h0 ^ OOB;
+#pragma unroll
+        for (int j = 0; j < LA; ++j) vA[j] |= j & 1 ? h1 : h0;
+#pragma unroll
+        for (int j = 0; j < LB; ++j) vB[j] |= j & 1 ? h1 : h0;
+      }
+#pragma unroll
+      for (int j = 0; j < LA; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lptr_t)(to + j * 1024), 16, vA[j], so, 0, 0);
+#pragma unroll
+      for (int j = 0; j < LB; ++j) __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, (lptr_t)(to + SA + j * 1024), 16, vB[j], so, 0, 0);
+      so += 128;
+      to = to + STAGE == end ? base : to + STAGE;
+    };
+    // lane l takes row l%16 of a 16-row block, k-chunk 4 kk + l/16; two sets, this stage's and the next one's
+    const uint32_t f_off = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16);
+    typedef const volatile __attribute__((address_space(3))) bf16x8_t *frag_t;   // (volatile: pinned)
+    bf16x8_t fa[2][2][NA], fb[2][2][NB];
+    uint32_t from = base;                                  // place of the next stage to read
+    auto read = [&](int f) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const uint32_t at = from + (f_off ^ (kk * 64));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) fb[f][kk][j] = *(frag_t)(at + SA + j * 2048);
+#pragma unroll
+        for (int i = 0; i < NA; ++i) fa[f][kk][i] = *(frag_t)(at + i * 2048);
+      }
+      from = from + STAGE == end ? base : from + STAGE;
+    };
+    f32x4_t acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int f) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[f][kk][j], fa[f][kk][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // A stage whose fragments have been asked for: once they are here its place is free, and once only R - 2
+    // stages are on their way the next one has landed.
+    auto step = [&](int f) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(L * (R - 2)) : "memory");
+      read(f ^ 1);
+      request();
+      multiply(f);
+    };
+    // the last R stages, AFTER of them behind this one: nothing is asked for any more
+    auto finish = [&](auto &&self, auto after, auto set) -> void {
+      constexpr int AFTER = decltype(after)::value, f = decltype(set)::value;
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(AFTER ? L * (AFTER - 1) : 0) : "memory");
+      if constexpr (AFTER > 0) read(f ^ 1);
+      multiply(f);
+      if constexpr (AFTER > 0) self(self, std::integral_constant<int, AFTER - 1>{}, std::integral_constant<int, f ^ 1>{});
+    };
+    if (ns >= (uint32_t)R) {
+#pragma unroll
+      for (int d = 0; d < R; ++d) request();
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * (R - 1)) : "memory");
+      read(0);
+      uint32_t pairs = (ns - R) / 2;
+      if ((ns - R) & 1) {
+        step(0);
+        for (; pairs; --pairs) { step(1); step(0); }
+        finish(finish, std::integral_constant<int, R - 1>{}, std::integral_constant<int, 1>{});
+      } else {
+        for (; pairs; --pairs) { step(0); step(1); }
+        finish(finish, std::integral_constant<int, R - 1>{}, std::integral_constant<int, 0>{});
+      }
+    } else {
+      for (uint32_t d = 0; d < ns; ++d) request();
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      for (uint32_t d = 0; d < ns; ++d) {
+        read(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        multiply(0);
+      }
+    }
+    // B was the first MFMA operand: four neighbouring columns per lane, or eight after the swaps (see GemmTileT)
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    auto pack = [](float x, float y) {
+      if constexpr (NAN7FC0) return f32_to_bf16(x) | (uint32_t)f32_to_bf16(y) << 16;
+      const f32x2_t p = {x, y};
+      return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
+    };
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const uint32_t row = by * TM + i * 16 + (lane & 15), col = bx * TN + (lane >> 4) * (4 * NB);
+      uint32_t w[2 * NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        w[2 * j] = pack(acc[i][j][0], acc[i][j][1]);
+        w[2 * j + 1] = pack(acc[i][j][2], acc[i][j][3]);
+      }
+      if constexpr (NB == 2) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(w[q]), "+v"(w[2 + q]));
+      }
+      if (row < a.m) {
+        uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
+        if (col + 4 * NB <= a.n) {
+          __builtin_memcpy(g, w, 8 * NB);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4 * NB; ++e)
+            if (col + e < a.n) g[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
+        }
+      }
+    }
+#endif
+  }
+};
 // The small GEMM's own blocks stop at their ends only, as its waves fit beside a request's.
 struct GemmSmallBody : GemmTileT<1, 1, true> {
   static constexpr bool TEAMS = true;

@@ -49,14 +49,17 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // ---------------------------------------------------------------------------- registry
 typedef hipError_t (*FootprintFn)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
-constexpr uint32_t kMaxNative = 7;   // kernels that one operator's original form chooses from
+constexpr uint32_t kMaxNative = 9;   // kernels that one operator's original form chooses from
+// How an original form is launched: on the high-priority stream; beside best-effort workgroups that leave
+// little LDS.
+constexpr uint32_t kUrgent = 1u, kBeside = 2u;
 
 struct KernelOps {
   const char *name;
   size_t args_size;
   bool transformable;  // false: native form only
   int (*grid)(const void *args, tally_dim3 *g, tally_dim3 *b);
-  hipError_t (*native)(hipStream_t, const void *args, tally_dim3 g, uint32_t urgent);
+  hipError_t (*native)(hipStream_t, const void *args, tally_dim3 g, uint32_t how);
   hipError_t (*sliced)(hipStream_t, const void *args, uint32_t nblocks, const SliceCtl &);
   hipError_t (*ptb)(hipStream_t, const void *args, const PtbCtl &);
   hipError_t (*init)();
@@ -71,7 +74,7 @@ struct KernelOps {
   FootprintFn footprint_native[kMaxNative];
   // which of them a launch of these arguments takes: in its original form, with the number of
   // its workgroups (null: the first, one workgroup per logical block), and in slices (null: the same)
-  uint32_t (*native_choice)(const void *args, uint64_t *groups);
+  uint32_t (*native_choice)(const void *args, uint32_t how, uint64_t *groups);
   uint32_t (*sliced_choice)(const void *args);
   // parts the persistent-worker form splits each of `blocks` logical blocks in (null: never), and
   // how many whole blocks each worker takes first
@@ -85,11 +88,11 @@ struct KernelOps {
 };
 
 template <class Body>
-hipError_t launch_native_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+hipError_t launch_native_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
   typename Body::Args a;
   memcpy(&a, args, sizeof(a));
   hipLaunchKernelGGL(native_kernel<Body>, dim3(g.x, g.y, g.z), dim3(Body::THREADS), Body::DYN_LDS,
-                     s, a, urgent);
+                     s, a, how & kUrgent);
   return hipGetLastError();
 }
 template <class Body>
@@ -172,7 +175,7 @@ hipError_t footprint_attn(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_p
   *regs_per_lane = ((uint32_t)attr.numRegs + 7u) & ~7u;
   return hipSuccess;
 }
-uint32_t attn_choice(const void *args, uint64_t *groups) {
+uint32_t attn_choice(const void *args, uint32_t, uint64_t *groups) {
   tally_attn_decode_args a;
   memcpy(&a, args, sizeof(a));
   *groups = (uint64_t)kAttnSplits * a.heads;
@@ -188,18 +191,18 @@ uint32_t rows_range(const void *args) {
   return a.cols <= Narrow::MAX_COLS ? 0 : a.cols <= Wide::MAX_COLS ? 1 : 2;
 }
 template <class Wide, class Narrow>
-uint32_t rows_choice(const void *args, uint64_t *groups) {
+uint32_t rows_choice(const void *args, uint32_t, uint64_t *groups) {
   typename Wide::Args a;
   memcpy(&a, args, sizeof(a));
   *groups = ((uint64_t)a.rows + 3) / 4;
   return rows_range<Wide, Narrow>(args);
 }
 template <class Wide, class Narrow, class Team>
-hipError_t launch_native_rows_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+hipError_t launch_native_rows_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
   switch (rows_range<Wide, Narrow>(args)) {
-    case 0: return launch_native_t<Narrow>(s, args, g, urgent);
-    case 1: return launch_native_t<Wide>(s, args, g, urgent);
-    default: return launch_native_t<Team>(s, args, g, urgent);
+    case 0: return launch_native_t<Narrow>(s, args, g, how);
+    case 1: return launch_native_t<Wide>(s, args, g, how);
+    default: return launch_native_t<Team>(s, args, g, how);
   }
 }
 template <class Wide, class Narrow, class Team>
@@ -235,23 +238,38 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // and the same order from k = 512 to 8192.  Below k = 128 there is no loop to speak of and the
 // large tiles' long prologue and epilogue lose to 128x64 (4352 x 4864 x 64: 15.4 against 13.3),
 // unless the output is one that GemmBodyT writes past the caches.
-// 16x16 tiles of a single wave (see GemmTileT) pay up to three for two compute units and from the third
-// stage on (k = 64 x 768 tiles 2.52 against 2.38, 100 x 200 x 96 2.31 both).  They ask for half as many
-// bytes ahead and read operands twice as often.  With operands in the caches they are 4 to 9 % faster
-// than 32x32 tiles at every k; with a weight matrix that comes from memory it depends on k, and on whether
-// the larger tiles are whole or their second half asks for nothing (us in 32x32 / 16x16 tiles, caches
-// and memory, launched back to back):
-//   16 x 6144 x 768     3.89 / 3.80   4.67 / 4.79        32 x 3072 x 1280   4.68 / 4.42   6.21 / 5.70
-//   16 x 2048 x 1536    5.07 / 4.73   5.52 / 6.06        64 x 1536 x 1536   5.18 / 4.81   6.13 / 6.04
-//   48 x 2048 x 2048    6.00 / 5.61   6.60 / 7.25       128 x  768 x 2048   6.02 / 5.64   6.77 / 7.06
-//   16 x 6144 x 3072    7.92 / 7.56   9.63 / 10.96      128 x  768 x 3072   7.78 / 7.35   9.25 / 9.33
-//  144 x  672 x 3072    7.86 / 7.37   8.59 / 9.26       128 x  768 x 4096   9.57 / 9.07  10.77 / 11.59
-// So up to k = 768 always, up to 3072 where the larger tiles are whole, and not beyond.
-enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, k16 };
-GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
-  const uint32_t n16 = cdiv(a.n, 16), m16 = cdiv(a.m, 16);
-  if (a.k > 128 && a.k <= ((n16 | m16) & 1 ? 768u : 3072u) && (uint64_t)n16 * m16 * a.batch <= 384) return GemmCover::k16;
-  const uint64_t t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
+// Tiles of one wave (GemmWaveT) pay from the third stage on and where there are few of them: they keep more
+// bytes on their way and fewer instructions between them, but read operands more often.  Counted in 16x16
+// blocks of the output, us for 32x32 or 32x64 tiles, the better / 16x16 / 16x32 / 32x16, with operands from the
+// caches and with a weight matrix from memory:
+//   128 x  768 x 1536 (384)    5.3 / 4.1 / 5.1 / 5.1     5.3 / 4.2 / 5.1 / 5.2
+//    16 x 8192 x 3072 (512)    9.6 / 9.0 / 9.2 / 9.4    10.7 / 10.5 / 13.5 / 13.4
+//    64 x 3072 x  384 (768)    3.5 / 2.9 / 3.1 / 3.2     3.5 / 2.9 / 3.1 / 3.2
+//    64 x 3072 x 3072 (768)    8.1 / 7.1 / 8.6 / 8.7     9.8 / 9.9 / 12.4 / 11.9
+//   200 x 1000 x  768 (819)    4.0 / 3.9 / 3.8 / 3.9     4.0 / 3.9 / 3.9 / 3.9
+//    33 x 5000 x 1536 (939)    7.2 / 5.7 / 5.6 / 5.9     7.9 / 7.7 / 7.6 / 7.6
+//   256 x 1024 x 1536 (1024)   5.5 / 5.4 / 5.3 / 5.3     5.6 / 5.7 / 5.7 / 5.8
+//   256 x 1024 x 3072 (1024)   8.2 / 8.4 / 8.4 / 8.3     8.9 / 10.5 / 10.8 / 10.4
+//   128 x 2304 x 3072 (1152)  11.1 / 11.2 / 10.0 / 9.0  12.6 / 15.6 / 14.6 / 12.5
+//    90 x 3400 x  768 (1278)   5.2 / 4.9 / 4.6 / 4.7     5.4 / 5.7 / 5.4 / 5.4
+//    90 x 3400 x 1536 (1278)   7.5 / 7.5 / 6.7 / 6.9     8.1 / 9.8 / 9.0 / 9.1
+//   128 x 3072 x 1536 (1536)   7.0 / 7.3 / 6.2 / 5.9     7.7 / 9.5 / 8.3 / 7.6
+//   256 x 2048 x  768 (2048)   5.0 / 6.3 / 4.9 / 4.7     5.0 / 6.7 / 5.3 / 4.9
+//   256 x 2048 x 1536 (2048)   7.0 / 9.9 / 7.5 / 6.9     7.5 / 12.0 / 9.5 / 8.4
+// So 16x16 up to three per compute unit, then 32x16 up to eight blocks per unit, or 16x32 where a last row of
+// 32x16 tiles would be half empty, as far as k goes.
+// Beside best-effort workgroups that leave LDS for one of them on a compute unit (kBeside) more than 256 would
+// run in rounds: there operands go through registers (the nine-kernel layer beside paused 256x256 tiles 43.5 us
+// from the request to its completion, 54 in one-wave tiles throughout).
+enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16 };
+GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how) {
+  const uint64_t t16 = (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch, t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
+  const bool odd = cdiv(a.m, 16) & 1;
+  if (a.k > 128 && (!(how & kBeside) || t16 <= 256)) {
+    if (t16 <= 768) return GemmCover::kWave16;
+    if (a.k <= (t16 <= 1024 ? 2048u : t16 <= 1536 ? (odd ? 1024u : 3072u) : t16 <= 2048 ? 768u : 0u))
+      return odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
+  }
   if ((uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32;
   if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32x64;
   if (t64 <= 512) return GemmCover::k64;
@@ -260,61 +278,71 @@ GemmCover gemm_cover(const tally_gemm_bf16_args &a) {
   return GemmCover::k256x256;
 }
 template <class Body>
-hipError_t launch_gemm_cover(hipStream_t s, const tally_gemm_bf16_args &a, uint32_t tn, uint32_t tm, uint32_t urgent) {
-  return launch_native_t<Body>(s, &a, {cdiv(a.n, tn), cdiv(a.m, tm), a.batch}, urgent);
+hipError_t launch_gemm_cover(hipStream_t s, const tally_gemm_bf16_args &a, uint32_t tn, uint32_t tm, uint32_t how) {
+  return launch_native_t<Body>(s, &a, {cdiv(a.n, tn), cdiv(a.m, tm), a.batch}, how);
+}
+template <int NA, int NB, bool CANON>
+hipError_t launch_gemm_wave(hipStream_t s, const tally_gemm_bf16_args &a, uint32_t how) {
+  const dim3 g = GemmWaveT<NA, NB, CANON>::grid(a);
+  return launch_native_t<GemmWaveT<NA, NB, CANON>>(s, &a, {g.x, g.y, g.z}, how);
 }
 // Body: what covers the output where the rule asks for tiles at least as large
 template <class Body>
-hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t urgent) {
+hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  switch (gemm_cover(a)) {
-    case GemmCover::k16: return launch_gemm_cover<GemmTileT<1, 1, false, 1>>(s, a, 16, 16, urgent);
-    case GemmCover::k32: return launch_gemm_cover<GemmTile32>(s, a, 32, 32, urgent);
-    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, urgent);
-    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, urgent);
-    case GemmCover::k128x64: return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, urgent);
-    case GemmCover::k256x128: return launch_gemm_cover<GemmN128Body>(s, a, 128, 256, urgent);
-    default: return launch_native_t<Body>(s, args, g, urgent);
+  switch (gemm_cover(a, how)) {
+    case GemmCover::kWave16: return launch_gemm_wave<1, 1, false>(s, a, how);
+    case GemmCover::kWave16x32: return launch_gemm_wave<1, 2, false>(s, a, how);
+    case GemmCover::kWave32x16: return launch_gemm_wave<2, 1, false>(s, a, how);
+    case GemmCover::k32: return launch_gemm_cover<GemmTile32>(s, a, 32, 32, how);
+    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2>>(s, a, 64, 32, how);
+    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2>>(s, a, 64, 64, how);
+    case GemmCover::k128x64: return launch_gemm_cover<GemmTileT<4, 2>>(s, a, 64, 128, how);
+    case GemmCover::k256x128: return launch_gemm_cover<GemmN128Body>(s, a, 128, 256, how);
+    default: return launch_native_t<Body>(s, args, g, how);
   }
 }
 // The ragged GEMM: only the tiles with predicated edges, which also fit beside a paused
 // best-effort tile.  128x64 tiles pay from two per compute unit (512 x 4096 x 4096, 256 of them,
 // 29 us with 64x64 and 32; 1024 x 4096 x 4096, 512, 54 and 47).
-GemmCover gemm_cover_small(const tally_gemm_bf16_args &a) {
-  const GemmCover c = gemm_cover(a);
-  if (c == GemmCover::k16 || c == GemmCover::k32 || c == GemmCover::k32x64) return c;
+GemmCover gemm_cover_small(const tally_gemm_bf16_args &a, uint32_t how) {
+  const GemmCover c = gemm_cover(a, how);
+  if (c <= GemmCover::k32x64 || c >= GemmCover::kWave16) return c;
   return (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512 ? GemmCover::k128x64 : GemmCover::k64;
 }
-hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t urgent) {
+hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t how) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  switch (gemm_cover_small(a)) {
-    case GemmCover::k16: return launch_gemm_cover<GemmTileT<1, 1, true, 1>>(s, a, 16, 16, urgent);
-    case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, urgent);
-    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2, true>>(s, a, 64, 32, urgent);
-    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2, true>>(s, a, 64, 64, urgent);
-    default: return launch_gemm_cover<GemmTileT<4, 2, true>>(s, a, 64, 128, urgent);
+  switch (gemm_cover_small(a, how)) {
+    case GemmCover::kWave16: return launch_gemm_wave<1, 1, true>(s, a, how);
+    case GemmCover::kWave16x32: return launch_gemm_wave<1, 2, true>(s, a, how);
+    case GemmCover::kWave32x16: return launch_gemm_wave<2, 1, true>(s, a, how);
+    case GemmCover::k32: return launch_gemm_cover<GemmSmallBody>(s, a, 32, 32, how);
+    case GemmCover::k32x64: return launch_gemm_cover<GemmTileT<1, 2, true>>(s, a, 64, 32, how);
+    case GemmCover::k64: return launch_gemm_cover<GemmTileT<2, 2, true>>(s, a, 64, 64, how);
+    default: return launch_gemm_cover<GemmTileT<4, 2, true>>(s, a, 64, 128, how);
   }
 }
 // which of the kernels in kOps (in the order of GemmCover) and how many workgroups of it
 uint32_t gemm_choice(const tally_gemm_bf16_args &a, GemmCover c, uint32_t tn, uint64_t *groups) {
-  const uint32_t tile[][2] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}, {256, 128}, {256, tn}, {16, 16}};
+  const uint32_t tile[][2] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}, {256, 128}, {256, tn}, {16, 16}, {16, 32}, {32, 16}};
   const uint32_t i = (uint32_t)c;
   *groups = (uint64_t)cdiv(a.m, tile[i][0]) * cdiv(a.n, tile[i][1]) * a.batch;
   return i;
 }
 template <uint32_t TN>
-uint32_t gemm_native_choice(const void *args, uint64_t *groups) {
+uint32_t gemm_native_choice(const void *args, uint32_t how, uint64_t *groups) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  return gemm_choice(a, gemm_cover(a), TN, groups);
+  return gemm_choice(a, gemm_cover(a, how), TN, groups);
 }
-uint32_t gemm_small_native_choice(const void *args, uint64_t *groups) {
+uint32_t gemm_small_native_choice(const void *args, uint32_t how, uint64_t *groups) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  return gemm_choice(a, gemm_cover_small(a), 32, groups);
+  return gemm_choice(a, gemm_cover_small(a, how), 32, groups);
 }
+constexpr uint32_t kWaveTileLds = GemmWaveT<1, 2>::R * GemmWaveT<1, 2>::STAGE;
 template <GemmCover C>
 uint32_t gemm_sliced_choice(const void *) { return (uint32_t)C; }
 
@@ -513,6 +541,8 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
 #define GEMM_TILES(Tile32, canon)                                                                         \
   footprint_native_t<Tile32>, footprint_native_t<GemmTileT<1, 2, canon>>,                                 \
   footprint_native_t<GemmTileT<2, 2, canon>>, footprint_native_t<GemmTileT<4, 2, canon>>
+#define GEMM_WAVE_TILES(canon)                                                                            \
+  footprint_native_t<GemmWaveT<1, 1, canon>>, footprint_native_t<GemmWaveT<1, 2, canon>>, footprint_native_t<GemmWaveT<2, 1, canon>>
 #define OPS_ROWS(Wide, Narrow, NarrowDeep, Team, occupancy, nm, gridfn)                                   \
   {nm, sizeof(Wide::Args), true, gridfn, launch_native_rows_t<Wide, Narrow, Team>,                        \
    launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
@@ -523,7 +553,7 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
    footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
-                       footprint_native_t<GemmTileT<1, 1, false, 1>>},                                    \
+                       GEMM_WAVE_TILES(false)},                                                           \
    gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr, false}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
@@ -541,7 +571,7 @@ const KernelOps kOps[TALLY_K_COUNT] = {
      nullptr, nullptr, nullptr, nullptr, false},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
-     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, footprint_native_t<GemmTileT<1, 1, true, 1>>},
+     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, GEMM_WAVE_TILES(true)},
      gemm_small_native_choice,
      gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes,
      false},
@@ -627,6 +657,7 @@ struct tally_ctx {
   uint32_t yield_every;      // steps between two looks at the pause word (a power of two)
   void *static_attn_scratch; // this device's address of static_scratch
   std::atomic<uint32_t> wait_seq;   // numbers the markers that waits put on a stream
+  std::atomic<int> heavy_jobs;      // jobs whose workgroups leave little LDS (leaves_little_lds), launched or about to be
   int device;
   int live_jobs;
   // profile-guided configuration (Section 4.2): per (kernel, grid, block) the candidate
@@ -644,6 +675,7 @@ struct tally_job {
   uint32_t total;
   int kind;
   int slot;
+  bool heavy;                // counted in the context's heavy_jobs
   CoverRec *cover;
   std::atomic<int> state;
   std::atomic<uint32_t> progress;
@@ -720,6 +752,19 @@ int settle_relay(tally_ctx *ctx, int slot) {
   }
 }
 
+// Does a workgroup of `foot` leave LDS for no more than two one-wave GEMM tiles beside it?
+bool leaves_little_lds(const tally_ctx *ctx, const uint32_t *foot) { return foot[0] + 3 * kWaveTileLds > ctx->lds_per_cu; }
+uint32_t hi_launch(const tally_ctx *ctx) { return kUrgent | (ctx->heavy_jobs.load() > 0 ? kBeside : 0u); }
+// What one workgroup of a job of this kind occupies.
+const uint32_t *job_footprint(const tally_ctx *ctx, const tally_kernel_desc *desc, int kind, uint64_t *groups) {
+  const KernelOps &ops = kOps[desc->kernel_id];
+  if (kind == KIND_PTB) return ctx->foot_worker[desc->kernel_id];
+  uint32_t i = 0;
+  if (kind == KIND_SLICED) i = ops.sliced_choice ? ops.sliced_choice(desc->args) : 0;
+  else if (ops.native_choice) i = ops.native_choice(desc->args, 0u, groups);
+  return ctx->foot_native[desc->kernel_id][i];
+}
+
 int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverage, tally_job **out) {
   const KernelOps *ops;
   tally_dim3 g;
@@ -776,6 +821,9 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
   memset(j->h_base(), 0, kHostSlotBytes);
   *j->h_ended() = ctx->wait_seq.load();
   ctx->slot_used[slot] = true;
+  uint64_t groups;
+  j->heavy = leaves_little_lds(ctx, job_footprint(ctx, desc, kind, &groups));
+  if (j->heavy) ctx->heavy_jobs++;
   ctx->live_jobs++;
   *out = j;
   return TALLY_OK;
@@ -1102,6 +1150,7 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
   memset(c->slot_relay, 0, sizeof(c->slot_relay));
   c->live_jobs = 0;
   c->wait_seq = 0;
+  c->heavy_jobs = 0;
   c->next_slot = 0;
   c->n_shunned = 0;
   c->n_side = 0;
@@ -1234,7 +1283,7 @@ int tally_launch_native(tally_ctx *ctx, const tally_kernel_desc *desc, int on_hi
   tally_dim3 g;
   int rc = check_desc(desc, &ops, &g);
   if (rc) return rc;
-  HIPCHK(ops->native(on_hi_stream ? ctx->hi : ctx->be, desc->args, g, on_hi_stream ? 1u : 0u));
+  HIPCHK(ops->native(on_hi_stream ? ctx->hi : ctx->be, desc->args, g, on_hi_stream ? hi_launch(ctx) : 0u));
   return TALLY_OK;
 }
 
@@ -1486,6 +1535,7 @@ int tally_job_free(tally_job *job) {
     (void)hipFree(job->cover);
   }
   ctx->slot_used[job->slot] = false;
+  if (job->heavy) ctx->heavy_jobs--;
   ctx->live_jobs--;
   delete job;
   return TALLY_OK;
@@ -1892,10 +1942,10 @@ struct tally_sched {
 namespace {
 
 // What the kernel occupies that a launch in its original form takes, and its workgroups.
-const uint32_t *native_footprint(tally_ctx *ctx, const tally_kernel_desc *desc, uint64_t *groups) {
+const uint32_t *native_footprint(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t how, uint64_t *groups) {
   const KernelOps &ops = kOps[desc->kernel_id];
   *groups = (uint64_t)desc->grid.x * desc->grid.y * desc->grid.z;
-  return ctx->foot_native[desc->kernel_id][ops.native_choice ? ops.native_choice(desc->args, groups) : 0];
+  return ctx->foot_native[desc->kernel_id][ops.native_choice ? ops.native_choice(desc->args, how, groups) : 0];
 }
 
 // Per-compute-unit demand of the workgroups a best-effort kernel puts on the GPU at once
@@ -1907,10 +1957,8 @@ int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_confi
   int rc = check_desc(desc, &ops, &g);
   if (rc) return rc;
   const uint64_t total = (uint64_t)g.x * g.y * g.z;
-  uint64_t groups = cfg.param < total ? cfg.param : total;
-  const uint32_t *ft = ctx->foot_worker[desc->kernel_id];
-  if (cfg.kind == 1) ft = ctx->foot_native[desc->kernel_id][ops->sliced_choice ? ops->sliced_choice(desc->args) : 0];
-  if (cfg.kind == 2) ft = native_footprint(ctx, desc, &groups);
+  uint64_t groups = cfg.kind != 2 && cfg.param < total ? cfg.param : total;
+  const uint32_t *ft = job_footprint(ctx, desc, (int)cfg.kind, &groups);
   const uint32_t l = ft[0], w = ft[1], r = ft[2];
   const uint64_t per_cu = (groups + ctx->num_cus - 1) / ctx->num_cus;
   const uint64_t cap = 64;  // beyond any compute unit's capacity: keeps the products small
@@ -2096,7 +2144,14 @@ void be_thread_main(tally_sched *s) {
           if (rc) break;
           uint32_t l = 0, w = 0, r = 0;
           (void)item_demand(ctx, &cl.cur.desc, cfg, &l, &w, &r);
-          if (admit(c, l, w, r)) {
+          // A request's kernels are chosen by what is resident.  The job counts before the flag is looked at
+          // again: either it is seen there or the request is seen here.
+          const bool admitted = admit(c, l, w, r);
+          if (admitted) ctx->heavy_jobs++;
+          if (admitted && s->opts.policy != 2 && s->hi_active.load()) {
+            ctx->heavy_jobs--;
+            vacate(cl);
+          } else if (admitted) {
             ctx->cur_be = cl.be;
             ctx->cur_ctl = cl.ctl;
             tally_be_item it = {&cl.cur.desc, cfg};
@@ -2105,6 +2160,7 @@ void be_thread_main(tally_sched *s) {
             rc = launch_be_item(ctx, &it, &j);
             ctx->cur_be = ctx->be;
             ctx->cur_ctl = ctx->ctl;
+            ctx->heavy_jobs--;
             if (rc) break;
             cl.profiling = prof;
             set_job(cl, j);
@@ -2237,22 +2293,26 @@ int tally_sched_submit_hi(tally_sched *s, const tally_kernel_desc *kernels, uint
   if (!s || !kernels || n == 0) return TALLY_ERR_INVALID_ARG;
   if (s->hi_inflight) return TALLY_ERR_BAD_STATE;
   tally_ctx *ctx = s->ctx;
-  uint32_t hl = 0, hw = 0, hr = 0;  // largest demand of one high-priority workgroup
   for (uint32_t i = 0; i < n; ++i) {
     const KernelOps *ops;
     tally_dim3 g;
     int rc = check_desc(&kernels[i], &ops, &g);
     if (rc) return rc;
+  }
+  // the request time is published before the flag that makes the other thread read it, and the flag is up
+  // before the jobs are counted: a job that this misses has not been launched (see be_thread_main)
+  s->t_preempt = now_us();
+  s->hi_active = true;
+  const uint32_t how = hi_launch(ctx);
+  uint32_t hl = 0, hw = 0, hr = 0;  // largest demand of one high-priority workgroup
+  for (uint32_t i = 0; i < n; ++i) {
     uint64_t groups;
-    const uint32_t *ft = native_footprint(ctx, &kernels[i], &groups);
+    const uint32_t *ft = native_footprint(ctx, &kernels[i], how, &groups);
     hl = ft[0] > hl ? ft[0] : hl;
     hw = ft[1] > hw ? ft[1] : hw;
     const uint32_t per_simd = ((ft[1] + 3) / 4) * ft[2];
     hr = per_simd > hr ? per_simd : hr;
   }
-  // the request time is published before the flag that makes the other thread read it
-  s->t_preempt = now_us();
-  s->hi_active = true;
   if (s->opts.policy == 0) {   // preempt_best_effort_kernel()
     for (uint32_t c = 0; c < s->n_clients; ++c) {
       BeClient &cl = s->clients[c];
@@ -2267,7 +2327,11 @@ int tally_sched_submit_hi(tally_sched *s, const tally_kernel_desc *kernels, uint
     }
   }
   int rc = TALLY_OK;
-  for (uint32_t i = 0; i < n && rc == TALLY_OK; ++i) rc = tally_launch_native(ctx, &kernels[i], 1);
+  for (uint32_t i = 0; i < n && rc == TALLY_OK; ++i) {
+    const tally_dim3 &g = kernels[i].grid;                 // (checked above)
+    const hipError_t e = kOps[kernels[i].kernel_id].native(ctx->hi, kernels[i].args, g, how);
+    if (e != hipSuccess) { g_last_hip = (int)e; rc = TALLY_ERR_HIP; }
+  }
   if (rc == TALLY_OK) rc = tally_marker(ctx, 1, ++s->hi_seq);
   if (rc != TALLY_OK) { s->hi_active = false; return rc; }
   s->hi_inflight = true;

@@ -505,6 +505,41 @@ def test_gemm_one_wave_tiles(env, m, n, k, batch):
         assert torch.equal(C2, one_worker)
 
 
+@pytest.mark.parametrize("k", [160, 288, 320, 352, 768])
+@pytest.mark.parametrize("m,n,batch", [(200, 1000, 1), (250, 1001, 1), (33, 5000, 1), (50, 4100, 1), (512, 1024, 1), (17, 50, 200), (40, 50, 100)])
+def test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch):
+    """768 to 2048 blocks of 16x16: tiles of one wave with two of them, 16x32 where the blocks' rows are odd in
+    number and 32x16 where they are even; fewer stages than a tile keeps on their way, as many, one more and
+    more, a last stage half full, columns of tiles that do not divide by eight, NaN beyond K and between the
+    rows, nothing written behind C; the same bits as one worker's 32x32 blocks."""
+    B, ctx, torch = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + n + k)
+    nan = float("nan")
+    Ap = torch.full((batch, m + 1, k + 40), nan, dtype=torch.bfloat16, device="cuda")
+    Bp = torch.full((batch, n + 1, k + 8), nan, dtype=torch.bfloat16, device="cuda")
+    Ap[:, :m, :k] = torch.randn(batch, m, k, device="cuda", generator=gen)
+    Bp[:, :n, :k] = torch.randn(batch, n, k, device="cuda", generator=gen)
+    buf = torch.full((batch * m * n + 8,), 7.0, dtype=torch.bfloat16, device="cuda")
+    Cd = buf[:batch * m * n].view(batch, m, n)
+    kern = B.gemm_bf16(Ap[:, :m, :k], Bp[:, :n, :k], Cd, small=True)
+    torch.cuda.synchronize()
+    job = ctx.launch_ptb(kern, 256)
+    assert job.wait() == B.JOB_COMPLETE
+    job.free()
+    torch.cuda.synchronize()
+    want = Cd.clone()
+    Cd.fill_(7.0)
+    torch.cuda.synchronize()
+    ctx.launch_native(kern, hi=True)
+    torch.cuda.synchronize()
+    assert torch.equal(Cd, want) and bool((buf[batch * m * n:] == 7.0).all())
+    row, col = m - 1, n - 1
+    ref = (Ap[:, row, :k].double() * Bp[:, col, :k].double()).sum(1)
+    mag = (Ap[:, row, :k].double() * Bp[:, col, :k].double()).abs().sum(1)
+    assert ((Cd[:, row, col].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + k * 2.0 ** -24 * mag).all()
+
+
 @pytest.mark.parametrize("tile,m,n,k,batch", [
     ("256", 256, 256, 96, 1), ("256", 512, 512, 1056, 1), ("256", 512, 768, 288, 1), ("256", 1024, 1024, 544, 1),
     ("256", 1024, 2048, 2080, 1), ("256", 2048, 2048, 64, 1), ("256", 4352, 4864, 96, 1), ("256", 1280, 1280, 2048, 1),

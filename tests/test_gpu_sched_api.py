@@ -404,6 +404,38 @@ def test_a_request_is_judged_by_the_kernel_it_launches(env, m, n, k, small):
         ctx.set_yield_bound_us(1000)
 
 
+@pytest.mark.parametrize("m,n,k", [(100, 500, 416), (128, 1500, 416), (128, 2300, 1056)])
+def test_requests_beside_large_tiles_give_the_same_bits(env, m, n, k):
+    """The small GEMM beside resident 256x256 tiles takes 32x32 or 32x64 tiles whose operands go through
+    registers, alone tiles of one wave: the outputs are the same bits."""
+    B, ctx, torch = env
+    be = B.gemm_bf16(_bf16_zeros(torch, 1, 4096, 32768), _bf16_zeros(torch, 1, 4096, 32768), _bf16_zeros(torch, 1, 4096, 4096))
+    A, Bt = (torch.randn(1, r, k, device="cuda").to(torch.bfloat16) for r in (m, n))
+    C = _bf16_zeros(torch, 1, m, n)
+    hi = B.gemm_bf16(A, Bt, C, small=True)
+    torch.cuda.synchronize()
+    ctx.launch_native(hi, hi=True)
+    torch.cuda.synchronize()
+    alone = C.clone()
+    C.zero_()
+    torch.cuda.synchronize()
+    s = ctx.scheduler()
+    try:
+        s.submit_be(be, (B.CFG_PTB, 256, 1))
+        t0 = time.perf_counter()
+        while time.perf_counter() - t0 < 3e-4:
+            pass
+        s.submit_hi([hi])
+        while s.poll():
+            pass
+        while s.stats()["be_kernels_done"] == 0:
+            s.poll()
+    finally:
+        s.close()
+    torch.cuda.synchronize()
+    assert torch.equal(C, alone) and bool((C != 0).any())
+
+
 def test_admission_counts_the_workgroups_of_the_original_form(env):
     """4096 x 4096 x 64 in its original form is 2048 workgroups of 128x64, eight per compute unit:
     beside another client's workers it has to wait, where 256 workgroups of the large tile (one per
