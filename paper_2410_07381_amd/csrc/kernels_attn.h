@@ -13,6 +13,7 @@
 
 #include "../../include/tally.h"
 #include "kernels_stream.h"
+#include "launch_forms.h"
 
 namespace tally {
 
@@ -176,14 +177,11 @@ inline hipError_t launch_attn_decode(hipStream_t s, const void *args, tally_dim3
   memcpy(&a, args, sizeof(a));
   const uint32_t chunk = attn_decode_chunk(a);
   if (chunk > kAttnMaxChunk) return hipErrorInvalidValue;
-  if (attn_decode_waves(a) == 8)
-    hipLaunchKernelGGL(attn_decode_partial<8>, dim3(kAttnSplits, a.heads), dim3(512), 0, s, a, chunk, urgent);
-  else
-    hipLaunchKernelGGL(attn_decode_partial<4>, dim3(kAttnSplits, a.heads), dim3(256), 0, s, a, chunk, urgent);
-  hipError_t e = hipGetLastError();
+  const bool eight = attn_decode_waves(a) == 8;
+  const hipError_t e = launch(eight ? attn_decode_partial<8> : attn_decode_partial<4>, dim3(kAttnSplits, a.heads),
+                              dim3(eight ? 512 : 256), 0, s, a, chunk, urgent);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_decode_combine, dim3(a.heads), dim3(128), 0, s, a);
-  return hipGetLastError();
+  return launch(attn_decode_combine, dim3(a.heads), dim3(128), 0, s, a);
 }
 
 }  // namespace tally

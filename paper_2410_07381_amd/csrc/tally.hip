@@ -91,25 +91,19 @@ template <class Body>
 hipError_t launch_native_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
   typename Body::Args a;
   memcpy(&a, args, sizeof(a));
-  hipLaunchKernelGGL(native_kernel<Body>, dim3(g.x, g.y, g.z), dim3(Body::THREADS), Body::DYN_LDS,
-                     s, a, how & kUrgent);
-  return hipGetLastError();
+  return launch(native_kernel<Body>, dim3(g.x, g.y, g.z), dim3(Body::THREADS), Body::DYN_LDS, s, a, how & kUrgent);
 }
 template <class Body>
 hipError_t launch_sliced_t(hipStream_t s, const void *args, uint32_t nblocks, const SliceCtl &c) {
   typename Body::Args a;
   memcpy(&a, args, sizeof(a));
-  hipLaunchKernelGGL(sliced_kernel<Body>, dim3(nblocks), dim3(Body::THREADS), Body::DYN_LDS, s, a,
-                     c);
-  return hipGetLastError();
+  return launch(sliced_kernel<Body>, dim3(nblocks), dim3(Body::THREADS), Body::DYN_LDS, s, a, c);
 }
 template <class Body>
 hipError_t launch_ptb_t(hipStream_t s, const void *args, const PtbCtl &c) {
   typename Body::Args a;
   memcpy(&a, args, sizeof(a));
-  hipLaunchKernelGGL(ptb_kernel<Body>, dim3(c.workers), dim3(Body::THREADS), Body::DYN_LDS, s,
-                     a, c);
-  return hipGetLastError();
+  return launch(ptb_kernel<Body>, dim3(c.workers), dim3(Body::THREADS), Body::DYN_LDS, s, a, c);
 }
 template <class Body>
 hipError_t init_t() {
@@ -952,8 +946,7 @@ int ptb_launch_segment(tally_job *j, uint32_t limit) {
   // slot's exit counter reaching the target, so it may start early; where kernels are run
   // strictly one at a time (counter collection under a profiler) it gives up when no
   // worker has shown up for a while, and a request raised after that goes unseen.
-  hipLaunchKernelGGL(relay_kernel, dim3(1), dim3(64), 0, j->ctl, c);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch(relay_kernel, dim3(1), dim3(64), 0, j->ctl, c);
   if (e != hipSuccess) {  // nothing was enqueued: the slot's bookkeeping is unchanged
     g_last_hip = (int)e;
     return TALLY_ERR_HIP;
@@ -994,9 +987,7 @@ int sliced_issue(tally_job *j) {
     HIPCHK(j->ops->sliced(j->be, j->args, n, c));
     j->issued += 1;
     j->next_off += n;
-    hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, j->be,
-                       (uint32_t *)(j->h_base_dev() + 128), j->issued);
-    HIPCHK(hipGetLastError());
+    HIPCHK(launch(marker_kernel, dim3(1), dim3(64), 0, j->be, (uint32_t *)(j->h_base_dev() + 128), j->issued));
   }
   return TALLY_OK;
 }
@@ -1489,8 +1480,7 @@ int tally_wait(tally_job *job, int *state) {
   bool marked = false;
   if (job->kind == KIND_PTB) {
     seq = ++job->ctx->wait_seq;
-    hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, job->be, (uint32_t *)(job->h_base_dev() + kHostEnded), seq);
-    marked = hipGetLastError() == hipSuccess;
+    marked = launch(marker_kernel, dim3(1), dim3(64), 0, job->be, (uint32_t *)(job->h_base_dev() + kHostEnded), seq) == hipSuccess;
   }
   for (uint32_t spins = 1;; ++spins) {
     int rc = tally_pump(job);
@@ -1574,9 +1564,7 @@ uint32_t tally_parts_executions(uint32_t pieces, uint64_t which) {
 
 int tally_marker(tally_ctx *ctx, int on_hi_stream, uint32_t value) {
   if (!ctx) return TALLY_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, on_hi_stream ? ctx->hi : ctx->be,
-                     ctx->marker_dev + (on_hi_stream ? 0 : 32), value);
-  HIPCHK(hipGetLastError());
+  HIPCHK(launch(marker_kernel, dim3(1), dim3(64), 0, on_hi_stream ? ctx->hi : ctx->be, ctx->marker_dev + (on_hi_stream ? 0 : 32), value));
   return TALLY_OK;
 }
 
@@ -1845,9 +1833,7 @@ int launch_be_item(tally_ctx *ctx, const tally_be_item *it, tally_job **out) {
   j->state = TALLY_JOB_RUNNING;
   hipError_t e = j->ops->native(j->be, j->args, j->grid, 0u);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(marker_kernel, dim3(1), dim3(64), 0, j->be,
-                       (uint32_t *)(j->h_base_dev() + 128), 1u);
-    e = hipGetLastError();
+    e = launch(marker_kernel, dim3(1), dim3(64), 0, j->be, (uint32_t *)(j->h_base_dev() + 128), 1u);
   }
   if (e != hipSuccess) {
     g_last_hip = (int)e;
