@@ -212,7 +212,7 @@ int tally_mfma_ceiling_tflops(tally_ctx *ctx, uint32_t reps, double *tflops);
 /* What one workgroup of a kernel occupies on a compute unit: LDS bytes, 64-lane waves,
  * registers per lane (vector and accumulation registers together, as allocated).
  * form 0: persistent-worker kernel, 1: original form (of the kernels that it chooses from by
- * the sizes, the largest of each figure).  The scheduler uses these figures, in the original
+ * the sizes beside best-effort jobs, the largest of each figure).  The scheduler uses these figures, in the original
  * form those of the kernel that the launch takes, for admission among best-effort clients and
  * to decide whether paused best-effort workers leave room for the high-priority kernels. */
 int tally_kernel_footprint(tally_ctx *ctx, uint32_t kernel_id, int form, uint32_t *lds_bytes,

@@ -417,6 +417,53 @@ struct GemmBodyT {
 using GemmBody = GemmBodyT<4>;
 using GemmN128Body = GemmBodyT<2>;
 
+// Blocks of 16x16 next to one another in a row of blocks, from column col0 on, to C.  B was the first MFMA
+// operand, so lane l, register r of a block holds row l%16, column 4 (l/16) + r: four neighbours of one row,
+// packed to 8 bytes.  Of two column blocks the swaps make eight neighbours per lane (group l/16 columns 8 (l/16)
+// .. +7 of the 32), so that whole 64-byte pieces leave (4352 x 4864 x 64 13.3 us; 18.8 as 32-byte pieces).
+template <bool NAN7FC0, int RB>
+__device__ __forceinline__ void store_blocks(const tally_gemm_bf16_args &a, uint32_t bz, uint32_t row, uint32_t col0,
+                                             uint32_t lane, const f32x4_t (&acc)[RB]) {
+#ifdef __HIP_DEVICE_COMPILE__
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  auto pack = [](float x, float y) {
+    if constexpr (NAN7FC0) return f32_to_bf16(x) | (uint32_t)f32_to_bf16(y) << 16;
+    const f32x2_t p = {x, y};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
+  };
+  auto store = [&](auto wide, int j) {                     // `wide` blocks from j on
+    constexpr int W = decltype(wide)::value;
+    uint32_t w[2 * W];
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      w[2 * e] = pack(acc[j + e][0], acc[j + e][1]);
+      w[2 * e + 1] = pack(acc[j + e][2], acc[j + e][3]);
+    }
+    if constexpr (W == 2) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(w[q]), "+v"(w[2 + q]));
+    }
+    const uint32_t col = col0 + 16 * j + (lane >> 4) * (4 * W);
+    if (row < a.m) {
+      uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
+      if (col + 4 * W <= a.n) {
+        // (rows start at any multiple of 2 bytes and are stored alike: 413 x 741 x 640 x 12 in 19.0 us,
+        // 23.5 with the widest aligned stores that each row allows)
+        __builtin_memcpy(g, w, 8 * W);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4 * W; ++e)
+          if (col + e < a.n) g[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
+      }
+    }
+  };
+#pragma unroll
+  for (int j = 0; j + 1 < RB; j += 2) store(std::integral_constant<int, 2>{}, j);
+  if constexpr (RB & 1) store(std::integral_constant<int, 1>{}, RB - 1);
+#endif
+}
+
 // The same operator with smaller tiles and predicated edges: (32 RA) x (32 RB) outputs per
 // workgroup, four waves in a 2x2 arrangement of RA x RB blocks of 16x16 each.  32x32 is the
 // logical block of the small or ragged GEMM (the high-priority inference-like layer, whose grid
@@ -635,44 +682,9 @@ struct GemmTileT {
         }
     };
     rest(rest, std::integral_constant<int, 0>{});
-    // B was the first MFMA operand, so lane l, register r of block (i, j) holds row 16 i + l%16,
-    // column 16 j + 4 (l/16) + r: four neighbours of one row, packed to 8 bytes.  Of two column
-    // blocks the swaps make eight neighbours per lane (group l/16 columns 8 (l/16) .. +7 of the
-    // 32), so that whole 64-byte pieces leave (4352 x 4864 x 64 13.3 us; 18.8 as 32-byte pieces).
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    auto pack = [](float x, float y) {
-      if constexpr (NAN7FC0) return f32_to_bf16(x) | (uint32_t)f32_to_bf16(y) << 16;
-      const f32x2_t p = {x, y};
-      return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
-    };
 #pragma unroll
-    for (int i = 0; i < RA; ++i) {
-      const uint32_t row = by * TM + (wm * RA + i) * 16 + (lane & 15);
-      const uint32_t col = bx * TN + wn * 16 * RB + (lane >> 4) * (4 * RB);
-      uint32_t w[2 * RB];
-#pragma unroll
-      for (int j = 0; j < RB; ++j) {
-        w[2 * j] = pack(acc[i][j][0], acc[i][j][1]);
-        w[2 * j + 1] = pack(acc[i][j][2], acc[i][j][3]);
-      }
-      if constexpr (RB == 2) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(w[q]), "+v"(w[2 + q]));
-      }
-      if (row < a.m) {
-        uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
-        if (col + 4 * RB <= a.n) {
-          // (rows start at any multiple of 2 bytes and are stored alike: 413 x 741 x 640 x 12 in 19.0 us,
-          // 23.5 with the widest aligned stores that each row allows)
-          __builtin_memcpy(g, w, 8 * RB);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4 * RB; ++e)
-            if (col + e < a.n) g[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
-        }
-      }
-    }
+    for (int i = 0; i < RA; ++i)
+      store_blocks<NAN7FC0>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);
 #endif
   }
 };
@@ -829,38 +841,153 @@ struct GemmWaveT {
         multiply(0);
       }
     }
-    // B was the first MFMA operand: four neighbouring columns per lane, or eight after the swaps (see GemmTileT)
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    auto pack = [](float x, float y) {
-      if constexpr (NAN7FC0) return f32_to_bf16(x) | (uint32_t)f32_to_bf16(y) << 16;
-      const f32x2_t p = {x, y};
-      return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, bf16x2_t));
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+      store_blocks<NAN7FC0>(a, bz, by * TM + i * 16 + (lane & 15), bx * TN, lane, acc[i]);
+#endif
+  }
+};
+// The same operator in tiles of (32 RA) x (32 RB), four waves in a 2x2 arrangement, whose operands go straight to
+// LDS, R stages of 64 k ahead in a ring, in the large tile's layout: for products between a few small tiles and
+// one 256x128 tile per compute unit, where nobody else needs the LDS (the tiles above are for those beside
+// best-effort workgroups).  Fragments are read a stage ahead, so that a stage has one barrier and a wave, alone on
+// its SIMD or one of two there, finds a read or a load to issue behind every MFMA.
+// What bounds it is what the compute unit brings in: a KB of operands takes 16 cycles to load to LDS, and 4 for
+// each of the two waves that read it, which is 96 (RA + RB) cycles a stage, against 32 RA RB of MFMA a wave: at
+// 128x128 768 and 512 (measured 810; 64x64 430 for 384).  Hence the times below, about 3 us and those stages.
+// us in tiles through registers, the best of 32x64, 64x64 and 128x64 / so, operands from the Infinity Cache:
+// 400 x 1200 x 2048 9.9 / 7.0 (32x64), 768 x 1024 x 2048 11.7 / 8.6 (64x64), 1000 x 1500 x 2048 16.1 / 10.8 (64x96),
+// 1500 x 1500 x 2048 22.1 / 14.1 (96x96), 1024 x 2048 x 2048 16.8 / 12.0 (128x64), 1000 x 2300 x 768 10.3 / 8.2 (128x96),
+// 512 x 6144 x 4096 44.0 / 27.9 (128x96), 2048 x 2048 x 2048 24.8 / 18.2 (128x128; 24.1 in 256x128).
+//
+// Workgroups go to the eight dies in turn.  Each die takes a run of tiles in an order that makes it a patch: bands
+// of H rows of tiles, column after column; the products of a batch follow one another, so that the dies' shares
+// differ by one tile (12 of 100 x 900 x 768 6.6 us, 13.4 with every product's remainder on the same dies).
+template <int RA, int RB, int R, bool NAN7FC0 = false>
+struct GemmRingT {
+  using Args = tally_gemm_bf16_args;
+  static constexpr int THREADS = 256;
+  static constexpr uint32_t TM = 32 * RA, TN = 32 * RB;
+  static constexpr int L = RA + RB;                       // loads of a wave and stage
+  static constexpr uint32_t SA = TM * 128, STAGE = SA + TN * 128;
+  static constexpr unsigned DYN_LDS = STAGE * R;
+  static constexpr int MIN_WAVES = 160 * 1024 / DYN_LDS;
+  static uint32_t groups(const Args &a) {                 // (as many for every die)
+    return (((a.n + TN - 1) / TN) * ((a.m + TM - 1) / TM) * a.batch + 7) / 8 * 8;
+  }
+  static __device__ __forceinline__ void run(const Args &a, uint32_t id, uint32_t, uint32_t) {
+#ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
+    extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
+    const uint32_t X = (a.n + TN - 1) / TN, Y = (a.m + TM - 1) / TM, T = X * Y * a.batch, q = T / 8, rest = T % 8;
+    const uint32_t die = id & 7, at = id >> 3;
+    if (at >= q + (die < rest ? 1 : 0)) return;
+    uint32_t t = die * q + (die < rest ? die : rest) + at;
+    const uint32_t bz = t / (X * Y);
+    t -= bz * (X * Y);
+    const uint32_t H = q >= 48 ? 8 : q >= 12 ? 4 : 2;
+    const uint32_t band = t / (H * X), in = t - band * H * X, h = Y - band * H < H ? Y - band * H : H;
+    const uint32_t bx = in / h, by = band * H + (in - bx * h);
+
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wm = wave >> 1, wn = wave & 1;
+    const uint32_t K = a.k;
+    const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
+    const uint32_t ns = (K + 63) / 64;
+    // A load moves 8 rows x 128 bytes to 1 KB of LDS; lane l supplies 16-byte slot l, that is row l/8, k-chunk
+    // (l%8) xor ((row/2)%8).  Load j of a wave takes rows 8 (4 j + wave) on.  A lane whose offset has its top bit
+    // set is outside the buffer and its slot is filled with zeros: rows past the matrix, k past K in a last stage
+    // that is half full, stages past the last one.
+    constexpr uint32_t OOB = 0x80000000u;
+    const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TM * LDA, 0x7fffffffu);
+    const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TN * LDB, 0x7fffffffu);
+    const uint32_t r8 = lane >> 3, c8 = (lane & 7) ^ (lane >> 4) ^ ((wave & 1) * 4);
+    uint32_t v[L];                                         // A's, then B's
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const bool isA = j < RA;
+      const uint32_t r = ((isA ? j : j - RA) * 4 + wave) * 8 + r8;
+      v[j] = (isA ? by * TM + r < a.m : bx * TN + r < a.n) ? (r * (isA ? LDA : LDB) + c8 * 8) * 2 : OOB;
+    }
+    const uint32_t base = (uint32_t)(uintptr_t)(lptr_t)tally_dyn_lds, end = base + R * STAGE;
+    uint32_t to = base + wave * 1024, so = 0, left = ns;   // the next stage to ask for: its place, its k in bytes, how many
+    auto open = [&]() {                                    // before a stage's loads
+      if (__builtin_expect(left <= 1, 0)) {
+        const uint32_t none = left == 0 ? OOB : (K & 32) && (c8 & 4) ? OOB : 0u;
+#pragma unroll
+        for (int j = 0; j < L; ++j) v[j] |= none;
+      }
+    };
+    auto load = [&](int j) {
+      const uint32_t at = to + (j < RA ? j * 4096 : SA + (j - RA) * 4096);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(j < RA ? rA : rB, (lptr_t)at, 16, v[j], so, 0, 0);
+    };
+    auto close = [&]() {
+      left = left ? left - 1 : 0;
+      so += 128;
+      to = to + STAGE >= end ? to + STAGE - R * STAGE : to + STAGE;
+    };
+    // lane l takes row l%16 of a 16-row block, k-chunk 4 kk + l/16; two sets, this stage's and the next one's
+    const uint32_t f_off = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16);
+    const uint32_t fA = wm * (16 * RA * 128) + f_off, fB = SA + wn * (16 * RB * 128) + f_off;
+    typedef const volatile __attribute__((address_space(3))) bf16x8_t *frag_t;   // (volatile: pinned)
+    bf16x8_t fa[2][2][RA], fb[2][2][RB];
+    uint32_t from = base;                                  // place of the next stage to read
+    auto read = [&](int f, int i) {                        // the i-th of 2 L
+      const int kk = i / L, j = i % L;
+      if (j < RB) fb[f][kk][j] = *(frag_t)(from + (fB ^ (kk * 64)) + j * 2048);
+      else fa[f][kk][j - RB] = *(frag_t)(from + (fA ^ (kk * 64)) + (j - RB) * 2048);
+    };
+    auto advance = [&]() { from = from + STAGE == end ? base : from + STAGE; };
+    f32x4_t acc[RA][RB];
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+#pragma unroll
+      for (int j = 0; j < RB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // A stage whose fragments are in registers or on their way there: once everybody's are, its place is free, and
+    // once only R - 2 stages are on their way the next one has landed.  Behind each MFMA goes a share of the next
+    // stage's reads and of the loads into the place that became free.
+    auto step = [&](int f) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * (R - 2)) : "memory");
+      __builtin_amdgcn_s_waitcnt(0xc07f);                  // lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      open();
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int M = 2 * RA * RB, O = 3 * L;
+#pragma unroll
+      for (int q = 0; q < M; ++q) {
+        const int kk = q / (RA * RB), i = q % (RA * RB) / RB, j = q % RB;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[f][kk][j], fa[f][kk][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int o = q * O / M; o < (q + 1) * O / M; ++o) {
+          if (o % 3 == 2) load(o / 3);
+          else read(f ^ 1, o / 3 * 2 + o % 3);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      advance();
+      close();
     };
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const uint32_t row = by * TM + i * 16 + (lane & 15), col = bx * TN + (lane >> 4) * (4 * NB);
-      uint32_t w[2 * NB];
+    for (int d = 0; d < R; ++d) {
+      open();
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        w[2 * j] = pack(acc[i][j][0], acc[i][j][1]);
-        w[2 * j + 1] = pack(acc[i][j][2], acc[i][j][3]);
-      }
-      if constexpr (NB == 2) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(w[q]), "+v"(w[2 + q]));
-      }
-      if (row < a.m) {
-        uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
-        if (col + 4 * NB <= a.n) {
-          __builtin_memcpy(g, w, 8 * NB);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4 * NB; ++e)
-            if (col + e < a.n) g[e] = (uint16_t)(w[e / 2] >> (16 * (e & 1)));
-        }
-      }
+      for (int j = 0; j < L; ++j) load(j);
+      close();
     }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * (R - 1)) : "memory");
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int i = 0; i < 2 * L; ++i) read(0, i);
+    advance();
+    for (uint32_t pairs = ns / 2; pairs; --pairs) { step(0); step(1); }
+    if (ns & 1) step(0);
+    // (nothing may land in LDS once it is somebody else's)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < RA; ++i)
+      store_blocks<NAN7FC0>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);
 #endif
   }
 };

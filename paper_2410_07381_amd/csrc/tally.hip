@@ -49,10 +49,11 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 // ---------------------------------------------------------------------------- registry
 typedef hipError_t (*FootprintFn)(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane);
-constexpr uint32_t kMaxNative = 9;   // kernels that one operator's original form chooses from
+constexpr uint32_t kMaxNative = 17;  // kernels that one operator's original form chooses from
+constexpr uint32_t kMaxShared = 9;   // the first of them: those that it takes beside best-effort jobs
 // How an original form is launched: on the high-priority stream; beside best-effort workgroups that leave
-// little LDS.
-constexpr uint32_t kUrgent = 1u, kBeside = 2u;
+// little LDS; beside any best-effort job.
+constexpr uint32_t kUrgent = 1u, kBeside = 2u, kShared = 4u;
 
 struct KernelOps {
   const char *name;
@@ -169,6 +170,9 @@ hipError_t footprint_attn(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_p
   *regs_per_lane = ((uint32_t)attr.numRegs + 7u) & ~7u;
   return hipSuccess;
 }
+hipError_t launch_native_attn(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
+  return launch_attn_decode(s, args, g, how & kUrgent);
+}
 uint32_t attn_choice(const void *args, uint32_t, uint64_t *groups) {
   tally_attn_decode_args a;
   memcpy(&a, args, sizeof(a));
@@ -255,15 +259,49 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // Beside best-effort workgroups that leave LDS for one of them on a compute unit (kBeside) more than 256 would
 // run in rounds: there operands go through registers (the nine-kernel layer beside paused 256x256 tiles 43.5 us
 // from the request to its completion, 54 in one-wave tiles throughout).
-enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16 };
-GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how) {
+// Where nobody else needs the LDS (kShared is not set) GemmRingT covers everything from k = 512 on that is less than
+// 160 tiles of 256x256.  The tile is the one for which the model at GemmRingT says the least: stages times
+// (RA + RB) for as many tiles as a compute unit gets, and 45 of those units, about 2 us, for every time it starts
+// anew.  One tile after the other on a unit that holds one at a time is a fifth slower than that (3000 x 3000 x
+// 2048 in 128x96 48.6 us, 42.7 in 96x96, two on a unit); 256x128 tiles count as 14.5.  Of 176 products of
+// k = 512 to 4096 it is within 8 % of the best tile for all but 9.  Below k = 512 tiles through registers start
+// and end faster (1024 x 1024 x 384 4.19 us, 4.30 in 64x64; 1024 x 2048 x 256 4.6 and 4.7).
+// They also replace the one-wave tiles where k is long for those:
+//   us one wave / so: 200 x 1000 x 2048 6.1 / 5.9 (from memory 8.4 / 6.0), 90 x 3400 x 1536 6.1 / 5.9 (9.5 / 8.0),
+//   3 of 100 x 900 x 1024 7.8 / 4.9; 128 x 3072 x 1024 4.3 / 5.0, 33 x 5000 x 1536 4.8 / 5.8 (7.8 / 7.2).
+enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16, kRing };
+#define GEMM_RINGS(X) X(1, 1, 8) X(1, 2, 6) X(2, 2, 5) X(2, 3, 7) X(4, 2, 3) X(3, 3, 3) X(4, 3, 5) X(4, 4, 4)
+#define GEMM_RING_ROW(ra, rb, r) {32 * ra, 32 * rb, GemmRingT<ra, rb, r>::MIN_WAVES},
+constexpr uint32_t kRings[][3] = {GEMM_RINGS(GEMM_RING_ROW)};   // tile, and how many fit a compute unit
+constexpr uint32_t kRingCount = sizeof(kRings) / sizeof(kRings[0]);
+static_assert(kMaxShared + kRingCount == kMaxNative && (uint32_t)GemmCover::kRing == kMaxShared, "one kernel each");
+GemmCover gemm_ring(const tally_gemm_bf16_args &a, bool n128) {
+  const uint64_t ns = cdiv(a.k, 64), rounds128 = cdiv((uint64_t)cdiv(a.m, 256) * cdiv(a.n, 128) * a.batch, 256);
+  GemmCover best = GemmCover::k256x128;
+  uint64_t least = n128 ? rounds128 * (145 * ns + 450) : ~0ull;
+  for (uint32_t i = 0; i < kRingCount; ++i) {
+    const uint64_t t = (uint64_t)cdiv(a.m, kRings[i][0]) * cdiv(a.n, kRings[i][1]) * a.batch, rounds = cdiv(t, 256);
+    const uint64_t unit = kRings[i][2] == 1 && rounds > 1 ? 12 : 10;
+    const uint64_t cost = rounds * ns * ((kRings[i][0] + kRings[i][1]) / 32) * unit + cdiv(t, 256 * kRings[i][2]) * 450;
+    if (cost < least) {
+      least = cost;
+      best = (GemmCover)((uint32_t)GemmCover::kRing + i);
+    }
+  }
+  return best;
+}
+// large: blocks of 256 rows, which cover the output without a remainder
+GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how, bool large) {
   const uint64_t t16 = (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch, t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
-  const bool odd = cdiv(a.m, 16) & 1;
+  const bool odd = cdiv(a.m, 16) & 1, ring = !(how & kShared) && a.k >= 512 && t64 <= (1u << 20);   // (a flat grid)
   if (a.k > 128 && (!(how & kBeside) || t16 <= 256)) {
     if (t16 <= 768) return GemmCover::kWave16;
-    if (a.k <= (t16 <= 1024 ? 2048u : t16 <= 1536 ? (odd ? 1024u : 3072u) : t16 <= 2048 ? 768u : 0u))
-      return odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
+    const uint32_t up_to = t16 <= 1024 ? (ring ? 1536u : 2048u)
+                         : t16 <= 1536 ? (odd ? (ring ? 768u : 1024u) : ring ? 1280u : 3072u)
+                         : t16 <= 2048 ? (odd && ring ? 512u : 768u) : 0u;
+    if (a.k <= up_to) return odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
   }
+  if (ring && !(large && (uint64_t)cdiv(a.n, 256) * cdiv(a.m, 256) * a.batch >= 160)) return gemm_ring(a, large);
   if ((uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32;
   if ((uint64_t)cdiv(a.n, 64) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32x64;
   if (t64 <= 512) return GemmCover::k64;
@@ -275,6 +313,29 @@ template <class Body>
 hipError_t launch_gemm_cover(hipStream_t s, const tally_gemm_bf16_args &a, uint32_t tn, uint32_t tm, uint32_t how) {
   return launch_native_t<Body>(s, &a, {cdiv(a.n, tn), cdiv(a.m, tm), a.batch}, how);
 }
+template <bool CANON>
+hipError_t launch_gemm_ring(hipStream_t s, const tally_gemm_bf16_args &a, GemmCover c, uint32_t how) {
+  uint32_t i = (uint32_t)GemmCover::kRing;
+#define GEMM_RING_LAUNCH(ra, rb, r)                                                                        \
+  if ((uint32_t)c == i++)                                                                                  \
+    return launch_native_t<GemmRingT<ra, rb, r, CANON>>(s, &a, {GemmRingT<ra, rb, r>::groups(a), 1, 1}, how);
+  GEMM_RINGS(GEMM_RING_LAUNCH)
+  return hipErrorInvalidValue;
+}
+template <bool CANON>
+hipError_t init_gemm_rings() {
+  hipError_t e = hipSuccess;
+#define GEMM_RING_INIT(ra, rb, r)                                                                          \
+  if (e == hipSuccess && GemmRingT<ra, rb, r>::DYN_LDS > 64 * 1024)                                        \
+    e = hipFuncSetAttribute((const void *)native_kernel<GemmRingT<ra, rb, r, CANON>>,                      \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, GemmRingT<ra, rb, r>::DYN_LDS);
+  GEMM_RINGS(GEMM_RING_INIT)
+  return e;
+}
+hipError_t init_gemm_small() {
+  const hipError_t e = init_t<GemmSmallBody>();
+  return e == hipSuccess ? init_gemm_rings<true>() : e;
+}
 template <int NA, int NB, bool CANON>
 hipError_t launch_gemm_wave(hipStream_t s, const tally_gemm_bf16_args &a, uint32_t how) {
   const dim3 g = GemmWaveT<NA, NB, CANON>::grid(a);
@@ -285,7 +346,9 @@ template <class Body>
 hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  switch (gemm_cover(a, how)) {
+  const GemmCover c = gemm_cover(a, how, true);
+  if (c >= GemmCover::kRing) return launch_gemm_ring<false>(s, a, c, how);
+  switch (c) {
     case GemmCover::kWave16: return launch_gemm_wave<1, 1, false>(s, a, how);
     case GemmCover::kWave16x32: return launch_gemm_wave<1, 2, false>(s, a, how);
     case GemmCover::kWave32x16: return launch_gemm_wave<2, 1, false>(s, a, how);
@@ -301,14 +364,16 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
 // best-effort tile.  128x64 tiles pay from two per compute unit (512 x 4096 x 4096, 256 of them,
 // 29 us with 64x64 and 32; 1024 x 4096 x 4096, 512, 54 and 47).
 GemmCover gemm_cover_small(const tally_gemm_bf16_args &a, uint32_t how) {
-  const GemmCover c = gemm_cover(a, how);
+  const GemmCover c = gemm_cover(a, how, false);
   if (c <= GemmCover::k32x64 || c >= GemmCover::kWave16) return c;
   return (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512 ? GemmCover::k128x64 : GemmCover::k64;
 }
 hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3, uint32_t how) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  switch (gemm_cover_small(a, how)) {
+  const GemmCover c = gemm_cover_small(a, how);
+  if (c >= GemmCover::kRing) return launch_gemm_ring<true>(s, a, c, how);
+  switch (c) {
     case GemmCover::kWave16: return launch_gemm_wave<1, 1, true>(s, a, how);
     case GemmCover::kWave16x32: return launch_gemm_wave<1, 2, true>(s, a, how);
     case GemmCover::kWave32x16: return launch_gemm_wave<2, 1, true>(s, a, how);
@@ -321,15 +386,15 @@ hipError_t launch_native_gemm_small(hipStream_t s, const void *args, tally_dim3,
 // which of the kernels in kOps (in the order of GemmCover) and how many workgroups of it
 uint32_t gemm_choice(const tally_gemm_bf16_args &a, GemmCover c, uint32_t tn, uint64_t *groups) {
   const uint32_t tile[][2] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}, {256, 128}, {256, tn}, {16, 16}, {16, 32}, {32, 16}};
-  const uint32_t i = (uint32_t)c;
-  *groups = (uint64_t)cdiv(a.m, tile[i][0]) * cdiv(a.n, tile[i][1]) * a.batch;
+  const uint32_t i = (uint32_t)c, *t = c >= GemmCover::kRing ? kRings[i - (uint32_t)GemmCover::kRing] : tile[i];
+  *groups = (uint64_t)cdiv(a.m, t[0]) * cdiv(a.n, t[1]) * a.batch;
   return i;
 }
 template <uint32_t TN>
 uint32_t gemm_native_choice(const void *args, uint32_t how, uint64_t *groups) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  return gemm_choice(a, gemm_cover(a, how), TN, groups);
+  return gemm_choice(a, gemm_cover(a, how, true), TN, groups);
 }
 uint32_t gemm_small_native_choice(const void *args, uint32_t how, uint64_t *groups) {
   tally_gemm_bf16_args a;
@@ -395,6 +460,7 @@ struct GemmParts {
         e = hipFuncSetAttribute((const void *)ptb_kernel<Tail>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 Tail::DYN_LDS);
     }
+    if (e == hipSuccess) e = init_gemm_rings<false>();
     return e;
   }
 };
@@ -537,6 +603,8 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
   footprint_native_t<GemmTileT<2, 2, canon>>, footprint_native_t<GemmTileT<4, 2, canon>>
 #define GEMM_WAVE_TILES(canon)                                                                            \
   footprint_native_t<GemmWaveT<1, 1, canon>>, footprint_native_t<GemmWaveT<1, 2, canon>>, footprint_native_t<GemmWaveT<2, 1, canon>>
+#define GEMM_RING_FOOT_F(ra, rb, r) , footprint_native_t<GemmRingT<ra, rb, r, false>>
+#define GEMM_RING_FOOT_T(ra, rb, r) , footprint_native_t<GemmRingT<ra, rb, r, true>>
 #define OPS_ROWS(Wide, Narrow, NarrowDeep, Team, occupancy, nm, gridfn)                                   \
   {nm, sizeof(Wide::Args), true, gridfn, launch_native_rows_t<Wide, Narrow, Team>,                        \
    launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
@@ -547,7 +615,7 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
    footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
-                       GEMM_WAVE_TILES(false)},                                                           \
+                       GEMM_WAVE_TILES(false) GEMM_RINGS(GEMM_RING_FOOT_F)},                                                           \
    gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr, false}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
@@ -560,12 +628,12 @@ const KernelOps kOps[TALLY_K_COUNT] = {
              "softmax_f32", grid_softmax),
     OPS_ROWS(LayerNormBody, LayerNormNarrowBody, LayerNormNarrowDeepBody, LayerNormTeamBody,
              (occupancy_capped_t<LayerNormBody, 2>), "layernorm_f32", grid_layernorm),
-    {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_attn_decode,
+    {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_native_attn,
      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice,
      nullptr, nullptr, nullptr, nullptr, false},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
-     launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_t<GemmSmallBody>, occupancy_t<GemmSmallBody>,
-     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, GEMM_WAVE_TILES(true)},
+     launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_gemm_small, occupancy_t<GemmSmallBody>,
+     pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, GEMM_WAVE_TILES(true) GEMM_RINGS(GEMM_RING_FOOT_T)},
      gemm_small_native_choice,
      gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes,
      false},
@@ -651,7 +719,8 @@ struct tally_ctx {
   uint32_t yield_every;      // steps between two looks at the pause word (a power of two)
   void *static_attn_scratch; // this device's address of static_scratch
   std::atomic<uint32_t> wait_seq;   // numbers the markers that waits put on a stream
-  std::atomic<int> heavy_jobs;      // jobs whose workgroups leave little LDS (leaves_little_lds), launched or about to be
+  std::atomic<int> jobs;            // best-effort jobs, launched or about to be
+  std::atomic<int> heavy_jobs;      // those whose workgroups leave little LDS (leaves_little_lds)
   int device;
   int live_jobs;
   // profile-guided configuration (Section 4.2): per (kernel, grid, block) the candidate
@@ -748,14 +817,15 @@ int settle_relay(tally_ctx *ctx, int slot) {
 
 // Does a workgroup of `foot` leave LDS for no more than two one-wave GEMM tiles beside it?
 bool leaves_little_lds(const tally_ctx *ctx, const uint32_t *foot) { return foot[0] + 3 * kWaveTileLds > ctx->lds_per_cu; }
-uint32_t hi_launch(const tally_ctx *ctx) { return kUrgent | (ctx->heavy_jobs.load() > 0 ? kBeside : 0u); }
+uint32_t be_launch(const tally_ctx *ctx) { return ctx->jobs.load() > 0 ? kShared : 0u; }
+uint32_t hi_launch(const tally_ctx *ctx) { return kUrgent | be_launch(ctx) | (ctx->heavy_jobs.load() > 0 ? kBeside : 0u); }
 // What one workgroup of a job of this kind occupies.
 const uint32_t *job_footprint(const tally_ctx *ctx, const tally_kernel_desc *desc, int kind, uint64_t *groups) {
   const KernelOps &ops = kOps[desc->kernel_id];
   if (kind == KIND_PTB) return ctx->foot_worker[desc->kernel_id];
   uint32_t i = 0;
   if (kind == KIND_SLICED) i = ops.sliced_choice ? ops.sliced_choice(desc->args) : 0;
-  else if (ops.native_choice) i = ops.native_choice(desc->args, 0u, groups);
+  else if (ops.native_choice) i = ops.native_choice(desc->args, kShared, groups);
   return ctx->foot_native[desc->kernel_id][i];
 }
 
@@ -817,6 +887,7 @@ int new_job(tally_ctx *ctx, const tally_kernel_desc *desc, int kind, int coverag
   ctx->slot_used[slot] = true;
   uint64_t groups;
   j->heavy = leaves_little_lds(ctx, job_footprint(ctx, desc, kind, &groups));
+  ctx->jobs++;
   if (j->heavy) ctx->heavy_jobs++;
   ctx->live_jobs++;
   *out = j;
@@ -1141,7 +1212,7 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
   memset(c->slot_relay, 0, sizeof(c->slot_relay));
   c->live_jobs = 0;
   c->wait_seq = 0;
-  c->heavy_jobs = 0;
+  c->jobs = c->heavy_jobs = 0;
   c->next_slot = 0;
   c->n_shunned = 0;
   c->n_side = 0;
@@ -1274,7 +1345,7 @@ int tally_launch_native(tally_ctx *ctx, const tally_kernel_desc *desc, int on_hi
   tally_dim3 g;
   int rc = check_desc(desc, &ops, &g);
   if (rc) return rc;
-  HIPCHK(ops->native(on_hi_stream ? ctx->hi : ctx->be, desc->args, g, on_hi_stream ? hi_launch(ctx) : 0u));
+  HIPCHK(ops->native(on_hi_stream ? ctx->hi : ctx->be, desc->args, g, on_hi_stream ? hi_launch(ctx) : be_launch(ctx)));
   return TALLY_OK;
 }
 
@@ -1381,7 +1452,7 @@ int tally_kernel_footprint(tally_ctx *ctx, uint32_t kernel_id, int form, uint32_
     return TALLY_ERR_INVALID_ARG;
   if (form == 0 && !kOps[kernel_id].transformable) return TALLY_ERR_UNSUPPORTED;
   uint32_t most[3] = {0, 0, 0};
-  for (uint32_t f = 0; f < (form == 0 ? 1u : kMaxNative); ++f)
+  for (uint32_t f = 0; f < (form == 0 ? 1u : kMaxShared); ++f)
     for (int i = 0; i < 3; ++i) {
       const uint32_t v = form == 0 ? ctx->foot_worker[kernel_id][i] : ctx->foot_native[kernel_id][f][i];
       if (v > most[i]) most[i] = v;
@@ -1526,6 +1597,7 @@ int tally_job_free(tally_job *job) {
   }
   ctx->slot_used[job->slot] = false;
   if (job->heavy) ctx->heavy_jobs--;
+  ctx->jobs--;
   ctx->live_jobs--;
   delete job;
   return TALLY_OK;
@@ -1831,7 +1903,7 @@ int launch_be_item(tally_ctx *ctx, const tally_be_item *it, tally_job **out) {
   int rc = new_job(ctx, it->kernel, KIND_NATIVE, 0, &j);
   if (rc) return rc;
   j->state = TALLY_JOB_RUNNING;
-  hipError_t e = j->ops->native(j->be, j->args, j->grid, 0u);
+  hipError_t e = j->ops->native(j->be, j->args, j->grid, kShared);
   if (e == hipSuccess) {
     e = launch(marker_kernel, dim3(1), dim3(64), 0, j->be, (uint32_t *)(j->h_base_dev() + 128), 1u);
   }
@@ -2133,9 +2205,10 @@ void be_thread_main(tally_sched *s) {
           // A request's kernels are chosen by what is resident.  The job counts before the flag is looked at
           // again: either it is seen there or the request is seen here.
           const bool admitted = admit(c, l, w, r);
-          if (admitted) ctx->heavy_jobs++;
+          if (admitted) { ctx->jobs++; ctx->heavy_jobs++; }
           if (admitted && s->opts.policy != 2 && s->hi_active.load()) {
             ctx->heavy_jobs--;
+            ctx->jobs--;
             vacate(cl);
           } else if (admitted) {
             ctx->cur_be = cl.be;
@@ -2147,6 +2220,7 @@ void be_thread_main(tally_sched *s) {
             ctx->cur_be = ctx->be;
             ctx->cur_ctl = ctx->ctl;
             ctx->heavy_jobs--;
+            ctx->jobs--;
             if (rc) break;
             cl.profiling = prof;
             set_job(cl, j);

@@ -540,6 +540,45 @@ def test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch):
     assert ((Cd[:, row, col].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + k * 2.0 ** -24 * mag).all()
 
 
+@pytest.mark.parametrize("m,n,k,batch", [
+    (512, 500, 1568, 1), (500, 512, 2080, 1),                                   # 32x32: as many stages ahead, more
+    (225, 1250, 544, 5), (399, 1200, 1056, 1),                                  # 32x64
+    (300, 3000, 512, 1), (1, 16300, 2080, 1), (1000, 1025, 544, 1),             # 64x64: one die with a tile more
+    (777, 1777, 544, 1), (100, 900, 576, 12),                                   # 64x96: one row of tiles a band
+    (1500, 1500, 544, 1), (413, 741, 544, 12),                                  # 96x96
+    (1025, 2047, 544, 1), (256, 8192, 512, 1), (129, 65, 512, 128),             # 128x64
+    (1000, 2300, 512, 1), (1000, 2300, 800, 1), (384, 8000, 544, 1),            # 128x96
+    (2000, 2001, 544, 1), (1024, 1024, 1056, 3), (2048, 4100, 576, 1)])         # 128x128, rounds of them
+def test_gemm_tiles_whose_operands_go_straight_to_lds(env, m, n, k, batch):
+    """Products between a few small tiles and one large tile per compute unit, k from 512 on, while no
+    best-effort job is there: fewer stages than the ring has places, as many and more, odd and even, a last
+    stage half full, rows and columns past the matrix, bands of tiles that are cut short; and the tiles taken
+    beside a job (here a stopped one) give the same bits."""
+    B, ctx, torch = env
+    test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + n + k)
+    A = torch.randn(batch, m, k, device="cuda", generator=gen).to(torch.bfloat16)
+    Bt = torch.randn(batch, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.full((batch, m, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C, small=True)
+    x, y = torch.zeros(4096, device="cuda"), torch.zeros(4096, device="cuda")
+    torch.cuda.synchronize()
+    ctx.launch_native(kern)
+    torch.cuda.synchronize()
+    alone = C.clone()
+    C.fill_(7.0)
+    torch.cuda.synchronize()
+    job = ctx.launch_ptb(B.saxpy(x, y, 1.0), 1, stop_at=3)
+    assert job.wait() == B.JOB_STOPPED
+    ctx.launch_native(kern, hi=True)
+    torch.cuda.synchronize()
+    job.resume()
+    job.wait()
+    job.free()
+    assert torch.equal(C, alone)
+
+
 @pytest.mark.parametrize("tile,m,n,k,batch", [
     ("256", 256, 256, 96, 1), ("256", 512, 512, 1056, 1), ("256", 512, 768, 288, 1), ("256", 1024, 1024, 544, 1),
     ("256", 1024, 2048, 2080, 1), ("256", 2048, 2048, 64, 1), ("256", 4352, 4864, 96, 1), ("256", 1280, 1280, 2048, 1),
