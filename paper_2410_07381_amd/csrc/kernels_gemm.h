@@ -854,15 +854,17 @@ struct GemmWaveT {
 // its SIMD or one of two there, finds a read or a load to issue behind every MFMA.
 // What bounds it is what the compute unit brings in: a KB of operands takes 16 cycles to load to LDS, and 4 for
 // each of the two waves that read it, which is 96 (RA + RB) cycles a stage, against 32 RA RB of MFMA a wave: at
-// 128x128 768 and 512 (measured 810; 64x64 430 for 384).  Hence the times below, about 3 us and those stages.
+// 128x128 768 and 512 (measured 810; 64x64 430 for 384).  Hence the times below, about 2.5 us and those stages.
+// The last R stages ask for nothing any more (as loads outside the buffers, which take as long as others, they were
+// 0.5 us of every tile).
 // us in tiles through registers, the best of 32x64, 64x64 and 128x64 / so, operands from the Infinity Cache:
-// 400 x 1200 x 2048 9.9 / 7.0 (32x64), 768 x 1024 x 2048 11.7 / 8.6 (64x64), 1000 x 1500 x 2048 16.1 / 10.8 (64x96),
-// 1500 x 1500 x 2048 22.1 / 14.1 (96x96), 1024 x 2048 x 2048 16.8 / 12.0 (128x64), 1000 x 2300 x 768 10.3 / 8.2 (128x96),
-// 512 x 6144 x 4096 44.0 / 27.9 (128x96), 2048 x 2048 x 2048 24.8 / 18.2 (128x128; 24.1 in 256x128).
+// 400 x 1200 x 2048 9.9 / 7.0 (32x64), 1024 x 1024 x 2048 12.0 / 8.4 (64x64), 1000 x 1500 x 2048 16.5 / 9.9 (64x96),
+// 1500 x 1500 x 2048 22.0 / 13.7 (96x96), 1024 x 2048 x 2048 16.8 / 11.6 (128x64), 1000 x 2300 x 768 10.6 / 7.6 (128x96),
+// 512 x 6144 x 4096 43.1 / 26.1 (128x96), 2048 x 2048 x 2048 25.8 / 18.0 (128x128; 24.1 in 256x128).
 //
 // Workgroups go to the eight dies in turn.  Each die takes a run of tiles in an order that makes it a patch: bands
 // of H rows of tiles, column after column; the products of a batch follow one another, so that the dies' shares
-// differ by one tile (12 of 100 x 900 x 768 6.6 us, 13.4 with every product's remainder on the same dies).
+// differ by one tile (12 of 100 x 900 x 768 6.1 us, 13.4 with every product's remainder on the same dies).
 template <int RA, int RB, int R, bool NAN7FC0 = false>
 struct GemmRingT {
   using Args = tally_gemm_bf16_args;
@@ -872,12 +874,19 @@ struct GemmRingT {
   static constexpr uint32_t SA = TM * 128, STAGE = SA + TN * 128;
   static constexpr unsigned DYN_LDS = STAGE * R;
   static constexpr int MIN_WAVES = 160 * 1024 / DYN_LDS;
+  static constexpr bool YIELDS = true;
+  static constexpr int ROUND = 4;                         // stages between two looks at the pause word, at least
+  // share of a tile between asking for the pause word and pausing on the answer a question later, or from the last
+  // answer to the end (see look_round); host side, for turnaround estimates
+  static double pause_fraction(const Args &a, uint32_t every) {
+    const uint32_t ns = (a.k + 63) / 64, apart = every / 2 > ROUND ? every / 2 : ROUND;
+    return ns > apart + ROUND + R ? (double)(apart + ROUND + R) / ns : 1.0;
+  }
   static uint32_t groups(const Args &a) {                 // (as many for every die)
     return (((a.n + TN - 1) / TN) * ((a.m + TM - 1) / TM) * a.batch + 7) / 8 * 8;
   }
   static __device__ __forceinline__ void run(const Args &a, uint32_t id, uint32_t, uint32_t) {
 #ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
-    extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
     const uint32_t X = (a.n + TN - 1) / TN, Y = (a.m + TM - 1) / TM, T = X * Y * a.batch, q = T / 8, rest = T % 8;
     const uint32_t die = id & 7, at = id >> 3;
     if (at >= q + (die < rest ? 1 : 0)) return;
@@ -886,8 +895,17 @@ struct GemmRingT {
     t -= bz * (X * Y);
     const uint32_t H = q >= 48 ? 8 : q >= 12 ? 4 : 2;
     const uint32_t band = t / (H * X), in = t - band * H * X, h = Y - band * H < H ? Y - band * H : H;
-    const uint32_t bx = in / h, by = band * H + (in - bx * h);
-
+    const uint32_t bx = in / h;
+    run_tile<false>(a, bx, band * H + (in - bx * h), bz, YieldCtl{nullptr, 0, 0, 15, false});
+#endif
+  }
+  static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
+    run_tile<true>(a, bx, by, bz, ctl);
+  }
+  template <bool YIELD>
+  static __device__ __forceinline__ void run_tile(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
+#ifdef __HIP_DEVICE_COMPILE__
+    extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t wm = wave >> 1, wn = wave & 1;
@@ -897,7 +915,7 @@ struct GemmRingT {
     // A load moves 8 rows x 128 bytes to 1 KB of LDS; lane l supplies 16-byte slot l, that is row l/8, k-chunk
     // (l%8) xor ((row/2)%8).  Load j of a wave takes rows 8 (4 j + wave) on.  A lane whose offset has its top bit
     // set is outside the buffer and its slot is filled with zeros: rows past the matrix, k past K in a last stage
-    // that is half full, stages past the last one.
+    // that is half full.
     constexpr uint32_t OOB = 0x80000000u;
     const buf_t rA = make_buf(a.A + bz * a.stride_a + (uint64_t)by * TM * LDA, 0x7fffffffu);
     const buf_t rB = make_buf(a.Bt + bz * a.stride_b + (uint64_t)bx * TN * LDB, 0x7fffffffu);
@@ -912,8 +930,8 @@ struct GemmRingT {
     const uint32_t base = (uint32_t)(uintptr_t)(lptr_t)tally_dyn_lds, end = base + R * STAGE;
     uint32_t to = base + wave * 1024, so = 0, left = ns;   // the next stage to ask for: its place, its k in bytes, how many
     auto open = [&]() {                                    // before a stage's loads
-      if (__builtin_expect(left <= 1, 0)) {
-        const uint32_t none = left == 0 ? OOB : (K & 32) && (c8 & 4) ? OOB : 0u;
+      if (--left == 0 && (K & 32)) {
+        const uint32_t none = c8 & 4 ? OOB : 0u;
 #pragma unroll
         for (int j = 0; j < L; ++j) v[j] |= none;
       }
@@ -923,7 +941,6 @@ struct GemmRingT {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(j < RA ? rA : rB, (lptr_t)at, 16, v[j], so, 0, 0);
     };
     auto close = [&]() {
-      left = left ? left - 1 : 0;
       so += 128;
       to = to + STAGE >= end ? to + STAGE - R * STAGE : to + STAGE;
     };
@@ -945,13 +962,15 @@ struct GemmRingT {
 #pragma unroll
       for (int j = 0; j < RB; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // A stage whose fragments are in registers or on their way there: once everybody's are, its place is free, and
-    // once only R - 2 stages are on their way the next one has landed.  Behind each MFMA goes a share of the next
-    // stage's reads and of the loads into the place that became free.
-    auto step = [&](int f) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * (R - 2)) : "memory");
+    // once no more than AFTER stages are on their way the next one has landed.  Behind each MFMA goes a share of the
+    // next stage's reads and of the loads into the place that became free.
+    auto step = [&](auto after, auto set, auto next, auto more) {
+      constexpr int AFTER = decltype(after)::value, f = decltype(set)::value;
+      constexpr bool READ = decltype(next)::value, LOAD = decltype(more)::value;
+      if constexpr (READ) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * AFTER) : "memory");
       __builtin_amdgcn_s_waitcnt(0xc07f);                  // lgkmcnt(0)
-      __builtin_amdgcn_s_barrier();
-      open();
+      if constexpr (READ) __builtin_amdgcn_s_barrier();
+      if constexpr (LOAD) open();
       __builtin_amdgcn_sched_barrier(0);
       constexpr int M = 2 * RA * RB, O = 3 * L;
 #pragma unroll
@@ -961,30 +980,97 @@ struct GemmRingT {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int o = q * O / M; o < (q + 1) * O / M; ++o) {
-          if (o % 3 == 2) load(o / 3);
-          else read(f ^ 1, o / 3 * 2 + o % 3);
+          if (o % 3 != 2 && READ) read(f ^ 1, o / 3 * 2 + o % 3);
+          if (o % 3 == 2 && LOAD) load(o / 3);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      advance();
-      close();
+      if constexpr (READ) advance();
+      if constexpr (LOAD) close();
     };
+    typedef std::integral_constant<int, 0> set0;
+    typedef std::integral_constant<int, 1> set1;
+    typedef std::integral_constant<int, R - 2> full;
+    auto pair = [&]() {
+      step(full{}, set0{}, std::true_type{}, std::true_type{});
+      step(full{}, set1{}, std::true_type{}, std::true_type{});
+    };
+    auto to_set0 = [&]() {                                 // the fragments just read
 #pragma unroll
-    for (int d = 0; d < R; ++d) {
+      for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+        for (int i = 0; i < RA; ++i) fa[0][kk][i] = fa[1][kk][i];
+#pragma unroll
+        for (int j = 0; j < RB; ++j) fb[0][kk][j] = fb[1][kk][j];
+      }
+    };
+    auto begin = [&]() {
+#pragma unroll
+      for (int i = 0; i < 2 * L; ++i) read(0, i);
+      advance();
+    };
+    auto request = [&]() {
       open();
 #pragma unroll
       for (int j = 0; j < L; ++j) load(j);
       close();
+    };
+    // the last stages, AFTER of them behind this one: nothing is asked for any more
+    auto finish = [&](auto &&self, auto after, auto set) -> void {
+      constexpr int AFTER = decltype(after)::value, f = decltype(set)::value;
+      step(std::integral_constant<int, (AFTER > 0 ? AFTER - 1 : 0)>{}, set, std::bool_constant<(AFTER > 0)>{}, std::false_type{});
+      if constexpr (AFTER > 0) self(self, std::integral_constant<int, AFTER - 1>{}, std::integral_constant<int, f ^ 1>{});
+    };
+    // Looks at the pause word (see GemmTileT): one lane asks among the operands' loads at the start of a round and
+    // has the answer at the start of the next, when no operand that was asked for after it is waited for yet.
+    uint32_t pause_left = ctl.ticks, look = 0;
+    const buf_t rF = make_buf(ctl.flag, YIELD && ctl.ticks != 0 ? 4 : 0);
+    const uint32_t v_look = threadIdx.x == 0 ? 0u : OOB, look_mask = (ctl.mask >> 1) & ~(ROUND - 1u);   // in stages
+    auto look_round = [&](uint32_t c) {
+      if (__builtin_amdgcn_readfirstlane(look) == ctl.epoch) yield_while_preempted(ctl, pause_left);
+      look = __builtin_amdgcn_raw_buffer_load_b32(rF, v_look | ((c & look_mask) == look_mask ? 0u : OOB), 0, 16);  // (sc1)
+    };
+    if constexpr (YIELD) {
+      if (ctl.look_first && ctl.ticks != 0 && wave == 0 && ns >= 16) yield_while_preempted(ctl, pause_left);
+      __syncthreads();                                     // (LDS may have been another tile's)
     }
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * (R - 1)) : "memory");
-    __builtin_amdgcn_s_barrier();
+    if (ns >= (uint32_t)R) {
 #pragma unroll
-    for (int i = 0; i < 2 * L; ++i) read(0, i);
-    advance();
-    for (uint32_t pairs = ns / 2; pairs; --pairs) { step(0); step(1); }
-    if (ns & 1) step(0);
-    // (nothing may land in LDS once it is somebody else's)
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      for (int d = 0; d < R; ++d) request();
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L * (R - 1)) : "memory");
+      __builtin_amdgcn_s_barrier();
+      begin();
+      uint32_t c = ns - R;
+      if (c & 1) {
+        step(full{}, set0{}, std::true_type{}, std::true_type{});
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        to_set0();
+      }
+      c >>= 1;
+      if constexpr (YIELD) {
+        static_assert(ROUND == 4, "two pairs");
+        if (c & 1) pair();
+        for (c >>= 1; c; --c) {
+          look_round(c * ROUND);
+          pair();
+          pair();
+        }
+      } else {
+        for (; c; --c) pair();
+      }
+      finish(finish, std::integral_constant<int, R - 1>{}, set0{});
+    } else {
+      for (uint32_t d = 0; d < ns; ++d) request();
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      begin();
+      for (uint32_t d = 1; d < ns; ++d) {
+        step(set0{}, set0{}, std::true_type{}, std::false_type{});
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        to_set0();
+      }
+      step(set0{}, set0{}, std::false_type{}, std::false_type{});
+    }
 #pragma unroll
     for (int i = 0; i < RA; ++i)
       store_blocks<NAN7FC0>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);

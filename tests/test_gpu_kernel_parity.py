@@ -548,9 +548,10 @@ def test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch):
     (1500, 1500, 544, 1), (413, 741, 544, 12),                                  # 96x96
     (1025, 2047, 544, 1), (256, 8192, 512, 1), (129, 65, 512, 128),             # 128x64
     (1000, 2300, 512, 1), (1000, 2300, 800, 1), (384, 8000, 544, 1),            # 128x96
-    (2000, 2001, 544, 1), (1024, 1024, 1056, 3), (2048, 4100, 576, 1)])         # 128x128, rounds of them
+    (2000, 2001, 544, 1), (1024, 1024, 1056, 3), (2048, 4100, 576, 1),          # 128x128, rounds of them
+    (1024, 1000, 320, 1), (1025, 2047, 128, 1), (413, 741, 160, 12), (999, 2300, 256, 1), (1500, 1500, 2080, 1)])
 def test_gemm_tiles_whose_operands_go_straight_to_lds(env, m, n, k, batch):
-    """Products between a few small tiles and one large tile per compute unit, k from 512 on, while no
+    """Products between a few small tiles and one large tile per compute unit, while no
     best-effort job is there: fewer stages than the ring has places, as many and more, odd and even, a last
     stage half full, rows and columns past the matrix, bands of tiles that are cut short; and the tiles taken
     beside a job (here a stopped one) give the same bits."""
