@@ -469,8 +469,8 @@ __device__ __forceinline__ void store_blocks(const tally_gemm_bf16_args &a, uint
 // logical block of the small or ragged GEMM (the high-priority inference-like layer, whose grid
 // is often far smaller than the GPU and where every kernel is a chain of memory latencies);
 // 32x64, 64x64 and 128x64 cover its original form where the 32x32 tiles are more than the
-// compute units, and they are what the large tile's grid is covered with, or its blocks are
-// handed out in, where there are too few of its own (see gemm_cover and GemmParts).
+// compute units, and the large tile's where there are too few of those, beside best-effort jobs
+// and where K is short (see gemm_cover).
 //
 // Every tile of every size, the 256-row tiles included, adds its products in the same order:
 // one accumulator per output, k ascending, one 16x16x32 MFMA per 32 of it with B first, one
@@ -875,12 +875,14 @@ struct GemmRingT {
   static constexpr unsigned DYN_LDS = STAGE * R;
   static constexpr int MIN_WAVES = 160 * 1024 / DYN_LDS;
   static constexpr bool YIELDS = true;
-  static constexpr int ROUND = 4;                         // stages between two looks at the pause word, at least
-  // share of a tile between asking for the pause word and pausing on the answer a question later, or from the last
-  // answer to the end (see look_round); host side, for turnaround estimates
+  // stages between two looks at the pause word, at least, which is also how long a look takes (R - 2 stages after it
+  // the operands asked for before it have to be there anyway)
+  static constexpr int ROUND = RA * RB >= 8 ? 2 : 4;
+  // share of a tile between asking for the pause word and pausing on the answer to the next question, or the end of
+  // the tile (see look_round); host side, for turnaround estimates
   static double pause_fraction(const Args &a, uint32_t every) {
     const uint32_t ns = (a.k + 63) / 64, apart = every / 2 > ROUND ? every / 2 : ROUND;
-    return ns > apart + ROUND + R ? (double)(apart + ROUND + R) / ns : 1.0;
+    return ns > apart + ROUND ? (double)(apart + ROUND) / ns : 1.0;
   }
   static uint32_t groups(const Args &a) {                 // (as many for every die)
     return (((a.n + TN - 1) / TN) * ((a.m + TM - 1) / TM) * a.batch + 7) / 8 * 8;
@@ -1015,20 +1017,27 @@ struct GemmRingT {
       for (int j = 0; j < L; ++j) load(j);
       close();
     };
-    // the last stages, AFTER of them behind this one: nothing is asked for any more
-    auto finish = [&](auto &&self, auto after, auto set) -> void {
-      constexpr int AFTER = decltype(after)::value, f = decltype(set)::value;
-      step(std::integral_constant<int, (AFTER > 0 ? AFTER - 1 : 0)>{}, set, std::bool_constant<(AFTER > 0)>{}, std::false_type{});
-      if constexpr (AFTER > 0) self(self, std::integral_constant<int, AFTER - 1>{}, std::integral_constant<int, f ^ 1>{});
-    };
     // Looks at the pause word (see GemmTileT): one lane asks among the operands' loads at the start of a round and
-    // has the answer at the start of the next, when no operand that was asked for after it is waited for yet.
+    // has the answer at the start of the next; the last question goes out before the last R stages.
     uint32_t pause_left = ctl.ticks, look = 0;
     const buf_t rF = make_buf(ctl.flag, YIELD && ctl.ticks != 0 ? 4 : 0);
     const uint32_t v_look = threadIdx.x == 0 ? 0u : OOB, look_mask = (ctl.mask >> 1) & ~(ROUND - 1u);   // in stages
-    auto look_round = [&](uint32_t c) {
-      if (__builtin_amdgcn_readfirstlane(look) == ctl.epoch) yield_while_preempted(ctl, pause_left);
-      look = __builtin_amdgcn_raw_buffer_load_b32(rF, v_look | ((c & look_mask) == look_mask ? 0u : OOB), 0, 16);  // (sc1)
+    auto act = [&]() {
+      if (YIELD && __builtin_amdgcn_readfirstlane(look) == ctl.epoch) yield_while_preempted(ctl, pause_left);
+    };
+    auto look_round = [&](bool ask) {
+      act();
+      look = __builtin_amdgcn_raw_buffer_load_b32(rF, v_look | (ask ? 0u : OOB), 0, 16);  // (sc1)
+    };
+    // the last stages, AFTER of them behind this one: nothing is asked for any more
+    auto finish = [&](auto &&self, auto after, auto set) -> void {
+      constexpr int AFTER = decltype(after)::value, f = decltype(set)::value;
+      if constexpr (YIELD && AFTER == 1) {
+        static_assert(R - 2 <= ROUND || !YIELD, "an answer is acted on a round later");
+        act();
+      }
+      step(std::integral_constant<int, (AFTER > 0 ? AFTER - 1 : 0)>{}, set, std::bool_constant<(AFTER > 0)>{}, std::false_type{});
+      if constexpr (AFTER > 0) self(self, std::integral_constant<int, AFTER - 1>{}, std::integral_constant<int, f ^ 1>{});
     };
     if constexpr (YIELD) {
       if (ctl.look_first && ctl.ticks != 0 && wave == 0 && ns >= 16) yield_while_preempted(ctl, pause_left);
@@ -1048,13 +1057,16 @@ struct GemmRingT {
       }
       c >>= 1;
       if constexpr (YIELD) {
-        static_assert(ROUND == 4, "two pairs");
-        if (c & 1) pair();
-        for (c >>= 1; c; --c) {
-          look_round(c * ROUND);
-          pair();
-          pair();
+        if (ROUND == 4) {
+          if (c & 1) pair();
+          c >>= 1;
         }
+        for (; c; --c) {
+          look_round((c * ROUND & look_mask) == look_mask);
+          pair();
+          if (ROUND == 4) pair();
+        }
+        look_round(true);
       } else {
         for (; c; --c) pair();
       }

@@ -411,59 +411,101 @@ template <GemmCover C>
 uint32_t gemm_sliced_choice(const void *) { return (uint32_t)C; }
 
 // Persistent workers of a grid so small that a worker per part of a block suffices: the smallest
-// parts for which it does.  PX x PY parts of a 256 x TN block, in the order of gemm_cover's table
-// (one workgroup per compute unit, k = 2048: 6 / 12 / 17 / 25 us a part against 40 for a 256x256
-// block).  In parts the counter stays far below the bit that a request sets.
+// parts for which it does.  PX x PY parts of a 256 x TN block: 32x32 tiles, then those of GemmRingT in what LDS a
+// whole block takes.  In parts the counter stays far below the bit that a request sets.
+// us of a job of 256 workers, from the launch call to the host's knowing of its end, in tiles through registers and
+// 256x128 / so: 768 x 1024 x 2048 26.1 / 22.5 (32x64 parts), 1024 x 1024 x 2048 27.2 / 23.1 (64x64), 1024 x 2048 x
+// 2048 32.8 / 26.8 (128x64), 2048 x 2048 x 2048 38.8 / 32.7 and x 8192 105 / 75 (128x128), 1024 x 2048 x 128 18.2 / 17.7,
+// of 256x128 blocks 2048 x 1152 x 2048 35.9 / 29.1.
 template <class Body>
 struct GemmParts {
   static constexpr uint32_t X = Body::TILE_N / 32, Y = Body::TILE / 32;
+  static constexpr int R128 = Body::DYN_LDS >= 128 * 1024 ? 4 : 3;
   typedef PartsBody<GemmTile32, X, Y> P32;
-  typedef PartsBody<GemmTileT<2, 2>, X / 2, Y / 2> P64;
-  typedef PartsBody<GemmTileT<4, 2>, X / 2, Y / 4> P128;
+  typedef PartsBody<GemmRingT<1, 2, 6>, X / 2, Y> P64;
+  typedef PartsBody<GemmRingT<2, 2, 6>, X / 2, Y / 2> P64x64;
+  typedef PartsBody<GemmRingT<4, 2, 4>, X / 2, Y / 4> P128x64;
+  typedef PartsBody<GemmRingT<4, 4, R128>, X / 4, Y / 4> P128;
   typedef PartsBody<GemmN128Body, X / 4, 1> PN128;
   typedef TailBody<Body, GemmN128Body, X / 4, 1> Tail;
+  static constexpr bool WIDE = PN128::PARTS > 1;           // a 256x128 tile is less than a block
   static uint32_t parts(uint64_t blocks, uint32_t workers, uint32_t chunk, uint32_t *whole) {
     *whole = 0;
-    for (uint32_t p : {P32::PARTS, P64::PARTS, P128::PARTS, PN128::PARTS})
+    for (uint32_t p : {P32::PARTS, P64::PARTS, P64x64::PARTS, P128x64::PARTS, P128::PARTS, PN128::PARTS})
       if (blocks * p <= workers) return p;
     // The last round of several, where all of its blocks find a worker per half: 0.6 of a block's
     // time instead of one (256 workers, 4352 x 4864: 323 blocks, at k = 2080 122 -> 107 us, at
-    // k = 8192 357 -> 313; 8192 x 4608, a third round of 64 blocks, 535 -> 493)
-    if (Tail::PARTS > 1 && chunk == 1 && blocks > workers && blocks % workers != 0 &&
-        blocks % workers * Tail::PARTS <= workers) {
+    // k = 8192 357 -> 313; 8192 x 4608, a third round of 64 blocks, 535 -> 493).  (Quarters of 128x128 as
+    // GemmRingT has them take 412 registers beside the large tile's accumulators: no request would fit.)
+    if (WIDE && chunk == 1 && blocks > workers && blocks % workers != 0 && blocks % workers * Tail::PARTS <= workers) {
       *whole = (uint32_t)(blocks / workers);
       return Tail::PARTS;
     }
     return 1;
   }
+  // what takes them: f(a type whose `type` is the body)
+  template <class T> struct Is { typedef T type; };
+  template <class F>
+  static auto with(uint32_t parts, uint32_t whole, F f) {
+    if (parts == 1) return f(Is<Body>());
+    if constexpr (WIDE) {
+      if (whole) return f(Is<Tail>());
+      if (parts == PN128::PARTS) return f(Is<PN128>());
+    }
+    if (parts == P32::PARTS) return f(Is<P32>());
+    if (parts == P64::PARTS) return f(Is<P64>());
+    if (parts == P64x64::PARTS) return f(Is<P64x64>());
+    return parts == P128x64::PARTS ? f(Is<P128x64>()) : f(Is<P128>());
+  }
   static hipError_t launch(hipStream_t s, const void *args, const PtbCtl &c) {
-    if (c.parts == 1) return launch_ptb_t<Body>(s, args, c);
-    if constexpr (Tail::PARTS > 1)
-      if (c.whole) return launch_ptb_t<Tail>(s, args, c);
-    if (c.parts == P32::PARTS) return launch_ptb_t<P32>(s, args, c);
-    if (c.parts == P64::PARTS) return launch_ptb_t<P64>(s, args, c);
-    if (c.parts == P128::PARTS) return launch_ptb_t<P128>(s, args, c);
-    if constexpr (PN128::PARTS > 1) return launch_ptb_t<PN128>(s, args, c);
-    return hipErrorInvalidValue;
+    return with(c.parts, c.whole, [&](auto b) { return launch_ptb_t<typename decltype(b)::type>(s, args, c); });
   }
   static double pause_fraction(const void *args, uint32_t every, uint32_t parts, uint32_t whole) {
     tally_gemm_bf16_args a;
     memcpy(&a, args, sizeof(a));
     if (parts == 1 || whole) return Body::pause_fraction(a, every);
-    if (parts == P32::PARTS) return P32::Sub::pause_fraction(a, every);
-    if (parts == P64::PARTS) return P64::Sub::pause_fraction(a, every);
-    if (parts == P128::PARTS) return P128::Sub::pause_fraction(a, every);
-    return PN128::Sub::pause_fraction(a, every);
+    return with(parts, 0, [&](auto b) {
+      typedef typename decltype(b)::type T;
+      if constexpr (std::is_same_v<T, Body>) return Body::pause_fraction(a, every);
+      else return T::Sub::pause_fraction(a, every);
+    });
+  }
+  // the most that any of them occupies, whichever a job takes
+  static hipError_t footprint(uint32_t *lds_bytes, uint32_t *waves, uint32_t *regs_per_lane) {
+    hipError_t e = footprint_t<Body>(lds_bytes, waves, regs_per_lane);
+    auto most = [&](auto b) {
+      uint32_t l, w, r;
+      if (e == hipSuccess) e = footprint_t<typename decltype(b)::type>(&l, &w, &r);
+      if (e != hipSuccess) return;
+      *lds_bytes = l > *lds_bytes ? l : *lds_bytes;
+      *regs_per_lane = r > *regs_per_lane ? r : *regs_per_lane;
+    };
+    most(Is<P32>());
+    most(Is<P64>());
+    most(Is<P64x64>());
+    most(Is<P128x64>());
+    most(Is<P128>());
+    if constexpr (WIDE) {
+      most(Is<PN128>());
+      most(Is<Tail>());
+    }
+    return e;
   }
   static hipError_t init() {
     hipError_t e = init_t<Body>();
-    if constexpr (PN128::PARTS > 1) {
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)ptb_kernel<PN128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                PN128::DYN_LDS);
-      if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)ptb_kernel<Tail>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                Tail::DYN_LDS);
+    auto allow = [&](auto b) {
+      typedef typename decltype(b)::type T;
+      static_assert(T::DYN_LDS <= Body::DYN_LDS, "what a paused worker is taken to occupy");
+      if (e == hipSuccess && T::DYN_LDS > 64 * 1024)
+        e = hipFuncSetAttribute((const void *)ptb_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, T::DYN_LDS);
+    };
+    allow(Is<P64>());
+    allow(Is<P64x64>());
+    allow(Is<P128x64>());
+    allow(Is<P128>());
+    if constexpr (WIDE) {
+      allow(Is<PN128>());
+      allow(Is<Tail>());
     }
     if (e == hipSuccess) e = init_gemm_rings<false>();
     return e;
@@ -619,7 +661,7 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
 #define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
-   footprint_t<Body>, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
+   GemmParts<Body>::footprint, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
                        GEMM_WAVE_TILES(false) GEMM_RINGS(GEMM_RING_FOOT_F)},                                                           \
    gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr, false}
 

@@ -741,3 +741,41 @@ def test_requests_around_a_shared_last_round_leave_a_prefix(env):
     # (1e-5 of the sum of a row, as for the row kernels' other comparisons)
     ref = torch.softmax(x[:: 97].double(), dim=1)
     assert (y[:: 97].double() - ref).abs().max() <= 1e-5 * ref.max() + 1e-7
+
+
+@pytest.mark.parametrize("tile,m,n", [("256", 768, 512), ("256", 1024, 768), ("256", 1024, 2048), ("256", 1536, 2048),
+                                      ("128", 768, 512), ("128", 1024, 768), ("128", 1024, 1536), ("128", 2048, 2048)])
+@pytest.mark.parametrize("k", [32, 96, 160, 224, 352, 416, 736, 1312])
+def test_parts_of_blocks_as_tiles_straight_to_lds(env, tile, m, n, k):
+    """256 workers on so few blocks that each takes a part, 32x64, 64x64, 128x64 or 128x128: fewer stages than
+    the part keeps on their way, as many, one to four and more beyond, a last stage half full; a job preempted
+    with a pause and resumed; the same bits as one worker's whole blocks and as the original form's."""
+    B, ctx, torch = env
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + n + k)
+    A = torch.randn(1, m, k, device="cuda", generator=gen).to(torch.bfloat16)
+    Bt = torch.randn(1, n, k, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.full((1, m, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    kern = B.gemm_bf16(A, Bt, C, n128=tile == "128")
+    torch.cuda.synchronize()
+
+    def bits(run):
+        C.fill_(7.0)
+        torch.cuda.synchronize()
+        run()
+        torch.cuda.synchronize()
+        return C.clone()
+
+    def job(workers, preempt=False):
+        j = ctx.launch_ptb(kern, workers)
+        if preempt:
+            j.preempt(pause=True)
+            j.end_pause()
+        while j.wait() != B.JOB_COMPLETE:
+            j.resume()
+        j.free()
+
+    want = bits(lambda: job(1))
+    assert torch.equal(bits(lambda: job(256)), want)
+    assert torch.equal(bits(lambda: job(256, preempt=True)), want)
+    assert torch.equal(bits(lambda: ctx.launch_native(kern)), want)
