@@ -260,16 +260,18 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // run in rounds: there operands go through registers (the nine-kernel layer beside paused 256x256 tiles 43.5 us
 // from the request to its completion, 54 in one-wave tiles throughout).
 // Where nobody else needs the LDS (kShared is not set) GemmRingT covers everything that is less than 160 tiles of
-// 256x256, from k = 320 on, or k = 128 where there are more than 512 tiles of 64x64.  The tile is the one for which
-// the model at GemmRingT says the least: (RA + RB) for each stage of as many tiles as a compute unit gets, and
-// 10 + 8 (RA + RB) of those units, of 0.05 us, for every time it starts anew.  One tile after the other on a unit
-// that holds one at a time is a fifth slower than that (3000 x 3000 x 2048 in 128x96 48.6 us, 42.7 in 96x96, two on
-// a unit); six stages ahead instead of three are a tenth faster and 1 us longer under way (1280 x 1280 x 4096 22.2
-// and 19.3, x 768 6.0 and 6.6); 256x128 tiles count as 14.5.  Of 197 products of k = 128 to 4096 it is within 8 %
-// of the best tile for all but 14, those of the tiles below included (some of one wave, weights from memory).
+// 256x256, from k = 320 on, or k = 128 where there are more than 512 tiles of 64x64.  The tile is the one for
+// which the model at GemmRingT says the least: (RA + RB) for each stage of as many tiles as
+// a compute unit gets, and 10 + 8 (RA + RB) of those units, of 0.05 us, for every time it starts anew.  One tile
+// after the other on a unit that holds one at a time is a fifth slower than that (3000 x 3000 x 2048 in 128x96
+// 48.6 us, 42.7 in 96x96, two on a unit); six stages ahead instead of three are a tenth faster and 1 us longer under
+// way (1280 x 1280 x 4096 22.2 and 19.3, x 768 6.0 and 6.6); 256x128 tiles count as 14.5, 128x64 through registers
+// as 6.6, four on a unit (2048 x 4096 x 448 in those 13.8 us, 15.2 in 128x128 or 96x96).  Of 197 products of k = 128 to
+// 4096 it is within 8 % of the best tile for all but 16 with operands in the caches and all but 25 with weights
+// from memory, those of the tiles below included.
 // For less work tiles through registers are as fast or faster (1024 x 1024 x 256 3.64 us, 3.78 in 64x64).
 // One-wave tiles end earlier beside these, us one wave / so: 200 x 1000 x 2048 6.1 / 5.5 (from memory 8.5 / 5.6),
-// 90 x 3400 x 1536 6.1 / 5.7 (9.5 / 7.8), 3 of 100 x 900 x 1024 7.8 / 4.6; 128 x 3072 x 1024 4.3 / 4.8.
+// 90 x 3400 x 1536 6.1 / 5.7 (9.5 / 7.8), 3 of 100 x 900 x 1024 7.8 / 4.6; but 128 x 3072 x 3072 8.6 / 9.1.
 enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16, kRing };
 #define GEMM_RINGS(X) X(1, 1, 8) X(1, 2, 6) X(2, 2, 5) X(2, 3, 4) X(4, 2, 3) X(3, 3, 3) X(4, 2, 6) X(3, 3, 6) X(4, 3, 5) X(4, 4, 4)
 #define GEMM_RING_ROW(ra, rb, r) {32 * ra, 32 * rb, GemmRingT<ra, rb, r>::MIN_WAVES, r},
@@ -278,8 +280,13 @@ constexpr uint32_t kRingCount = sizeof(kRings) / sizeof(kRings[0]);
 static_assert(kMaxShared + kRingCount == kMaxNative && (uint32_t)GemmCover::kRing == kMaxShared, "one kernel each");
 GemmCover gemm_ring(const tally_gemm_bf16_args &a, bool n128) {
   const uint64_t ns = cdiv(a.k, 64), rounds128 = cdiv((uint64_t)cdiv(a.m, 256) * cdiv(a.n, 128) * a.batch, 256);
-  GemmCover best = GemmCover::k256x128;
-  uint64_t least = n128 ? rounds128 * (145 * ns + 10 * (10 + 8 * 12)) : ~0ull;
+  const uint64_t through = (uint64_t)cdiv(a.m, 128) * cdiv(a.n, 64) * a.batch;   // 128x64 tiles through registers
+  GemmCover best = GemmCover::k128x64;
+  uint64_t least = cdiv(through, 256) * ns * 66 + cdiv(through, 1024) * 580;
+  if (n128 && rounds128 * (145 * ns + 10 * (10 + 8 * 12)) < least) {
+    best = GemmCover::k256x128;
+    least = rounds128 * (145 * ns + 10 * (10 + 8 * 12));
+  }
   for (uint32_t i = 0; i < kRingCount; ++i) {
     const uint64_t t = (uint64_t)cdiv(a.m, kRings[i][0]) * cdiv(a.n, kRings[i][1]) * a.batch, rounds = cdiv(t, 256);
     const uint64_t size = (kRings[i][0] + kRings[i][1]) / 32, per_cu = kRings[i][2];
@@ -297,12 +304,12 @@ GemmCover gemm_ring(const tally_gemm_bf16_args &a, bool n128) {
 GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how, bool large) {
   const uint64_t t16 = (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch, t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
   const bool odd = cdiv(a.m, 16) & 1;
-  const bool ring = !(how & kShared) && (a.k >= 320 || (a.k >= 128 && t64 > 512)) &&
-                   t64 <= (1u << 20);                      // (a flat grid)
+  const bool ring = !(how & kShared) && t64 <= (1u << 20) &&         // (a flat grid)
+                   a.k >= (t64 > 512 ? 128u : 320u);
   if (a.k > 128 && (!(how & kBeside) || t16 <= 256)) {
     if (t16 <= 768) return GemmCover::kWave16;
     const uint32_t up_to = t16 <= 1024 ? (ring ? 1536u : 2048u)
-                         : t16 <= 1536 ? (odd ? (ring ? 768u : 1024u) : ring ? 1280u : 3072u)
+                         : t16 <= 1536 ? (odd ? (ring ? 768u : 1024u) : ring && t16 <= 1408 ? 1280u : 3072u)
                          : t16 <= 2048 ? (odd && ring ? 512u : 768u) : 0u;
     if (a.k <= up_to) return odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
   }
