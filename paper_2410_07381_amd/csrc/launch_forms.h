@@ -125,7 +125,7 @@ constexpr uint32_t kFlagCopyStride = 32;  // in 32-bit words
 // indices stand for `last_chunk` blocks.  Nothing else knows: an index is turned into blocks where a
 // worker runs it and where progress is told to the host.
 // Softmax as 256 x 4, whole fetches / so, us: 9001 x 8192 (51 third fetches / 203 of one block) 142 / 126,
-// 700 x 6000 (44 fetches / 175) 39 / 23, 5000 x 2048 32.8 / 29.6, 200000 x 300 (49 rounds) 172 both.
+// 700 x 6000 (44 fetches / 175) 39 / 23, 5000 x 2048 32.8 / 29.6 (see last_round).
 __device__ __forceinline__ uint32_t block_at(const PtbCtl &c, uint32_t index) {
   if (index <= c.last_from) return index;
   const uint32_t b = c.last_from + (index - c.last_from) / c.chunk * c.last_chunk;
