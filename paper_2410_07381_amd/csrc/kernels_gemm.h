@@ -702,10 +702,13 @@ using GemmTile32 = GemmTileT<1, 1>;
 // 128 x 768 x 3072 7.7 / 6.1, 128 x 768 x 768 3.7 / 3.2, 128 x 2304 x 768 4.9 / 4.1, 128 x 3072 x 768 4.9 / 4.2,
 // 48 x 2048 x 3072 7.7 / 6.3, 100 x 1000 x 1536 5.3 / 4.2, 256 x 1024 x 768 4.0 / 3.8, 33 x 5000 x 768 5.1 / 4.0.
 //
-// Tiles of one column of tiles share a panel of B.  Workgroups go to the dies in turn, so a grid of (8, rows of
-// tiles, columns of tiles / 8) sends a column's tiles to one die, and next to one another in time; with columns
-// along the grid's first extent that is so only where they are a multiple of eight (100 x 1000 x 3072, 63 columns,
-// 8.8 us, 6.6 so; 128 x 3072 x 768, 96, 4.6 and 4.2).
+// Tiles of one column of tiles share a panel of B, tiles of one row a panel of A.  The longer side of the output
+// is what has many panels, and each die takes a run of those, so that it reads its share of the larger operand and
+// all of the smaller one.  Workgroups go to the dies in turn, hence a grid of (8, tiles of a panel, panels of a die);
+// the panels of a batch follow one another.  us with columns dealt out to the dies whatever the shape (those of a
+// batch in a plain grid) / so, operands from the caches and from memory: 8192 x 16 x 1536 21.7 / 4.0 and 27.6 / 6.6,
+// 2048 x 64 x 4096 15.2 / 7.0 and 16.4 / 10.3, 512 x 128 x 1536 3.9 / 3.8 and 4.2 / 3.9,
+// 12 of 112 x 73 x 1696 7.8 / 4.3 and 8.3 / 6.1; with columns along the grid's first extent 100 x 1000 x 3072 8.8 / 6.6.
 template <int NA, int NB, bool NAN7FC0 = false>
 struct GemmWaveT {
   using Args = tally_gemm_bf16_args;
@@ -721,16 +724,21 @@ struct GemmWaveT {
   static constexpr unsigned DYN_LDS = STAGE * R;
   static dim3 grid(const Args &a) {
     const uint32_t x = (a.n + TN - 1) / TN, y = (a.m + TM - 1) / TM;
-    return a.batch == 1 ? dim3(8, y, (x + 7) / 8) : dim3(x, y, a.batch);
+    return dim3(8, a.m > a.n ? x : y, ((a.m > a.n ? y : x) * a.batch + 7) / 8);
   }
-  static __device__ __forceinline__ void run(const Args &a, uint32_t bx, uint32_t by, uint32_t bz) {
+  static __device__ __forceinline__ void run(const Args &a, uint32_t die, uint32_t in, uint32_t at) {
 #ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
     extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
-    if (a.batch == 1) {
-      bx += 8 * bz;
-      bz = 0;
-      if (bx * TN >= a.n) return;
+    const bool tall = a.m > a.n;
+    const uint32_t panels = tall ? (a.m + TM - 1) / TM : (a.n + TN - 1) / TN;   // of a product
+    const uint32_t q = panels * a.batch / 8, rest = panels * a.batch % 8;
+    if (at >= q + (die < rest ? 1 : 0)) return;
+    uint32_t panel = die * q + (die < rest ? die : rest) + at, bz = 0;
+    if (a.batch > 1) {
+      bz = panel / panels;
+      panel -= bz * panels;
     }
+    const uint32_t bx = tall ? in : panel, by = tall ? panel : in;
     const uint32_t lane = threadIdx.x;
     const uint32_t K = a.k;
     const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;

@@ -238,31 +238,32 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // unless the output is one that GemmBodyT writes past the caches.
 // Tiles of one wave (GemmWaveT) pay from the third stage on and where there are few of them: they keep more
 // bytes on their way and fewer instructions between them, but read operands more often.  Counted in 16x16
-// blocks of the output, us for 32x32 or 32x64 tiles, the better / 16x16 / 16x32 / 32x16, with operands from the
-// caches and with a weight matrix from memory:
-//   128 x  768 x 1536 (384)    5.3 / 4.1 / 5.1 / 5.1     5.3 / 4.2 / 5.1 / 5.2
-//    16 x 8192 x 3072 (512)    9.6 / 9.0 / 9.2 / 9.4    10.7 / 10.5 / 13.5 / 13.4
-//    64 x 3072 x  384 (768)    3.5 / 2.9 / 3.1 / 3.2     3.5 / 2.9 / 3.1 / 3.2
-//    64 x 3072 x 3072 (768)    8.1 / 7.1 / 8.6 / 8.7     9.8 / 9.9 / 12.4 / 11.9
-//   200 x 1000 x  768 (819)    4.0 / 3.9 / 3.8 / 3.9     4.0 / 3.9 / 3.9 / 3.9
-//    33 x 5000 x 1536 (939)    7.2 / 5.7 / 5.6 / 5.9     7.9 / 7.7 / 7.6 / 7.6
-//   256 x 1024 x 1536 (1024)   5.5 / 5.4 / 5.3 / 5.3     5.6 / 5.7 / 5.7 / 5.8
-//   256 x 1024 x 3072 (1024)   8.2 / 8.4 / 8.4 / 8.3     8.9 / 10.5 / 10.8 / 10.4
-//   128 x 2304 x 3072 (1152)  11.1 / 11.2 / 10.0 / 9.0  12.6 / 15.6 / 14.6 / 12.5
-//    90 x 3400 x  768 (1278)   5.2 / 4.9 / 4.6 / 4.7     5.4 / 5.7 / 5.4 / 5.4
-//    90 x 3400 x 1536 (1278)   7.5 / 7.5 / 6.7 / 6.9     8.1 / 9.8 / 9.0 / 9.1
-//   128 x 3072 x 1536 (1536)   7.0 / 7.3 / 6.2 / 5.9     7.7 / 9.5 / 8.3 / 7.6
-//   256 x 2048 x  768 (2048)   5.0 / 6.3 / 4.9 / 4.7     5.0 / 6.7 / 5.3 / 4.9
-//   256 x 2048 x 1536 (2048)   7.0 / 9.9 / 7.5 / 6.9     7.5 / 12.0 / 9.5 / 8.4
-// So 16x16 up to three per compute unit, then 32x16 up to eight blocks per unit, or 16x32 where a last row of
-// 32x16 tiles would be half empty, as far as k goes.
+// blocks of the output, us for 32x32 or 32x64 tiles, the better / 16x16 / 16x32 or 32x16 / the best GemmRingT,
+// with both operands from the caches and from memory:
+//  8192 x   16 x 1536 (512)    5.2 / 3.9 / 4.6 / 4.7     6.7 /  6.5 /  8.3 /  6.6
+//    94 x  799 x 2464 (300)    6.8 / 5.3 / 6.2 / 6.1     7.3 /  5.5 /  7.2 /  6.5
+//  1000 x  128 x 4096 (504)   10.1 / 7.3 / 9.1 / 8.6    11.6 / 10.0 / 14.5 / 10.7
+//   512 x  384 x 1536 (768)    5.3 / 5.0 / 4.8 / 4.7     5.5 /  5.4 /  5.4 /  4.8
+//   512 x  384 x 4096 (768)   10.3 / 9.1 / 9.3 / 8.8    11.1 / 13.6 / 15.0 / 10.4
+//   200 x 1000 x  768 (819)    3.8 / 3.9 / 3.5 / 3.5     3.9 /  3.8 /  3.8 /  3.6
+//  1000 x  256 x  320 (1008)   3.1 / 3.1 / 2.6 / 3.1     3.4 /  3.2 /  2.9 /  3.2
+//    90 x 3400 x  768 (1278)   4.7 / 4.6 / 4.1 / 4.1     5.2 /  5.5 /  5.5 /  4.9
+//   128 x 3072 x  768 (1536)   4.7 / 4.5 / 3.8 / 4.1     4.8 /  5.0 /  4.4 /  4.4
+//  4096 x   96 x 1536 (1536)   7.1 / 7.4 / 6.2 / 5.8     7.6 / 11.3 /  9.6 /  7.4
+//  2048 x  256 x  320 (2048)   3.4 / 4.6 / 3.1 / 3.4     3.7 /  4.9 /  3.2 /  3.6
+//  2048 x  256 x  768 (2048)   4.7 / 5.8 / 4.3 / 4.3     4.9 /  6.2 /  4.5 /  4.3
+// So 16x16 up to five for two compute units; then two blocks to a tile up to eight per unit, for k from three
+// stages to eight, with the pair along the longer side only where the blocks of the shorter one are odd in number
+// and a last tile would be half empty.  Of 473 products of up to 2048 blocks, two tall ones for each wide one, one
+// takes over 4 % longer than in tiles through registers (16384 x 32 x 4096 from memory, 33.4 and 31.9); the mean is
+// 0.83 of those with operands from the caches and 0.87 from memory, 0.88 and 0.90 beside best-effort jobs.
 // Beside best-effort workgroups that leave LDS for one of them on a compute unit (kBeside) more than 256 would
 // run in rounds: there operands go through registers (the nine-kernel layer beside paused 256x256 tiles 43.5 us
 // from the request to its completion, 54 in one-wave tiles throughout).
 // Where nobody else needs the LDS (kShared is not set) GemmRingT covers everything that is less than 160 tiles of
-// 256x256, from k = 320 on, or k = 128 where there are more than 512 tiles of 64x64.  The tile is the one for
-// which the model at GemmRingT says the least: (RA + RB) for each stage of as many tiles as
-// a compute unit gets, and 10 + 8 (RA + RB) of those units, of 0.05 us, for every time it starts anew.  One tile
+// 256x256, from k = 320 on, k = 160 up to 2048 blocks of 16x16, or k = 128 where there are more than 512 tiles of
+// 64x64.  The tile is the one for which the model at GemmRingT says the least: (RA + RB) for each stage of as many
+// tiles as a compute unit gets, and 10 + 8 (RA + RB) of those units, of 0.05 us, for every time it starts anew.  One tile
 // after the other on a unit that holds one at a time is a fifth slower than that (3000 x 3000 x 2048 in 128x96
 // 48.6 us, 42.7 in 96x96, two on a unit); six stages ahead instead of three are a tenth faster and 1 us longer under
 // way (1280 x 1280 x 4096 22.2 and 19.3, x 768 6.0 and 6.6); 256x128 tiles count as 14.5, 128x64 through registers
@@ -270,8 +271,6 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // 4096 it is within 8 % of the best tile for all but 16 with operands in the caches and all but 25 with weights
 // from memory, those of the tiles below included.
 // For less work tiles through registers are as fast or faster (1024 x 1024 x 256 3.64 us, 3.78 in 64x64).
-// One-wave tiles end earlier beside these, us one wave / so: 200 x 1000 x 2048 6.1 / 5.5 (from memory 8.5 / 5.6),
-// 90 x 3400 x 1536 6.1 / 5.7 (9.5 / 7.8), 3 of 100 x 900 x 1024 7.8 / 4.6; but 128 x 3072 x 3072 8.6 / 9.1.
 enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16, kRing };
 #define GEMM_RINGS(X) X(1, 1, 8) X(1, 2, 6) X(2, 2, 5) X(2, 3, 4) X(4, 2, 3) X(3, 3, 3) X(4, 2, 6) X(3, 3, 6) X(4, 3, 5) X(4, 4, 4)
 #define GEMM_RING_ROW(ra, rb, r) {32 * ra, 32 * rb, GemmRingT<ra, rb, r>::MIN_WAVES, r},
@@ -303,15 +302,14 @@ GemmCover gemm_ring(const tally_gemm_bf16_args &a, bool n128) {
 // large: blocks of 256 rows, which cover the output without a remainder
 GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how, bool large) {
   const uint64_t t16 = (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch, t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
-  const bool odd = cdiv(a.m, 16) & 1;
   const bool ring = !(how & kShared) && t64 <= (1u << 20) &&         // (a flat grid)
-                   a.k >= (t64 > 512 ? 128u : 320u);
+                   a.k >= (t64 > 512 ? 128u : t16 <= 2048 ? 160u : 320u);
   if (a.k > 128 && (!(how & kBeside) || t16 <= 256)) {
-    if (t16 <= 768) return GemmCover::kWave16;
-    const uint32_t up_to = t16 <= 1024 ? (ring ? 1536u : 2048u)
-                         : t16 <= 1536 ? (odd ? (ring ? 768u : 1024u) : ring && t16 <= 1408 ? 1280u : 3072u)
-                         : t16 <= 2048 ? (odd && ring ? 512u : 768u) : 0u;
-    if (a.k <= up_to) return odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
+    if (t16 <= 640) return GemmCover::kWave16;
+    if (t16 <= 2048 && a.k > 160 && a.k <= 512) {
+      const bool tall = a.m > a.n, odd = cdiv(tall ? a.n : a.m, 16) & 1;   // (the shorter side)
+      return tall != odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
+    }
   }
   if (ring && !(large && (uint64_t)cdiv(a.n, 256) * cdiv(a.m, 256) * a.batch >= 160)) return gemm_ring(a, large);
   if ((uint64_t)cdiv(a.n, 32) * cdiv(a.m, 32) * a.batch <= 256) return GemmCover::k32;

@@ -540,6 +540,39 @@ def test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch):
     assert ((Cd[:, row, col].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + k * 2.0 ** -24 * mag).all()
 
 
+@pytest.mark.parametrize("m,n,k,batch", [(8192, 16, 416, 1), (2001, 1, 544, 1), (1000, 100, 800, 1), (113, 112, 352, 1), (17, 16, 800, 1),
+                                         (300, 20, 416, 12), (33, 50, 352, 50), (2032, 112, 416, 1), (8190, 64, 480, 1), (1003, 200, 352, 1)])
+def test_gemm_one_wave_tiles_of_narrow_outputs(env, m, n, k, batch):
+    """Fewer panels of tiles than dies, along either side, and more; panels of a batch that do not divide by eight."""
+    test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch)
+    test_gemm_one_wave_tiles_of_two_blocks(env, n, m, k, batch)
+
+
+@pytest.mark.parametrize("m,n,k", [(8192, 16, 1536), (2032, 112, 1536), (4096, 32, 2048), (2048, 64, 4096), (8192, 8, 768)])
+def test_a_narrow_product_takes_no_longer_than_its_transpose(env, m, n, k):
+    """The two ask for the same work; with a narrow one on a few of the eight dies it took 1.6 to 5 times as long."""
+    B, ctx, torch = env
+    A, Bt = (torch.randn(1, r, k, device="cuda").to(torch.bfloat16) for r in (m, n))
+    kerns = [B.gemm_bf16(A, Bt, torch.empty(1, m, n, dtype=torch.bfloat16, device="cuda"), small=True),
+             B.gemm_bf16(Bt, A, torch.empty(1, n, m, dtype=torch.bfloat16, device="cuda"), small=True)]
+    hi = ctx._streams[0]
+    us = [[], []]
+    torch.cuda.synchronize()
+    for attempt in range(7):
+        for i, kern in enumerate(kerns):
+            with torch.cuda.stream(hi):
+                torch.cuda._sleep(400000)                  # (the launches below queue up behind it)
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record(hi)
+                for _ in range(40):
+                    ctx.launch_native(kern, hi=True)
+                e1.record(hi)
+                e1.synchronize()
+                us[i].append(e0.elapsed_time(e1) * 25)
+    narrow, wide = (sorted(t)[3] for t in us)
+    assert narrow < 1.35 * wide, (narrow, wide)
+
+
 @pytest.mark.parametrize("m,n,k,batch", [
     (512, 500, 1568, 1), (500, 512, 2080, 1),                                   # 32x32: as many stages ahead, more
     (225, 1250, 544, 5), (399, 1200, 1056, 1),                                  # 32x64
