@@ -266,10 +266,13 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // tiles as a compute unit gets, and 10 + 8 (RA + RB) of those units, of 0.05 us, for every time it starts anew.  One tile
 // after the other on a unit that holds one at a time is a fifth slower than that (3000 x 3000 x 2048 in 128x96
 // 48.6 us, 42.7 in 96x96, two on a unit); six stages ahead instead of three are a tenth faster and 1 us longer under
-// way (1280 x 1280 x 4096 22.2 and 19.3, x 768 6.0 and 6.6); 256x128 tiles count as 14.5, 128x64 through registers
-// as 6.6, four on a unit (2048 x 4096 x 448 in those 13.8 us, 15.2 in 128x128 or 96x96).  Of 197 products of k = 128 to
-// 4096 it is within 8 % of the best tile for all but 16 with operands in the caches and all but 25 with weights
-// from memory, those of the tiles below included.
+// way (1280 x 1280 x 4096 22.2 and 19.3, x 768 6.0 and 6.6); 256x128 tiles count as 16.5 (17.8 in a batch, whose
+// tiles are not dealt out to the dies by product), 256x256 tiles as 20.5 and 24 x 10 to start, 128x64 through
+// registers as 7.8, four on a unit (2048 x 4096 x 448 in those 13.8 us, 15.2 in 128x128 or 96x96).
+// Without the large tiles among them, where smaller ones need another round for a few: us in the best of the others
+// / 256x256: 3 of 5632 x 512 x 768 36.2 (128x64) / 20.4, 3 of 1280 x 2560 x 2400 66.9 / 51.9,
+// 3328 x 3072 x 6304 153 (128x128) / 111.  Of 597 products of k = 128 to 8192 the choice takes 1 % longer than the
+// best tile in the mean, and over 6 % longer in 49 with operands from the caches and 29 from memory.
 // For less work tiles through registers are as fast or faster (1024 x 1024 x 256 3.64 us, 3.78 in 64x64).
 enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16, kRing };
 #define GEMM_RINGS(X) X(1, 1, 8) X(1, 2, 6) X(2, 2, 5) X(2, 3, 4) X(4, 2, 3) X(3, 3, 3) X(4, 2, 6) X(3, 3, 6) X(4, 3, 5) X(4, 4, 4)
@@ -277,21 +280,26 @@ enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, k
 constexpr uint32_t kRings[][4] = {GEMM_RINGS(GEMM_RING_ROW)};   // tile, how many fit a compute unit, stages
 constexpr uint32_t kRingCount = sizeof(kRings) / sizeof(kRings[0]);
 static_assert(kMaxShared + kRingCount == kMaxNative && (uint32_t)GemmCover::kRing == kMaxShared, "one kernel each");
-GemmCover gemm_ring(const tally_gemm_bf16_args &a, bool n128) {
-  const uint64_t ns = cdiv(a.k, 64), rounds128 = cdiv((uint64_t)cdiv(a.m, 256) * cdiv(a.n, 128) * a.batch, 256);
+// large: the columns of the operator's blocks of 256 rows (0: it has none)
+GemmCover gemm_ring(const tally_gemm_bf16_args &a, uint32_t large) {
+  const uint64_t ns = cdiv(a.k, 64);
   const uint64_t through = (uint64_t)cdiv(a.m, 128) * cdiv(a.n, 64) * a.batch;   // 128x64 tiles through registers
   GemmCover best = GemmCover::k128x64;
-  uint64_t least = cdiv(through, 256) * ns * 66 + cdiv(through, 1024) * 580;
-  if (n128 && rounds128 * (145 * ns + 10 * (10 + 8 * 12)) < least) {
-    best = GemmCover::k256x128;
-    least = rounds128 * (145 * ns + 10 * (10 + 8 * 12));
+  uint64_t least = cdiv(through, 256) * ns * 78 + cdiv(through, 1024) * 880;
+  for (uint32_t tn = 128; tn <= large; tn += 128) {
+    const uint64_t rounds = cdiv((uint64_t)cdiv(a.m, 256) * cdiv(a.n, tn) * a.batch, 256);
+    const uint64_t cost = rounds * (tn == 128 ? (a.batch == 1 ? 165 : 178) * ns + 1060 : 205 * ns + 1200);
+    if (cost < least) {
+      least = cost;
+      best = tn == 128 ? GemmCover::k256x128 : GemmCover::k256x256;
+    }
   }
   for (uint32_t i = 0; i < kRingCount; ++i) {
     const uint64_t t = (uint64_t)cdiv(a.m, kRings[i][0]) * cdiv(a.n, kRings[i][1]) * a.batch, rounds = cdiv(t, 256);
     const uint64_t size = (kRings[i][0] + kRings[i][1]) / 32, per_cu = kRings[i][2];
     const bool deep = per_cu == 1 && kRings[i][3] >= 6;
-    const uint64_t unit = per_cu == 1 && rounds > 1 ? 12 : deep ? 9 : 10;
-    const uint64_t cost = rounds * ns * size * unit + cdiv(t, 256 * per_cu) * 10 * (10 + 8 * size + (deep ? 20 : 0));
+    const uint64_t unit = per_cu == 1 && rounds > 1 ? 24 : deep ? 17 : 20;   // half units
+    const uint64_t cost = rounds * ns * size * unit / 2 + cdiv(t, 256 * per_cu) * 10 * (10 + 8 * size + (deep ? 20 : 0));
     if (cost < least) {
       least = cost;
       best = (GemmCover)((uint32_t)GemmCover::kRing + i);
@@ -299,8 +307,8 @@ GemmCover gemm_ring(const tally_gemm_bf16_args &a, bool n128) {
   }
   return best;
 }
-// large: blocks of 256 rows, which cover the output without a remainder
-GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how, bool large) {
+// large: as above; such blocks cover the output without a remainder
+GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how, uint32_t large) {
   const uint64_t t16 = (uint64_t)cdiv(a.n, 16) * cdiv(a.m, 16) * a.batch, t64 = (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 64) * a.batch;
   const bool ring = !(how & kShared) && t64 <= (1u << 20) &&         // (a flat grid)
                    a.k >= (t64 > 512 ? 128u : t16 <= 2048 ? 160u : 320u);
@@ -356,7 +364,7 @@ template <class Body>
 hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, uint32_t how) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  const GemmCover c = gemm_cover(a, how, true);
+  const GemmCover c = gemm_cover(a, how, Body::TILE_N);
   if (c >= GemmCover::kRing) return launch_gemm_ring<false>(s, a, c, how);
   switch (c) {
     case GemmCover::kWave16: return launch_gemm_wave<1, 1, false>(s, a, how);
@@ -374,7 +382,7 @@ hipError_t launch_native_gemm_t(hipStream_t s, const void *args, tally_dim3 g, u
 // best-effort tile.  128x64 tiles pay from two per compute unit (512 x 4096 x 4096, 256 of them,
 // 29 us with 64x64 and 32; 1024 x 4096 x 4096, 512, 54 and 47).
 GemmCover gemm_cover_small(const tally_gemm_bf16_args &a, uint32_t how) {
-  const GemmCover c = gemm_cover(a, how, false);
+  const GemmCover c = gemm_cover(a, how, 0);
   if (c <= GemmCover::k32x64 || c >= GemmCover::kWave16) return c;
   return (uint64_t)cdiv(a.n, 64) * cdiv(a.m, 128) * a.batch >= 512 ? GemmCover::k128x64 : GemmCover::k64;
 }
@@ -404,7 +412,7 @@ template <uint32_t TN>
 uint32_t gemm_native_choice(const void *args, uint32_t how, uint64_t *groups) {
   tally_gemm_bf16_args a;
   memcpy(&a, args, sizeof(a));
-  return gemm_choice(a, gemm_cover(a, how, true), TN, groups);
+  return gemm_choice(a, gemm_cover(a, how, TN), TN, groups);
 }
 uint32_t gemm_small_native_choice(const void *args, uint32_t how, uint64_t *groups) {
   tally_gemm_bf16_args a;

@@ -548,6 +548,48 @@ def test_gemm_one_wave_tiles_of_narrow_outputs(env, m, n, k, batch):
     test_gemm_one_wave_tiles_of_two_blocks(env, n, m, k, batch)
 
 
+def _us_of_launches(torch, launches_of, stream, launches=40, attempts=7):
+    """Median time of one launch on `stream`, of each way of launching, in turn."""
+    us = [[] for _ in launches_of]
+    torch.cuda.synchronize()
+    for attempt in range(attempts):
+        for t, launch in zip(us, launches_of):
+            with torch.cuda.stream(stream):
+                torch.cuda._sleep(400000)                  # (the launches below queue up behind it)
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record(stream)
+                for _ in range(launches):
+                    launch()
+                e1.record(stream)
+                e1.synchronize()
+                t.append(e0.elapsed_time(e1) * 1000 / launches)
+    return [sorted(t)[attempts // 2] for t in us]
+
+
+@pytest.mark.parametrize("m,n,k,batch,small", [(5632, 512, 768, 3, False), (1280, 2560, 2400, 3, False), (3328, 3072, 6304, 1, False),
+                                               (4096, 768, 576, 3, False), (1000, 2300, 768, 1, True), (400, 1200, 2048, 1, True),
+                                               (128, 3072, 768, 1, True), (90, 3400, 1536, 1, True)])
+def test_tiles_that_need_the_whole_gpu_are_not_slower(env, m, n, k, batch, small):
+    """A product alone on the GPU has all tiles to choose from, beside a best-effort job (here a stopped
+    one) only some of them."""
+    B, ctx, torch = env
+    A, Bt = (torch.randn(batch, r, k, device="cuda").to(torch.bfloat16) for r in (m, n))
+    kern = B.gemm_bf16(A, Bt, torch.empty(batch, m, n, dtype=torch.bfloat16, device="cuda"), small=small)
+    launch, hi = lambda: ctx.launch_native(kern, hi=True), ctx._streams[0]
+    x, y = torch.zeros(4096, device="cuda"), torch.zeros(4096, device="cuda")
+    torch.cuda.synchronize()
+    alone, beside = [], []
+    for attempt in range(3):
+        alone += _us_of_launches(torch, [launch], hi, 10, 3)
+        job = ctx.launch_ptb(B.saxpy(x, y, 1.0), 1, stop_at=3)
+        assert job.wait() == B.JOB_STOPPED
+        beside += _us_of_launches(torch, [launch], hi, 10, 3)
+        job.resume()
+        job.wait()
+        job.free()
+    assert min(alone) < 1.1 * min(beside), (alone, beside)
+
+
 @pytest.mark.parametrize("m,n,k", [(8192, 16, 1536), (2032, 112, 1536), (4096, 32, 2048), (2048, 64, 4096), (8192, 8, 768)])
 def test_a_narrow_product_takes_no_longer_than_its_transpose(env, m, n, k):
     """The two ask for the same work; with a narrow one on a few of the eight dies it took 1.6 to 5 times as long."""
@@ -555,21 +597,7 @@ def test_a_narrow_product_takes_no_longer_than_its_transpose(env, m, n, k):
     A, Bt = (torch.randn(1, r, k, device="cuda").to(torch.bfloat16) for r in (m, n))
     kerns = [B.gemm_bf16(A, Bt, torch.empty(1, m, n, dtype=torch.bfloat16, device="cuda"), small=True),
              B.gemm_bf16(Bt, A, torch.empty(1, n, m, dtype=torch.bfloat16, device="cuda"), small=True)]
-    hi = ctx._streams[0]
-    us = [[], []]
-    torch.cuda.synchronize()
-    for attempt in range(7):
-        for i, kern in enumerate(kerns):
-            with torch.cuda.stream(hi):
-                torch.cuda._sleep(400000)                  # (the launches below queue up behind it)
-                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-                e0.record(hi)
-                for _ in range(40):
-                    ctx.launch_native(kern, hi=True)
-                e1.record(hi)
-                e1.synchronize()
-                us[i].append(e0.elapsed_time(e1) * 25)
-    narrow, wide = (sorted(t)[3] for t in us)
+    narrow, wide = _us_of_launches(torch, [lambda k=k: ctx.launch_native(k, hi=True) for k in kerns], ctx._streams[0])
     assert narrow < 1.35 * wide, (narrow, wide)
 
 
