@@ -245,6 +245,7 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 //  1000 x  128 x 4096 (504)   10.1 / 7.3 / 9.1 / 8.6    11.6 / 10.0 / 14.5 / 10.7
 //   512 x  384 x 1536 (768)    5.3 / 5.0 / 4.8 / 4.7     5.5 /  5.4 /  5.4 /  4.8
 //   512 x  384 x 4096 (768)   10.3 / 9.1 / 9.3 / 8.8    11.1 / 13.6 / 15.0 / 10.4
+//   256 x  768 x  928 (768)    4.1 / 3.5 / 3.8 / 3.8     4.3 /  3.8 /  4.1 /  3.9
 //   200 x 1000 x  768 (819)    3.8 / 3.9 / 3.5 / 3.5     3.9 /  3.8 /  3.8 /  3.6
 //  1000 x  256 x  320 (1008)   3.1 / 3.1 / 2.6 / 3.1     3.4 /  3.2 /  2.9 /  3.2
 //    90 x 3400 x  768 (1278)   4.7 / 4.6 / 4.1 / 4.1     5.2 /  5.5 /  5.5 /  4.9
@@ -252,10 +253,10 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 //  4096 x   96 x 1536 (1536)   7.1 / 7.4 / 6.2 / 5.8     7.6 / 11.3 /  9.6 /  7.4
 //  2048 x  256 x  320 (2048)   3.4 / 4.6 / 3.1 / 3.4     3.7 /  4.9 /  3.2 /  3.6
 //  2048 x  256 x  768 (2048)   4.7 / 5.8 / 4.3 / 4.3     4.9 /  6.2 /  4.5 /  4.3
-// So 16x16 up to five for two compute units; then two blocks to a tile up to eight per unit, for k from three
-// stages to eight, with the pair along the longer side only where the blocks of the shorter one are odd in number
-// and a last tile would be half empty.  Of 473 products of up to 2048 blocks, two tall ones for each wide one, one
-// takes over 4 % longer than in tiles through registers (16384 x 32 x 4096 from memory, 33.4 and 31.9); the mean is
+// So 16x16 up to five for two compute units, or three for one up to k = 1024; then two blocks to a tile up to eight
+// per unit, for k from three stages to eight, with the pair along the longer side only where the blocks of the
+// shorter one are odd in number and a last tile would be half empty.  Of 473 products of up to 2048 blocks, more tall than wide, two
+// take over 4 % longer than in tiles through registers (16384 x 32 x 4096 from memory, 33.4 and 31.9); the mean is
 // 0.83 of those with operands from the caches and 0.87 from memory, 0.88 and 0.90 beside best-effort jobs.
 // Beside best-effort workgroups that leave LDS for one of them on a compute unit (kBeside) more than 256 would
 // run in rounds: there operands go through registers (the nine-kernel layer beside paused 256x256 tiles 43.5 us
@@ -313,7 +314,7 @@ GemmCover gemm_cover(const tally_gemm_bf16_args &a, uint32_t how, uint32_t large
   const bool ring = !(how & kShared) && t64 <= (1u << 20) &&         // (a flat grid)
                    a.k >= (t64 > 512 ? 128u : t16 <= 2048 ? 160u : 320u);
   if (a.k > 128 && (!(how & kBeside) || t16 <= 256)) {
-    if (t16 <= 640) return GemmCover::kWave16;
+    if (t16 <= (a.k <= 1024 ? 768u : 640u)) return GemmCover::kWave16;
     if (t16 <= 2048 && a.k > 160 && a.k <= 512) {
       const bool tall = a.m > a.n, odd = cdiv(tall ? a.n : a.m, 16) & 1;   // (the shorter side)
       return tall != odd ? GemmCover::kWave16x32 : GemmCover::kWave32x16;
