@@ -157,7 +157,15 @@ size_t tally_attn_decode_scratch_bytes(uint32_t heads);
 
 /* Original form: one launch of the whole logical grid on the high-priority stream
  * (on_hi_stream != 0) or on the best-effort stream (Section 4.2: high-priority
- * kernels are launched with the default configuration).  Asynchronous. */
+ * kernels are launched with the default configuration).  Asynchronous.
+ * The GEMM operators have tiles of several sizes, which give the same bits, and this call chooses:
+ * while a job exists (from its launch to tally_job_free, a stopped or finished one too), or a product
+ * that was launched here on the best-effort stream in tiles that fill a compute unit has not ended,
+ * tiles that find room beside others; else those that are fastest on a GPU of their own.  What is
+ * launched later changes nothing: a product that still waits on its stream, or is replayed from a
+ * captured graph, runs in the tiles chosen here.  To learn of the end of such a best-effort product,
+ * the first product on the high-priority stream behind it puts a marker kernel of some microseconds
+ * on the best-effort stream, unless that is being captured. */
 int tally_launch_native(tally_ctx *ctx, const tally_kernel_desc *desc, int on_hi_stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight

@@ -86,6 +86,8 @@ struct KernelOps {
   uint32_t (*team_bytes)(uint32_t workers, uint32_t chunk);
   // the blocks of a fetch are taken together: their number is left alone (last_round)
   bool together;
+  // the original form's kernel depends on what else is on the GPU
+  bool chooses;
 };
 
 template <class Body>
@@ -266,8 +268,8 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // 64x64.  The tile is the one for which the model at GemmRingT says the least: (RA + RB) for each stage of as many
 // tiles as a compute unit gets, and 10 + 8 (RA + RB) of those units, of 0.05 us, for every time it starts anew.  One tile
 // after the other on a unit that holds one at a time is a fifth slower than that (3000 x 3000 x 2048 in 128x96
-// 48.6 us, 42.7 in 96x96, two on a unit); six stages ahead instead of three are a tenth faster and 1 us longer under
-// way (1280 x 1280 x 4096 22.2 and 19.3, x 768 6.0 and 6.6); 256x128 tiles count as 16.5 (17.8 in a batch, whose
+// 48.6 us, 42.7 in 96x96, two on a unit); five stages ahead instead of three are a tenth faster and 1 us longer under
+// way (1280 x 1280 x 4096 22.2 and 19.9, x 768 6.0 and 6.6); 256x128 tiles count as 16.5 (17.8 in a batch, whose
 // tiles are not dealt out to the dies by product), 256x256 tiles as 20.5 and 24 x 10 to start, 128x64 through
 // registers as 7.8, four on a unit (2048 x 4096 x 448 in those 13.8 us, 15.2 in 128x128 or 96x96).
 // Without the large tiles among them, where smaller ones need another round for a few: us in the best of the others
@@ -275,8 +277,11 @@ hipError_t launch_ptb_rows_t(hipStream_t s, const void *args, const PtbCtl &c) {
 // 3328 x 3072 x 6304 153 (128x128) / 111.  Of 597 products of k = 128 to 8192 the choice takes 1 % longer than the
 // best tile in the mean, and over 6 % longer in 49 with operands from the caches and 29 from memory.
 // For less work tiles through registers are as fast or faster (1024 x 1024 x 256 3.64 us, 3.78 in 64x64).
+// None of them fills more of a compute unit than 128 KB alone or 160 KB as two that come and go: beside the long ones,
+// which may be a best-effort product's, a request's tiles through registers find 16 to 24 KB (1280 x 1280 x 4096 in
+// tiles of 144 KB, 128 x 768 x 3072 beside it 30.7 us from the call to its end, 21.6 so).
 enum class GemmCover { k32, k32x64, k64, k128x64, k256x128, k256x256, kWave16, kWave16x32, kWave32x16, kRing };
-#define GEMM_RINGS(X) X(1, 1, 8) X(1, 2, 6) X(2, 2, 5) X(2, 3, 4) X(4, 2, 3) X(3, 3, 3) X(4, 2, 6) X(3, 3, 6) X(4, 3, 5) X(4, 4, 4)
+#define GEMM_RINGS(X) X(1, 1, 8) X(1, 2, 6) X(2, 2, 5) X(2, 3, 4) X(4, 2, 3) X(3, 3, 3) X(4, 2, 5) X(3, 3, 5) X(4, 3, 4) X(4, 4, 4)
 #define GEMM_RING_ROW(ra, rb, r) {32 * ra, 32 * rb, GemmRingT<ra, rb, r>::MIN_WAVES, r},
 constexpr uint32_t kRings[][4] = {GEMM_RINGS(GEMM_RING_ROW)};   // tile, how many fit a compute unit, stages
 constexpr uint32_t kRingCount = sizeof(kRings) / sizeof(kRings[0]);
@@ -298,7 +303,7 @@ GemmCover gemm_ring(const tally_gemm_bf16_args &a, uint32_t large) {
   for (uint32_t i = 0; i < kRingCount; ++i) {
     const uint64_t t = (uint64_t)cdiv(a.m, kRings[i][0]) * cdiv(a.n, kRings[i][1]) * a.batch, rounds = cdiv(t, 256);
     const uint64_t size = (kRings[i][0] + kRings[i][1]) / 32, per_cu = kRings[i][2];
-    const bool deep = per_cu == 1 && kRings[i][3] >= 6;
+    const bool deep = per_cu == 1 && kRings[i][3] >= 5;
     const uint64_t unit = per_cu == 1 && rounds > 1 ? 24 : deep ? 17 : 20;   // half units
     const uint64_t cost = rounds * ns * size * unit / 2 + cdiv(t, 256 * per_cu) * 10 * (10 + 8 * size + (deep ? 20 : 0));
     if (cost < least) {
@@ -657,7 +662,7 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
   {nm, sizeof(Body::Args), true, gridfn, launch_native_t<Body>, launch_sliced_t<Body>,     \
    launch_ptb_t<Body>, init_t<Body>, occupancy_t<Body>, pause_fraction_t<Body>,              \
    footprint_t<Body>, {footprint_native_t<Body>}, nullptr, nullptr, nullptr, block_bytes<Body>, Body::team_bytes, \
-   TakesTogether<Body>::value}
+   TakesTogether<Body>::value, false}
 
 #define GEMM_TILES(Tile32, canon)                                                                         \
   footprint_native_t<Tile32>, footprint_native_t<GemmTileT<1, 2, canon>>,                                 \
@@ -671,13 +676,13 @@ struct TakesTogether<Body, std::enable_if_t<Body::TOGETHER>> : std::true_type {}
    launch_sliced_rows_t<Wide, Narrow, Team>, launch_ptb_rows_t<Wide, NarrowDeep, Team>, init_t<Wide>,     \
    occupancy, pause_fraction_t<Wide>, footprint_t<Wide>,                                                  \
    {footprint_native_t<Narrow>, footprint_native_t<Wide>, footprint_native_t<Team>},                      \
-   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>, nullptr, block_bytes<Wide>, Wide::team_bytes, false}
+   rows_choice<Wide, Narrow>, rows_range<Wide, Narrow>, nullptr, block_bytes<Wide>, Wide::team_bytes, false, false}
 #define OPS_GEMM(Body, nm, gridfn, slices)                                                                \
   {nm, sizeof(Body::Args), true, gridfn, launch_native_gemm_t<Body>, launch_sliced_t<Body>,               \
    GemmParts<Body>::launch, GemmParts<Body>::init, occupancy_t<Body>, GemmParts<Body>::pause_fraction,    \
    GemmParts<Body>::footprint, {GEMM_TILES(GemmTile32, false), footprint_native_t<GemmN128Body>, footprint_native_t<Body>,    \
                        GEMM_WAVE_TILES(false) GEMM_RINGS(GEMM_RING_FOOT_F)},                                                           \
-   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr, false}
+   gemm_native_choice<Body::TILE_N>, gemm_sliced_choice<slices>, GemmParts<Body>::parts, nullptr, nullptr, false, true}
 
 const KernelOps kOps[TALLY_K_COUNT] = {
     OPS(SaxpyBody, "saxpy", grid_saxpy),
@@ -691,13 +696,13 @@ const KernelOps kOps[TALLY_K_COUNT] = {
              (occupancy_capped_t<LayerNormBody, 2>), "layernorm_f32", grid_layernorm),
     {"attn_decode_bf16", sizeof(tally_attn_decode_args), false, grid_attn, launch_native_attn,
      nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, {footprint_attn<4>, footprint_attn<8>}, attn_choice,
-     nullptr, nullptr, nullptr, nullptr, false},
+     nullptr, nullptr, nullptr, nullptr, false, false},
     {"gemm_bf16_small", sizeof(GemmSmallBody::Args), true, grid_gemm_small, launch_native_gemm_small,
      launch_sliced_t<GemmSmallBody>, launch_ptb_t<GemmSmallBody>, init_gemm_small, occupancy_t<GemmSmallBody>,
      pause_fraction_t<GemmSmallBody>, footprint_t<GemmSmallBody>, {GEMM_TILES(GemmSmallBody, true), nullptr, nullptr, GEMM_WAVE_TILES(true) GEMM_RINGS(GEMM_RING_FOOT_T)},
      gemm_small_native_choice,
      gemm_sliced_choice<GemmCover::k32>, nullptr, block_bytes<GemmSmallBody>, GemmSmallBody::team_bytes,
-     false},
+     false, true},
     OPS_GEMM(GemmN128Body, "gemm_bf16_n128", grid_gemm_n128, GemmCover::k256x128),
 };
 
@@ -782,6 +787,8 @@ struct tally_ctx {
   std::atomic<uint32_t> wait_seq;   // numbers the markers that waits put on a stream
   std::atomic<int> jobs;            // best-effort jobs, launched or about to be
   std::atomic<int> heavy_jobs;      // those whose workgroups leave little LDS (leaves_little_lds)
+  std::atomic<uint32_t> native_be;  // launches in the original form on the caller's best-effort stream (see native_done)
+  std::atomic<uint32_t> native_asked;  // of them, how many lie before the last marker of native_done()
   int device;
   int live_jobs;
   // profile-guided configuration (Section 4.2): per (kernel, grid, block) the candidate
@@ -878,8 +885,40 @@ int settle_relay(tally_ctx *ctx, int slot) {
 
 // Does a workgroup of `foot` leave LDS for no more than two one-wave GEMM tiles beside it?
 bool leaves_little_lds(const tally_ctx *ctx, const uint32_t *foot) { return foot[0] + 3 * kWaveTileLds > ctx->lds_per_cu; }
+// A product in its original form on the best-effort stream is no job, and a tile that fills more than half of a
+// compute unit's LDS stays there for all of its k: beside those a request takes the tiles that it takes beside a heavy
+// job (behind a launch of 8192^3, call to completion: 128 x 768 x 3072 26.8 us, 32.3 in the tiles for a GPU of its
+// own, 512 x 512 x 2048 22.6 and 101).  Smaller ones make room soon enough (12 of 413 x 741 x 640 again and again,
+// 96x96 tiles, 512 x 512 x 2048 21.1 us so and 28.0 in the tiles for beside jobs).
+// Have all such kernels ended?  The answer is the word of a marker behind them, which is enqueued (ask_native_done)
+// only where somebody wants to know: the first one to ask is told no.  (hipStreamQuery on a busy stream takes 16 us
+// of the caller's time, a marker behind every launch 3 us of the stream's.)
+bool native_done(const tally_ctx *ctx) {
+  return __atomic_load_n(ctx->marker_host + 48, __ATOMIC_ACQUIRE) == ctx->native_be.load() || ctx->hi == ctx->be;
+}
+void ask_native_done(tally_ctx *ctx) {
+  const uint32_t launched = ctx->native_be.load();   // (counted behind the launch call: the marker follows them all)
+  hipStreamCaptureStatus capture;
+  if (native_done(ctx) || ctx->native_asked.exchange(launched) == launched) return;
+  if (hipStreamIsCapturing(ctx->be, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+      launch(marker_kernel, dim3(1), dim3(64), 0, ctx->be, ctx->marker_dev + 48, launched) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->native_asked = launched - 1;                // (not now: asked for again by the next one)
+  }
+}
+// How a kernel in its original form is launched on one of the streams.
 uint32_t be_launch(const tally_ctx *ctx) { return ctx->jobs.load() > 0 ? kShared : 0u; }
-uint32_t hi_launch(const tally_ctx *ctx) { return kUrgent | be_launch(ctx) | (ctx->heavy_jobs.load() > 0 ? kBeside : 0u); }
+uint32_t hi_launch(const tally_ctx *ctx) {
+  if (!native_done(ctx)) return kUrgent | kShared | kBeside;
+  return kUrgent | (ctx->jobs.load() > 0 ? kShared : 0u) | (ctx->heavy_jobs.load() > 0 ? kBeside : 0u);
+}
+// What the kernel occupies that a launch in its original form takes, and its workgroups.
+const uint32_t *native_footprint(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t how, uint64_t *groups) {
+  const KernelOps &ops = kOps[desc->kernel_id];
+  *groups = (uint64_t)desc->grid.x * desc->grid.y * desc->grid.z;
+  return ctx->foot_native[desc->kernel_id][ops.native_choice ? ops.native_choice(desc->args, how, groups) : 0];
+}
+
 // What one workgroup of a job of this kind occupies.
 const uint32_t *job_footprint(const tally_ctx *ctx, const tally_kernel_desc *desc, int kind, uint64_t *groups) {
   const KernelOps &ops = kOps[desc->kernel_id];
@@ -1276,6 +1315,7 @@ int tally_create(tally_ctx **out, void *hip_stream_hi, void *hip_stream_be) {
   c->live_jobs = 0;
   c->wait_seq = 0;
   c->jobs = c->heavy_jobs = 0;
+  c->native_be = c->native_asked = 0;
   c->next_slot = 0;
   c->n_shunned = 0;
   c->n_side = 0;
@@ -1408,7 +1448,13 @@ int tally_launch_native(tally_ctx *ctx, const tally_kernel_desc *desc, int on_hi
   tally_dim3 g;
   int rc = check_desc(desc, &ops, &g);
   if (rc) return rc;
-  HIPCHK(ops->native(on_hi_stream ? ctx->hi : ctx->be, desc->args, g, on_hi_stream ? hi_launch(ctx) : be_launch(ctx)));
+  const uint32_t how = on_hi_stream ? hi_launch(ctx) : be_launch(ctx);
+  HIPCHK(ops->native(on_hi_stream ? ctx->hi : ctx->be, desc->args, g, how));
+  if (ops->chooses) {
+    uint64_t groups;
+    if (on_hi_stream) ask_native_done(ctx);
+    else if (2 * native_footprint(ctx, desc, how, &groups)[0] > ctx->lds_per_cu) ctx->native_be++;
+  }
   return TALLY_OK;
 }
 
@@ -2062,13 +2108,6 @@ struct tally_sched {
 
 namespace {
 
-// What the kernel occupies that a launch in its original form takes, and its workgroups.
-const uint32_t *native_footprint(tally_ctx *ctx, const tally_kernel_desc *desc, uint32_t how, uint64_t *groups) {
-  const KernelOps &ops = kOps[desc->kernel_id];
-  *groups = (uint64_t)desc->grid.x * desc->grid.y * desc->grid.z;
-  return ctx->foot_native[desc->kernel_id][ops.native_choice ? ops.native_choice(desc->args, how, groups) : 0];
-}
-
 // Per-compute-unit demand of the workgroups a best-effort kernel puts on the GPU at once
 // (all its workers; one slice; the whole grid for a native launch), spread evenly.
 int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_config &cfg, uint32_t *lds,
@@ -2456,6 +2495,8 @@ int tally_sched_submit_hi(tally_sched *s, const tally_kernel_desc *kernels, uint
     if (e != hipSuccess) { g_last_hip = (int)e; rc = TALLY_ERR_HIP; }
   }
   if (rc == TALLY_OK) rc = tally_marker(ctx, 1, ++s->hi_seq);
+  for (uint32_t i = 0; i < n; ++i)
+    if (kOps[kernels[i].kernel_id].chooses) { ask_native_done(ctx); break; }
   if (rc != TALLY_OK) { s->hi_active = false; return rc; }
   s->hi_inflight = true;
   return TALLY_OK;

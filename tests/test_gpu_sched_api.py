@@ -436,6 +436,71 @@ def test_requests_beside_large_tiles_give_the_same_bits(env, m, n, k):
     assert torch.equal(C, alone) and bool((C != 0).any())
 
 
+@pytest.mark.parametrize("be", [(8192, 8192, 8192), (1280, 1280, 16384)])
+def test_a_request_runs_beside_a_product_that_is_no_job(env, be):
+    """A product launched in its original form on the best-effort stream counts too: the request takes
+    tiles that fit beside its 256x256, or 128x64, tiles and does not wait for their end (100 and 30 us of
+    a product that takes 22 alone), with the bits that it gives alone."""
+    B, ctx, torch = env
+    m, n, k = be
+    big = B.gemm_bf16(_bf16_zeros(torch, 1, m, k), _bf16_zeros(torch, 1, n, k), _bf16_zeros(torch, 1, m, n))
+    A, Bt = (torch.randn(1, 512, 2048, device="cuda").to(torch.bfloat16) for _ in range(2))
+    C = _bf16_zeros(torch, 1, 512, 512)
+    hi, stream = B.gemm_bf16(A, Bt, C, small=True), ctx._streams[0]
+    took, bits = {False: [], True: []}, []
+    for attempt in range(21):
+        for beside in (False, True):
+            C.zero_()
+            torch.cuda.synchronize()
+            if beside:
+                ctx.launch_native(big)
+                t0 = time.perf_counter()
+                while time.perf_counter() - t0 < 4e-5:
+                    pass
+            t0 = time.perf_counter()
+            ctx.launch_native(hi, hi=True)
+            stream.synchronize()
+            took[beside].append(time.perf_counter() - t0)
+            torch.cuda.synchronize()
+            bits.append(C.clone())
+    alone, beside = (sorted(took[b])[10] for b in (False, True))
+    assert beside < 1.3 * alone, (alone, beside)
+    assert all(torch.equal(b, bits[0]) for b in bits) and bool((bits[0] != 0).any())
+
+
+@pytest.mark.parametrize("captured", ["hi", "be"])
+def test_products_chosen_under_capture(env, captured):
+    """Asking for the end of a best-effort product neither ends a capture nor lands in it: the graph gives
+    the eager bits on every replay, and so does the product launched on the other stream meanwhile."""
+    B, ctx, torch = env
+    def product(m, n, k, small):
+        A, Bt = (torch.randn(1, r, k, device="cuda").to(torch.bfloat16) for r in (m, n))
+        C = _bf16_zeros(torch, 1, m, n)
+        return B.gemm_bf16(A, Bt, C, small=small), C
+    (hi, C_hi), (be, C_be) = product(300, 520, 1056, True), product(2048, 2048, 2048, False)
+    torch.cuda.synchronize()
+    ctx.launch_native(hi, hi=True)
+    ctx.launch_native(be)
+    torch.cuda.synchronize()
+    want_hi, want_be = C_hi.clone(), C_be.clone()
+    ctx.launch_native(be)                                  # (outstanding at the capture's start)
+    graph, stream = torch.cuda.CUDAGraph(), ctx._streams[captured == "be"]
+    with torch.cuda.graph(graph, stream=stream):
+        if captured == "be":
+            ctx.launch_native(be)
+        ctx.launch_native(hi, hi=True)                     # on the stream that is captured, or on the other
+    torch.cuda.synchronize()
+    for replay in range(4):
+        C_hi.zero_()
+        C_be.zero_()
+        torch.cuda.synchronize()
+        ctx.launch_native(be if captured == "hi" else hi, hi=captured == "be")
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C_hi, want_hi) and torch.equal(C_be, want_be)
+
+
 def test_admission_counts_the_workgroups_of_the_original_form(env):
     """4096 x 4096 x 64 in its original form is 2048 workgroups of 128x64, eight per compute unit:
     beside another client's workers it has to wait, where 256 workgroups of the large tile (one per
