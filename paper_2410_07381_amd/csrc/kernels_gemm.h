@@ -421,7 +421,8 @@ using GemmN128Body = GemmBodyT<2>;
 // operand, so lane l, register r of a block holds row l%16, column 4 (l/16) + r: four neighbours of one row,
 // packed to 8 bytes.  Of two column blocks the swaps make eight neighbours per lane (group l/16 columns 8 (l/16)
 // .. +7 of the 32), so that whole 64-byte pieces leave (4352 x 4864 x 64 13.3 us; 18.8 as 32-byte pieces).
-template <bool NAN7FC0, int RB>
+// NT: past the caches, for outputs whose rows all start at 16 bytes and have no remainder.
+template <bool NAN7FC0, bool NT, int RB>
 __device__ __forceinline__ void store_blocks(const tally_gemm_bf16_args &a, uint32_t bz, uint32_t row, uint32_t col0,
                                              uint32_t lane, const f32x4_t (&acc)[RB]) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -445,8 +446,11 @@ __device__ __forceinline__ void store_blocks(const tally_gemm_bf16_args &a, uint
         asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(w[q]), "+v"(w[2 + q]));
     }
     const uint32_t col = col0 + 16 * j + (lane >> 4) * (4 * W);
-    if (row < a.m) {
-      uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
+    uint16_t *g = a.C + bz * a.stride_c + (uint64_t)row * a.n + col;
+    if constexpr (NT) {
+      static_assert(W == 2, "16 bytes");
+      __builtin_nontemporal_store(u32x4_nt{w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4_nt *>(g));
+    } else if (row < a.m) {
       if (col + 4 * W <= a.n) {
         // (rows start at any multiple of 2 bytes and are stored alike: 413 x 741 x 640 x 12 in 19.0 us,
         // 23.5 with the widest aligned stores that each row allows)
@@ -684,7 +688,7 @@ struct GemmTileT {
     rest(rest, std::integral_constant<int, 0>{});
 #pragma unroll
     for (int i = 0; i < RA; ++i)
-      store_blocks<NAN7FC0>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);
+      store_blocks<NAN7FC0, false>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);
 #endif
   }
 };
@@ -851,7 +855,7 @@ struct GemmWaveT {
     }
 #pragma unroll
     for (int i = 0; i < NA; ++i)
-      store_blocks<NAN7FC0>(a, bz, by * TM + i * 16 + (lane & 15), bx * TN, lane, acc[i]);
+      store_blocks<NAN7FC0, false>(a, bz, by * TM + i * 16 + (lane & 15), bx * TN, lane, acc[i]);
 #endif
   }
 };
@@ -912,6 +916,7 @@ struct GemmRingT {
   static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
     run_tile<true>(a, bx, by, bz, ctl);
   }
+  // (YIELD: the best-effort form, which covers blocks of 256 rows and 128 columns and writes past the caches)
   template <bool YIELD>
   static __device__ __forceinline__ void run_tile(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -1093,7 +1098,7 @@ struct GemmRingT {
     }
 #pragma unroll
     for (int i = 0; i < RA; ++i)
-      store_blocks<NAN7FC0>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);
+      store_blocks<NAN7FC0, YIELD>(a, bz, by * TM + (wm * RA + i) * 16 + (lane & 15), bx * TN + wn * 16 * RB, lane, acc[i]);
 #endif
   }
 };

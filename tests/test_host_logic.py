@@ -165,6 +165,35 @@ def test_every_mirrored_struct_has_the_header_layout(B, tmp_path):
     assert got == want
 
 
+def _device_code(B, tmp_path):
+    """The built library's code object for the GPU, and a way to run one of the LLVM tools on it."""
+    import subprocess
+    llvm = "/opt/rocm/llvm/bin"
+    tools = {t: os.path.join(llvm, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf", "llvm-objdump")}
+    if not all(os.path.exists(t) for t in tools.values()):
+        pytest.skip("LLVM binary tools not installed")
+    fat, co = str(tmp_path / "fat.bin"), str(tmp_path / "dev.co")
+    subprocess.run([tools["llvm-objcopy"], "-O", "binary", "--only-section=.hip_fatbin", B.LIB_PATH, fat], check=True)
+    subprocess.run([tools["clang-offload-bundler"], "--unbundle", "--type=o", f"--input={fat}",
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--output={co}"], check=True)
+    return lambda tool, *args: subprocess.run([tools[tool], *args, co], check=True, capture_output=True, text=True).stdout
+
+
+def test_workers_write_gemm_outputs_past_the_caches(B, tmp_path):
+    """The best-effort forms keep the caches for the high-priority job: workers write large blocks, and the
+    parts of 32x64 to 128x128 that few blocks are handed out in, with non-temporal stores (the one or two
+    other stores of 16 bytes in a kernel are those of the coverage record)."""
+    run = _device_code(B, tmp_path)
+    names = [l.split()[-1] for l in run("llvm-readelf", "-sW").splitlines() if " FUNC " in l and "ptb_kernel" in l]
+    names = [n for n in names if "GemmRingT" in n or "GemmBodyT" in n]
+    assert sum("GemmRingT" in n for n in names) >= 8 and any("GemmRingT" not in n for n in names)
+    for name in names:
+        code = run("llvm-objdump", "-d", f"--disassemble-symbols={name}")
+        stores = [l for l in code.splitlines() if "store_dwordx4" in l]
+        past = sum(" nt" in l for l in stores)
+        assert past > 0 and len(stores) - past <= 2 and "store_short" not in code, name
+
+
 def test_static_scratch_is_a_global_symbol_of_the_device_code(B, tmp_path):
     """The runtime finds a device variable by name among the code object's global symbols.
     A file-scope static device array referenced from host code is given global binding by
