@@ -266,11 +266,14 @@ def test_workers_pause_inside_long_blocks_while_preempted(env):
         assert_bf16_close(got[0, r, c], a["C"][0, r, c])
 
 
-@pytest.mark.parametrize("m,n,k", [(256, 512, 1 << 18), (512, 1024, 1 << 17), (1024, 2048, 1 << 16)])
-def test_workers_on_parts_of_blocks_pause_as_well(env, m, n, k):
-    """Fewer blocks than workers over a long K, handed out in parts of 32x32, 64x64 and 128x64: a
-    pausing request raised mid-part suspends the workers until the pause is ended; the numbers are
-    those of an undisturbed run."""
+@pytest.mark.parametrize("m,n,k,n128", [
+    (256, 512, 1 << 18, False), (512, 1024, 1 << 17, False), (768, 1024, 1 << 17, False), (1024, 2048, 1 << 16, False),
+    (2048, 2048, 1 << 16, False), (512, 1024, 1 << 17, True), (768, 1024, (1 << 17) + 32, True), (1024, 2048, 1 << 16, True),
+    (2048, 2048, (1 << 16) + 96, True)])
+def test_workers_on_parts_of_blocks_pause_as_well(env, m, n, k, n128):
+    """Fewer blocks than workers over a long K, handed out in parts of 32x32, and of 32x64, 64x64, 128x64
+    and 128x128 (for blocks of 256 columns and of 128): a pausing request raised mid-part suspends the
+    workers until the pause is ended; the numbers are those of an undisturbed run."""
     import time
     B, ctx, torch = env
     gen = torch.Generator(device="cuda")
@@ -278,7 +281,7 @@ def test_workers_on_parts_of_blocks_pause_as_well(env, m, n, k):
     A = torch.randn(1, m, k, device="cuda", generator=gen).to(torch.bfloat16)
     Bt = torch.randn(1, n, k, device="cuda", generator=gen).to(torch.bfloat16)
     C = torch.empty(1, m, n, dtype=torch.bfloat16, device="cuda")
-    kern = B.gemm_bf16(A, Bt, C)
+    kern = B.gemm_bf16(A, Bt, C, n128=n128)
 
     def run(pause_s):
         C.fill_(float("nan"))
