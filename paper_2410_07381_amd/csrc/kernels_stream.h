@@ -331,7 +331,7 @@ struct GemvBody {
       const uint4 xv = buf_ld16(rx, lane * 16, j * kWave * 16);
       float &acc = j % 4 == 0 ? acc0 : j % 4 == 1 ? acc1 : j % 4 == 2 ? acc2 : acc3;
       acc = dot8(wv[j], xv, acc);
-      if (j == 3) __builtin_amdgcn_sched_barrier(0);       // (x's loads by fours, as above)
+      if (j == 3) __builtin_amdgcn_sched_barrier(0);       // (x's loads by fours, for the registers)
     }
 #endif
   }
@@ -350,22 +350,26 @@ struct GemvBody {
     // waves fit on a SIMD, and with four loads each the eight waves of a compute unit had
     // 32 KB on their way where the HBM's latency times the unit's share of its bandwidth
     // asks for ~45 KB: the decode-like request ran at 4.3 TB/s co-located against 5.6 alone.
-    // The operand x comes from the caches; its loads are taken four at a time to stay
-    // within the 64 registers that let two waves fit.
+    // The operand x comes from the caches.  Loads return in order, so each of the first four of the row is followed by
+    // x's, and the last four take registers that the first products leave free, within the 64 that let two waves
+    // fit (4096 x 4096 from memory 7.05 us; all eight of the row first 7.30, in the compiler's order 7.20).
     for (; DEEP && first + 8 * kWave <= nvec; first += 8 * kWave) {
       const uint32_t v = first + lane;
-      const uint4 w0 = w[v], w1 = w[v + kWave], w2 = w[v + 2 * kWave], w3 = w[v + 3 * kWave];
-      const uint4 w4 = w[v + 4 * kWave], w5 = w[v + 5 * kWave], w6 = w[v + 6 * kWave], w7 = w[v + 7 * kWave];
-      uint4 x0 = x[v], x1 = x[v + kWave], x2 = x[v + 2 * kWave], x3 = x[v + 3 * kWave];
+      const uint4 w0 = w[v], x0 = x[v], w1 = w[v + kWave], x1 = x[v + kWave];
+      const uint4 w2 = w[v + 2 * kWave], x2 = x[v + 2 * kWave], w3 = w[v + 3 * kWave], x3 = x[v + 3 * kWave];
+      const uint4 x4 = x[v + 4 * kWave], x5 = x[v + 5 * kWave];
+      __builtin_amdgcn_sched_barrier(0);
       acc0 = dot8(w0, x0, acc0);
       acc1 = dot8(w1, x1, acc1);
       acc2 = dot8(w2, x2, acc2);
+      const uint4 x6 = x[v + 6 * kWave], x7 = x[v + 7 * kWave];
+      const uint4 w4 = w[v + 4 * kWave], w5 = w[v + 5 * kWave], w6 = w[v + 6 * kWave], w7 = w[v + 7 * kWave];
+      __builtin_amdgcn_sched_barrier(0);
       acc3 = dot8(w3, x3, acc3);
-      x0 = x[v + 4 * kWave]; x1 = x[v + 5 * kWave]; x2 = x[v + 6 * kWave]; x3 = x[v + 7 * kWave];
-      acc0 = dot8(w4, x0, acc0);
-      acc1 = dot8(w5, x1, acc1);
-      acc2 = dot8(w6, x2, acc2);
-      acc3 = dot8(w7, x3, acc3);
+      acc0 = dot8(w4, x4, acc0);
+      acc1 = dot8(w5, x5, acc1);
+      acc2 = dot8(w6, x6, acc2);
+      acc3 = dot8(w7, x7, acc3);
     }
     for (; !DEEP && first + 4 * kWave <= nvec; first += 4 * kWave) {
       const uint32_t v = first + lane;
@@ -376,15 +380,21 @@ struct GemvBody {
       acc3 = dot8(w3, x[v + 3 * kWave], acc3);
     }
     // What is left of the row is one batch more: taken four vectors and then one by one it was up to four
-    // memory latencies in a row (us so / now: 700 x 16000 6.40 / 5.34, 16000 x 520 5.5 / 4.9, 4096 x 11008
-    // 15.3 / 14.8, 20000 x 6000 41.5 / 40.3; asking for eight where there are two costs 8000 x 1000 0.6 us).
-    switch ((nvec - first + kWave - 1) / kWave) {
-      case 0: break;
-      case 1: rest<1>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
-      case 2: rest<2>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
-      case 3: rest<3>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
-      case 4: rest<4>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3); break;
-      default: if constexpr (DEEP) rest<8>(w + first, x + first, nvec - first, lane, acc0, acc1, acc2, acc3);
+    // memory latencies in a row (us so / now: 700 x 16000 5.7 / 4.4, 3000 x 3592 4.7 / 3.3, 8425 x 1616 6.1 / 4.1),
+    // and asking for eight where there are five costs as much as eight (7771 x 2224 6.1 / 5.0, from memory 9.2 / 7.3).
+    // The row is made known to be the same in a wave, so that the buffers' descriptors are in scalar registers.
+    if (const uint32_t left = nvec - first) {
+      const uint4 *e = reinterpret_cast<const uint4 *>(a.W + (uint64_t)__builtin_amdgcn_readfirstlane(row) * a.k) + first;
+      switch ((left + kWave - 1) / kWave) {
+        case 1: rest<1>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 2: rest<2>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 3: rest<3>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 4: rest<4>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 5: if constexpr (DEEP) rest<5>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 6: if constexpr (DEEP) rest<6>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 7: if constexpr (DEEP) rest<7>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        default: if constexpr (DEEP) rest<8>(e, x + first, left, lane, acc0, acc1, acc2, acc3);
+      }
     }
     float s = wave_sum((acc0 + acc1) + (acc2 + acc3));
     if (lane == 0) a.y[row] = f32_to_bf16(s);

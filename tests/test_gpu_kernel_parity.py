@@ -703,7 +703,7 @@ def test_gemv(env, n, k, form):
     assert_bf16_close(host(y), a["y"])
 
 
-@pytest.mark.parametrize("k", [8, 504, 512, 520, 1024, 1032, 1536, 1544, 2040, 2048, 2056, 2560, 3584, 3592, 4088, 4096, 4104, 6152, 8200, 11008])
+@pytest.mark.parametrize("k", [8, 504, 512, 520, 1024, 1032, 1536, 1544, 2040, 2048, 2056, 2560, 2568, 3072, 3080, 3584, 3592, 4088, 4096, 4104, 6152, 8200, 11008])
 def test_gemv_row_ends(env, k):
     """Every number of vectors that a lane can have left behind the whole batches, each with the last one whole,
     one lane and all but one: nothing beyond a row or x is read (NaNs lie there), and both forms give the same bits."""

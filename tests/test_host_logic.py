@@ -194,6 +194,17 @@ def test_workers_write_gemm_outputs_past_the_caches(B, tmp_path):
         assert past > 0 and len(stores) - past <= 2 and "store_short" not in code, name
 
 
+def test_gemv_keeps_its_buffer_descriptors_in_scalar_registers(B, tmp_path):
+    """The end of a row is read through a buffer that ends with it; were the row's number not known to be the
+    same in a wave, each of those loads would be a loop over the lanes' descriptors."""
+    run = _device_code(B, tmp_path)
+    names = [l.split()[-1] for l in run("llvm-readelf", "-sW").splitlines() if " FUNC " in l and "native_kernel" in l and "GemvBody" in l]
+    assert len(set(names)) == 1
+    code = run("llvm-objdump", "-d", f"--disassemble-symbols={names[0]}")
+    assert code.count("buffer_load_dwordx4") >= 2 * (1 + 2 + 3 + 4 + 5 + 6 + 7 + 8)
+    assert code.count("v_readfirstlane_b32") <= 2
+
+
 def test_static_scratch_is_a_global_symbol_of_the_device_code(B, tmp_path):
     """The runtime finds a device variable by name among the code object's global symbols.
     A file-scope static device array referenced from host code is given global binding by
