@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "../../include/tally.h"
+#include "admission.h"
 #include "kernels_attn.h"
 #include "kernels_gemm.h"
 #include "kernels_stream.h"
@@ -2068,7 +2069,7 @@ struct BeClient {
   int profiling = -1;            // candidate index this invocation measures, or -1
   double t_launch = 0.0;
   bool preempt_seen = false;     // a preemption request was raised against the current segment
-  uint32_t dl = 0, dw = 0, dr = 0;   // per-compute-unit demand of its resident workgroups
+  Demand resident{0, 0, 0};      // what its workgroups on the GPU occupy of a compute unit
   uint64_t ticket = 0;           // place in the queue of clients waiting for room (0: not waiting)
   std::atomic<uint64_t> kernels_done{0}, steps_done{0};
 };
@@ -2110,8 +2111,7 @@ namespace {
 
 // Per-compute-unit demand of the workgroups a best-effort kernel puts on the GPU at once
 // (all its workers; one slice; the whole grid for a native launch), spread evenly.
-int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_config &cfg, uint32_t *lds,
-                uint32_t *waves, uint32_t *regs) {
+int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_config &cfg, Demand *d) {
   const KernelOps *ops;
   tally_dim3 g;
   int rc = check_desc(desc, &ops, &g);
@@ -2123,9 +2123,9 @@ int item_demand(tally_ctx *ctx, const tally_kernel_desc *desc, const tally_confi
   const uint64_t per_cu = (groups + ctx->num_cus - 1) / ctx->num_cus;
   const uint64_t cap = 64;  // beyond any compute unit's capacity: keeps the products small
   const uint32_t n = (uint32_t)(per_cu < cap ? per_cu : cap);
-  *lds = n * l;
-  *waves = n * w;
-  *regs = n * ((w + 3) / 4) * r;  // per SIMD: a workgroup's waves go round the four SIMDs
+  d->lds = n * l;
+  d->waves = n * w;
+  d->regs = n * ((w + 3) / 4) * r;  // per SIMD: a workgroup's waves go round the four SIMDs
   return TALLY_OK;
 }
 
@@ -2169,33 +2169,16 @@ void be_thread_main(tally_sched *s) {
   tally_ctx *ctx = s->ctx;
   int rc = TALLY_OK;
   if (hipSetDevice(ctx->device) != hipSuccess) { s->rc = TALLY_ERR_HIP; return; }
-  // A kernel is put on the GPU only if all the workgroups it brings fit beside the
-  // best-effort workgroups already resident: a dispatch that waits for resources blocks
-  // its hardware pipe for every queue mapped to that pipe, the high-priority queue
-  // possibly among them (two 128 KB-LDS GEMMs launched together held high-priority
-  // kernels back for milliseconds).  Clients that have to wait are served first come,
-  // first served.  A client with the GPU to itself is always admitted.
-  auto admit = [&](uint32_t c, uint32_t l, uint32_t w, uint32_t r) -> bool {
-    BeClient &cl = s->clients[c];
-    if (cl.ticket == 0) cl.ticket = ++s->next_ticket;
-    uint32_t lds = 0, waves = 0, regs = 0, others = 0;
-    for (uint32_t o = 0; o < s->n_clients; ++o) {
-      if (o == c) continue;
-      const BeClient &oc = s->clients[o];
-      if (oc.ticket != 0 && oc.ticket < cl.ticket) return false;
-      if (oc.dw) others++;
-      lds += oc.dl;
-      waves += oc.dw;
-      regs += oc.dr;
-    }
-    // (one wave slot and 32 registers are kept back for the newcomer's relay)
-    if (others && (lds + l > ctx->lds_per_cu || waves + w > 31u || regs + r > 480u)) return false;
-    SpinGuard g(cl.lock);
-    cl.dl = l; cl.dw = w; cl.dr = r;
-    cl.ticket = 0;
-    return true;
+  // may(): asked last, see admission.h
+  auto admit = [&](uint32_t c, const Demand &d, auto may) -> bool {
+    return tally::admit(s->clients, s->n_clients, c, d, ctx->lds_per_cu, &s->next_ticket, [&]() {
+      if (!may()) return false;
+      SpinGuard g(s->clients[c].lock);
+      s->clients[c].resident = d;
+      return true;
+    });
   };
-  auto vacate = [&](BeClient &cl) { SpinGuard g(cl.lock); cl.dl = cl.dw = cl.dr = 0; };
+  auto vacate = [&](BeClient &cl) { SpinGuard g(cl.lock); cl.resident = Demand{0, 0, 0}; };
   auto set_job = [&](BeClient &cl, tally_job *j) { SpinGuard g(cl.lock); cl.job = j; };
   auto note_preempt = [&](double us) {
     s->n_preempts++;
@@ -2264,12 +2247,12 @@ void be_thread_main(tally_sched *s) {
           } else if (closing) {
             // best-effort work is switched off: the kernel stays stopped where it is
           } else if (!hold) {
-            uint32_t l = 0, w = 0, r = 0;
+            Demand d{0, 0, 0};
             tally_config cfg{};
             cfg.kind = (uint32_t)be->kind;
             cfg.param = be->kind == KIND_PTB ? be->workers : be->slice_blocks;
-            (void)item_demand(ctx, &cl.cur.desc, cfg, &l, &w, &r);
-            if (admit(c, l, w, r)) {
+            (void)item_demand(ctx, &cl.cur.desc, cfg, &d);
+            if (admit(c, d, []() { return true; })) {
               rc = tally_resume(be);   // kernel.resume()
               if (rc) break;
               // a request that arrived while the resume was being made saw a stopped job
@@ -2302,17 +2285,19 @@ void be_thread_main(tally_sched *s) {
           int prof = -1;
           rc = choose_config(s, cl.cur, &cfg, &prof);
           if (rc) break;
-          uint32_t l = 0, w = 0, r = 0;
-          (void)item_demand(ctx, &cl.cur.desc, cfg, &l, &w, &r);
+          Demand d{0, 0, 0};
+          (void)item_demand(ctx, &cl.cur.desc, cfg, &d);
           // A request's kernels are chosen by what is resident.  The job counts before the flag is looked at
-          // again: either it is seen there or the request is seen here.
-          const bool admitted = admit(c, l, w, r);
-          if (admitted) { ctx->jobs++; ctx->heavy_jobs++; }
-          if (admitted && s->opts.policy != 2 && s->hi_active.load()) {
+          // again: either it is seen there or the request is seen here, and the client keeps its place.
+          const bool admitted = admit(c, d, [&]() {
+            ctx->jobs++;
+            ctx->heavy_jobs++;
+            if (s->opts.policy == 2 || !s->hi_active.load()) return true;
             ctx->heavy_jobs--;
             ctx->jobs--;
-            vacate(cl);
-          } else if (admitted) {
+            return false;
+          });
+          if (admitted) {
             ctx->cur_be = cl.be;
             ctx->cur_ctl = cl.ctl;
             tally_be_item it = {&cl.cur.desc, cfg};
@@ -2483,7 +2468,8 @@ int tally_sched_submit_hi(tally_sched *s, const tally_kernel_desc *kernels, uint
       // Workers may pause inside their blocks only if every kernel of the request fits
       // beside the paused workgroups on a compute unit; otherwise the request would wait
       // for them while they wait for it: then they give way at block boundaries only.
-      const bool fits = cl.dl + hl <= ctx->lds_per_cu && cl.dw + hw <= 32u && cl.dr + hr <= 512u;
+      const Demand &d = cl.resident;
+      const bool fits = d.lds + hl <= ctx->lds_per_cu && d.waves + hw <= 32u && d.regs + hr <= 512u;
       if (fits && !(s->opts.flags & TALLY_SCHED_NO_PAUSE)) (void)tally_preempt_pausing(cl.job);
       else (void)tally_preempt(cl.job);
     }

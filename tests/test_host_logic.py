@@ -205,6 +205,46 @@ def test_gemv_keeps_its_buffer_descriptors_in_scalar_registers(B, tmp_path):
     assert code.count("v_readfirstlane_b32") <= 2
 
 
+def test_a_client_that_a_request_holds_back_keeps_its_place(tmp_path):
+    """Best-effort clients are served first come, first served.  One whose turn has come while a request arrives
+    is not launched; it goes on waiting in its place and not behind those that came later."""
+    import subprocess
+    src = tmp_path / "admission.cpp"
+    src.write_text(r"""
+#include <cstdio>
+#include "admission.h"
+struct Client { uint64_t ticket = 0; tally::Demand resident{0, 0, 0}; };
+int main() {
+  Client c[3];
+  uint64_t last = 0;
+  const tally::Demand whole{131072, 4, 352}, small{16384, 4, 64};
+  auto go = [&](uint32_t i, const tally::Demand &d, bool request) {
+    const bool in = tally::admit(c, 3, i, d, 163840, &last, [&]() { return !request; });
+    if (in) c[i].resident = d;
+    return (int)in;
+  };
+  int r[9];
+  r[0] = go(0, whole, false);              // 0 has the GPU
+  r[1] = go(1, whole, false);              // 1 waits, then 2
+  r[2] = go(2, small, false);
+  c[0].resident = {0, 0, 0};               // 0 leaves
+  r[3] = go(2, small, false);              // not before 1
+  r[4] = go(1, whole, true);               // 1's turn, and a request arrives
+  r[5] = go(2, small, false);              // still not before 1
+  r[6] = go(0, whole, false);              // 0 comes again, behind both
+  r[7] = go(1, whole, false);
+  r[8] = go(2, small, false);              // fits beside 1
+  for (int i = 0; i < 9; ++i) printf("%d ", r[i]);
+  return 0;
+}
+""")
+    exe = tmp_path / "admission"
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_07381_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", csrc, str(src), "-o", str(exe)], check=True, timeout=60)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=10).stdout.split()
+    assert out == list("100000011")
+
+
 def test_static_scratch_is_a_global_symbol_of_the_device_code(B, tmp_path):
     """The runtime finds a device variable by name among the code object's global symbols.
     A file-scope static device array referenced from host code is given global binding by
