@@ -48,6 +48,7 @@
 
 #include "../../include/tally.h"
 #include "kernels_stream.h"
+#include "gemm_cover.h"
 #include "launch_forms.h"
 
 namespace tally {
@@ -58,9 +59,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 typedef const __attribute__((address_space(1))) void *gptr_t;
 typedef __attribute__((address_space(3))) void *lptr_t;
-
-// bytes of output from which GemmBodyT writes it past the caches
-constexpr uint64_t kGemmBigOutput = 128ull << 20;
 
 // NB = 32-column strips per wave: 4 gives the 256x256 tile, 2 a 256x128 tile (128
 // accumulators per lane) for operands whose n is only a multiple of 128.
@@ -733,16 +731,8 @@ struct GemmWaveT {
   static __device__ __forceinline__ void run(const Args &a, uint32_t die, uint32_t in, uint32_t at) {
 #ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
     extern __shared__ __align__(1024) unsigned char tally_dyn_lds[];
-    const bool tall = a.m > a.n;
-    const uint32_t panels = tall ? (a.m + TM - 1) / TM : (a.n + TN - 1) / TN;   // of a product
-    const uint32_t q = panels * a.batch / 8, rest = panels * a.batch % 8;
-    if (at >= q + (die < rest ? 1 : 0)) return;
-    uint32_t panel = die * q + (die < rest ? die : rest) + at, bz = 0;
-    if (a.batch > 1) {
-      bz = panel / panels;
-      panel -= bz * panels;
-    }
-    const uint32_t bx = tall ? in : panel, by = tall ? panel : in;
+    uint32_t bx, by, bz;
+    if (!wave_tile(a, TM, TN, die, in, at, &bx, &by, &bz)) return;
     const uint32_t lane = threadIdx.x;
     const uint32_t K = a.k;
     const uint32_t LDA = a.lda ? a.lda : K, LDB = a.ldb ? a.ldb : K;
@@ -901,16 +891,9 @@ struct GemmRingT {
   }
   static __device__ __forceinline__ void run(const Args &a, uint32_t id, uint32_t, uint32_t) {
 #ifdef __HIP_DEVICE_COMPILE__  // (buffer resources have no type in the host compiler's pass)
-    const uint32_t X = (a.n + TN - 1) / TN, Y = (a.m + TM - 1) / TM, T = X * Y * a.batch, q = T / 8, rest = T % 8;
-    const uint32_t die = id & 7, at = id >> 3;
-    if (at >= q + (die < rest ? 1 : 0)) return;
-    uint32_t t = die * q + (die < rest ? die : rest) + at;
-    const uint32_t bz = t / (X * Y);
-    t -= bz * (X * Y);
-    const uint32_t H = q >= 48 ? 8 : q >= 12 ? 4 : 2;
-    const uint32_t band = t / (H * X), in = t - band * H * X, h = Y - band * H < H ? Y - band * H : H;
-    const uint32_t bx = in / h;
-    run_tile<false>(a, bx, band * H + (in - bx * h), bz, YieldCtl{nullptr, 0, 0, 15, false});
+    uint32_t bx, by, bz;
+    if (!ring_tile(a, TM, TN, id, &bx, &by, &bz)) return;
+    run_tile<false>(a, bx, by, bz, YieldCtl{nullptr, 0, 0, 15, false});
 #endif
   }
   static __device__ __forceinline__ void run_yielding(const Args &a, uint32_t bx, uint32_t by, uint32_t bz, const YieldCtl ctl) {

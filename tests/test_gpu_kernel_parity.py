@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import tally_inputs as TI
+from gemm_tiles import GEMM_TILES
 from oracle import kernels as OK
 from oracle import schedules as OS
 
@@ -468,9 +469,8 @@ def test_gemm_small_original_form_larger_tiles(env, m, n, k, batch):
 @pytest.mark.parametrize("m,n,batch", [(1, 1, 1), (17, 33, 3), (70, 130, 8), (128, 768, 1), (100, 880, 1), (15, 16, 384), (256, 256, 1),
                                        (17, 50, 48)])
 def test_gemm_one_wave_tiles(env, m, n, k, batch):
-    """Up to 384 tiles of 16x16, the original form takes tiles of a single wave from the third stage
-    on (where their number is odd either way, up to the twelfth): rows and columns past the matrix, three
-    to seventeen stages, a last stage half full, NaN beyond K and between the rows, nothing written
+    """Up to 640 tiles of 16x16 the original form takes tiles of a single wave from the third stage
+    on: rows and columns past the matrix, three to seventeen stages, a last stage half full, NaN beyond K and between the rows, nothing written
     behind C; the same bits as one worker's 32x32 blocks."""
     B, ctx, torch = env
     from gpu_util import dev, host, assert_bf16_close
@@ -508,10 +508,10 @@ def test_gemm_one_wave_tiles(env, m, n, k, batch):
 @pytest.mark.parametrize("k", [160, 288, 320, 352, 768])
 @pytest.mark.parametrize("m,n,batch", [(200, 1000, 1), (250, 1001, 1), (33, 5000, 1), (50, 4100, 1), (512, 1024, 1), (17, 50, 200), (40, 50, 100)])
 def test_gemm_one_wave_tiles_of_two_blocks(env, m, n, k, batch):
-    """768 to 2048 blocks of 16x16: tiles of one wave with two of them, 16x32 where the blocks' rows are odd in
-    number and 32x16 where they are even; fewer stages than a tile keeps on their way, as many, one more and
-    more, a last stage half full, columns of tiles that do not divide by eight, NaN beyond K and between the
-    rows, nothing written behind C; the same bits as one worker's 32x32 blocks."""
+    """640 to 2048 blocks of 16x16: tiles of one wave with two of them for k from three stages to eight, 16x32 or
+    32x16 by which side has an odd number, ring tiles for other k; a last stage half full, columns of tiles
+    that do not divide by eight, NaN beyond K and between the rows, nothing written behind C; the same bits as
+    one worker's 32x32 blocks."""
     B, ctx, torch = env
     gen = torch.Generator(device="cuda")
     gen.manual_seed(m + n + k)
@@ -602,14 +602,14 @@ def test_a_narrow_product_takes_no_longer_than_its_transpose(env, m, n, k):
 
 
 @pytest.mark.parametrize("m,n,k,batch", [
-    (512, 500, 1568, 1), (500, 512, 2080, 1),                                   # 32x32: as many stages ahead, more
-    (225, 1250, 544, 5), (399, 1200, 1056, 1),                                  # 32x64
-    (300, 3000, 512, 1), (1, 16300, 2080, 1), (1000, 1025, 544, 1),             # 64x64: one die with a tile more
-    (777, 1777, 544, 1), (100, 900, 576, 12),                                   # 64x96: one row of tiles a band
-    (1500, 1500, 544, 1), (413, 741, 544, 12),                                  # 96x96
-    (1025, 2047, 544, 1), (256, 8192, 512, 1), (129, 65, 512, 128),             # 128x64
-    (1000, 2300, 512, 1), (1000, 2300, 800, 1), (384, 8000, 544, 1),            # 128x96
-    (2000, 2001, 544, 1), (1024, 1024, 1056, 3), (2048, 4100, 576, 1),          # 128x128, rounds of them
+    (512, 500, 1568, 1), (500, 512, 2080, 1),
+    (225, 1250, 544, 5), (399, 1200, 1056, 1),
+    (300, 3000, 512, 1), (1, 16300, 2080, 1), (1000, 1025, 544, 1),
+    (777, 1777, 544, 1), (100, 900, 576, 12),
+    (1500, 1500, 544, 1), (413, 741, 544, 12),
+    (1025, 2047, 544, 1), (256, 8192, 512, 1), (129, 65, 512, 128),
+    (1000, 2300, 512, 1), (1000, 2300, 800, 1), (384, 8000, 544, 1),
+    (2000, 2001, 544, 1), (1024, 1024, 1056, 3), (2048, 4100, 576, 1),
     (1024, 1000, 320, 1), (1025, 2047, 128, 1), (413, 741, 160, 12), (999, 2300, 256, 1), (1500, 1500, 2080, 1)])
 def test_gemm_tiles_whose_operands_go_straight_to_lds(env, m, n, k, batch):
     """Products between a few small tiles and one large tile per compute unit, while no
@@ -680,6 +680,12 @@ def test_gemm_bits_do_not_depend_on_form_or_schedule(env, tile, m, n, k, batch):
                          ("1 block left", lambda: ctx.launch_ptb(kern, 256, stop_at=total - 1)),
                          ("3 blocks left", lambda: ctx.launch_ptb(kern, 256, stop_at=max(total - 3, 0)))]:
         assert torch.equal(bits(launch), want), what
+
+
+@pytest.mark.parametrize("tile,cover", list(GEMM_TILES))
+def test_every_tile_that_covers_a_product(env, tile, cover):
+    for shape in GEMM_TILES[tile, cover]:
+        test_gemm_bits_do_not_depend_on_form_or_schedule(env, tile, *shape)
 
 
 # ------------------------------------------------------------------ GEMV

@@ -406,8 +406,8 @@ def test_a_request_is_judged_by_the_kernel_it_launches(env, m, n, k, small):
 
 @pytest.mark.parametrize("m,n,k", [(100, 500, 416), (128, 1500, 416), (128, 2300, 1056)])
 def test_requests_beside_large_tiles_give_the_same_bits(env, m, n, k):
-    """The small GEMM beside resident 256x256 tiles takes 32x32 or 32x64 tiles whose operands go through
-    registers, alone tiles of one wave: the outputs are the same bits."""
+    """The small GEMM beside resident 256x256 tiles takes few tiles of one wave, or 32x32 or 32x64 tiles whose
+    operands go through registers, alone tiles of one wave or ring tiles: the outputs are the same bits."""
     B, ctx, torch = env
     be = B.gemm_bf16(_bf16_zeros(torch, 1, 4096, 32768), _bf16_zeros(torch, 1, 4096, 32768), _bf16_zeros(torch, 1, 4096, 4096))
     A, Bt = (torch.randn(1, r, k, device="cuda").to(torch.bfloat16) for r in (m, n))
@@ -428,6 +428,7 @@ def test_requests_beside_large_tiles_give_the_same_bits(env, m, n, k):
         s.submit_hi([hi])
         while s.poll():
             pass
+        assert s.stats()["be_kernels_done"] == 0           # (the request ran while the product was there)
         while s.stats()["be_kernels_done"] == 0:
             s.poll()
     finally:

@@ -205,6 +205,115 @@ def test_gemv_keeps_its_buffer_descriptors_in_scalar_registers(B, tmp_path):
     assert code.count("v_readfirstlane_b32") <= 2
 
 
+@pytest.fixture(scope="module")
+def gemm_rules(tmp_path_factory):
+    """The rules for the tiles of a GEMM as a program: for every m, n, k, batch, columns of the operator's large blocks
+    (0: the ragged one) and what else is on the GPU, the tile that is chosen."""
+    import subprocess
+    src = tmp_path_factory.mktemp("rules") / "rules.cpp"
+    src.write_text(r"""
+#include <cstdio>
+#include <set>
+#include <tuple>
+#include "gemm_cover.h"
+using namespace tally;
+int main() {
+  const char *names[] = {"32x32", "32x64", "64x64", "128x64", "256x128", "256x256", "wave16", "wave16x32", "wave32x16"};
+  const uint32_t tiles[][2] = {{16, 16}, {16, 32}, {32, 16}};
+  tally_gemm_bf16_args a{};
+  uint32_t large, how;
+  while (scanf("%u %u %u %u %u %u", &a.m, &a.n, &a.k, &a.batch, &large, &how) == 6) {
+    const int c = (int)(large ? gemm_cover(a, how, large) : gemm_cover_small(a, how)), ring = c - (int)GemmCover::kRing;
+    // every tile of the output once, by the workgroups of the grid, and how many the busiest and the idlest die have
+    std::set<std::tuple<uint32_t, uint32_t, uint32_t>> seen;
+    size_t runs = 0, most = 0, least = ~(size_t)0, want = 0;
+    uint32_t x, y, z, tm = 0, tn = 0;
+    if (ring >= 0) { tm = kRings[ring][0]; tn = kRings[ring][1]; }
+    else if (c >= (int)GemmCover::kWave16) { tm = tiles[c - (int)GemmCover::kWave16][0]; tn = tiles[c - (int)GemmCover::kWave16][1]; }
+    if (tm) {
+      const uint32_t X = cdiv(a.n, tn), Y = cdiv(a.m, tm), T = X * Y * a.batch;
+      const uint32_t in = a.m > a.n ? X : Y, at = cdiv((uint64_t)(a.m > a.n ? Y : X) * a.batch, 8);
+      want = T;
+      for (uint32_t die = 0; die < 8; ++die) {
+        size_t here = 0;
+        if (ring >= 0) {
+          for (uint32_t id = die; id < cdiv(T, 8) * 8; id += 8)
+            if (ring_tile(a, tm, tn, id, &x, &y, &z)) { ++here; if (x < X && y < Y && z < a.batch) seen.insert({x, y, z}); }
+        } else {
+          for (uint32_t i = 0; i < in; ++i)
+            for (uint32_t p = 0; p < at; ++p)
+              if (wave_tile(a, tm, tn, die, i, p, &x, &y, &z)) { ++here; if (x < X && y < Y && z < a.batch) seen.insert({x, y, z}); }
+        }
+        runs += here;
+        most = here > most ? here : most;
+        least = here < least ? here : least;
+      }
+    }
+    if (ring >= 0) printf("%ux%u/%u", kRings[ring][0], kRings[ring][1], kRings[ring][3]);
+    else printf("%s", names[c]);
+    printf(" %d %zu %zu\n", seen.size() == want && runs == want, most, least);
+  }
+  return 0;
+}
+""")
+    exe = src.with_suffix("")
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_07381_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", csrc, str(src), "-o", str(exe)], check=True, timeout=60)
+
+    def rules(cases):
+        lines = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True, text=True,
+                               check=True, timeout=60).stdout.split("\n")
+        return [(l.split()[0], *map(int, l.split()[1:])) for l in lines if l]
+    return rules
+
+
+LARGE = {"small": 0, "128": 128, "256": 256}
+SHARED, BESIDE = 4, 2                     # as in gemm_cover.h
+
+
+def test_the_shapes_of_each_tile_reach_it(gemm_rules):
+    """The GPU tests run every kernel that an original form chooses from; a rule that changes shows here."""
+    from gemm_tiles import GEMM_TILES
+    cases = [(key, s) for key, shapes in GEMM_TILES.items() for s in shapes]
+    for (key, s), got in zip(cases, gemm_rules([(*s, LARGE[key[0]], 0) for key, s in cases])):
+        assert got[0] == key[1] and got[1] == 1, (key, s, got)
+    rings = {"32x32/8", "32x64/6", "64x64/5", "64x96/4", "128x64/3", "96x96/3", "128x64/5", "96x96/5", "128x96/4", "128x128/4"}
+    for tile in LARGE:
+        assert {c for t, c in GEMM_TILES if t == tile} >= rings | {"wave16", "wave16x32", "wave32x16"}
+
+
+def test_gemm_tiles_are_dealt_out_to_all_dies(gemm_rules):
+    """Each tile goes to one workgroup, and no die has more than a panel, or a tile, beyond its share: for tall and
+    wide outputs, few panels, batches."""
+    import random
+    rng = random.Random(1)
+    cases = [(8192, 16, 1536, 1), (2032, 112, 1536, 1), (4096, 32, 2048, 1), (16, 8192, 768, 1), (17, 16, 768, 50), (1, 1, 768, 1)]
+    cases += [(rng.randint(1, 2500), rng.randint(1, 2500), 32 * rng.randint(5, 60), rng.choice([1, 1, 3, 12])) for _ in range(400)]
+    cases += [(rng.randint(1, 5000), rng.randint(1, 60), 32 * rng.randint(5, 60), rng.choice([1, 1, 3, 12])) for _ in range(200)]
+    for (m, n, k, batch), (tile, once, most, least) in zip(cases, gemm_rules([(*c, 0, 0) for c in cases])):
+        if tile in ("64x64", "128x64", "32x32", "32x64"):
+            continue                                       # (a plain grid)
+        assert once == 1, (m, n, k, batch)
+        if tile.startswith("wave"):
+            tm, tn = {"wave16": (16, 16), "wave16x32": (16, 32), "wave32x16": (32, 16)}[tile]
+            panel = -(-n // tn) if m > n else -(-m // tm)
+            assert most - least <= panel and panel <= 64, (m, n, k, batch)
+        else:
+            assert most - least <= 1, (m, n, k, batch)
+
+
+def test_products_beside_others_take_tiles_that_fit_there(gemm_rules):
+    """Beside best-effort workgroups no tile needs more than a 16x16 one of a wave or those through registers have."""
+    import random
+    rng = random.Random(2)
+    cases = [(rng.randint(1, 3000), rng.randint(1, 3000), 32 * rng.randint(1, 130), rng.choice([1, 1, 3, 12])) for _ in range(400)]
+    for how in (SHARED, SHARED | BESIDE):
+        for (m, n, k, batch), got in zip(cases, gemm_rules([(*c, 0, how) for c in cases])):
+            assert "/" not in got[0]
+            if how & BESIDE and got[0].startswith("wave"):
+                assert got[0] == "wave16" and -(-m // 16) * -(-n // 16) * batch <= 256
+
+
 def test_a_client_that_a_request_holds_back_keeps_its_place(tmp_path):
     """Best-effort clients are served first come, first served.  One whose turn has come while a request arrives
     is not launched; it goes on waiting in its place and not behind those that came later."""
