@@ -318,7 +318,7 @@ struct GemvBody {
   static __device__ __forceinline__ void run(const Args &a, uint32_t x, uint32_t y, uint32_t z) { run_t<true>(a, x, y, z); }
   // `left` vectors of a row, N to a lane, from buffers that end with the row: a lane past it gets zeros, which
   // add nothing
-  template <int N>
+  template <int N, bool DEEP>
   static __device__ __forceinline__ void rest(const uint4 *w, const uint4 *x, uint32_t left, uint32_t lane, float &acc0,
                                               float &acc1, float &acc2, float &acc3) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -326,11 +326,17 @@ struct GemvBody {
     uint4 wv[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) wv[j] = buf_ld16(rw, lane * 16, j * kWave * 16);
+    uint4 xv[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      const uint4 xv = buf_ld16(rx, lane * 16, j * kWave * 16);
+      if (DEEP || j == 0) {
+#pragma unroll
+        for (int i = j; i < (DEEP ? j + 1 : N); ++i) xv[i] = buf_ld16(rx, lane * 16, i * kWave * 16);
+        // (in a worker the compiler would wait for each of x's loads before the next)
+        if constexpr (!DEEP) __builtin_amdgcn_sched_barrier(0);
+      }
       float &acc = j % 4 == 0 ? acc0 : j % 4 == 1 ? acc1 : j % 4 == 2 ? acc2 : acc3;
-      acc = dot8(wv[j], xv, acc);
+      acc = dot8(wv[j], xv[j], acc);
       if (j == 3) __builtin_amdgcn_sched_barrier(0);       // (x's loads by fours, for the registers)
     }
 #endif
@@ -386,14 +392,14 @@ struct GemvBody {
     if (const uint32_t left = nvec - first) {
       const uint4 *e = reinterpret_cast<const uint4 *>(a.W + (uint64_t)__builtin_amdgcn_readfirstlane(row) * a.k) + first;
       switch ((left + kWave - 1) / kWave) {
-        case 1: rest<1>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        case 2: rest<2>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        case 3: rest<3>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        case 4: rest<4>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        case 5: if constexpr (DEEP) rest<5>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        case 6: if constexpr (DEEP) rest<6>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        case 7: if constexpr (DEEP) rest<7>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
-        default: if constexpr (DEEP) rest<8>(e, x + first, left, lane, acc0, acc1, acc2, acc3);
+        case 1: rest<1, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 2: rest<2, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 3: rest<3, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 4: rest<4, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 5: if constexpr (DEEP) rest<5, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 6: if constexpr (DEEP) rest<6, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        case 7: if constexpr (DEEP) rest<7, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3); break;
+        default: if constexpr (DEEP) rest<8, DEEP>(e, x + first, left, lane, acc0, acc1, acc2, acc3);
       }
     }
     float s = wave_sum((acc0 + acc1) + (acc2 + acc3));
