@@ -351,7 +351,7 @@ struct GemvBody {
     const uint4 *x = reinterpret_cast<const uint4 *>(a.x);
     float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;   // vector j of a lane goes to accumulator j mod 4
     uint32_t first = 0;                                    // of the batch
-    // Eight 16-byte loads of the row in flight per lane (8 KB per wave; a 4096-wide row is
+    // Batches of eight 16-byte loads of the row per lane (8 KB per wave; a 4096-wide row is
     // one such batch).  Beside the paused tiles of a best-effort GEMM only two of these
     // waves fit on a SIMD, and with four loads each the eight waves of a compute unit had
     // 32 KB on their way where the HBM's latency times the unit's share of its bandwidth
